@@ -15,6 +15,7 @@ struct GemmArgs {
     int32_t recordA, recordB;
     int32_t eadj;                 // -2*bias - (wa-2) - (wb-2)
     int64_t K;
+    int32_t bias;                 // exponent bias of both operands
 };
 
 // One instance per block size, each compiled in its own translation unit.

@@ -29,6 +29,7 @@ GemmArgs fragment_args(int64_t M, int64_t N, int64_t K, const void* A, mx_format
     g.recordA = ga.record; g.recordB = gb.record;
     const int bias = (1 << (fa.exp_bits - 1)) - 1;
     g.eadj = -2 * bias - (fa.mant_bits - 2) - (fb.mant_bits - 2);
+    g.bias = bias;
     return g;
 }
 }  // namespace mx
@@ -53,8 +54,6 @@ extern "C" mx_status mx_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, con
         return gemm_bf16(batch, M, N, K, A_packed, B_packed, Y, ldy, batch_stride_y, (hipStream_t)stream);
     if (layout == MX_LAYOUT_MATRIX)
         return gemm_scaled(batch, M, N, K, A_packed, fa, B_packed, fb, Y, ldy, batch_stride_y, (hipStream_t)stream);
-    const FragGeom ga = frag_geom(M, K, fa.block, fa.mant_bits);
-    if (ceil_div(ga.groups, 4) > 65535) return MX_ERR_UNSUPPORTED;
     const GemmArgs g = fragment_args(M, N, K, A_packed, fa, B_packed, fb, Y, ldy, batch_stride_y);
     hipStream_t st = (hipStream_t)stream;
     if (M <= 2) {      // one or two rows: dot-product kernel; three to eight: MFMA streaming kernel

@@ -7,6 +7,8 @@
 // accumulator.  The left operand feeds the MFMA "A" side, so in the 32x32 result a lane owns one
 // output column n and its 16 registers are 16 rows m: the right operand's block exponent is one
 // value per lane, the left operand's is one value per register.
+#include <type_traits>
+
 #include "mx_gemm.h"
 #include "mx_frag.h"
 
@@ -21,8 +23,159 @@ typedef v4i_t v4i;
 typedef v16i_t v16i;
 
 // ------------------------------------------------------------------------------------------------
-// General kernel: a workgroup of four waves owns a 128 x 128 tile of Y; each wave a 64 x 64
-// quarter (2 x 2 row groups).  Fragments come straight from global memory in lane order.
+// General kernel (M > 8): a workgroup of NW waves owns one 32 x 32 tile of Y, its waves take the K chunks
+// round-robin and their partial tiles are added through LDS at the end.  Fragments come straight from global
+// memory in lane order, one chunk ahead of the arithmetic.
+//
+// Bound: vector instruction issue (at M = 128, N = K = 5120: 30.6 us, 234 us before; at 32 rows 12.5 us, 238 before;
+// 13824 -> 5120 at 32 rows 26 us, 631 before).  Every block of 32 x 32 outputs costs one MFMA (two for block 64) and 16 block
+// sums per lane, each of which is scaled and added: exponent sum, conversion, multiply-add (3 instructions) when all
+// block exponents of the chunk lie within [-31, 32], which makes 2^(Ea+Eb+c) a normal fp32 number that one integer
+// instruction builds; otherwise (also for zero blocks, whose byte is 0) with ldexp (4 instructions).  The row exponents
+// are turned through LDS, because a lane needs 16 rows' exponents and would otherwise extract each from its row's dword.
+// Waves split K rather than owning larger tiles because the products that arrive here are short in M (the batch of a
+// decode step, a short prompt): a 128 x 128 tile per workgroup left most of the chip idle, and the K loop of one wave
+// is a serial chain of loads, matrix instructions and scaling.
+// ------------------------------------------------------------------------------------------------
+template <int WA, int WB, int B>
+__global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArgs g) {
+    constexpr int kDwA = Piece<WA, B>::kDw, kDwB = Piece<WB, B>::kDw;
+    constexpr int kHalfDw = B / 8;       // int8 dwords per lane per block
+    constexpr int D = 2 * (kDwA + kDwB + 2) <= 64 ? 2 : 1;               // chunks in registers
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];       // xe[NW][4][32], red[NW/2][16][64]
+    const int nw = (int)blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = lane & 31, h = lane >> 5;
+    // workgroup n runs on XCD n % 8: an XCD gets a contiguous range of tiles, row tiles fastest, so that the workgroups
+    // that read one column group's records do so behind one L2
+    const int64_t total = g.groupsA * g.groupsB, per_xcd = (total + 7) / 8;
+    const int64_t lin = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per_xcd || lin >= total) return;               // whole workgroup, before any barrier
+    const int64_t gb = lin / g.groupsA, ga = lin - gb * g.groupsA;
+    const int64_t bz = blockIdx.y;
+    const uint8_t* Abase = g.A + bz * g.matrixA + ga * g.chunks * g.recordA;
+    const uint8_t* Bbase = g.B + bz * g.matrixB + gb * g.chunks * g.recordB;
+    const int eadj = g.eadj - Unpack<WA, B>::kScaleLog2 - Unpack<WB, B>::kScaleLog2;
+    uint32_t* xe = lds + wave * 128;
+    float* red = reinterpret_cast<float*>(lds + nw * 128);
+
+    float acc[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    uint32_t pa[D][kDwA], pb[D][kDwB], ea4[D], eb4[D];
+    // chunk t of this wave.  Past the end it is the last chunk again (loaded, not used): no load sits under a condition,
+    // so the waits count exactly what is in flight; the record's address is scalar and the lanes' offsets stay put.
+    auto fetch = [&](int s, int64_t t) {
+        int64_t c = wave + t * nw;
+        c = c < g.chunks ? c : g.chunks - 1;
+        const uint8_t* ra = Abase + c * g.recordA;
+        const uint8_t* rb = Bbase + c * g.recordB;
+        load_dwords<kDwB>(rb + lane * (kDwB * 4), pb[s]);
+        load_dwords<1>(rb + 64 * (kDwB * 4) + i * 4, &eb4[s]);
+        load_dwords<kDwA>(ra + lane * (kDwA * 4), pa[s]);
+        load_dwords<1>(ra + 64 * (kDwA * 4) + i * 4, &ea4[s]);
+    };
+    // exponent bytes rebased to bias 127 and moved up by 32: [96, 159] becomes the bytes whose top bits are 10
+    const uint32_t move = (uint32_t)(127 - g.bias + 32) * 0x01010101u, neutral = (uint32_t)g.bias * 0x01010101u;
+    const bool arow = ga * 32 + i < g.M, brow = gb * 32 + i < g.N;       // padding rows take a neutral exponent
+    const bool upper = ga * 32 + 16 < g.M;                               // rows 16..31 of the tile exist
+
+    const int64_t per_wave = (g.chunks - wave + nw - 1) / nw;           // may be negative: none
+    if (per_wave > 0) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) fetch(s, s);
+    }
+    for (int64_t t0 = 0; t0 < per_wave; t0 += D) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            if (t0 + s < per_wave) {                                     // scalar condition: no load depends on it
+                const uint32_t ea = arow ? ea4[s] : neutral, eb = brow ? eb4[s] : neutral;
+                // row exponents -> LDS as integers [block][row]: each lane half writes two of its row's four blocks
+                const uint32_t e2 = h ? ea >> 16 : ea;
+                xe[(2 * h) * 32 + i] = e2 & 0xFFu;
+                xe[(2 * h + 1) * 32 + i] = (e2 >> 8) & 0xFFu;
+                const uint32_t off = (((ea + move) ^ 0x80808080u) | ((eb + move) ^ 0x80808080u)) & 0xC0C0C0C0u;
+                const bool narrow = __builtin_amdgcn_ballot_w64(off != 0) == 0;
+                __builtin_amdgcn_wave_barrier();                         // the wave's own LDS writes come first
+                auto chunk = [&](auto narrowc, auto upperc) {
+                    constexpr bool NARROW = decltype(narrowc)::value;
+                    constexpr int NQ = decltype(upperc)::value ? 4 : 2;  // groups of eight rows
+                    auto term = [&](float& a, int d, int e, int ebj) {
+                        if constexpr (NARROW) a = __builtin_fmaf((float)d, __uint_as_float((uint32_t)(e + ebj) << 23), a);
+                        else a += __builtin_ldexpf((float)d, e + ebj - 127);
+                    };
+                    // one block after the other, pinned: the other waves of the SIMD cover the matrix instruction's
+                    // latency, two blocks' sums at a time would not fit the registers next to the prefetched chunk
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        int4 e[NQ];
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) e[q] = *reinterpret_cast<const int4*>(xe + j * 32 + 8 * q + 4 * h);
+                        uint32_t fa[kHalfDw], fb[kHalfDw];
+                        Unpack<WA, B>::run(pa[s], j, fa);
+                        Unpack<WB, B>::run(pb[s], j, fb);
+                        const v16i d = block_mfma<B>(fa, fb);
+                        const int ebj = (int)((eb >> (8 * j)) & 0xFFu) + eadj + 127;
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) {
+                            term(acc[4 * q], d[4 * q], e[q].x, ebj);
+                            term(acc[4 * q + 1], d[4 * q + 1], e[q].y, ebj);
+                            term(acc[4 * q + 2], d[4 * q + 2], e[q].z, ebj);
+                            term(acc[4 * q + 3], d[4 * q + 3], e[q].w, ebj);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                // an empty statement that may change the pieces keeps the compiler from unpacking all four blocks ahead
+                // of the branch, for both of its sides, in registers it does not have
+                auto opaque = [&]() {
+#pragma unroll
+                    for (int d = 0; d < kDwA; ++d) asm volatile("" : "+v"(pa[s][d]));
+#pragma unroll
+                    for (int d = 0; d < kDwB; ++d) asm volatile("" : "+v"(pb[s][d]));
+                };
+                opaque();
+                if (narrow) {
+                    if (upper) chunk(std::true_type{}, std::true_type{}); else { opaque(); chunk(std::true_type{}, std::false_type{}); }
+                } else {
+                    opaque();
+                    chunk(std::false_type{}, std::true_type{});
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            fetch(s, t0 + s + D);                                        // the slot is free: refill it
+        }
+    }
+
+    // partial tiles of the waves, always added in the same order: the upper half of the waves hands over to the lower
+    // half, then every output is one thread's sum over the remaining waves
+    const int half = nw / 2;
+    if (wave >= half) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[((wave - half) * 16 + r) * 64 + lane] = acc[r];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] += acc[r];
+    }
+    __syncthreads();
+    float* Y = g.Y + bz * g.batch_stride_y;
+    for (int t = threadIdx.x; t < 1024; t += nw * 64) {
+        const int r = t >> 6, l = t & 63;
+        float s = 0.f;
+        for (int w = 0; w < half; ++w) s += red[(w * 16 + r) * 64 + l];
+        const int64_t m = ga * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
+        const int64_t n = gb * 32 + (l & 31);
+        // written once and not read again by this kernel: a streaming store keeps the operands in the L2
+        if (m < g.M && n < g.N) __builtin_nontemporal_store(s, &Y[m * g.ldy + n]);
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The form for products that fill the chip with 128 x 128 tiles and whose operands are dear to unpack: a workgroup of
+// four waves owns such a tile, each wave a 64 x 64 quarter (2 x 2 row groups), so that an unpacked fragment is used
+// twice.  Fragments come straight from global memory in lane order.
 // ------------------------------------------------------------------------------------------------
 template <int WA, int WB, int B>
 __global__ __launch_bounds__(256) void gemm_fragment_kernel(GemmArgs g) {
@@ -355,8 +508,28 @@ mx_status launch(const GemmArgs& g, int64_t batch, hipStream_t st) {
         dim3 grid((unsigned)g.groupsB, (unsigned)batch);
         hipLaunchKernelGGL((gemv_fragment_kernel<WA, WB, B, kGemvWaves>), grid, dim3(kGemvWaves * 64), 0, st, g);
     } else {
-        dim3 grid((unsigned)ceil_div(g.groupsB, 4), (unsigned)ceil_div(g.groupsA, 4), (unsigned)batch);
-        hipLaunchKernelGGL((gemm_fragment_kernel<WA, WB, B>), grid, dim3(256), 0, st, g);
+        // waves per tile: as many as the tiles leave the chip room for (about 4096 waves fill it)
+        const int64_t tiles = g.groupsA * g.groupsB * batch;
+        // 4- and 8-bit codes unpack in an instruction or none per dword; for the other widths (about ten each) and for
+        // blocks of 64 (half the block sums per unpacked element) the 128 x 128 form is the faster one once its
+        // workgroups fill the chip twice: at 2048 x 4096 x 4096 with 6 by 5 bits, block 32, 251 against 269 us, with
+        // 8 by 8 bits, block 64, 194 against 261 us; with 8 by 4 bits it is slower, 202 against 172 us (block 32),
+        // 370 against 263 us (block 16).
+        constexpr bool kDear = B == 64 || (WA != 4 && WA != 8) || (WB != 4 && WB != 8);
+        if constexpr (kDear) {
+            if (ceil_div(g.groupsA, 4) * ceil_div(g.groupsB, 4) * batch >= 512 && ceil_div(g.groupsA, 4) <= 65535) {
+                dim3 grid((unsigned)ceil_div(g.groupsB, 4), (unsigned)ceil_div(g.groupsA, 4), (unsigned)batch);
+                hipLaunchKernelGGL((gemm_fragment_kernel<WA, WB, B>), grid, dim3(256), 0, st, g);
+                MX_HIP_LAUNCH_CHECK();
+                return MX_OK;
+            }
+        }
+        const int max_nw = B >= 32 ? 8 : 16;
+        const int nw = tiles >= 1024 ? 4 : tiles >= 512 ? 8 : max_nw;
+        if (g.groupsA * g.groupsB > 0x7ffffff0LL) return MX_ERR_UNSUPPORTED;
+        const size_t smem = (size_t)nw * 512 + (size_t)(nw / 2) * 4096;
+        dim3 grid((unsigned)(ceil_div(g.groupsA * g.groupsB, 8) * 8), (unsigned)batch);
+        hipLaunchKernelGGL((gemm_tile_kernel<WA, WB, B>), grid, dim3(nw * 64), smem, st, g);
     }
     MX_HIP_LAUNCH_CHECK();
     return MX_OK;
