@@ -64,6 +64,71 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// The quantized ending (QOUT).  Bias of column n, decoded from the canonical MXInt row; 0 past the last column.
+__device__ __forceinline__ float bias_value(const BfArgs& g, int64_t n) {
+    if (n >= g.N) return 0.f;
+    const int64_t bit = n * g.wbias;
+    const int sh = (int)(bit & 7);
+    uint32_t code = g.bias_mant[bit >> 3];
+    if (sh + g.wbias > 8) code |= (uint32_t)g.bias_mant[(bit >> 3) + 1] << 8;
+    const int q = ((int)((code >> sh) << (32 - g.wbias))) >> (32 - g.wbias);
+    return __builtin_ldexpf((float)q, (int)g.bias_exps[n >> 4] - g.bias_b - (g.wbias - 2));
+}
+
+// Eight results of one row (16-byte aligned in LDS) plus their columns' bias; zeros outside the matrix.
+__device__ __forceinline__ void biased_half_block(const BfArgs& g, bool inside, const float* t, const float* bias, float* v) {
+    const float4 t0 = *reinterpret_cast<const float4*>(t);
+    const float4 t1 = *reinterpret_cast<const float4*>(t + 4);
+    v[0] = t0.x; v[1] = t0.y; v[2] = t0.z; v[3] = t0.w;
+    v[4] = t1.x; v[5] = t1.y; v[6] = t1.z; v[7] = t1.w;
+    if (!inside) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = 0.f;
+    } else if (g.bias_mant != nullptr) {
+        const float4 b0 = *reinterpret_cast<const float4*>(bias);
+        const float4 b1 = *reinterpret_cast<const float4*>(bias + 4);
+        v[0] += b0.x; v[1] += b0.y; v[2] += b0.z; v[3] += b0.w;
+        v[4] += b1.x; v[5] += b1.y; v[6] += b1.z; v[7] += b1.w;
+    }
+}
+
+// Lane 32h + i holds half h of block kf of row 32*rt + i: completes the block maximum with its partner lane, quantizes
+// and stores its 16 bytes of the output's fragment.  Called by whole waves.
+__device__ __forceinline__ void quantize_half_block(const BfArgs& g, uint8_t* obase, int64_t rt, int64_t row, int64_t kf,
+                                                    const float* v, int lane) {
+    const int h = lane >> 5;
+    const float qmax = (float)((1 << (g.wo - 1)) - 1);
+    uint32_t am = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const uint32_t ab = __float_as_uint(v[e]) & 0x7fffffffu;
+        am = ab > am ? ab : am;
+    }
+    const uint32_t o = (uint32_t)__shfl_xor((int)am, 32, 64);
+    am = o > am ? o : am;
+    if (g.brows_o == 2) {                     // two-row blocks: the neighbouring lane holds the other row
+        const uint32_t o2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)am, 0xB1, 0xF, 0xF, true);
+        am = o2 > am ? o2 : am;
+    }
+    const int ef = (int)(am >> 23);
+    int E = ef == 0 ? -127 : ef - 127;
+    E = E < -g.bias_o ? -g.bias_o : E;
+    E = E > g.emax_o ? g.emax_o : E;
+    uint32_t out[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float sc = __builtin_ldexpf(v[e], (g.wo - 2) - E);
+        float r = g.rnd_o == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
+        r = __builtin_fminf(__builtin_fmaxf(r, -qmax), qmax);
+        r += 0.0f;                           // -0.0 -> +0.0
+        out[e >> 1] |= bf16_of(r, E - (g.wo - 2)) << (16 * (e & 1));
+    }
+    if (rt < g.go.row_tiles && kf < g.go.ksteps * 2)
+        *reinterpret_cast<uint4*>(obase + bf_frag(g.go, rt, kf >> 1, (int)(kf & 1), lane)) =
+            make_uint4(out[0], out[1], out[2], out[3]);
+    if (h == 0 && row < g.M && kf < g.go.nblk) obase[g.go.frag_bytes + row * g.go.nblk + kf] = (uint8_t)(E + g.bias_o);
+}
+
 // S: LDS stages.  The stage of step ks is free once its fragments are in registers, i.e. from the
 // barrier of step ks on, so the copy of step ks+S is issued during step ks.
 // OCC: workgroups the register and LDS budget must leave room for on one compute unit.
@@ -213,23 +278,10 @@ __global__ __launch_bounds__(256, OCC) void gemm_bf16_kernel(BfArgs g) {
         // the bias of the workgroup's columns, decoded once
         float* bias_lds = reinterpret_cast<float*>(smem) + 4 * 32 * PITCH;
         if (g.bias_mant != nullptr) {
-            for (int c = threadIdx.x; c < 64 * TN; c += 256) {
-                const int64_t n = bn * (64 * TN) + c;
-                float bv = 0.f;
-                if (n < g.N) {
-                    const int64_t bit = n * g.wbias;
-                    const int sh = (int)(bit & 7);
-                    uint32_t code = g.bias_mant[bit >> 3];
-                    if (sh + g.wbias > 8) code |= (uint32_t)g.bias_mant[(bit >> 3) + 1] << 8;
-                    const int q = ((int)((code >> sh) << (32 - g.wbias))) >> (32 - g.wbias);
-                    bv = __builtin_ldexpf((float)q, (int)g.bias_exps[n >> 4] - g.bias_b - (g.wbias - 2));
-                }
-                bias_lds[c] = bv;
-            }
+            for (int c = threadIdx.x; c < 64 * TN; c += 256) bias_lds[c] = bias_value(g, bn * (64 * TN) + c);
             __syncthreads();
         }
         uint8_t* obase = g.out + bz * g.go.matrix;
-        const float qmax = (float)((1 << (g.wo - 1)) - 1);
 #pragma unroll
         for (int ta = 0; ta < RA; ++ta) {
 #pragma unroll
@@ -243,47 +295,9 @@ __global__ __launch_bounds__(256, OCC) void gemm_bf16_kernel(BfArgs g) {
                 const int64_t kf = rtB0 * 2 + f;          // block along N
                 const int64_t col0 = kf * 16 + h * 8;
                 const bool inside = row < g.M && col0 < g.N;
-                const float4 t0 = *reinterpret_cast<const float4*>(tile + i * PITCH + f * 16 + h * 8);
-                const float4 t1 = *reinterpret_cast<const float4*>(tile + i * PITCH + f * 16 + h * 8 + 4);
-                float v[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
-                if (!inside) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = 0.f;
-                } else if (g.bias_mant != nullptr) {
-                    const float4 b0 = *reinterpret_cast<const float4*>(bias_lds + wn * (32 * RB) + f * 16 + h * 8);
-                    const float4 b1 = *reinterpret_cast<const float4*>(bias_lds + wn * (32 * RB) + f * 16 + h * 8 + 4);
-                    v[0] += b0.x; v[1] += b0.y; v[2] += b0.z; v[3] += b0.w;
-                    v[4] += b1.x; v[5] += b1.y; v[6] += b1.z; v[7] += b1.w;
-                }
-                uint32_t am = 0;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const uint32_t ab = __float_as_uint(v[e]) & 0x7fffffffu;
-                    am = ab > am ? ab : am;
-                }
-                const uint32_t o = (uint32_t)__shfl_xor((int)am, 32, 64);
-                am = o > am ? o : am;
-                if (g.brows_o == 2) {                     // two-row blocks: the neighbouring lane holds the other row
-                    const uint32_t o2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)am, 0xB1, 0xF, 0xF, true);
-                    am = o2 > am ? o2 : am;
-                }
-                const int ef = (int)(am >> 23);
-                int E = ef == 0 ? -127 : ef - 127;
-                E = E < -g.bias_o ? -g.bias_o : E;
-                E = E > g.emax_o ? g.emax_o : E;
-                uint32_t out[4] = {0, 0, 0, 0};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float sc = __builtin_ldexpf(v[e], (g.wo - 2) - E);
-                    float r = g.rnd_o == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
-                    r = __builtin_fminf(__builtin_fmaxf(r, -qmax), qmax);
-                    r += 0.0f;                           // -0.0 -> +0.0
-                    out[e >> 1] |= bf16_of(r, E - (g.wo - 2)) << (16 * (e & 1));
-                }
-                if (rt < g.go.row_tiles && kf < g.go.ksteps * 2)
-                    *reinterpret_cast<uint4*>(obase + bf_frag(g.go, rt, kf >> 1, (int)(kf & 1), lane)) =
-                        make_uint4(out[0], out[1], out[2], out[3]);
-                if (h == 0 && row < g.M && kf < g.go.nblk) obase[g.go.frag_bytes + row * g.go.nblk + kf] = (uint8_t)(E + g.bias_o);
+                float v[8];
+                biased_half_block(g, inside, tile + i * PITCH + f * 16 + h * 8, bias_lds + wn * (32 * RB) + f * 16 + h * 8, v);
+                quantize_half_block(g, obase, rt, row, kf, v, lane);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -300,6 +314,138 @@ __global__ __launch_bounds__(256, OCC) void gemm_bf16_kernel(BfArgs g) {
                 const int64_t m = (rtA0 + ta) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
                 // written once and not read again by this kernel: a streaming store keeps the operands in the L2
                 if (m < g.M && n < g.N) __builtin_nontemporal_store(acc[ta][tb][r], &Y[m * g.ldy + n]);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Products with at most one workgroup per compute unit: eight waves own one (32*RA) x (32*RB) tile of Y and take its K
+// steps round-robin, fragments come straight from global memory (the layout is the lane order), D steps ahead, and
+// the eight partial tiles are added through LDS in wave order at the end.  No barrier and no LDS traffic in the K loop.
+//
+// Bound: the latency of the operand loads (a step comes from the last-level cache or HBM), so what counts is how many
+// compute units work and how many bytes each has in flight: eight waves hold up to 24 KiB each.  The 128 x 256 tile
+// of the kernel above leaves most of the chip idle at these sizes and walks K in one serial chain of barriers.
+// Measured, widths 6 and 4: 128 x 768 x 768 13.2 -> 4.7 us, 128 x 768 x 3072 31.2 -> 6.4 us, 128 x 4096 x 4096
+// 39.7 -> 13.4 us, 256 x 4096 x 4096 40 -> 17.6 us.
+// ------------------------------------------------------------------------------------------------
+constexpr int kSplitWaves = 8;
+constexpr int kSplitPitch = 36;                                       // floats per row of a summed 32 x 32 tile
+
+template <int RA, int RB, bool QOUT>
+__global__ __launch_bounds__(kSplitWaves * 64) void gemm_bf16_split_kernel(BfArgs g) {
+    constexpr int NW = kSplitWaves;
+    constexpr int D = 3;                                             // K steps in registers
+    constexpr int BUFS = RA * RB == 1 ? 1 : 2;
+    extern __shared__ __attribute__((aligned(16))) float red[];      // [buffers][NW][16][64], then QOUT: tile, bias
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n, per_xcd = (tiles + 7) / 8;
+    const int64_t lin = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per_xcd || lin >= tiles) return;            // whole workgroup, before any barrier
+    const int64_t bn = lin / g.tiles_m, bm = lin - bn * g.tiles_m;
+    const int64_t bz = blockIdx.y;
+    const uint8_t* srcA[RA];
+    const uint8_t* srcB[RB];
+#pragma unroll
+    for (int t = 0; t < RA; ++t) {
+        int64_t rt = bm * RA + t;
+        rt = rt < g.tilesA ? rt : g.tilesA - 1;                       // tiles past the matrix: its last one again, not stored
+        srcA[t] = g.A + bz * g.matrixA + rt * g.ksteps * kBfUnitBytes;
+    }
+#pragma unroll
+    for (int t = 0; t < RB; ++t) {
+        int64_t rt = bn * RB + t;
+        rt = rt < g.tilesB ? rt : g.tilesB - 1;
+        srcB[t] = g.B + bz * g.matrixB + rt * g.ksteps * kBfUnitBytes;
+    }
+    const uint32_t lane16 = lane * 16;
+
+    v16f acc[RA][RB];
+#pragma unroll
+    for (int ta = 0; ta < RA; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < RB; ++tb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[ta][tb][r] = 0.f;
+    v4i fa[D][RA][2], fb[D][RB][2];
+    // step t of this wave.  Past the end it is the last step again (loaded, not used): no load sits under a condition, so
+    // the waits count exactly what is in flight.
+    auto fetch = [&](int s, int64_t t) {
+        int64_t ks = wave + t * NW;
+        ks = ks < g.ksteps ? ks : g.ksteps - 1;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+#pragma unroll
+            for (int n = 0; n < RB; ++n) fb[s][n][f] = *reinterpret_cast<const v4i*>(srcB[n] + ks * kBfUnitBytes + f * 1024 + lane16);
+#pragma unroll
+            for (int n = 0; n < RA; ++n) fa[s][n][f] = *reinterpret_cast<const v4i*>(srcA[n] + ks * kBfUnitBytes + f * 1024 + lane16);
+        }
+    };
+    const int64_t per_wave = (g.ksteps - wave + NW - 1) / NW;         // not positive: none
+    if (per_wave > 0) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) fetch(s, s);
+    }
+    for (int64_t t0 = 0; t0 < per_wave; t0 += D) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            if (t0 + s < per_wave) {                                  // scalar condition: no load depends on it
+#pragma unroll
+                for (int f = 0; f < 2; ++f)
+#pragma unroll
+                    for (int ta = 0; ta < RA; ++ta)
+#pragma unroll
+                        for (int tb = 0; tb < RB; ++tb)
+                            acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                __builtin_bit_cast(v8bf, fa[s][ta][f]), __builtin_bit_cast(v8bf, fb[s][tb][f]), acc[ta][tb], 0, 0, 0);
+            }
+            fetch(s, t0 + s + D);                                     // the slot is free: refill it
+        }
+    }
+
+    // one 32 x 32 tile after the other: every wave's partial sums -> LDS, then each output is one thread's sum over the
+    // waves.  Two buffers: the next tile is written while slower threads still read this one.
+    float* qtile = red + BUFS * NW * 1024;
+    float* bias_lds = qtile + 32 * kSplitPitch;
+    if constexpr (QOUT) {
+        if (g.bias_mant != nullptr)
+            for (int c = threadIdx.x; c < 32 * RB; c += NW * 64) bias_lds[c] = bias_value(g, bn * (32 * RB) + c);
+    }
+#pragma unroll
+    for (int ta = 0; ta < RA; ++ta) {
+#pragma unroll
+        for (int tb = 0; tb < RB; ++tb) {
+            float* buf = red + (BUFS == 1 ? 0 : ((ta * RB + tb) & 1)) * NW * 1024;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) buf[(wave * 16 + r) * 64 + lane] = acc[ta][tb][r];
+            __syncthreads();
+            for (int t = threadIdx.x; t < 1024; t += NW * 64) {
+                const int r = t >> 6, l = t & 63;
+                float s = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) s += buf[(w * 16 + r) * 64 + l];
+                const int mi = 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), ni = l & 31;
+                if constexpr (QOUT) {
+                    qtile[mi * kSplitPitch + ni] = s;
+                } else {
+                    const int64_t m = (bm * RA + ta) * 32 + mi, n = (bn * RB + tb) * 32 + ni;
+                    // written once and not read again by this kernel: a streaming store keeps the operands in the L2
+                    if (m < g.M && n < g.N) __builtin_nontemporal_store(s, &g.Y[bz * g.batch_stride_y + m * g.ldy + n]);
+                }
+            }
+            if constexpr (QOUT) {
+                __syncthreads();
+                const int i = lane & 31, h = lane >> 5;
+                const int64_t rt = bm * RA + ta, row = rt * 32 + i;
+                for (int f = wave; f < 2; f += NW) {
+                    const int64_t kf = (bn * RB + tb) * 2 + f;        // block along N
+                    const int64_t col0 = kf * 16 + h * 8;
+                    float v[8];
+                    biased_half_block(g, row < g.M && col0 < g.N, qtile + i * kSplitPitch + f * 16 + h * 8,
+                                      bias_lds + tb * 32 + f * 16 + h * 8, v);
+                    quantize_half_block(g, g.out + bz * g.go.matrix, rt, row, kf, v, lane);
+                }
             }
         }
     }
@@ -322,11 +468,50 @@ mx_status launch_bf16(BfArgs& g, int64_t batch, hipStream_t st) {
     return MX_OK;
 }
 
+template <int RA, int RB, bool QOUT>
+mx_status launch_bf16_split(BfArgs& g, int64_t batch, hipStream_t st) {
+    constexpr int smem = (RA * RB == 1 ? 1 : 2) * kSplitWaves * 4096 + (QOUT ? 32 * kSplitPitch * 4 + 32 * RB * 4 : 0);
+    auto kern = gemm_bf16_split_kernel<RA, RB, QOUT>;
+    static std::atomic<uint64_t> done{0};
+    if (!allow_dynamic_lds((const void*)kern, smem, done)) return MX_ERR_DEVICE;
+    // a quantized result also covers the padding rows and columns of its layout
+    const int64_t tiles_m = ceil_div(QOUT ? g.go.row_tiles * 32 : g.M, 32 * RA);
+    const int64_t tiles_n = ceil_div(QOUT ? g.go.ksteps * 32 : g.N, 32 * RB);
+    if (tiles_m * tiles_n > 0x7ffffff0LL) return MX_ERR_UNSUPPORTED;
+    g.tiles_m = (int32_t)tiles_m;
+    g.tiles_n = (int32_t)tiles_n;
+    dim3 grid((unsigned)(ceil_div(tiles_m * tiles_n, 8) * 8), (unsigned)batch);
+    hipLaunchKernelGGL(kern, grid, dim3(kSplitWaves * 64), smem, st, g);
+    MX_HIP_LAUNCH_CHECK();
+    return MX_OK;
+}
+
+// The smallest tile that needs no more than one workgroup per compute unit: small tiles put more compute units to work,
+// but load more bytes per product, and with a second round of workgroups the next larger tile was the faster one.  The
+// three smallest tiles split K over their waves, the others share their operands through LDS.  Measured with 8 by 4 bits
+// (us; the form taken first): 128 x 4096 x 4096 32x64 13.4, 32x32 14.7, 64x64 17; 256 x 4096 x 4096 64x64 17.6, 64x128
+// 19.6; 512 x 4096 x 4096 64x128 20.6, 64x64 32, 128x256 41; 700 x 4096 x 4096 128x128 26, 64x128 34, 128x256 41; 1500 x
+// 4096 x 4096 128x256 45, 128x128 53.  Tiles of 128 x 128 are taken again, two workgroups on a compute unit, where
+// 128 x 256 would need a second round that fills less than the chip (1024 x 11008 x 4096: 78 against 93 us).
+// With at least two tiles of 128 x 256 per compute unit two workgroups share one (three stages each), so that one
+// workgroup's barrier and copy waits hide under the other's MFMAs; otherwise one runs alone with four stages.
+template <bool QOUT>
+mx_status pick_bf16(BfArgs& g, int64_t batch, hipStream_t st) {
+    const int64_t rows = ceil_div(g.M, 32), cols = ceil_div(g.N, 32);
+    auto groups = [&](int ra, int rb) { return ceil_div(rows, ra) * ceil_div(cols, rb) * batch; };
+    constexpr int64_t kCus = 256;
+    if (groups(1, 1) <= kCus) return launch_bf16_split<1, 1, QOUT>(g, batch, st);
+    if (groups(1, 2) <= kCus) return launch_bf16_split<1, 2, QOUT>(g, batch, st);
+    if (groups(2, 2) <= kCus) return launch_bf16_split<2, 2, QOUT>(g, batch, st);
+    if (groups(2, 4) <= kCus) return launch_bf16<1, 2, 6, 2, QOUT>(g, batch, st);
+    const int64_t tiles = groups(4, 8);
+    if (groups(4, 4) <= kCus || (tiles > kCus && tiles < 2 * kCus)) return launch_bf16<2, 2, 5, 2, QOUT>(g, batch, st);
+    if (tiles >= 2 * kCus) return launch_bf16<2, 4, 3, 2, QOUT>(g, batch, st);
+    return launch_bf16<2, 4, 4, 1, QOUT>(g, batch, st);
+}
+
 }  // namespace
 
-// Tile 128 x 256, four waves.  With at least two tiles per compute unit two workgroups share one
-// (three stages each), so that one workgroup's barrier and copy waits hide under the other's
-// MFMAs; otherwise one workgroup per compute unit runs with four stages.
 mx_status gemm_bf16(int64_t batch, int64_t M, int64_t N, int64_t K, const void* A, const void* B, float* Y,
                     int64_t ldy, int64_t batch_stride_y, hipStream_t st) {
     const BfGeom ga = bf_geom(M, K), gb = bf_geom(N, K);
@@ -336,9 +521,7 @@ mx_status gemm_bf16(int64_t batch, int64_t M, int64_t N, int64_t K, const void* 
     g.matrixA = ga.matrix; g.matrixB = gb.matrix; g.ldy = ldy; g.batch_stride_y = batch_stride_y;
     g.tiles_m = g.tiles_n = 0;
     g.out = nullptr; g.bias_mant = g.bias_exps = nullptr;
-    const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 256) * batch;
-    if (tiles >= 2 * 256) return launch_bf16<2, 4, 3, 2, false>(g, batch, st);
-    return launch_bf16<2, 4, 4, 1, false>(g, batch, st);
+    return pick_bf16<false>(g, batch, st);
 }
 
 // The same product with the bias added and the result quantized to `fo` (block 16, blocks along N),
@@ -358,9 +541,7 @@ mx_status gemm_bf16_q(int64_t batch, int64_t M, int64_t N, int64_t K, const void
     g.wo = fo.mant_bits; g.bias_o = (1 << (fo.exp_bits - 1)) - 1;
     g.emax_o = ((1 << fo.exp_bits) - 1) - g.bias_o;
     g.rnd_o = fo.rounding; g.brows_o = fo.block_rows;
-    const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 256) * batch;
-    if (tiles >= 2 * 256) return launch_bf16<2, 4, 3, 2, true>(g, batch, st);
-    return launch_bf16<2, 4, 4, 1, true>(g, batch, st);
+    return pick_bf16<true>(g, batch, st);
 }
 
 }  // namespace mx

@@ -35,3 +35,54 @@ def test_fragment_product_tiles_and_waves(M, N, K, block, wa, wb):
         torch.cuda.synchronize()
         y_ref, mag = orc.gemm(qa, ea, wa, qb, eb, wb, block, want_mag=True)
         check_product(host(y)[0], y_ref, mag, "%dx%dx%d bytes %d..%d" % (M, N, K, lo, hi - 1))
+
+
+MAT = mx.MX_LAYOUT_MATRIX
+# (row tiles, column tiles) of 32: one size in the range of each form of the matrix-layout product, from the smallest
+# tile with K split over the waves to more than one round of the largest
+MATRIX_FORMS = [(1, 2), (2, 200), (4, 200), (4, 400), (4, 900), (3, 1500), (4, 2400)]
+
+
+@pytest.mark.parametrize("rt,ct", MATRIX_FORMS)
+@pytest.mark.parametrize("block,wa,wb,K", [(16, 8, 4, 48), (16, 6, 3, 32 * 9), (32, 8, 4, 64 * 9), (32, 4, 3, 96),
+                                           (32, 5, 6, 64 * 3), (64, 3, 8, 64)])
+def test_matrix_product_forms(rt, ct, block, wa, wb, K):
+    """Ragged rows and columns, waves without a K step or with one more than others; exponent sums span fewer than
+    24 - wa - wb binades, so the sums are exact up to the final additions."""
+    M, N = rt * 32 - 13, ct * 32 - 5
+    if K * ct > 64 * 1500:
+        K = {16: 48, 32: 96, 64: 64}[block]
+    rng = np.random.default_rng(M * 31 + N + K)
+    qa, ea = random_operand(rng, M, K, block, wa, 122, 126)
+    qb, eb = random_operand(rng, N, K, block, wb, 120, 123)
+    A, fa = gpu_operand(qa, ea, block, wa, layout=MAT)
+    B, fb = gpu_operand(qb, eb, block, wb, layout=MAT)
+    y = torch.full((M, N + 3), 7.0, device="cuda")
+    mx.mx_gemm(1, M, N, K, A, fa, B, fb, MAT, y, N + 3, 0)
+    torch.cuda.synchronize()
+    y = host(y)
+    assert (y[:, N:] == 7.0).all(), "columns past N written"
+    y_ref, mag = orc.gemm(qa, ea, wa, qb, eb, wb, block, want_mag=True)
+    check_product(y[:, :N], y_ref, mag, "%dx%dx%d block %d" % (M, N, K, block))
+
+
+@pytest.mark.parametrize("rt,ct", [(1, 3), (2, 200), (4, 200), (4, 400), (4, 900), (4, 2400)])
+@pytest.mark.parametrize("block,wx,wo", [(16, 8, 6), (32, 8, 8), (64, 6, 4), (32, 4, 8)])
+def test_matrix_product_forms_quantized_output(rt, ct, block, wx, wo):
+    """mx_gemm_q in each form, against mx_gemm of the same operands quantized afterwards: with exact sums (few
+    binades, 24 bits hold them) the packed bytes are the same, padding rows and columns included."""
+    M, N, K = rt * 32 - 13, ct * 32 - (block if block < 64 else 0), 2 * block
+    N -= N % block
+    rng = np.random.default_rng(M * 31 + N)
+    qa, ea = random_operand(rng, M, K, block, wx, 124, 126)
+    qb, eb = random_operand(rng, N, K, block, 4, 120, 122)
+    A, fa = gpu_operand(qa, ea, block, wx, layout=MAT)
+    B, fb = gpu_operand(qb, eb, block, 4, layout=MAT)
+    fo = mx.fmt(block, wo)
+    out = torch.full((mx.mx_packed_bytes(1, M, N, fo, MAT),), 255, dtype=torch.uint8, device="cuda")
+    mx.mx_gemm_q(1, M, N, K, A, fa, B, fb, MAT, None, None, fb, fo, out)
+    want = torch.full_like(out, 255)
+    y = mx.gemm(A, fa, B, fb, M, N, K, layout=MAT)
+    mx.mx_quantize_pack(y, 1, M, N, N, 0, fo, MAT, want)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(out), host(want))
