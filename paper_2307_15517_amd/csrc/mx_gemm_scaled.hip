@@ -16,7 +16,8 @@
 // Structure: a workgroup of four waves (2 x 2) owns a (64*TM) x (64*TN) tile of Y.  Per K step of
 // 64 the operand units are copied global -> LDS with 16-byte direct-to-LDS loads (the layout in
 // HBM is the LDS image, so the copy is linear and the fragment reads are conflict-free b128
-// reads), double buffered with one barrier per step.
+// reads), double buffered with one barrier per step.  Products too small to fill the chip with such tiles run with
+// smaller ones, the smallest with a K loop split over the waves (gemm_scaled_split_kernel).
 #include <type_traits>
 
 #include "mx_gemm.h"
@@ -105,6 +106,101 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+// The quantized ending (QO != 0).  Bias of column n, decoded from the canonical MXInt row; 0 past the last column.
+__device__ __forceinline__ float bias_value(const ScaledArgs& g, int64_t n) {
+    if (n >= g.N) return 0.f;
+    const int64_t bit = n * g.wbias;
+    const int sh = (int)(bit & 7);
+    uint32_t code = g.bias_mant[bit >> 3];
+    if (sh + g.wbias > 8) code |= (uint32_t)g.bias_mant[(bit >> 3) + 1] << 8;
+    const int q = ((int)((code >> sh) << (32 - g.wbias))) >> (32 - g.wbias);
+    return __builtin_ldexpf((float)q, (int)g.bias_exps[n / g.blk_bias] - g.bias_b - (g.wbias - 2));
+}
+
+// Lane 32h + i takes the 32 results t32 of row 32*rt + i that a fragment of the next product's left operand gives it at K
+// step ks, adds the bias, and runs the quantizer of mx_quantize_pack on them.  Called by whole waves.
+template <int QO>
+__device__ __forceinline__ void quantize_step(const ScaledArgs& g, uint8_t* obase, int64_t rt, int64_t row, int64_t ks,
+                                              const float* t32, const float* bias32, int lane) {
+    const int h = lane >> 5;
+    const float qmax = (float)((1 << (g.wo - 1)) - 1);
+    const int64_t col0 = ks * 64 + h * 32;
+    const bool inside = row < g.M && col0 < g.N;
+    float v[32];
+#pragma unroll
+    for (int q4 = 0; q4 < 8; ++q4) {
+        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (inside) {
+            t = *reinterpret_cast<const float4*>(t32 + 4 * q4);
+            if (g.bias_mant != nullptr) {
+                const float4 b = *reinterpret_cast<const float4*>(bias32 + 4 * q4);
+                t.x += b.x; t.y += b.y; t.z += b.z; t.w += b.w;
+            }
+        }
+        v[4 * q4] = t.x; v[4 * q4 + 1] = t.y; v[4 * q4 + 2] = t.z; v[4 * q4 + 3] = t.w;
+    }
+    uint32_t am = 0;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {
+        const uint32_t ab = __float_as_uint(v[e]) & 0x7fffffffu;
+        am = ab > am ? ab : am;
+    }
+    if (g.blk_o == 64) {                      // the two halves of a lane pair form one block
+        const uint32_t o = (uint32_t)__shfl_xor((int)am, 32, 64);
+        am = o > am ? o : am;
+    }
+    if (g.brows_o == 2) {                     // two-row blocks: the neighbouring lane holds the other row
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)am, 0xB1, 0xF, 0xF, true);
+        am = o > am ? o : am;
+    }
+    const int ef = (int)(am >> 23);
+    int E = ef == 0 ? -127 : ef - 127;
+    E = E < -g.bias_o ? -g.bias_o : E;
+    E = E > g.emax_o ? g.emax_o : E;
+    const int shift = (g.wo - 2) - E;
+    v16f lo0, lo1, hi0, hi1;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {
+        const float sc = __builtin_ldexpf(v[e], shift);
+        float r = g.rnd_o == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
+        r = __builtin_fminf(__builtin_fmaxf(r, -qmax), qmax);
+        float hi = 0.f, lo = r;
+        if (QO == 2) {
+            hi = __builtin_floorf(r * 0.0625f + 0.5f);      // h = floor((q + 8) / 16)
+            lo = r - 16.f * hi;
+        }
+        lo += 0.0f;                                          // -0.0 -> +0.0
+        if (e & 1) { lo1[e >> 1] = lo; hi1[e >> 1] = hi; }
+        else       { lo0[e >> 1] = lo; hi0[e >> 1] = hi; }
+    }
+    if (rt < g.go.row_tiles && ks < g.go.ksteps) {
+        const v6i fl = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(lo0, lo1, 2.0f);   // codes of piece / 2
+        uint8_t* unit = obase + mat_unit(g.go, QO == 2 ? rt : rt >> 1, ks);
+        const int lslot = QO == 2 ? 1 : (int)(rt & 1);
+        *reinterpret_cast<uint4*>(unit + frag_lo(lslot, lane)) =
+            make_uint4((uint32_t)fl[0], (uint32_t)fl[1], (uint32_t)fl[2], (uint32_t)fl[3]);
+        *reinterpret_cast<uint2*>(unit + frag_hi(lslot, lane)) = make_uint2((uint32_t)fl[4], (uint32_t)fl[5]);
+        if (QO == 2) {
+            const v6i fh = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(hi0, hi1, 2.0f);
+            *reinterpret_cast<uint4*>(unit + frag_lo(0, lane)) =
+                make_uint4((uint32_t)fh[0], (uint32_t)fh[1], (uint32_t)fh[2], (uint32_t)fh[3]);
+            *reinterpret_cast<uint2*>(unit + frag_hi(0, lane)) = make_uint2((uint32_t)fh[4], (uint32_t)fh[5]);
+        }
+        // the lane's scale byte of this K step (bytes of one dword come from different waves)
+        obase[g.go.frag_bytes + ((rt * (g.go.ksteps / 4) + (ks >> 2)) * 64 + lane) * 4 + (ks & 3)] =
+            inside ? (uint8_t)(E + 127) : (uint8_t)0;
+    }
+}
+
+// f(B), f(B + 1), ..., f(E - 1) with the number as a compile-time constant: what indexes register arrays below.
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
+    }
 }
 
 // S: LDS stages.  The stage of step ks is free once its fragments are in registers, i.e. from
@@ -256,14 +352,14 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
     };
     // the units this wave reads per K step: first those of A, then those of B
     constexpr int NUA = (PA == 2) ? RA : RA / 2, NUB = (PB == 2) ? RB : RB / 2;
-    auto read_unit = [&](int n, int stage, auto setc) {
-        constexpr int set = decltype(setc)::value;
+    auto read_unit = [&](auto nc, int stage, auto setc) {
+        constexpr int n = decltype(nc)::value, set = decltype(setc)::value;
         const uint8_t* st = smem + stage * STAGE;
-        if (n < NUA) {
+        if constexpr (n < NUA) {
             if constexpr (PA == 2) load_unit(st + (wm * RA + n) * kUnitBytes, fa[set][n][0], fa[set][n][1]);
             else load_unit(st + (wm * NUA + n) * kUnitBytes, fa[set][2 * n][0], fa[set][2 * n + 1][0]);
         } else {
-            const int t = n - NUA;
+            constexpr int t = n - NUA;
             if constexpr (PB == 2) load_unit(st + (UA + wn * RB + t) * kUnitBytes, fb[set][t][0], fb[set][t][1]);
             else load_unit(st + (UA + wn * NUB + t) * kUnitBytes, fb[set][2 * t][0], fb[set][2 * t + 1][0]);
         }
@@ -301,8 +397,7 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
         }
         __syncthreads();
         if (!copier) {
-#pragma unroll
-            for (int n = 0; n < NUA + NUB; ++n) read_unit(n, 0, std::integral_constant<int, 0>{});
+            static_for<0, NUA + NUB>([&](auto nc) { read_unit(nc, 0, std::integral_constant<int, 0>{}); });
             read_scales(0, nxA, nxB);
         }
     }
@@ -346,22 +441,19 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
         auto kstep = [&](auto jc) {
             constexpr int j = decltype(jc)::value;
             constexpr int set = j & 1;
-            const int64_t ks = ks4 * 4 + j;
             const int nxt = cur + 1 == S ? 0 : cur + 1;
             // side work of this step, in issue order: LDS reads for step ks+1, copies for step ks+S,
             // at j == 0 the scale copies of the next group, at j == 3 the read of those scales
             constexpr int NCP = WS ? 0 : NI, NSCP = WS ? 0 : NSC;      // copies issued by this wave
             constexpr int NAUX = (NUA + NUB) + NCP + (j == 0 ? NSCP : 0) + (j == 3 ? 1 : 0);
             constexpr int NSLOT = NM > MX_SCALED_TAIL_MFMAS ? NM - MX_SCALED_TAIL_MFMAS : 1;
-            auto aux = [&](int x) {
-                if (x < NUA + NUB) { read_unit(x, nxt, std::integral_constant<int, set ^ 1>{}); return; }
-                x -= NUA + NUB;
-                if (j == 0) {                             // the scale copies go ahead of the step's data copies
-                    if (x < NSCP) { issue_scale_one(x, ks4 + 1, (int)((ks4 + 1) & 1)); return; }
-                    x -= NSCP;
-                }
-                if (x < NCP) { copy_item(src[x] + copy_off, lds0 + cur * STAGE + dst[x]); return; }
-                if (j == 3) read_scales((int)((ks4 + 1) & 1), nxA, nxB);
+            constexpr int X0 = NUA + NUB, X1 = X0 + (j == 0 ? NSCP : 0);   // the scale copies go ahead of the step's data copies
+            auto aux = [&](auto xc) {
+                constexpr int x = decltype(xc)::value;
+                if constexpr (x < X0) read_unit(xc, nxt, std::integral_constant<int, set ^ 1>{});
+                else if constexpr (x < X1) issue_scale_one(x - X0, ks4 + 1, (int)((ks4 + 1) & 1));
+                else if constexpr (x < X1 + NCP) copy_item(src[x - X1] + copy_off, lds0 + cur * STAGE + dst[x - X1]);
+                else read_scales((int)((ks4 + 1) & 1), nxA, nxB);
             };
             __builtin_amdgcn_sched_barrier(0);
             // newer than D(ks+1): the data copies of the last S-2 steps, and at j == 1 the scale copies
@@ -370,9 +462,9 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
             // one piece pair after the other: consecutive MFMAs never share an accumulator
-#pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                const int tb = m % RB, ta = (m / RB) % RA, pb = (m / (RA * RB)) % PB, pa = m / (RA * RB * PB);
+            static_for<0, NM>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                constexpr int tb = m % RB, ta = (m / RB) % RA, pb = (m / (RA * RB)) % PB, pa = m / (RA * RB * PB);
                 // piece 0 of a two-piece operand is the high one: scale byte + 4
                 const int sa = (int)(scA[ta] + ((PA == 2 && pa == 0) ? 0x04040404u : 0u));
                 const int sb = (int)(scB[tb] + ((PB == 2 && pb == 0) ? 0x04040404u : 0u));
@@ -380,12 +472,9 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
                     operand(fa[set][ta][pa]), operand(fb[set][tb][pb]), acc[ta][tb], 2, 2, j, sa, j, sb);
                 // the side work goes between the first NSLOT MFMAs: the step ends on MFMAs alone, so the LDS reads
                 // have returned by the time the next step's barrier waits for them
-                if (m < NSLOT) {
-#pragma unroll
-                    for (int x = m * NAUX / NSLOT; x < (m + 1) * NAUX / NSLOT; ++x) aux(x);
-                }
+                if constexpr (m < NSLOT) static_for<m * NAUX / NSLOT, (m + 1) * NAUX / NSLOT>(aux);
                 __builtin_amdgcn_sched_barrier(0);        // pin the interleaving as written
-            }
+            });
             cur = nxt;
             copy_off = copy_off + kUnitBytes < last_off ? copy_off + kUnitBytes : last_off;
         };
@@ -410,23 +499,10 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
         float* tile = reinterpret_cast<float*>(smem) + wave * (32 * PITCH);
         float* bias_lds = reinterpret_cast<float*>(smem) + 4 * 32 * PITCH;
         if (g.bias_mant != nullptr) {                    // the bias of the workgroup's columns, decoded once
-            for (int c = threadIdx.x; c < 64 * TN; c += 256) {
-                const int64_t n = bn * (64 * TN) + c;
-                float bv = 0.f;
-                if (n < g.N) {
-                    const int64_t bit = n * g.wbias;
-                    const int sh = (int)(bit & 7);
-                    uint32_t code = g.bias_mant[bit >> 3];
-                    if (sh + g.wbias > 8) code |= (uint32_t)g.bias_mant[(bit >> 3) + 1] << 8;
-                    const int q = ((int)((code >> sh) << (32 - g.wbias))) >> (32 - g.wbias);
-                    bv = __builtin_ldexpf((float)q, (int)g.bias_exps[n / g.blk_bias] - g.bias_b - (g.wbias - 2));
-                }
-                bias_lds[c] = bv;
-            }
+            for (int c = threadIdx.x; c < 64 * TN; c += 256) bias_lds[c] = bias_value(g, bn * (64 * TN) + c);
             __syncthreads();
         }
         uint8_t* obase = g.out + bz * g.go.matrix;
-        const float qmax = (float)((1 << (g.wo - 1)) - 1);
 #pragma unroll
         for (int ta = 0; ta < RA; ++ta) {
 #pragma unroll
@@ -439,72 +515,8 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
 #pragma unroll
             for (int ksl = 0; ksl < RB / 2; ++ksl) {
                 const int64_t ks = rtB0 / 2 + ksl;        // K step of the output operand
-                const int64_t col0 = ks * 64 + h * 32;
-                const bool inside = row < g.M && col0 < g.N;
-                float v[32];
-#pragma unroll
-                for (int q4 = 0; q4 < 8; ++q4) {
-                    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (inside) {
-                        t = *reinterpret_cast<const float4*>(tile + i * PITCH + ksl * 64 + h * 32 + 4 * q4);
-                        if (g.bias_mant != nullptr) {
-                            const float4 b = *reinterpret_cast<const float4*>(bias_lds + wn * (32 * RB) + ksl * 64 + h * 32 + 4 * q4);
-                            t.x += b.x; t.y += b.y; t.z += b.z; t.w += b.w;
-                        }
-                    }
-                    v[4 * q4] = t.x; v[4 * q4 + 1] = t.y; v[4 * q4 + 2] = t.z; v[4 * q4 + 3] = t.w;
-                }
-                uint32_t am = 0;
-#pragma unroll
-                for (int e = 0; e < 32; ++e) {
-                    const uint32_t ab = __float_as_uint(v[e]) & 0x7fffffffu;
-                    am = ab > am ? ab : am;
-                }
-                if (g.blk_o == 64) {                      // the two halves of a lane pair form one block
-                    const uint32_t o = (uint32_t)__shfl_xor((int)am, 32, 64);
-                    am = o > am ? o : am;
-                }
-                if (g.brows_o == 2) {                     // two-row blocks: the neighbouring lane holds the other row
-                    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)am, 0xB1, 0xF, 0xF, true);
-                    am = o > am ? o : am;
-                }
-                const int ef = (int)(am >> 23);
-                int E = ef == 0 ? -127 : ef - 127;
-                E = E < -g.bias_o ? -g.bias_o : E;
-                E = E > g.emax_o ? g.emax_o : E;
-                const int shift = (g.wo - 2) - E;
-                v16f lo0, lo1, hi0, hi1;
-#pragma unroll
-                for (int e = 0; e < 32; ++e) {
-                    const float sc = __builtin_ldexpf(v[e], shift);
-                    float r = g.rnd_o == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
-                    r = __builtin_fminf(__builtin_fmaxf(r, -qmax), qmax);
-                    float hi = 0.f, lo = r;
-                    if (QO == 2) {
-                        hi = __builtin_floorf(r * 0.0625f + 0.5f);      // h = floor((q + 8) / 16)
-                        lo = r - 16.f * hi;
-                    }
-                    lo += 0.0f;                                          // -0.0 -> +0.0
-                    if (e & 1) { lo1[e >> 1] = lo; hi1[e >> 1] = hi; }
-                    else       { lo0[e >> 1] = lo; hi0[e >> 1] = hi; }
-                }
-                if (rt < g.go.row_tiles && ks < g.go.ksteps) {
-                    const v6i fl = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(lo0, lo1, 2.0f);   // codes of piece / 2
-                    uint8_t* unit = obase + mat_unit(g.go, QO == 2 ? rt : rt >> 1, ks);
-                    const int lslot = QO == 2 ? 1 : (int)(rt & 1);
-                    *reinterpret_cast<uint4*>(unit + frag_lo(lslot, lane)) =
-                        make_uint4((uint32_t)fl[0], (uint32_t)fl[1], (uint32_t)fl[2], (uint32_t)fl[3]);
-                    *reinterpret_cast<uint2*>(unit + frag_hi(lslot, lane)) = make_uint2((uint32_t)fl[4], (uint32_t)fl[5]);
-                    if (QO == 2) {
-                        const v6i fh = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(hi0, hi1, 2.0f);
-                        *reinterpret_cast<uint4*>(unit + frag_lo(0, lane)) =
-                            make_uint4((uint32_t)fh[0], (uint32_t)fh[1], (uint32_t)fh[2], (uint32_t)fh[3]);
-                        *reinterpret_cast<uint2*>(unit + frag_hi(0, lane)) = make_uint2((uint32_t)fh[4], (uint32_t)fh[5]);
-                    }
-                    // the lane's scale byte of this K step (bytes of one dword come from different waves)
-                    obase[g.go.frag_bytes + ((rt * (g.go.ksteps / 4) + (ks >> 2)) * 64 + lane) * 4 + (ks & 3)] =
-                        inside ? (uint8_t)(E + 127) : (uint8_t)0;
-                }
+                quantize_step<QO>(g, obase, rt, row, ks, tile + i * PITCH + ksl * 64 + h * 32,
+                                  bias_lds + wn * (32 * RB) + ksl * 64 + h * 32, lane);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -526,6 +538,192 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Products with at most one workgroup per compute unit: eight waves own one (32*RA) x (32*RB) tile of Y and take its K
+// steps round-robin, fragments and scales come straight from global memory (the layout is the lane order), D steps
+// ahead, and the eight partial tiles are added through LDS in wave order at the end.  No barrier and no LDS traffic in
+// the K loop.
+//
+// Bound: the latency of the operand loads (a step comes from the last-level cache or HBM), so what counts is how many
+// compute units work and how many bytes each has in flight.  The 128 x 256 tile of the kernel above leaves most of the
+// chip idle at these sizes and walks K in one serial chain of barriers.  Measured, 8 by 4 bits, block 32: 128 x 768 x
+// 768 11.3 -> 4.9 us, 128 x 768 x 3072 20.9 -> 6.2 us, 128 x 4096 x 4096 25.4 -> 9.3 us.
+// D: one step more was slower at both tiles (5.6 and 9.9 us at the first and the last of these sizes).
+// ------------------------------------------------------------------------------------------------
+constexpr int kSplitWaves = 8;
+constexpr int kSplitPitch = 68;                                       // floats per row of a summed 32 x 64 tile
+
+template <int PA, int PB, int RA, int RB, int QO>
+__global__ __launch_bounds__(kSplitWaves * 64) void gemm_scaled_split_kernel(ScaledArgs g) {
+    constexpr int NW = kSplitWaves;
+    constexpr int D = RA * RB == 1 ? 3 : 2;                          // K steps in registers
+    constexpr int BUFS = RA * RB == 1 ? 1 : 2;
+    static_assert(QO == 0 || RB % 2 == 0, "the quantized ending takes whole K steps of the output");
+    extern __shared__ __attribute__((aligned(16))) float red[];      // [buffers][NW][16][64], then QO: tile, bias
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n, per_xcd = (tiles + 7) / 8;
+    const int64_t lin = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per_xcd || lin >= tiles) return;            // whole workgroup, before any barrier
+    const int64_t bn = lin / g.tiles_m, bm = lin - bn * g.tiles_m;
+    const int64_t bz = blockIdx.y;
+    const int64_t groups = g.ksteps / 4;
+    // fragment p of row tile rt: P = 2 unit rt, fragment p; P = 1 unit rt / 2, fragment rt % 2.  Tiles past the matrix
+    // re-read its last one (never stored).
+    const uint8_t* srcA[RA];
+    const uint8_t* srcB[RB];
+    const uint8_t* scaleA[RA];
+    const uint8_t* scaleB[RB];
+    int fragA[RA], fragB[RB];
+#pragma unroll
+    for (int t = 0; t < RA; ++t) {
+        int64_t rt = bm * RA + t;
+        rt = rt < g.tilesA ? rt : g.tilesA - 1;
+        fragA[t] = PA == 2 ? 0 : (int)(rt & 1);
+        srcA[t] = g.A + bz * g.matrixA + (PA == 2 ? rt : rt >> 1) * g.ksteps * kUnitBytes;
+        scaleA[t] = g.A + bz * g.matrixA + g.fragA + rt * groups * 256;
+    }
+#pragma unroll
+    for (int t = 0; t < RB; ++t) {
+        int64_t rt = bn * RB + t;
+        rt = rt < g.tilesB ? rt : g.tilesB - 1;
+        fragB[t] = PB == 2 ? 0 : (int)(rt & 1);
+        srcB[t] = g.B + bz * g.matrixB + (PB == 2 ? rt : rt >> 1) * g.ksteps * kUnitBytes;
+        scaleB[t] = g.B + bz * g.matrixB + g.fragB + rt * groups * 256;
+    }
+
+    v16f acc[RA][RB];
+#pragma unroll
+    for (int ta = 0; ta < RA; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < RB; ++tb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[ta][tb][r] = 0.f;
+    struct Frag { uint4 lo; uint2 hi; };
+    Frag fa[D][RA][PA], fb[D][RB][PB];
+    uint32_t sa[D][RA], sb[D][RB];
+    const uint32_t lane16 = lane * 16, lane8 = lane * 8, lane4 = lane * 4;
+    auto load = [&](const uint8_t* unit, int f, Frag& out) {
+        out.lo = *reinterpret_cast<const uint4*>(unit + f * 1024 + lane16);
+        out.hi = *reinterpret_cast<const uint2*>(unit + 2048 + f * 512 + lane8);
+    };
+    // step t of this wave.  Past the end it is the last step again (loaded, not used): no load sits under a condition, so
+    // the waits count exactly what is in flight.
+    auto fetch = [&](int s, int64_t t) {
+        int64_t ks = wave + t * NW;
+        ks = ks < g.ksteps ? ks : g.ksteps - 1;
+#pragma unroll
+        for (int n = 0; n < RB; ++n) {
+            sb[s][n] = *reinterpret_cast<const uint32_t*>(scaleB[n] + (ks >> 2) * 256 + lane4);
+#pragma unroll
+            for (int p = 0; p < PB; ++p) load(srcB[n] + ks * kUnitBytes, PB == 2 ? p : fragB[n], fb[s][n][p]);
+        }
+#pragma unroll
+        for (int n = 0; n < RA; ++n) {
+            sa[s][n] = *reinterpret_cast<const uint32_t*>(scaleA[n] + (ks >> 2) * 256 + lane4);
+#pragma unroll
+            for (int p = 0; p < PA; ++p) load(srcA[n] + ks * kUnitBytes, PA == 2 ? p : fragA[n], fa[s][n][p]);
+        }
+    };
+    auto operand = [](const Frag& f) {       // the fp6 forms read six of the eight operand dwords
+        return v8i{(int)f.lo.x, (int)f.lo.y, (int)f.lo.z, (int)f.lo.w, (int)f.hi.x, (int)f.hi.y, 0, 0};
+    };
+    const int64_t per_wave = (g.ksteps - wave + NW - 1) / NW;         // not positive: none
+    if (per_wave > 0) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) fetch(s, s);
+    }
+    for (int64_t t0 = 0; t0 < per_wave; t0 += D) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            if (t0 + s < per_wave) {                                  // scalar condition: no load depends on it
+                const int shift = 8 * (int)((wave + (t0 + s) * NW) & 3);
+                // piece 0 of a two-piece operand is the high one: scale byte + 4 (the byte is at most 250)
+                uint32_t ea[RA], eb[RB];
+#pragma unroll
+                for (int n = 0; n < RA; ++n) ea[n] = sa[s][n] >> shift;
+#pragma unroll
+                for (int n = 0; n < RB; ++n) eb[n] = sb[s][n] >> shift;
+                // one piece pair after the other: consecutive matrix instructions never share an accumulator
+#pragma unroll
+                for (int pa = 0; pa < PA; ++pa)
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                        for (int ta = 0; ta < RA; ++ta)
+#pragma unroll
+                            for (int tb = 0; tb < RB; ++tb)
+                                acc[ta][tb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                                    operand(fa[s][ta][pa]), operand(fb[s][tb][pb]), acc[ta][tb], 2, 2, 0,
+                                    (int)(ea[ta] + (PA == 2 && pa == 0 ? 4u : 0u)), 0, (int)(eb[tb] + (PB == 2 && pb == 0 ? 4u : 0u)));
+            }
+            fetch(s, t0 + s + D);                                     // the slot is free: refill it
+        }
+    }
+
+    // one 32 x 32 tile after the other: every wave's partial sums -> LDS, then each output is one thread's sum over the
+    // waves.  Two buffers: the next tile is written while slower threads still read this one.
+    float* qtile = red + BUFS * NW * 1024;
+    float* bias_lds = qtile + 32 * kSplitPitch;
+    if constexpr (QO != 0) {
+        if (g.bias_mant != nullptr)
+            for (int c = threadIdx.x; c < 32 * RB; c += NW * 64) bias_lds[c] = bias_value(g, bn * (32 * RB) + c);
+    }
+#pragma unroll
+    for (int ta = 0; ta < RA; ++ta) {
+#pragma unroll
+        for (int tb = 0; tb < RB; ++tb) {
+            float* buf = red + (BUFS == 1 ? 0 : ((ta * RB + tb) & 1)) * NW * 1024;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) buf[(wave * 16 + r) * 64 + lane] = acc[ta][tb][r];
+            __syncthreads();
+            for (int t = threadIdx.x; t < 1024; t += NW * 64) {
+                const int r = t >> 6, l = t & 63;
+                float s = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) s += buf[(w * 16 + r) * 64 + l];
+                s = __builtin_ldexpf(s, g.eadj);
+                const int mi = 8 * (r >> 2) + 4 * (l >> 5) + (r & 3), ni = l & 31;
+                if constexpr (QO != 0) {
+                    qtile[mi * kSplitPitch + (tb & 1) * 32 + ni] = s;
+                } else {
+                    const int64_t m = (bm * RA + ta) * 32 + mi, n = (bn * RB + tb) * 32 + ni;
+                    // written once and not read again by this kernel: a streaming store keeps the operands in the L2
+                    if (m < g.M && n < g.N) __builtin_nontemporal_store(s, &g.Y[bz * g.batch_stride_y + m * g.ldy + n]);
+                }
+            }
+            if constexpr (QO != 0) {
+                if (tb & 1) {                                         // a whole K step of the output: 64 columns
+                    __syncthreads();
+                    if (wave == 0) {
+                        const int i = lane & 31, h = lane >> 5;
+                        const int64_t rt = bm * RA + ta;
+                        quantize_step<QO>(g, g.out + bz * g.go.matrix, rt, rt * 32 + i, (bn * RB + tb) >> 1,
+                                          qtile + i * kSplitPitch + h * 32, bias_lds + (tb >> 1) * 64 + h * 32, lane);
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <int PA, int PB, int RA, int RB, int QO>
+mx_status launch_scaled_split(ScaledArgs& g, int64_t batch, hipStream_t st) {
+    constexpr int smem = (RA * RB == 1 ? 1 : 2) * kSplitWaves * 4096 + (QO ? 32 * kSplitPitch * 4 + 32 * RB * 4 : 0);
+    auto kern = gemm_scaled_split_kernel<PA, PB, RA, RB, QO>;
+    static std::atomic<uint64_t> done{0};
+    if (!allow_dynamic_lds((const void*)kern, smem, done)) return MX_ERR_DEVICE;
+    // a quantized result also covers the padding rows and columns of its layout
+    const int64_t tiles_m = ceil_div(QO ? g.go.row_tiles * 32 : g.M, 32 * RA);
+    const int64_t tiles_n = ceil_div(QO ? g.go.ksteps * 64 : g.N, 32 * RB);
+    if (tiles_m * tiles_n > 0x7ffffff0LL) return MX_ERR_UNSUPPORTED;
+    g.tiles_m = (int32_t)tiles_m;
+    g.tiles_n = (int32_t)tiles_n;
+    dim3 grid((unsigned)(ceil_div(tiles_m * tiles_n, 8) * 8), (unsigned)batch);
+    hipLaunchKernelGGL(kern, grid, dim3(kSplitWaves * 64), smem, st, g);
+    MX_HIP_LAUNCH_CHECK();
+    return MX_OK;
+}
+
 template <int PA, int PB, int TM, int TN, int S, int OCC, int QO = 0, int WS = 0>
 mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
     static_assert(WS == 0 || (OCC == 1 && QO == 0), "copy waves: one workgroup per compute unit, fp32 result");
@@ -537,7 +735,9 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
     auto kern = gemm_scaled_kernel<PA, PB, TM, TN, S, OCC, QO, WS>;
     static std::atomic<uint64_t> done{0};
     if (!allow_dynamic_lds((const void*)kern, smem, done)) return MX_ERR_DEVICE;
-    const int64_t tiles_m = ceil_div(g.M, 64 * TM), tiles_n = ceil_div(g.N, 64 * TN);
+    // a quantized result also covers the padding rows and columns of its layout
+    const int64_t tiles_m = ceil_div(QO ? g.go.row_tiles * 32 : g.M, 64 * TM);
+    const int64_t tiles_n = ceil_div(QO ? g.go.ksteps * 64 : g.N, 64 * TN);
     if (tiles_m * tiles_n > 0x7fffffffLL) return MX_ERR_UNSUPPORTED;
     if (g.ksteps * kUnitBytes > 0x7fffffffLL) return MX_ERR_UNSUPPORTED;       // 32-bit offsets along K
     g.tiles_m = (int32_t)tiles_m;
@@ -548,15 +748,40 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
     return MX_OK;
 }
 
-// Tile 128 (M) x 256 (N): the left operand costs more bytes per element when it has two mantissa
-// pieces, so the tile is wider along N.  When there are at least two tiles per compute unit and
-// the stages are small enough, two workgroups share a compute unit (three stages each), so that
-// one workgroup's barrier and copy waits hide under the other's MFMAs; otherwise one workgroup
-// per compute unit runs with four copy waves beside its four matrix waves and five stages (the
+// The smallest tile that needs no more than one workgroup per compute unit: small tiles put more compute units to work,
+// but load more bytes per product, and with a second round of workgroups the next larger tile was the faster one.  The
+// two smallest tiles split K over their waves, the others share their operands through LDS.  Measured with 8 by 4 bits,
+// block 32 (us; the form taken first): 128 x 4096 x 4096 32x64 9.3, 32x32 12.7, 64x128 13; 333 x 4096 x 4096 64x128 14.1,
+// 64x256 19.4, 128x256 28; 700 x 4096 x 4096 64x256 19.8, 64x128 20.9, 128x256 28; 1500 x 4096 x 4096 128x256 31, 64x256
+// 36.  Tiles of 64 x 256 are taken again, two workgroups on a compute unit, where 128 x 256 would need a second round
+// that fills less than the chip (700 x 11008 x 4096: 36 against 60 us, 1024 x 11008 x 4096: 52 against 61 us).  A wave
+// of a one-piece left operand takes whole units of 64 rows: it has 128 x 128 in the place of both 64-row forms (700 x
+// 4096 x 4096, 4 by 3 bits: 15 against 21.5 us for 128 x 256; 1024 x 11008 x 4096: 32 against 43 us).
+//
+// 128 (M) x 256 (N): the left operand costs more bytes per element when it has two mantissa pieces, so the tile is wider
+// along N.  When there are at least two tiles per compute unit and the stages are small enough, two workgroups share a
+// compute unit (three stages each), so that one workgroup's barrier and copy waits hide under the other's MFMAs;
+// otherwise one workgroup per compute unit runs with four copy waves beside its four matrix waves and five stages (the
 // copies of a K step are requested four steps ahead).
 template <int PA, int PB, int QO = 0>
 mx_status pick_tile(ScaledArgs& g, int64_t batch, hipStream_t st) {
-    const int64_t tiles = ceil_div(g.M, 128) * ceil_div(g.N, 256) * batch;
+    const int64_t rows = ceil_div(g.M, 32), cols = ceil_div(g.N, 32);
+    auto groups = [&](int ra, int rb) { return ceil_div(rows, ra) * ceil_div(cols, rb) * batch; };
+    constexpr int64_t kCus = 256;
+    if constexpr (QO == 0) {
+        if (groups(1, 1) <= kCus) return launch_scaled_split<PA, PB, 1, 1, QO>(g, batch, st);
+    }
+    if (groups(1, 2) <= kCus) return launch_scaled_split<PA, PB, 1, 2, QO>(g, batch, st);
+    const int64_t tiles = groups(4, 8);
+    const bool part_round = tiles > kCus && tiles < MX_SCALED_TWO_PER_CU_TILES;
+    if constexpr (PA == 2) {
+        if (groups(2, 4) <= kCus) return launch_scaled<PA, PB, 1, 2, 4, 2, QO>(g, batch, st);
+        if constexpr (PB == 1) {
+            if (groups(2, 8) <= kCus || part_round) return launch_scaled<PA, PB, 1, 4, 4, 2, QO>(g, batch, st);
+        }
+    } else {
+        if (groups(4, 4) <= kCus || part_round) return launch_scaled<PA, PB, 2, 2, 4, 2, QO>(g, batch, st);
+    }
     if constexpr (PB == 1) {
         if (tiles >= MX_SCALED_TWO_PER_CU_TILES) return launch_scaled<PA, PB, 2, 4, 3, 2, QO>(g, batch, st);
         if constexpr (QO == 0) return launch_scaled<PA, PB, 2, 4, 5, 1, 0, 1>(g, batch, st);
