@@ -20,7 +20,7 @@
 // other half (one exchange per block).
 //
 // Work split: a workgroup of four waves owns 128 queries of one head (a wave: one tile of 32, its
-// Q fragments stay in registers), two workgroups per compute unit; the K (and in sweep 2 the V^T)
+// Q fragments stay in registers), two workgroups per compute unit (few queries: attention_split_kernel); the K (and in sweep 2 the V^T)
 // units of one tile of 32 keys are copied global -> LDS with 16-byte direct-to-LDS loads, four
 // stages, one barrier per key tile.
 #include <type_traits>
@@ -46,6 +46,7 @@ struct AttnArgs {
     int64_t v_ksteps;              // K steps of the V^T geometry
     int64_t ldo, o_batch_stride;
     int64_t tiles_q, total;        // workgroup tiles per head, and in all
+    int32_t parts;                 // column parts per query tile (attention_split_kernel)
     float c;                       // scale * log2(e)
     int32_t wp, bias_p, emax_p;
     int32_t vec;                   // O rows may be stored as float4
@@ -415,6 +416,219 @@ __global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(At
     if (g.vec) store(std::true_type{}); else store(std::false_type{});
 }
 
+// ------------------------------------------------------------------------------------------------
+// Few queries (decoding, chunks of a prompt, few heads): a workgroup of eight waves owns 32 queries of one head and 32*DTW
+// columns of the result; its waves take the key tiles round-robin in both sweeps, with operands straight from global
+// memory (the layout is the lane order), and meet twice: for the row statistics between the sweeps and for the sum of
+// their partial results at the end, both in wave order through LDS.  The arithmetic on a key tile is that of the kernel
+// above.
+// ------------------------------------------------------------------------------------------------
+constexpr int kSplitWaves = 8;
+
+template <int KS, int DTW, int RND>
+__global__ __launch_bounds__(kSplitWaves * 64) void attention_split_kernel(AttnArgs g) {
+    constexpr int NW = kSplitWaves, NK = 2 * KS;
+    constexpr int PITCH = 65;                           // floats per result register of 64 lanes, skewed over the banks
+    __shared__ float stat[2][NW][64];
+    extern __shared__ __attribute__((aligned(16))) float red[];       // [2][NW][16][PITCH]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = lane & 31, h = lane >> 5;
+    // an XCD gets one contiguous range of (head, query tile, column part): those of a head share its K and V in the L2
+    const int64_t per_xcd = (g.total + 7) / 8;
+    const int64_t lin = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per_xcd || lin >= g.total) return;          // whole workgroup, before any barrier
+    const int part = (int)(lin % g.parts);
+    const int64_t tq = lin / g.parts, bz = tq / g.tiles_q, qt = tq - bz * g.tiles_q;
+    const uint8_t* Kbase = g.K + bz * g.matrixK;
+    const uint8_t* Vbase = g.V + bz * g.matrixV + (int64_t)part * DTW * g.v_ksteps * kBfUnitBytes;
+    const uint32_t lane16 = lane * 16;
+
+    // the wave's Q fragments and the permuted K rows: as in the kernel above
+    const int flip = g.c < 0.f ? (int)0x80008000u : 0;
+    const float c = __builtin_fabsf(g.c);
+    v4i qf[NK];
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+        qf[kk] = *reinterpret_cast<const v4i*>(g.Q + bz * g.matrixQ + (qt * KS + (kk >> 1)) * kBfUnitBytes + (kk & 1) * 1024 + lane16);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) qf[kk][d] ^= flip;
+    }
+    const int sig = (i & 0x13) | ((i & 4) << 1) | ((i & 8) >> 1);
+    const uint32_t koff = (32 * h + sig) * 16;
+
+    v4i kf[NK];
+    auto fetch_k = [&](int64_t kt) {                    // past the end: the last tile again (loaded, not used)
+        kt = kt < g.nt ? kt : g.nt - 1;
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk)
+            kf[kk] = *reinterpret_cast<const v4i*>(Kbase + (kt * KS + (kk >> 1)) * kBfUnitBytes + (kk & 1) * 1024 + koff);
+    };
+    v16f s;
+    auto scores = [&]() {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk)
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, kf[kk]), __builtin_bit_cast(v8bf, qf[kk]), s, 0, 0, 0);
+    };
+    // only the last key tile can hold keys past Sk; this lane's key 16*b + e is real iff 16*b + e < valid
+    const bool ragged = (g.Sk & 31) != 0;
+    const int valid = (int)(g.Sk - (g.nt - 1) * 32) - 8 * h;
+
+    float m_run = -__builtin_inff(), l_run = 0.f;
+    fetch_k(wave);
+    for (int64_t kt = wave; kt < g.nt; kt += NW) {
+        scores();
+        fetch_k(kt + NW);
+        auto tile = [&](auto ragc) {
+            constexpr bool RAG = decltype(ragc)::value;
+            auto masked = [&](int r) { return RAG && 16 * (r >> 3) + (r & 7) >= valid; };
+            float sm = -__builtin_inff();
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sm = __builtin_fmaxf(sm, masked(r) ? -__builtin_inff() : s[r]);
+            const float m_old = m_run;
+            m_run = __builtin_fmaxf(m_run, sm * c);
+            const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;
+            float sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                float arg = __builtin_fmaf(s[r], c, -m_use);
+                if (masked(r)) arg = -__builtin_inff();               // also when c is 0
+                sum += __builtin_amdgcn_exp2f(arg);
+            }
+            l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
+        };
+        if (ragged && kt == g.nt - 1) tile(std::true_type{}); else tile(std::false_type{});
+    }
+
+    // row statistics: the waves, and the two lane halves of each, hold disjoint keys of the same query
+    fetch_k(wave);                                      // the second sweep's first tile, under the exchange
+    stat[0][wave][lane] = m_run;
+    stat[1][wave][lane] = l_run;
+    __syncthreads();
+    float mrow;
+    {
+        float mf = -__builtin_inff();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mf = __builtin_fmaxf(mf, __builtin_fmaxf(stat[0][w][i], stat[0][w][32 + i]));
+        float l = 0.f;                                  // mf is finite: there is at least one key
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            l += stat[1][w][i] * __builtin_amdgcn_exp2f(stat[0][w][i] - mf);
+            l += stat[1][w][32 + i] * __builtin_amdgcn_exp2f(stat[0][w][32 + i] - mf);
+        }
+        mrow = mf + __builtin_amdgcn_logf(l);           // the same value in both halves and in every wave
+    }
+
+    v16f o[DTW];
+#pragma unroll
+    for (int dt = 0; dt < DTW; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+    const float qmax = (float)((1 << (g.wp - 1)) - 1);
+    const int wm2 = g.wp - 2;
+    v4i vf[DTW][2];
+    auto fetch_v = [&](int64_t kt) {
+        kt = kt < g.nt ? kt : g.nt - 1;
+#pragma unroll
+        for (int dt = 0; dt < DTW; ++dt)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                vf[dt][b] = *reinterpret_cast<const v4i*>(Vbase + (dt * g.v_ksteps + kt) * kBfUnitBytes + b * 1024 + lane16);
+    };
+    fetch_v(wave);
+    for (int64_t kt = wave; kt < g.nt; kt += NW) {
+        scores();
+        fetch_k(kt + NW);
+        v4i pf[2];
+        auto tile = [&](auto ragc) {
+            constexpr bool RAG = decltype(ragc)::value;
+            auto masked = [&](int r) { return RAG && 16 * (r >> 3) + (r & 7) >= valid; };
+            float mb[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                float sm = -__builtin_inff();
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sm = __builtin_fmaxf(sm, masked(8 * b + e) ? -__builtin_inff() : s[8 * b + e]);
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sm), __float_as_uint(sm), false, false);
+                sm = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+                const float m = __builtin_fmaf(sm, c, -mrow);
+                mb[b] = __builtin_fmaxf(m, g.pair + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                               0, __builtin_bit_cast(int, m), 0xB1, 0xF, 0xF, true)));
+            }
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                float m = __builtin_fmaxf(mb[b], g.wide + mb[b ^ 1]);
+                m = __builtin_fmaxf(m, -200.f);                       // also for all keys masked, or c = 0 with them
+                int E = (int)__builtin_floorf(m);
+                E = E < -g.bias_p ? -g.bias_p : E;
+                E = E > g.emax_p ? g.emax_p : E;
+                const int sh = wm2 - E;
+                const float off = (float)sh - mrow;
+                float el[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    float arg = __builtin_fmaf(s[8 * b + e], c, off);
+                    if (masked(8 * b + e)) arg = -__builtin_inff();
+                    const float sc = __builtin_amdgcn_exp2f(arg);
+                    float v = RND == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
+                    v = __builtin_fminf(v, qmax);                     // probabilities are not negative
+                    el[e] = __builtin_ldexpf(v, -sh);                 // an exact bfloat16 number
+                }
+#pragma unroll
+                for (int d = 0; d < 4; ++d)                           // the upper halves of two fp32 values
+                    pf[b][d] = (int)__builtin_amdgcn_perm(__float_as_uint(el[2 * d + 1]), __float_as_uint(el[2 * d]), 0x07060302u);
+            }
+        };
+        if (ragged && kt == g.nt - 1) tile(std::true_type{}); else tile(std::false_type{});
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int dt = 0; dt < DTW; ++dt)
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, vf[dt][b]), __builtin_bit_cast(v8bf, pf[b]), o[dt], 0, 0, 0);
+        fetch_v(kt + NW);
+    }
+
+    // the waves' partial results, one tile of 32 columns after the other: every output is one thread's sum over the
+    // waves.  Two buffers: the next tile is written while slower threads still read this one.
+    float* O = g.O + bz * g.o_batch_stride;
+#pragma unroll
+    for (int dt = 0; dt < DTW; ++dt) {
+        float* buf = red + (dt & 1) * NW * 16 * PITCH;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) buf[(wave * 16 + r) * PITCH + lane] = o[dt][r];
+        __syncthreads();
+        for (int t = threadIdx.x; t < 1024; t += NW * 64) {
+            // register r of lane 32h + i is element 8*(r/4) + 4h + r%4 of the tile's 32, query i
+            const int q = t >> 5, e = t & 31, r = 4 * (e >> 3) + (e & 3), l = 8 * (e & 4) + q;
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sum += buf[(w * 16 + r) * PITCH + l];
+            const int64_t row = qt * 32 + q;
+            const int d = (part * DTW + dt) * 32 + e;
+            if (row < g.Sq && d < (int)g.D) O[row * g.ldo + d] = sum;
+        }
+    }
+}
+
+template <int KS, int DTW>
+mx_status launch_attention_split(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
+    constexpr int smem = (DTW == 1 ? 1 : 2) * kSplitWaves * 16 * 65 * 4;
+    auto k0 = attention_split_kernel<KS, DTW, MX_RNE>;
+    auto k1 = attention_split_kernel<KS, DTW, MX_RTZ>;
+    static std::atomic<uint64_t> done0{0}, done1{0};
+    if (!allow_dynamic_lds((const void*)k0, smem, done0) || !allow_dynamic_lds((const void*)k1, smem, done1))
+        return MX_ERR_DEVICE;
+    g.tiles_q = g.q_tiles;
+    g.parts = parts;
+    g.total = g.tiles_q * batch * parts;
+    if (g.total > 0x7fffff00LL) return MX_ERR_UNSUPPORTED;
+    dim3 grid((unsigned)(ceil_div(g.total, 8) * 8));
+    hipLaunchKernelGGL(rnd == MX_RNE ? k0 : k1, grid, dim3(kSplitWaves * 64), smem, st, g);
+    MX_HIP_LAUNCH_CHECK();
+    return MX_OK;
+}
+
 template <int KS, int DT, int RQ>
 mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     constexpr int smem = kAttnStages * (KS + DT) * kBfUnitBytes;
@@ -433,8 +647,17 @@ mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) 
     return MX_OK;
 }
 
+// Up to 768 tiles of 32 queries (three rounds of one workgroup per compute unit) the split kernel is the faster one: the
+// 128-query workgroups take as long for one tile as for 256 (32 heads x 2048 keys x 128: 512 queries 74 us, 45 us split;
+// 8 heads x 2040 queries x 80: 66 against 39 us), past it they win (32 x 1024 x 1024 x 128: 47 against 53 us, 16 x 2040 x
+// 2048 x 128: 77 against 81 us).  With room for it every 32 columns of the result get a workgroup of their own, which
+// repeats the scores and saves registers, V and the sum (32 heads, one query, 1936 keys: 16.8 against 20.0 us); with more
+// than one such workgroup per compute unit that costs more than it saves (32 x 100 x 2048 x 128: 35 against 22 us).
 template <int KS, int DT>
 mx_status launch_attention_rq(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
+    const int64_t groups = g.q_tiles * batch;
+    if (groups * DT <= 256) return launch_attention_split<KS, 1>(g, batch, DT, rnd, st);
+    if (groups <= 768) return launch_attention_split<KS, DT>(g, batch, 1, rnd, st);
     return launch_attention<KS, DT, kAttnRQ>(g, batch, rnd, st);
 }
 
@@ -479,7 +702,7 @@ extern "C" mx_status mx_attention(int64_t batch, int64_t Sq, int64_t Sk, int64_t
     g.matrixQ = gq.matrix; g.matrixK = gk.matrix; g.matrixV = gv.matrix;
     g.q_tiles = gq.row_tiles; g.nt = gk.row_tiles; g.v_ksteps = gv.ksteps;
     g.ldo = ldo; g.o_batch_stride = o_batch_stride;
-    g.tiles_q = g.total = 0;
+    g.tiles_q = g.total = 0; g.parts = 1;
     g.c = scale * 1.4426950408889634f;
     g.wp = fp.mant_bits; g.bias_p = (1 << (fp.exp_bits - 1)) - 1;
     g.emax_p = ((1 << fp.exp_bits) - 1) - g.bias_p;

@@ -5,7 +5,7 @@ import torch
 
 from oracle import mx_oracle as orc
 from paper_2307_15517_amd import mx
-from test_gpu_parity import check_product, gpu_operand, host, random_operand
+from test_gpu_parity import check_product, gpu_operand, host, random_operand, run_attention
 
 pytestmark = pytest.mark.gpu
 
@@ -86,3 +86,16 @@ def test_matrix_product_forms_quantized_output(rt, ct, block, wx, wo):
     mx.mx_quantize_pack(y, 1, M, N, N, 0, fo, MAT, want)
     torch.cuda.synchronize()
     assert np.array_equal(host(out), host(want))
+
+
+@pytest.mark.parametrize("dim", [32, 64, 80, 128])
+@pytest.mark.parametrize("heads,Sq,Sk", [(2, 33, 16), (3, 7, 272), (12, 702, 272), (100, 258, 48)])
+def test_attention_forms(heads, Sq, Sk, dim):
+    """A workgroup per 32 queries and 32 columns, per 32 queries, per 128 queries: a ragged last tile of queries and of
+    keys, waves without a key tile, both rounding modes, one- and two-row blocks, both signs of the scale."""
+    rng = np.random.default_rng(heads * 1000 + Sk + dim)
+    Q = rng.standard_normal((heads, Sq, dim)).astype(np.float32)
+    K = rng.standard_normal((heads, Sk, dim)).astype(np.float32)
+    V = (rng.standard_normal((heads, Sk, dim)) * rng.choice([0.01, 1.0, 30.0], size=(heads, 1, dim))).astype(np.float32)
+    for rounding, rows, scale in ((mx.MX_RNE, 1, dim ** -0.5), (mx.MX_RTZ, 2 if Sq % 2 == 0 else 1, -0.7 * dim ** -0.5)):
+        run_attention(Q, K, V, (8, 7, 6, 5), scale, heads_checked=[0, heads - 1], rounding=rounding, block_rows=rows)
