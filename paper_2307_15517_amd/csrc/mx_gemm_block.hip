@@ -173,7 +173,7 @@ __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArg
 }
 
 // ------------------------------------------------------------------------------------------------
-// The form for products that fill the chip with 128 x 128 tiles and whose operands are dear to unpack: a workgroup of
+// The form for products in blocks of 64 that fill the chip with 128 x 128 tiles: a workgroup of
 // four waves owns such a tile, each wave a 64 x 64 quarter (2 x 2 row groups), so that an unpacked fragment is used
 // twice.  Fragments come straight from global memory in lane order.
 // ------------------------------------------------------------------------------------------------
@@ -510,13 +510,11 @@ mx_status launch(const GemmArgs& g, int64_t batch, hipStream_t st) {
     } else {
         // waves per tile: as many as the tiles leave the chip room for (about 4096 waves fill it)
         const int64_t tiles = g.groupsA * g.groupsB * batch;
-        // 4- and 8-bit codes unpack in an instruction or none per dword; for the other widths (about ten each) and for
-        // blocks of 64 (half the block sums per unpacked element) the 128 x 128 form is the faster one once its
-        // workgroups fill the chip twice: at 2048 x 4096 x 4096 with 6 by 5 bits, block 32, 251 against 269 us, with
-        // 8 by 8 bits, block 64, 194 against 261 us; with 8 by 4 bits it is slower, 202 against 172 us (block 32),
-        // 370 against 263 us (block 16).
-        constexpr bool kDear = B == 64 || (WA != 4 && WA != 8) || (WB != 4 && WB != 8);
-        if constexpr (kDear) {
+        // with blocks of 64 (half the block sums per unpacked element) the 128 x 128 form is the faster one once its
+        // workgroups fill the chip twice: 2048 x 4096 x 4096 with 8 by 8 bits 194 against 261 us.  With shorter blocks
+        // it never is: 218 against 212 us (6 by 5 bits, block 32), 202 against 172 us (8 by 4 bits, block 32), 366
+        // against 274 us (6 by 5 bits, block 16).
+        if constexpr (B == 64) {
             if (ceil_div(g.groupsA, 4) * ceil_div(g.groupsB, 4) * batch >= 512 && ceil_div(g.groupsA, 4) <= 65535) {
                 dim3 grid((unsigned)ceil_div(g.groupsB, 4), (unsigned)ceil_div(g.groupsA, 4), (unsigned)batch);
                 hipLaunchKernelGGL((gemm_fragment_kernel<WA, WB, B>), grid, dim3(256), 0, st, g);
