@@ -105,8 +105,8 @@ def status_string(status: int) -> str:
 
 
 def _stream(stream) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:                    # the raw handle: a torch.cuda.Stream object costs 2.8 us per call to make
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     if isinstance(stream, torch.cuda.Stream):
         return ctypes.c_void_p(stream.cuda_stream)
     return ctypes.c_void_p(int(stream))
