@@ -20,9 +20,14 @@
 // other half (one exchange per block).
 //
 // Work split: a workgroup of four waves owns 128 queries of one head (a wave: one tile of 32, its
-// Q fragments stay in registers), two workgroups per compute unit (few queries: attention_split_kernel); the K (and in sweep 2 the V^T)
-// units of one tile of 32 keys are copied global -> LDS with 16-byte direct-to-LDS loads, four
-// stages, one barrier per key tile.
+// Q fragments stay in registers), two workgroups per compute unit (few queries: attention_split_kernel); the K (and in
+// sweep 2 the V^T) units of one tile of 32 keys are copied global -> LDS with 16-byte direct-to-LDS loads, five
+// stages, one barrier per key tile.  Two query tiles per wave (363 registers, one workgroup) were slower, 128 us.
+//
+// Bound: vector issue (about 195 instructions, 33 of them exponentials, per tile and wave over both sweeps) at the clock
+// the matrix work leaves.  The second product of a key tile runs one tile behind its scores, so that no matrix
+// instruction is left without vector work under it: 16 heads x 2040 queries x 2048 keys x 128 76.7 -> 71 us, 32 x 2048 x
+// 2048 x 128 124.2 -> 122.5 us.
 #include <type_traits>
 
 #include "mx_bf16.h"
@@ -78,17 +83,13 @@ __device__ __forceinline__ void wait_vmcnt() {
 __device__ __forceinline__ void pin(float v) { asm volatile("" ::"v"(v)); }
 __device__ __forceinline__ void pin(int v) { asm volatile("" ::"v"(v)); }
 
-constexpr int kAttnStages = 4;
-// Query tiles of 32 per wave.  1: 205 registers, two workgroups per compute unit, accumulators in ordinary
-// registers (123 us at 32 x 2048 x 2048 x 128); 2: 363 registers, one workgroup, half the LDS reads per matrix
-// instruction but every score copied out of the accumulation registers (128 us).
-constexpr int kAttnRQ = 1;
+constexpr int kAttnStages = 5;
 
-// KS: K steps of 32 along the head dimension (2 or 4); DT: tiles of 32 along the head dimension of V;
-// RQ: query tiles of 32 per wave.  RQ = 2 needs more than 256 registers (one wave per SIMD); RQ = 1 leaves
-// room for two workgroups per compute unit, whose waves fill each other's waits.
-template <int KS, int DT, int RND, int RQ>
-__global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(AttnArgs g) {
+// KS: K steps of 32 along the head dimension (2 or 4); DT: tiles of 32 along the head dimension of V.  A wave owns one
+// tile of 32 queries; at most 256 registers and 80 KiB of LDS, so that two workgroups share a compute unit and their
+// waves fill each other's waits.
+template <int KS, int DT, int RND>
+__global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
     constexpr int S = kAttnStages;
     constexpr int NK = 2 * KS;                          // matrix instructions (16 elements) along the head dimension
     constexpr int STAGE = (KS + DT) * kBfUnitBytes;     // K units, then V^T units
@@ -111,19 +112,17 @@ __global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(At
     // the wave's Q fragments (right operand of S^T = K Q^T): lane 32h + i holds query i, elements 8h..8h+7.
     // A negative scale is carried by the operand (sign bits flipped: every product and sum changes
     // sign exactly), so that below the largest score is the largest argument of exp.
-    const int64_t qt0 = (bq * 4 + wave) * RQ;
+    const int64_t qt = bq * 4 + wave;
     const int flip = g.c < 0.f ? (int)0x80008000u : 0;
     const float c = __builtin_fabsf(g.c);
-    v4i qf[RQ][NK];
-#pragma unroll
-    for (int q = 0; q < RQ; ++q) {
-        int64_t rt = qt0 + q;
-        rt = rt < g.q_tiles ? rt : g.q_tiles - 1;       // tiles past the matrix re-read its last tile (never stored)
+    v4i qf[NK];
+    {
+        const int64_t rt = qt < g.q_tiles ? qt : g.q_tiles - 1;       // tiles past the matrix re-read its last tile (never stored)
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) {
-            qf[q][kk] = *reinterpret_cast<const v4i*>(Qbase + (rt * KS + (kk >> 1)) * kBfUnitBytes + (kk & 1) * 1024 + lane16);
+            qf[kk] = *reinterpret_cast<const v4i*>(Qbase + (rt * KS + (kk >> 1)) * kBfUnitBytes + (kk & 1) * 1024 + lane16);
 #pragma unroll
-            for (int d = 0; d < 4; ++d) qf[q][kk][d] ^= flip;
+            for (int d = 0; d < 4; ++d) qf[kk][d] ^= flip;
         }
     }
 
@@ -132,23 +131,22 @@ __global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(At
     const int sig = (i & 0x13) | ((i & 4) << 1) | ((i & 8) >> 1);
     const int koff = (32 * h + sig) * 16;
 
-    float m_run[RQ], l_run[RQ];                         // sweep 1: running maximum and sum of this lane's keys
-    float mrow[RQ];                                     // sweep 2: row maximum + log2(row sum), in the exp2 domain
-#pragma unroll
-    for (int q = 0; q < RQ; ++q) { m_run[q] = -__builtin_inff(); l_run[q] = 0.f; mrow[q] = 0.f; }
-    v16f o[DT][RQ];
+    float m_run = -__builtin_inff(), l_run = 0.f;       // sweep 1: running maximum and sum of this lane's keys
+    float mrow = 0.f;                                   // sweep 2: row maximum + log2(row sum), in the exp2 domain
+    v16f o[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int q = 0; q < RQ; ++q)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[dt][q][r] = 0.f;
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
     const float qmax = (float)((1 << (g.wp - 1)) - 1);
     const int wm2 = g.wp - 2;
 
     // scores of two consecutive key tiles live in two register sets: while the arithmetic on one tile's
-    // scores runs on the vector units, the matrix cores take the next tile's.
-    v16f s[2][RQ];
+    // scores runs on the vector units, the matrix cores take the next tile's.  The second product runs one tile
+    // behind: P^ of a tile is multiplied with its V under the arithmetic on the tile after it.
+    v16f s[2];
+    v4i pf[2][2];                                       // P^ of the tile in set 0 / 1, two fragments of 16 keys
+    v4i vf[DT][2];                                      // V^T of the tile before, replaced by this tile's piece by piece
 
     auto sweep = [&](auto pvc) {
         constexpr bool PV = decltype(pvc)::value;
@@ -179,7 +177,7 @@ __global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(At
             for (int q = 0; q < NL; ++q) copy16_to_lds(src[q] + kt * adv[q], lane16, lds0 + stage * STAGE + dst[q]);
         };
         // S^T of the key tile in `stage` into register set `set`: fragments first, then matrix instruction
-        // m = 0 .. 2*NK-1 one at a time (the caller slots vector work between them)
+        // kk = 0 .. NK-1 one at a time (the caller slots vector work between them)
         v4i kf[NK];
         auto read_k = [&](int stage) {
             const uint8_t* st = smem + stage * STAGE;
@@ -187,103 +185,99 @@ __global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(At
             for (int kk = 0; kk < NK; ++kk)
                 kf[kk] = *reinterpret_cast<const v4i*>(st + (kk >> 1) * kBfUnitBytes + (kk & 1) * 1024 + koff);
         };
-        auto score_mfma = [&](int m, auto setc) {
+        auto score_mfma = [&](int kk, auto setc) {
             constexpr int set = decltype(setc)::value;
-            const int kk = m / RQ, q = m % RQ;              // consecutive instructions never share an accumulator
             v16f zero;
 #pragma unroll
             for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-            s[set][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, kf[kk]), __builtin_bit_cast(v8bf, qf[q][kk]),
-                                                                kk == 0 ? zero : s[set][q], 0, 0, 0);
+            s[set] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, kf[kk]), __builtin_bit_cast(v8bf, qf[kk]),
+                                                             kk == 0 ? zero : s[set], 0, 0, 0);
         };
-        // One key tile: tile kt's scores are in set kt % 2, tile kt+1's are started into the other set.
-        // RAG: keys past Sk are masked (only the last tile can have them).
+        auto out_mfma = [&](int m, auto setc) {           // consecutive ones never share an accumulator (DT > 1)
+            constexpr int set = decltype(setc)::value;
+            const int b = m / DT, dt = m % DT;
+            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, vf[dt][b]),
+                                                            __builtin_bit_cast(v8bf, pf[set][b]), o[dt], 0, 0, 0);
+        };
+        auto read_v = [&](int m, int stage) {
+            const int b = m / DT, dt = m % DT;
+            vf[dt][b] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + (KS + dt) * kBfUnitBytes + b * 1024 + lane16);
+        };
+        // One key tile: tile kt's scores are in set kt % 2, tile kt+1's are started into the other set, and (sweep 2)
+        // tile kt-1's P^ V is added.  RAG: keys past Sk are masked (only the last tile can have them).
         // The instruction order is written out and pinned: one matrix instruction, then its share of the
-        // vector work (given as numbered units), so that both pipes stay busy with one wave per SIMD.
+        // vector work (given as numbered units), so that both pipes stay busy.
         auto body = [&](int64_t kt, int cur, auto setc, auto ragc) {
             constexpr int set = decltype(setc)::value;
             constexpr bool RAG = decltype(ragc)::value;
             const auto nset = std::integral_constant<int, set ^ 1>{};
-            const int nxt = cur + 1 == S ? 0 : cur + 1;
-            const uint8_t* st = smem + cur * STAGE;
-            v4i vf[PV ? DT : 1][2];
-            if constexpr (PV) {
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                    for (int b = 0; b < 2; ++b)
-                        vf[dt][b] = *reinterpret_cast<const v4i*>(st + (KS + dt) * kBfUnitBytes + b * 1024 + lane16);
-            }
-            // copies in flight, oldest first: tiles kt+1 .. kt+S-1.  Tile kt+1 has landed once only the newest
-            // S-2 tiles' copies are outstanding; the barrier publishes it and tells that every wave has taken
-            // what it needs of tile kt's stage, which the copy of tile kt+S overwrites.
-            wait_vmcnt<(S - 2) * NL>();
+            const int nxt = cur + 1 == S ? 0 : cur + 1, prv = cur == 0 ? S - 1 : cur - 1;
+            // copies in flight, oldest first: tiles kt+1 .. kt+S-2.  Tile kt+1 has landed once only the newest
+            // S-3 tiles' copies are outstanding; the barrier publishes it and tells that every wave has taken
+            // what it needs of tile kt-1's stage, which the copy of tile kt+S-1 overwrites.
+            wait_vmcnt<(S - 3) * NL>();
             __syncthreads();
-            issue(kt + S, cur);
+            issue(kt + S - 1, prv);
             read_k(nxt);
             const int valid = (int)(g.Sk - kt * 32) - 8 * h;   // this lane's key 16*b + e is real iff 16*b + e < valid
             auto masked = [&](int r) { return RAG && 16 * (r >> 3) + (r & 7) >= valid; };
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!PV) {
-                // units of one query tile: 0 = tile maximum and the new running maximum, 1..4 = four
-                // exponentials each, 5 = the running sum
+                // units: 0 = tile maximum and the new running maximum, 1..4 = four exponentials each, 5 = the running sum
                 constexpr int NU = 6;
-                float m_old[RQ], m_use[RQ], sum[RQ];
-                auto unit = [&](int q, int u) {
+                float m_old, m_use, sum;
+                auto unit = [&](int u) {
                     if (u == 0) {
                         float sm = -__builtin_inff();
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) sm = __builtin_fmaxf(sm, masked(r) ? -__builtin_inff() : s[set][q][r]);
-                        m_old[q] = m_run[q];
-                        m_run[q] = __builtin_fmaxf(m_run[q], sm * c);
-                        m_use[q] = m_run[q] == -__builtin_inff() ? 0.f : m_run[q];
-                        sum[q] = 0.f;
-                        pin(m_use[q]);
+                        for (int r = 0; r < 16; ++r) sm = __builtin_fmaxf(sm, masked(r) ? -__builtin_inff() : s[set][r]);
+                        m_old = m_run;
+                        m_run = __builtin_fmaxf(m_run, sm * c);
+                        m_use = m_run == -__builtin_inff() ? 0.f : m_run;
+                        sum = 0.f;
+                        pin(m_use);
                     } else if (u < 5) {
 #pragma unroll
                         for (int r = 4 * (u - 1); r < 4 * u; ++r) {
-                            float arg = __builtin_fmaf(s[set][q][r], c, -m_use[q]);
+                            float arg = __builtin_fmaf(s[set][r], c, -m_use);
                             if (masked(r)) arg = -__builtin_inff();   // also when c is 0
-                            sum[q] += __builtin_amdgcn_exp2f(arg);
+                            sum += __builtin_amdgcn_exp2f(arg);
                         }
-                        pin(sum[q]);
+                        pin(sum);
                     } else {
-                        l_run[q] = l_run[q] * __builtin_amdgcn_exp2f(m_old[q] - m_use[q]) + sum[q];
-                        pin(l_run[q]);
+                        l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
+                        pin(l_run);
                     }
                 };
-                constexpr int NM = RQ * NK;
 #pragma unroll
-                for (int m = 0; m < NM; ++m) {
+                for (int m = 0; m < NK; ++m) {
                     score_mfma(m, nset);
 #pragma unroll
-                    for (int x = m * (RQ * NU) / NM; x < (m + 1) * (RQ * NU) / NM; ++x) unit(x / NU, x % NU);
+                    for (int x = m * NU / NK; x < (m + 1) * NU / NK; ++x) unit(x);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
-                // One query tile = two blocks of 16 keys, this lane's half of each.  With a = log2 of the
+                // The tile is two blocks of 16 keys, this lane's half of each.  With a = log2 of the
                 // probability, the block exponent is the integer part of the largest a (the quantizer's
                 // floor(log2 max)) and the mantissas are round(2^(a - E + w - 2)): the arithmetic of mx_quantize
                 // on P.  exp2 grows with the score, so the maximum is taken over the scores themselves.
                 // Units: 0 = half-block maxima, their exchange with the other lane half, the exponents;
-                // 1..16 = one element each; 17, 18 = operand registers.  (Taking the elements four at a time,
-                // operation by operation, measured slower: the exponentials then queue behind each other.)
-                constexpr int NU = 19;
-                float el[RQ][16], off[RQ][2];
-                int sh[RQ][2];
-                v4i pf[RQ][2];
-                auto unit = [&](int q, int u) {
+                // 1..8 = two elements each, packed into their operand register.
+                constexpr int NU = 9;
+                float off[2];
+                int sh[2];
+                auto unit = [&](int u) {
                     if (u == 0) {
                         float mb[2];
 #pragma unroll
                         for (int b = 0; b < 2; ++b) {
                             float sm = -__builtin_inff();
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) sm = __builtin_fmaxf(sm, masked(8 * b + e) ? -__builtin_inff() : s[set][q][8 * b + e]);
+                            for (int e = 0; e < 8; ++e) sm = __builtin_fmaxf(sm, masked(8 * b + e) ? -__builtin_inff() : s[set][8 * b + e]);
                             // both lane halves get the larger of the two halves' values
                             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sm), __float_as_uint(sm), false, false);
                             sm = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-                            float m = __builtin_fmaf(sm, c, -mrow[q]);
+                            float m = __builtin_fmaf(sm, c, -mrow);
                             // two-row blocks: queries 2t and 2t+1 (neighbouring lanes) share the exponent, the larger
                             // of the two log-probabilities; one-row blocks add -inf to the neighbour's and keep their own
                             m = __builtin_fmaxf(m, g.pair + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
@@ -298,68 +292,64 @@ __global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(At
                             int E = (int)__builtin_floorf(m);
                             E = E < -g.bias_p ? -g.bias_p : E;
                             E = E > g.emax_p ? g.emax_p : E;
-                            sh[q][b] = wm2 - E;
-                            off[q][b] = (float)sh[q][b] - mrow[q];
-                            pin(off[q][b]);
+                            sh[b] = wm2 - E;
+                            off[b] = (float)sh[b] - mrow;
+                            pin(off[b]);
                         }
-                    } else if (u < 17) {
-                        const int r = u - 1, b = r >> 3;
-                        float arg = __builtin_fmaf(s[set][q][r], c, off[q][b]);
-                        if (masked(r)) arg = -__builtin_inff();
-                        const float sc = __builtin_amdgcn_exp2f(arg);
-                        float v = RND == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
-                        v = __builtin_fminf(v, qmax);                         // probabilities are not negative
-                        el[q][r] = __builtin_ldexpf(v, -sh[q][b]);            // an exact bfloat16 number
-                        pin(el[q][r]);
                     } else {
-                        const int b = u - 17;
+                        const int b = (u - 1) >> 2, d = (u - 1) & 3;
+                        float el[2];
 #pragma unroll
-                        for (int d = 0; d < 4; ++d)                           // the upper halves of two fp32 values
-                            pf[q][b][d] = (int)__builtin_amdgcn_perm(__float_as_uint(el[q][8 * b + 2 * d + 1]),
-                                                                     __float_as_uint(el[q][8 * b + 2 * d]), 0x07060302u);
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) pin(pf[q][b][d]);
+                        for (int x = 0; x < 2; ++x) {
+                            const int r = 8 * b + 2 * d + x;
+                            float arg = __builtin_fmaf(s[set][r], c, off[b]);
+                            if (masked(r)) arg = -__builtin_inff();
+                            const float sc = __builtin_amdgcn_exp2f(arg);
+                            float v = RND == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
+                            v = __builtin_fminf(v, qmax);                     // probabilities are not negative
+                            el[x] = __builtin_ldexpf(v, -sh[b]);              // an exact bfloat16 number
+                        }
+                        // the upper halves of two fp32 values
+                        pf[set][b][d] = (int)__builtin_amdgcn_perm(__float_as_uint(el[1]), __float_as_uint(el[0]), 0x07060302u);
+                        pin(pf[set][b][d]);
                     }
                 };
-                auto out_mfma = [&](int q, int m) {
-                    const int b = m / DT, dt = m % DT;
-                    o[dt][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, vf[dt][b]),
-                                                                       __builtin_bit_cast(v8bf, pf[q][b]), o[dt][q], 0, 0, 0);
-                };
-                // the next tile's scores under the vector work of the first query tile, every query tile's
-                // second product under the vector work of the following one, the last one's bare
-                constexpr int NM = RQ * NK;
-                unit(0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                // matrix instructions in turn: the second product of the tile before (each followed by the read of this
+                // tile's V into the registers it has freed) and the next tile's scores; vector work under all of them
+                constexpr int NO = 2 * DT, NM = NO + NK;
+                int mo = 0, mk = 0;
 #pragma unroll
                 for (int m = 0; m < NM; ++m) {
-                    score_mfma(m, nset);
-#pragma unroll
-                    for (int x = 1 + m * (NU - 1) / NM; x < 1 + (m + 1) * (NU - 1) / NM; ++x) unit(0, x);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int q = 1; q < RQ; ++q)
-#pragma unroll
-                    for (int m = 0; m < 2 * DT; ++m) {
-                        out_mfma(q - 1, m);
-#pragma unroll
-                        for (int x = m * NU / (2 * DT); x < (m + 1) * NU / (2 * DT); ++x) unit(q, x);
-                        __builtin_amdgcn_sched_barrier(0);
+                    if ((m + 1) * NO / NM > mo) {
+                        out_mfma(mo, nset);
+                        read_v(mo, cur);
+                        ++mo;
+                    } else {
+                        score_mfma(mk, nset);
+                        ++mk;
                     }
 #pragma unroll
-                for (int m = 0; m < 2 * DT; ++m) out_mfma(RQ - 1, m);
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int x = m * NU / NM; x < (m + 1) * NU / NM; ++x) unit(x);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         };
 
+        if constexpr (PV) {                               // no tile before the first one: adds zeros
 #pragma unroll
-        for (int st = 0; st < S; ++st) issue(st, st);
-        wait_vmcnt<(S - 1) * NL>();
+            for (int b = 0; b < 2; ++b) {
+                pf[1][b] = v4i{0, 0, 0, 0};
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) vf[dt][b] = v4i{0, 0, 0, 0};
+            }
+        }
+#pragma unroll
+        for (int st = 0; st < S - 1; ++st) issue(st, st);
+        wait_vmcnt<(S - 2) * NL>();
         __syncthreads();
         read_k(0);
 #pragma unroll
-        for (int m = 0; m < RQ * NK; ++m) score_mfma(m, std::integral_constant<int, 0>{});
+        for (int m = 0; m < NK; ++m) score_mfma(m, std::integral_constant<int, 0>{});
         // tiles in pairs (the register sets alternate); the last one or two tiles take the masking form
         int64_t kt = 0;
         int cur = 0;
@@ -369,20 +359,28 @@ __global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(At
             body(kt, cur, std::integral_constant<int, 1>{}, std::false_type{}); advance();
         }
         body(kt, cur, std::integral_constant<int, 0>{}, std::true_type{}); advance();
-        if (kt < g.nt) { body(kt, cur, std::integral_constant<int, 1>{}, std::true_type{}); advance(); }
+        if (kt < g.nt) {
+            body(kt, cur, std::integral_constant<int, 1>{}, std::true_type{}); advance();
+            if constexpr (PV) {
+#pragma unroll
+                for (int m = 0; m < 2 * DT; ++m) out_mfma(m, std::integral_constant<int, 1>{});
+            }
+        } else if constexpr (PV) {
+#pragma unroll
+            for (int m = 0; m < 2 * DT; ++m) out_mfma(m, std::integral_constant<int, 0>{});
+        }
         wait_vmcnt<0>();                                  // the clamped tail copies must not outlive the stage's next use
         __syncthreads();
     };
 
     sweep(std::false_type{});
     // row statistics: the two lane halves hold disjoint keys of the same query
-#pragma unroll
-    for (int q = 0; q < RQ; ++q) {
-        const float mo = __shfl_xor(m_run[q], 32, 64), lo = __shfl_xor(l_run[q], 32, 64);
-        const float mf = __builtin_fmaxf(m_run[q], mo);  // finite: there is at least one key
-        const float a = __fmul_rn(l_run[q], __builtin_amdgcn_exp2f(m_run[q] - mf));
+    {
+        const float mo = __shfl_xor(m_run, 32, 64), lo = __shfl_xor(l_run, 32, 64);
+        const float mf = __builtin_fmaxf(m_run, mo);     // finite: there is at least one key
+        const float a = __fmul_rn(l_run, __builtin_amdgcn_exp2f(m_run - mf));
         const float b = __fmul_rn(lo, __builtin_amdgcn_exp2f(mo - mf));
-        mrow[q] = mf + __builtin_amdgcn_logf(__fadd_rn(a, b));             // the same value in both halves
+        mrow = mf + __builtin_amdgcn_logf(__fadd_rn(a, b));                   // the same value in both halves
     }
     sweep(std::true_type{});
 
@@ -390,27 +388,24 @@ __global__ __launch_bounds__(256, RQ == 1 ? 2 : 1) void attention_bf16_kernel(At
     float* O = g.O + bz * g.o_batch_stride;
     auto store = [&](auto vecc) {
         constexpr bool VEC = decltype(vecc)::value;
+        const int64_t row = qt * 32 + i;
+        if (row < g.Sq) {
 #pragma unroll
-        for (int q = 0; q < RQ; ++q) {
-            const int64_t row = (qt0 + q) * 32 + i;
-            if (row < g.Sq) {
+            for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
+                for (int gq = 0; gq < 4; ++gq) {
+                    const int d = dt * 32 + 8 * gq + 4 * h;
+                    if (d < (int)g.D) {                      // D is a multiple of 16: four elements or none
+                        float* dst = O + row * g.ldo + d;
+                        if constexpr (VEC) {
+                            *reinterpret_cast<float4*>(dst) = make_float4(o[dt][4 * gq], o[dt][4 * gq + 1],
+                                                                          o[dt][4 * gq + 2], o[dt][4 * gq + 3]);
+                        } else {
 #pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        const int d = dt * 32 + 8 * gq + 4 * h;
-                        if (d < (int)g.D) {                  // D is a multiple of 16: four elements or none
-                            float* dst = O + row * g.ldo + d;
-                            if constexpr (VEC) {
-                                *reinterpret_cast<float4*>(dst) = make_float4(o[dt][q][4 * gq], o[dt][q][4 * gq + 1],
-                                                                              o[dt][q][4 * gq + 2], o[dt][q][4 * gq + 3]);
-                            } else {
-#pragma unroll
-                                for (int j = 0; j < 4; ++j) dst[j] = o[dt][q][4 * gq + j];
-                            }
+                            for (int j = 0; j < 4; ++j) dst[j] = o[dt][4 * gq + j];
                         }
                     }
-            }
+                }
         }
     };
     if (g.vec) store(std::true_type{}); else store(std::false_type{});
@@ -629,16 +624,16 @@ mx_status launch_attention_split(AttnArgs& g, int64_t batch, int parts, int rnd,
     return MX_OK;
 }
 
-template <int KS, int DT, int RQ>
+template <int KS, int DT>
 mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     constexpr int smem = kAttnStages * (KS + DT) * kBfUnitBytes;
-    static_assert(smem * (RQ == 1 ? 2 : 1) <= 160 * 1024, "LDS budget of one compute unit");
-    auto k0 = attention_bf16_kernel<KS, DT, MX_RNE, RQ>;
-    auto k1 = attention_bf16_kernel<KS, DT, MX_RTZ, RQ>;
+    static_assert(smem * 2 <= 160 * 1024, "LDS budget of one compute unit");
+    auto k0 = attention_bf16_kernel<KS, DT, MX_RNE>;
+    auto k1 = attention_bf16_kernel<KS, DT, MX_RTZ>;
     static std::atomic<uint64_t> done0{0}, done1{0};
     if (!allow_dynamic_lds((const void*)k0, smem, done0) || !allow_dynamic_lds((const void*)k1, smem, done1))
         return MX_ERR_DEVICE;
-    g.tiles_q = ceil_div(g.Sq, 128 * RQ);
+    g.tiles_q = ceil_div(g.Sq, 128);
     g.total = g.tiles_q * batch;
     if (g.total > 0x7fffff00LL) return MX_ERR_UNSUPPORTED;
     dim3 grid((unsigned)(ceil_div(g.total, 8) * 8));
@@ -654,11 +649,11 @@ mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) 
 // repeats the scores and saves registers, V and the sum (32 heads, one query, 1936 keys: 16.8 against 20.0 us); with more
 // than one such workgroup per compute unit that costs more than it saves (32 x 100 x 2048 x 128: 35 against 22 us).
 template <int KS, int DT>
-mx_status launch_attention_rq(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
+mx_status pick_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     const int64_t groups = g.q_tiles * batch;
     if (groups * DT <= 256) return launch_attention_split<KS, 1>(g, batch, DT, rnd, st);
     if (groups <= 768) return launch_attention_split<KS, DT>(g, batch, 1, rnd, st);
-    return launch_attention<KS, DT, kAttnRQ>(g, batch, rnd, st);
+    return launch_attention<KS, DT>(g, batch, rnd, st);
 }
 
 }  // namespace
@@ -712,6 +707,6 @@ extern "C" mx_status mx_attention(int64_t batch, int64_t Sq, int64_t Sk, int64_t
     const int dt = (int)ceil_div(D, 32);
     hipStream_t st = (hipStream_t)stream;
     if (gq.ksteps == 2)
-        return dt == 1 ? launch_attention_rq<2, 1>(g, batch, fp.rounding, st) : launch_attention_rq<2, 2>(g, batch, fp.rounding, st);
-    return dt == 3 ? launch_attention_rq<4, 3>(g, batch, fp.rounding, st) : launch_attention_rq<4, 4>(g, batch, fp.rounding, st);
+        return dt == 1 ? pick_attention<2, 1>(g, batch, fp.rounding, st) : pick_attention<2, 2>(g, batch, fp.rounding, st);
+    return dt == 3 ? pick_attention<4, 3>(g, batch, fp.rounding, st) : pick_attention<4, 4>(g, batch, fp.rounding, st);
 }
