@@ -203,6 +203,14 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
+// LDS of the quantized ending: the waves' turn-around tiles of 32 rows lie where the stages were, one per matrix wave, or
+// two when copy waves help; the bias of the 64*TN columns lies behind both.
+template <int TN, int WS> struct QoutLds {
+    static constexpr int kPitch = 32 * TN + 4;           // floats; the skew spreads the rows over the banks
+    static constexpr int kTiles = (WS ? 8 : 4) * 32 * kPitch * 4;
+    static constexpr int bias_offset(int pipe) { return pipe > kTiles ? pipe : kTiles; }
+};
+
 // S: LDS stages.  The stage of step ks is free once its fragments are in registers, i.e. from
 // the barrier of step ks on, so the copy of step ks+S is issued during step ks.
 // OCC: workgroups the register and LDS budget must leave room for on one compute unit.
@@ -386,6 +394,12 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
     // Inside a step the MFMAs (operands already in registers) are issued at once, and the LDS reads
     // for the next step, the copies for step ks+3 and the scale traffic are slotted between them so
     // that the matrix pipe never waits for them.
+    // the bias of the workgroup's columns, decoded by the matrix waves while the first stage is on its way
+    float* bias_lds = reinterpret_cast<float*>(smem + QoutLds<TN, WS>::bias_offset(kStages * STAGE + 2 * SCALES));
+    if constexpr (QO != 0) {
+        if (!copier && g.bias_mant != nullptr)
+            for (int c = threadIdx.x; c < 64 * TN; c += 256) bias_lds[c] = bias_value(g, bn * (64 * TN) + c);
+    }
     if (g.ksteps > 0) {
         if (copies) {
             issue(0, 0);
@@ -430,8 +444,9 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
             cstep(std::integral_constant<int, 3>{});
         }
         wait_vmcnt<0>();                                  // the clamped tail copies must not outlive the LDS
-        return;
+        if constexpr (QO == 0) return;                    // with a quantized ending they go on to its barriers
     }
+    if (!copier)
     for (int64_t ks4 = 0; ks4 < groups; ++ks4) {
 #pragma unroll
         for (int t = 0; t < RA; ++t) scA[t] = nxA[t];
@@ -492,33 +507,43 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
         // holds the 32 consecutive elements of row i' that a fragment of the next product's left operand
         // gives it, and runs the quantizer of mx_quantize_pack on them.
         static_assert(RB % 2 == 0, "a wave covers whole K steps of the output");
-        constexpr int PITCH = 32 * RB + 4;               // floats; the skew spreads the rows over the banks
-        // LDS: four tiles of 32 x PITCH floats, then the bias of the 64*TN columns (the launch sizes the
-        // allocation for whichever is larger, this or the stages)
-        __syncthreads();                                 // every wave is done reading the stages
+        constexpr int PITCH = QoutLds<TN, WS>::kPitch;
+        __syncthreads();                                 // every wave is done reading the stages, the bias is in LDS
         float* tile = reinterpret_cast<float*>(smem) + wave * (32 * PITCH);
-        float* bias_lds = reinterpret_cast<float*>(smem) + 4 * 32 * PITCH;
-        if (g.bias_mant != nullptr) {                    // the bias of the workgroup's columns, decoded once
-            for (int c = threadIdx.x; c < 64 * TN; c += 256) bias_lds[c] = bias_value(g, bn * (64 * TN) + c);
-            __syncthreads();
-        }
         uint8_t* obase = g.out + bz * g.go.matrix;
-#pragma unroll
-        for (int ta = 0; ta < RA; ++ta) {
+        auto turn = [&](int ta, float* to) {
 #pragma unroll
             for (int tb = 0; tb < RB; ++tb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    tile[(8 * (r >> 2) + 4 * h + (r & 3)) * PITCH + tb * 32 + i] = __builtin_ldexpf(acc[ta][tb][r], g.eadj);
-            __builtin_amdgcn_wave_barrier();
+                    to[(8 * (r >> 2) + 4 * h + (r & 3)) * PITCH + tb * 32 + i] = __builtin_ldexpf(acc[ta][tb][r], g.eadj);
+        };
+        auto quantize = [&](int ta, const float* from) {
             const int64_t rt = rtA0 + ta, row = rt * 32 + i;
 #pragma unroll
             for (int ksl = 0; ksl < RB / 2; ++ksl) {
                 const int64_t ks = rtB0 / 2 + ksl;        // K step of the output operand
-                quantize_step<QO>(g, obase, rt, row, ks, tile + i * PITCH + ksl * 64 + h * 32,
+                quantize_step<QO>(g, obase, rt, row, ks, from + i * PITCH + ksl * 64 + h * 32,
                                   bias_lds + wn * (32 * RB) + ksl * 64 + h * 32, lane);
             }
-            __builtin_amdgcn_wave_barrier();
+        };
+        if constexpr (WS) {
+            // the copy wave of the same position takes one of the two row tiles: turning and quantizing is a serial
+            // chain that nothing else covers with one workgroup per compute unit (2000 x 4096 x 4096, 8 by 4 bits:
+            // 39.2 us with the matrix waves alone, 36.7 us this way; 333 x 11008 x 4096: 32.7 -> 29.9 us)
+            static_assert(RA == 2, "one row tile per wave");
+            float* tile1 = tile + 4 * 32 * PITCH;
+            if (!copier) { turn(0, tile); turn(1, tile1); }
+            __syncthreads();
+            quantize(copier ? 1 : 0, copier ? tile1 : tile);
+        } else {
+#pragma unroll
+            for (int ta = 0; ta < RA; ++ta) {
+                turn(ta, tile);
+                __builtin_amdgcn_wave_barrier();
+                quantize(ta, tile);
+                __builtin_amdgcn_wave_barrier();
+            }
         }
         return;
     }
@@ -726,11 +751,10 @@ mx_status launch_scaled_split(ScaledArgs& g, int64_t batch, hipStream_t st) {
 
 template <int PA, int PB, int TM, int TN, int S, int OCC, int QO = 0, int WS = 0>
 mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
-    static_assert(WS == 0 || (OCC == 1 && QO == 0), "copy waves: one workgroup per compute unit, fp32 result");
+    static_assert(WS == 0 || OCC == 1, "copy waves: one workgroup per compute unit");
     constexpr int UA = (PA == 2) ? 2 * TM : TM, UB = (PB == 2) ? 2 * TN : TN;
     constexpr int pipe = S * (UA + UB) * kUnitBytes + 2 * (2 * TM + 2 * TN) * 256;
-    constexpr int turn = QO == 0 ? 0 : 4 * 32 * (32 * TN + 4) * 4 + 64 * TN * 4;     // quantized ending
-    constexpr int smem = pipe > turn ? pipe : turn;
+    constexpr int smem = QO == 0 ? pipe : QoutLds<TN, WS>::bias_offset(pipe) + 64 * TN * 4;
     static_assert(smem * OCC <= 160 * 1024, "LDS budget of one compute unit");
     auto kern = gemm_scaled_kernel<PA, PB, TM, TN, S, OCC, QO, WS>;
     static std::atomic<uint64_t> done{0};
@@ -784,8 +808,7 @@ mx_status pick_tile(ScaledArgs& g, int64_t batch, hipStream_t st) {
     }
     if constexpr (PB == 1) {
         if (tiles >= MX_SCALED_TWO_PER_CU_TILES) return launch_scaled<PA, PB, 2, 4, 3, 2, QO>(g, batch, st);
-        if constexpr (QO == 0) return launch_scaled<PA, PB, 2, 4, 5, 1, 0, 1>(g, batch, st);
-        return launch_scaled<PA, PB, 2, 4, 4, 1, QO>(g, batch, st);
+        return launch_scaled<PA, PB, 2, 4, 5, 1, QO, 1>(g, batch, st);
     } else {
         static_assert(QO == 0, "the quantized ending is built for one-piece right operands");
         return launch_scaled<PA, PB, 2, 4, 3, 1>(g, batch, st);
