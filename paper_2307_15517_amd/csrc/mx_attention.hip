@@ -642,17 +642,22 @@ mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) 
     return MX_OK;
 }
 
-// Up to 768 tiles of 32 queries (three rounds of one workgroup per compute unit) the split kernel is the faster one: the
-// 128-query workgroups take as long for one tile as for 256 (32 heads x 2048 keys x 128: 512 queries 74 us, 45 us split;
-// 8 heads x 2040 queries x 80: 66 against 39 us), past it they win (32 x 1024 x 1024 x 128: 47 against 53 us, 16 x 2040 x
-// 2048 x 128: 77 against 81 us).  With room for it every 32 columns of the result get a workgroup of their own, which
+// The split kernel takes one round of workgroups in a time that hardly depends on the number of keys while they are few,
+// the 128-query workgroups one tile of keys at a time for as long whether there is one of them or 256: with one round
+// the split kernel is the faster one (8 heads x 512 queries x 2048 keys x 128: 70 us, 22 us split; 32 x 256 x 32 x 128:
+// 7.5 and 7.1 us), with two from ten key tiles on (16 x 1024 x 256 x 128: 15.0 and 16.3 us, 16 x 1024 x 320 x 96: 16.6
+// and 15.1 us, 32 x 512 x 2048 x 128: 74 and 45 us), with three from about forty (24 x 1024 x 960 x 128: 38.6 and 39.6 us,
+// 24 x 1024 x 2048 x 128: 75 and 64 us), beyond that no more (16 x 2040 x 2048 x 128: 71 and 81 us).
+// With room for it every 32 columns of the result get a workgroup of their own, which
 // repeats the scores and saves registers, V and the sum (32 heads, one query, 1936 keys: 16.8 against 20.0 us); with more
 // than one such workgroup per compute unit that costs more than it saves (32 x 100 x 2048 x 128: 35 against 22 us).
 template <int KS, int DT>
 mx_status pick_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     const int64_t groups = g.q_tiles * batch;
     if (groups * DT <= 256) return launch_attention_split<KS, 1>(g, batch, DT, rnd, st);
-    if (groups <= 768) return launch_attention_split<KS, DT>(g, batch, 1, rnd, st);
+    const int64_t rounds = ceil_div(groups, DT <= 2 ? 512 : 256);      // two workgroups of at most 128 registers share a compute unit
+    if (groups <= 768 && g.nt >= (rounds == 1 ? 1 : rounds == 2 ? 10 : 40))
+        return launch_attention_split<KS, DT>(g, batch, 1, rnd, st);
     return launch_attention<KS, DT>(g, batch, rnd, st);
 }
 

@@ -89,7 +89,7 @@ def test_matrix_product_forms_quantized_output(rt, ct, block, wx, wo):
 
 
 @pytest.mark.parametrize("dim", [32, 64, 80, 128])
-@pytest.mark.parametrize("heads,Sq,Sk", [(2, 33, 16), (3, 7, 272), (12, 702, 272), (100, 258, 48)])
+@pytest.mark.parametrize("heads,Sq,Sk", [(2, 33, 16), (3, 7, 272), (12, 702, 272), (10, 702, 272), (12, 702, 336), (100, 258, 48)])
 def test_attention_forms(heads, Sq, Sk, dim):
     """A workgroup per 32 queries and 32 columns, per 32 queries, per 128 queries: a ragged last tile of queries and of
     keys, waves without a key tile, both rounding modes, one- and two-row blocks, both signs of the scale."""
