@@ -54,6 +54,7 @@ extern "C" mx_status mx_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, con
         return gemm_bf16(batch, M, N, K, A_packed, B_packed, Y, ldy, batch_stride_y, (hipStream_t)stream);
     if (layout == MX_LAYOUT_MATRIX)
         return gemm_scaled(batch, M, N, K, A_packed, fa, B_packed, fb, Y, ldy, batch_stride_y, (hipStream_t)stream);
+    if (M > 65535LL * 128) return MX_ERR_UNSUPPORTED;      // rows of 128 x 128 tiles lie along a 16-bit grid dimension
     const GemmArgs g = fragment_args(M, N, K, A_packed, fa, B_packed, fb, Y, ldy, batch_stride_y);
     hipStream_t st = (hipStream_t)stream;
     if (M <= 2) {      // one or two rows: dot-product kernel; three to eight: MFMA streaming kernel

@@ -148,3 +148,14 @@ def test_linear_workspace_bytes():
 
 def test_struct_layout():
     assert ctypes.sizeof(mx.mx_format) == 20
+
+
+def test_sizes_past_the_launch_limits_are_refused(lib):
+    """Products whose row count or K goes past what the kernels address, with pointers that nothing may touch: refused as
+    unsupported whatever tile the other sizes would select, before any launch."""
+    f8, f4 = mx.fmt(32, 8), mx.fmt(32, 4)
+    for block in (16, 32, 64):
+        fa, fb = mx.fmt(block, 8), mx.fmt(block, 4)
+        for N in (32, 4096):
+            assert mx.mx_gemm(1, 65535 * 128 + 1, N, 64, 256, fa, 512, fb, mx.MX_LAYOUT_FRAGMENT, 1024, N, 0, stream=0,
+                              check=False) == mx.MX_ERR_UNSUPPORTED
