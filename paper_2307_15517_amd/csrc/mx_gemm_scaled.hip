@@ -763,7 +763,6 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
     const int64_t tiles_m = ceil_div(QO ? g.go.row_tiles * 32 : g.M, 64 * TM);
     const int64_t tiles_n = ceil_div(QO ? g.go.ksteps * 64 : g.N, 64 * TN);
     if (tiles_m * tiles_n > 0x7fffffffLL) return MX_ERR_UNSUPPORTED;
-    if (g.ksteps * kUnitBytes > 0x7fffffffLL) return MX_ERR_UNSUPPORTED;       // 32-bit offsets along K
     g.tiles_m = (int32_t)tiles_m;
     g.tiles_n = (int32_t)tiles_n;
     dim3 grid((unsigned)(ceil_div(tiles_m * tiles_n, 8) * 8), (unsigned)batch);
@@ -789,6 +788,8 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
 // copies of a K step are requested four steps ahead).
 template <int PA, int PB, int QO = 0>
 mx_status pick_tile(ScaledArgs& g, int64_t batch, hipStream_t st) {
+    // 32-bit offsets along K in the staged forms, so the same limit whatever the tile
+    if (g.ksteps * kUnitBytes > 0x7fffffffLL) return MX_ERR_UNSUPPORTED;
     const int64_t rows = ceil_div(g.M, 32), cols = ceil_div(g.N, 32);
     auto groups = [&](int ra, int rb) { return ceil_div(rows, ra) * ceil_div(cols, rb) * batch; };
     constexpr int64_t kCus = 256;

@@ -159,3 +159,9 @@ def test_sizes_past_the_launch_limits_are_refused(lib):
         for N in (32, 4096):
             assert mx.mx_gemm(1, 65535 * 128 + 1, N, 64, 256, fa, 512, fb, mx.MX_LAYOUT_FRAGMENT, 1024, N, 0, stream=0,
                               check=False) == mx.MX_ERR_UNSUPPORTED
+    for M, N in ((16, 32), (33, 4096), (4096, 8192)):
+        for wa, wb in ((8, 4), (4, 4), (8, 8), (3, 8)):
+            assert mx.mx_gemm(1, M, N, 699052 * 64, 256, mx.fmt(32, wa), 512, mx.fmt(32, wb), mx.MX_LAYOUT_MATRIX, 1024, N, 0,
+                              stream=0, check=False) == mx.MX_ERR_UNSUPPORTED
+        assert mx.mx_gemm_q(1, M, N, 699052 * 64, 256, f8, 512, f4, mx.MX_LAYOUT_MATRIX, 0, 0, f4, f8, 1024, stream=0,
+                            check=False) == mx.MX_ERR_UNSUPPORTED
