@@ -173,9 +173,9 @@ __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArg
 }
 
 // ------------------------------------------------------------------------------------------------
-// The form for products in blocks of 64 that fill the chip with 128 x 128 tiles: a workgroup of
-// four waves owns such a tile, each wave a 64 x 64 quarter (2 x 2 row groups), so that an unpacked fragment is used
-// twice.  Fragments come straight from global memory in lane order.
+// The form for large products (see launch): a workgroup of four waves owns a 128 x 128 tile, each wave a 64 x 64
+// quarter (2 x 2 row groups), so that an unpacked fragment is used twice.  Fragments come straight from global memory in
+// lane order.
 // ------------------------------------------------------------------------------------------------
 template <int WA, int WB, int B>
 __global__ __launch_bounds__(256) void gemm_fragment_kernel(GemmArgs g) {
@@ -510,21 +510,21 @@ mx_status launch(const GemmArgs& g, int64_t batch, hipStream_t st) {
     } else {
         // waves per tile: as many as the tiles leave the chip room for (about 4096 waves fill it)
         const int64_t tiles = g.groupsA * g.groupsB * batch;
+        const int max_nw = B >= 32 ? 8 : 16;
+        const int nw = tiles >= 1024 ? 4 : tiles >= 512 ? 8 : max_nw;
         // with blocks of 64 (half the block sums per unpacked element) the 128 x 128 form is the faster one once its
         // workgroups fill the chip twice: 2048 x 4096 x 4096 with 8 by 8 bits 194 against 261 us.  With shorter blocks
         // it never is: 218 against 212 us (6 by 5 bits, block 32), 202 against 172 us (8 by 4 bits, block 32), 366
         // against 274 us (6 by 5 bits, block 16).
-        if constexpr (B == 64) {
-            if (ceil_div(g.groupsA, 4) * ceil_div(g.groupsB, 4) * batch >= 512 && ceil_div(g.groupsA, 4) <= 65535) {
-                dim3 grid((unsigned)ceil_div(g.groupsB, 4), (unsigned)ceil_div(g.groupsA, 4), (unsigned)batch);
-                hipLaunchKernelGGL((gemm_fragment_kernel<WA, WB, B>), grid, dim3(256), 0, st, g);
-                MX_HIP_LAUNCH_CHECK();
-                return MX_OK;
-            }
+        const bool large = B == 64 && ceil_div(g.groupsA, 4) * ceil_div(g.groupsB, 4) * batch >= 512;
+        // a grid dimension holds fewer than 2^32 work items: from 2^24 tiles (a result of 64 GiB) on there are too many
+        const bool past_grid = ceil_div(g.groupsA * g.groupsB, 8) * 8 * nw * 64 > 0xffffffffLL;
+        if (large || past_grid) {
+            dim3 grid((unsigned)ceil_div(g.groupsB, 4), (unsigned)ceil_div(g.groupsA, 4), (unsigned)batch);
+            hipLaunchKernelGGL((gemm_fragment_kernel<WA, WB, B>), grid, dim3(256), 0, st, g);
+            MX_HIP_LAUNCH_CHECK();
+            return MX_OK;
         }
-        const int max_nw = B >= 32 ? 8 : 16;
-        const int nw = tiles >= 1024 ? 4 : tiles >= 512 ? 8 : max_nw;
-        if (g.groupsA * g.groupsB > 0x7ffffff0LL) return MX_ERR_UNSUPPORTED;
         const size_t smem = (size_t)nw * 512 + (size_t)(nw / 2) * 4096;
         dim3 grid((unsigned)(ceil_div(g.groupsA * g.groupsB, 8) * 8), (unsigned)batch);
         hipLaunchKernelGGL((gemm_tile_kernel<WA, WB, B>), grid, dim3(nw * 64), smem, st, g);

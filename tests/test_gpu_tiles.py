@@ -99,3 +99,25 @@ def test_attention_forms(heads, Sq, Sk, dim):
     V = (rng.standard_normal((heads, Sk, dim)) * rng.choice([0.01, 1.0, 30.0], size=(heads, 1, dim))).astype(np.float32)
     for rounding, rows, scale in ((mx.MX_RNE, 1, dim ** -0.5), (mx.MX_RTZ, 2 if Sq % 2 == 0 else 1, -0.7 * dim ** -0.5)):
         run_attention(Q, K, V, (8, 7, 6, 5), scale, heads_checked=[0, heads - 1], rounding=rounding, block_rows=rows)
+
+
+def test_fragment_product_past_one_grid_dimension():
+    """131072 x 131072 results, 64 GiB: 2^24 tiles of 32 x 32, more than the work items of one grid dimension hold as
+    workgroups of 256.  Every element is written, sampled rows and columns (first and last among them) are right."""
+    n, K, block = 131072, 2048, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    f = mx.fmt(block, 4)
+    x = torch.randn((n, K), generator=g, device="cuda")
+    w = torch.randn((n, K), generator=g, device="cuda")
+    A, B = mx.quantize_pack(x, f), mx.quantize_pack(w, f)
+    idx = torch.tensor([0, 31, 32, 4097, 65535, 65536, 99999, n - 1], device="cuda")
+    xs, ws = host(x[idx]), host(w[idx])
+    del x, w
+    y = torch.full((n, n), float("nan"), device="cuda")
+    mx.mx_gemm(1, n, n, K, A, f, B, f, mx.MX_LAYOUT_FRAGMENT, y, n, 0)
+    torch.cuda.synchronize()
+    for r in range(0, n, 8192):
+        assert not torch.isnan(y[r:r + 8192]).any(), "rows %d.. not written" % r
+    y_ref, mag = orc.linear(xs, ws, block, 4, 4, want_mag=True)
+    check_product(host(y[idx][:, idx]), y_ref, mag, "64 GiB result")
