@@ -173,7 +173,7 @@ __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArg
 }
 
 // ------------------------------------------------------------------------------------------------
-// The form for large products (see launch): a workgroup of four waves owns a 128 x 128 tile, each wave a 64 x 64
+// The form for large products and short K (see large_tiles_faster): a workgroup of four waves owns a 128 x 128 tile, each wave a 64 x 64
 // quarter (2 x 2 row groups), so that an unpacked fragment is used twice.  Fragments come straight from global memory in
 // lane order.
 // ------------------------------------------------------------------------------------------------
@@ -476,6 +476,31 @@ __global__ __launch_bounds__(NW * 64) void gemv_stream_kernel(GemmArgs g) {
     }
 }
 
+// Which of the two forms for M > 8 is the faster one: the sum that estimates its time (us) is the smaller.  The 128 x 128
+// form: every compute unit takes its share of the tiles, a cost per K chunk and one per tile (launch, store).  The 32 x 32
+// form: rounds of workgroups (8 waves of a compute unit are resident, 16 with blocks of 16), each with the chunks its
+// slowest wave takes one after the other and a cost of its own (launch, sum over the waves, store), and the vector work of
+// all blocks.  So the split over the waves wins while K is long enough to divide or the tiles are too few to fill the chip,
+// and the large tile wins on short K: 32 x 2304 x 5504 x 32 (block 32) 357 us, 1601 us with small tiles; 2064 x 4992 x 160
+// 26 and 40 us; 2048 x 4096 x 4096, 8 by 8 bits in blocks of 64, 194 and 261 us, but 6 by 5 bits in blocks of 32 218 and
+// 212 us, 8 by 4 bits in blocks of 16 or 32 366 and 274, 202 and 172 us.  The coefficients are least squares over 19159
+// shapes (M 9 to 32768, N 16 to 14000, K 16 to 12000, batch 1 to 32, all widths), both forms timed on each: the choice
+// costs 0.3 % against always taking the faster one, and more than 10 % at one shape in 120.
+struct FormCost { float base128, step128, chunk128, tile128, base32, step32, round_step32, round32, chunk32; };
+
+inline bool large_tiles_faster(int block, int64_t chunks, int64_t tiles32, int64_t tiles128, int nw) {
+    const FormCost k = block == 16 ? FormCost{1.98f, 0.63f, 2.38f, 2.15f, 0.51f, 1.33f, 0.19f, 2.63f, 0.083f}
+                     : block == 32 ? FormCost{1.66f, 0.80f, 2.57f, 2.46f, 2.12f, 0.99f, 0.32f, 1.47f, 0.089f}
+                                   : FormCost{1.09f, 0.65f, 3.59f, 3.23f, 1.44f, 1.53f, 0.65f, 1.57f, 0.15f};
+    const int resident = (block == 16 ? 16 : 8) / nw;                // workgroups of the 32 x 32 form on a compute unit
+    const float c = (float)chunks, steps = (float)ceil_div(chunks, nw);
+    const float share128 = (float)ceil_div(tiles128, 256), rounds32 = (float)ceil_div(tiles32, 256 * resident);
+    const float t128 = k.base128 + k.step128 * c + share128 * (k.chunk128 * c + k.tile128);
+    const float t32 = k.base32 + k.step32 * steps + rounds32 * (k.round_step32 * steps + k.round32) +
+                      k.chunk32 * c * (float)tiles32 / 256.f;
+    return t128 < t32;
+}
+
 constexpr int kStreamDepth = 5;
 
 template <int WA, int WB, int B, int MR, int NW>
@@ -512,11 +537,7 @@ mx_status launch(const GemmArgs& g, int64_t batch, hipStream_t st) {
         const int64_t tiles = g.groupsA * g.groupsB * batch;
         const int max_nw = B >= 32 ? 8 : 16;
         const int nw = tiles >= 1024 ? 4 : tiles >= 512 ? 8 : max_nw;
-        // with blocks of 64 (half the block sums per unpacked element) the 128 x 128 form is the faster one once its
-        // workgroups fill the chip twice: 2048 x 4096 x 4096 with 8 by 8 bits 194 against 261 us.  With shorter blocks
-        // it never is: 218 against 212 us (6 by 5 bits, block 32), 202 against 172 us (8 by 4 bits, block 32), 366
-        // against 274 us (6 by 5 bits, block 16).
-        const bool large = B == 64 && ceil_div(g.groupsA, 4) * ceil_div(g.groupsB, 4) * batch >= 512;
+        const bool large = large_tiles_faster(B, g.chunks, tiles, ceil_div(g.groupsA, 4) * ceil_div(g.groupsB, 4) * batch, nw);
         // a grid dimension holds fewer than 2^32 work items: from 2^24 tiles (a result of 64 GiB) on there are too many
         const bool past_grid = ceil_div(g.groupsA * g.groupsB, 8) * 8 * nw * 64 > 0xffffffffLL;
         if (large || past_grid) {

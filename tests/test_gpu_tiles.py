@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
     (33, 1, 9 * 128, 32, 6, 5),        # one column, eight waves and one chunk more
     (64, 64, 3 * 256, 64, 8, 8),
     (40, 32 * 270, 128, 16, 8, 4),     # 540 tiles: eight waves each
-    (70, 32 * 350 + 5, 64, 16, 4, 4),  # 1053 tiles: four waves each
+    (70, 32 * 350 + 5, 64, 16, 4, 4),  # one chunk under 1053 tiles: 128 x 128 instead
+    (40, 32 * 530 + 5, 336, 16, 4, 4), # 1062 tiles: four waves each, one with a second chunk
 ])
 def test_fragment_product_tiles_and_waves(M, N, K, block, wa, wb):
     """Block exponents on both sides of the range in which the scales are built by an integer instruction (bytes 96 to
@@ -121,3 +122,61 @@ def test_fragment_product_past_one_grid_dimension():
         assert not torch.isnan(y[r:r + 8192]).any(), "rows %d.. not written" % r
     y_ref, mag = orc.linear(xs, ws, block, 4, 4, want_mag=True)
     check_product(host(y[idx][:, idx]), y_ref, mag, "64 GiB result")
+
+
+@pytest.mark.parametrize("M,N,K,block,wa,wb,batch", [
+    (1300, 4100, 128, 16, 8, 4, 1),        # two chunks of K: 363 tiles of 128 x 128, both edges ragged
+    (2048 - 13, 4096 - 5, 64 + 32, 32, 6, 5, 1),
+    (190, 257, 64, 32, 7, 3, 20),          # 120 tiles over a batch, the last columns one wide
+    (2048 - 13, 4096 - 5, 3 * 256 + 64, 64, 8, 7, 1),
+    (700, 1000, 256, 64, 3, 6, 2),         # 96 tiles, one chunk
+    (1024, 4096, 3 * 256, 64, 5, 2, 2),    # 512 tiles, no edge
+])
+def test_fragment_product_large_tiles(M, N, K, block, wa, wb, batch):
+    """The 128 x 128 form: widths that are spread from 2, 3, 5, 6 and 7 bits, exponents over 60 binades, zero blocks, ragged
+    edges, batches.  Sampled rows (edges of tiles and of the matrix) over all columns, and nothing past N written."""
+    rng = np.random.default_rng(M + N + K)
+    rows = np.unique(np.concatenate([[0, 31, 32, 127, 128, M - 1], rng.integers(0, M, 10)]))
+    ops = []
+    for b in range(batch):
+        qa, ea = random_operand(rng, M, K, block, wa, 90, 151)
+        qb, eb = random_operand(rng, N, K, block, wb, 100, 161)
+        zero = rng.random(ea.shape) < 0.1
+        ea[zero] = 0
+        qa.reshape(M, K // block, block)[zero] = 0
+        ops.append((qa, ea, qb, eb))
+    cat = lambda k: np.stack([o[k] for o in ops])
+    A, fa = gpu_operand(cat(0), cat(1), block, wa, batch=batch)
+    B, fb = gpu_operand(cat(2), cat(3), block, wb, batch=batch)
+    y = torch.full((batch, M, N + 3), 7.0, device="cuda")
+    mx.mx_gemm(batch, M, N, K, A, fa, B, fb, mx.MX_LAYOUT_FRAGMENT, y, N + 3, M * (N + 3))
+    torch.cuda.synchronize()
+    assert (y[:, :, N:] == 7.0).all(), "columns past N written"
+    assert not (y[:, :, :N] == 7.0).all(dim=2).any(), "rows not written"
+    for b, (qa, ea, qb, eb) in enumerate(ops):
+        y_ref, mag = orc.gemm(qa[rows], ea[rows], wa, qb, eb, wb, block, want_mag=True)
+        check_product(host(y[b, rows, :N]), y_ref, mag, "large tiles, batch entry %d" % b)
+
+
+def test_fragment_product_with_short_k_runs_at_the_rate_of_its_stores():
+    """One chunk of K under a 1.6 GB result: the product is a store of its result and little else.  With 32 x 32 tiles
+    whose waves divide K it took 4.1 times a fill of the same buffer, with 128 x 128 tiles 0.9."""
+    batch, M, N, K = 32, 2304, 5504, 32
+    fa, fb = mx.fmt(32, 8), mx.fmt(32, 4)
+    A = mx.quantize_pack(torch.randn((batch, M, K), device="cuda"), fa)
+    B = mx.quantize_pack(torch.randn((batch, N, K), device="cuda"), fb)
+    y = torch.empty((batch, M, N), device="cuda")
+    product = mx.bound("mx_gemm", batch, M, N, K, A, fa, B, fb, mx.MX_LAYOUT_FRAGMENT, y, N, M * N)
+
+    def best(call):
+        times = []
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            call()
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+    fill = best(lambda: y.fill_(1.0))
+    assert best(product) < 2.0 * fill
