@@ -501,11 +501,13 @@ inline bool large_tiles_faster(int block, int64_t chunks, int64_t tiles32, int64
     return t128 < t32;
 }
 
-constexpr int kStreamDepth = 5;
+// Chunks in flight per wave: five, and three or two where five do not fit the 128 registers of the 16-wave form (records of
+// 20 and more dwords per lane) and would be spilled to memory and read back for every chunk.
+template <int WB, int B, int NW> constexpr int kStreamDepth = NW < 16 || Piece<WB, B>::kDw < 20 ? 5 : Piece<WB, B>::kDw < 24 ? 3 : 2;
 
 template <int WA, int WB, int B, int MR, int NW>
 mx_status launch_stream(const GemmArgs& g, int64_t batch, size_t smem, hipStream_t st) {
-    auto kern = gemv_stream_kernel<WA, WB, B, NW, kStreamDepth, MR>;
+    auto kern = gemv_stream_kernel<WA, WB, B, NW, kStreamDepth<WB, B, NW>, MR>;
     static std::atomic<uint64_t> done{0};
     if (!allow_dynamic_lds((const void*)kern, 160 * 1024, done)) return MX_ERR_DEVICE;
     dim3 grid((unsigned)g.groupsB, (unsigned)batch);

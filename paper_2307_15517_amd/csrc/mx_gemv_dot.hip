@@ -247,7 +247,9 @@ __global__ __launch_bounds__(NW * 64) void gemv_dot_kernel(DotArgs a) {
     }
 }
 
-constexpr int kDotDepth = 5;
+// Chunks of weights in flight per wave: five, and three or two where five do not fit the 128 registers of the 16-wave form
+// (records of 20 and more dwords per lane) and would be spilled to memory and read back for every chunk.
+template <int WB, int B, int NW> constexpr int kDotDepth = NW < 16 || Piece<WB, B>::kDw < 20 ? 5 : Piece<WB, B>::kDw < 24 ? 3 : 2;
 
 // NW: 8 waves per workgroup when there are enough column groups to fill the chip, 16 when there are
 // few (each workgroup then has to keep twice as many bytes in flight).
@@ -256,7 +258,7 @@ mx_status launch_dot_nw(const DotArgs& a, int64_t batch, hipStream_t st) {
     const size_t smem = ((size_t)MP * a.g.chunks * 4 * 2 * (B / 8) + (size_t)MP * a.g.chunks) * 4 +
                         (size_t)NW * MP * 32 * 4;
     if (smem > 160 * 1024) return MX_ERR_UNSUPPORTED;
-    auto kern = gemv_dot_kernel<WB, B, MP, NW, kDotDepth>;
+    auto kern = gemv_dot_kernel<WB, B, MP, NW, kDotDepth<WB, B, NW>>;
     static std::atomic<uint64_t> done{0};
     if (!allow_dynamic_lds((const void*)kern, 160 * 1024, done)) return MX_ERR_DEVICE;
     dim3 grid((unsigned)a.g.groupsB, (unsigned)batch);

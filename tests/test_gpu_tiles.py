@@ -246,3 +246,25 @@ def test_a_smaller_matrix_product_is_not_the_slower_one(block, wa, wb, batch, M,
     y = torch.empty((batch, larger, N), device="cuda")
     times = [best_time(mx.bound("mx_gemm", batch, m, N, K, A, fa, B, fb, MAT, y, N, m * N)) for m in (M, larger, M, larger)]
     assert min(times[0], times[2]) < 1.05 * min(times[1], times[3]), times
+
+
+@pytest.mark.parametrize("M", [1, 2, 5])
+@pytest.mark.parametrize("wx,ww", [(8, 5), (4, 6), (6, 7), (8, 8)])
+def test_decode_rings_of_wide_records(M, wx, ww):
+    """Blocks of 64 with 5 to 8 bits on few columns: sixteen waves with rings of three or two chunks, on K of fewer chunks
+    than waves, of one more than a turn of all rings and of a partial last chunk."""
+    rng = np.random.default_rng(100 * M + 10 * wx + ww)
+    N = 70
+    for K in (64, 256 * 5, 256 * 49 + 128):
+        x = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-6, 7, size=(M, K // 64)).repeat(64, axis=1))).astype(np.float32)
+        wt = (rng.standard_normal((N, K)) * 0.05).astype(np.float32)
+        fx, fw = mx.fmt(64, wx), mx.fmt(64, ww)
+        xd = torch.from_numpy(x).cuda()
+        A, B = mx.quantize_pack(xd, fx), mx.quantize_pack(torch.from_numpy(wt).cuda(), fw)
+        y = torch.full((2, M, N), 3.0, device="cuda")
+        mx.mx_linear(xd, M, K, K, fx, mx.linear_workspace(M, K, N, fx, fw, "cuda"), B, N, fw, mx.MX_LAYOUT_FRAGMENT, y[0], N)
+        mx.mx_gemm(1, M, N, K, A, fx, B, fw, mx.MX_LAYOUT_FRAGMENT, y[1], N, 0)
+        torch.cuda.synchronize()
+        y_ref, mag = orc.linear(x, wt, 64, wx, ww, want_mag=True)
+        for k in (0, 1):
+            check_product(host(y[k]), y_ref, mag, "M %d K %d widths %d %d" % (M, K, wx, ww))
