@@ -173,13 +173,14 @@ __global__ __launch_bounds__(256) void quantize_minifloat_kernel(MiniArgs a) {
 // its number shifted: no division by the row length or the block.  Bound by HBM (5 bytes and 1/block per element); 1001 x
 // 4096: 7.8 us with one item per thread and its two divisions, 6.3 us with four items, all loads first;
 // 2048 x 11008: 23.9 -> 19.0 us.
+template <int ITEMS>
 __global__ __launch_bounds__(256) void dequantize_minifloat_kernel(MiniArgs a, int block_log2) {
-    const int64_t first = (int64_t)blockIdx.x * (256 * kMiniItems) + threadIdx.x;
+    const int64_t first = (int64_t)blockIdx.x * (256 * ITEMS) + threadIdx.x;
     const int m = a.m, e = a.e, cmax = (1 << e) - 1;
-    uint32_t codes[kMiniItems];
-    int sb[kMiniItems];
+    uint32_t codes[ITEMS];
+    int sb[ITEMS];
 #pragma unroll
-    for (int u = 0; u < kMiniItems; ++u) {
+    for (int u = 0; u < ITEMS; ++u) {
         const int64_t it = first + u * 256;
         codes[u] = 0; sb[u] = 0;
         if (it < a.items_per_row) {
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(256) void dequantize_minifloat_kernel(MiniArgs a, i
         }
     }
 #pragma unroll
-    for (int u = 0; u < kMiniItems; ++u) {
+    for (int u = 0; u < ITEMS; ++u) {
         const int64_t it = first + u * 256;
         float out[4];
 #pragma unroll
@@ -264,10 +265,14 @@ extern "C" mx_status mx_dequantize_minifloat(const uint8_t* codes, const uint8_t
     a.rows = 1; a.cols = batch * rows * cols; a.row_stride = a.cols; a.batch_stride = 0;
     a.items_per_row = a.cols / 4;
     a.e = f.exp_bits; a.m = f.mant_bits; a.rnd = f.rounding;
-    const int64_t blocks = ceil_div(a.items_per_row, 256 * kMiniItems);
+    // up to half a million elements one item per thread: four leave the chip too few threads and the longer program costs its
+    // fetch (32768 to 65536 elements: median 3.26 us with four, 2.96 with one; 2^18 to 2^19 3.40 and 3.10; 2^19 to 2^20 3.59
+    // with four, 3.65 with one and the divisions)
+    const bool small = a.cols <= (1 << 19);
+    const int64_t blocks = ceil_div(a.items_per_row, 256 * (small ? 1 : kMiniItems));
     if (blocks > 0x7fffffffLL) return MX_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(dequantize_minifloat_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, a,
-                       (int)__builtin_ctz((unsigned)f.block));
+    hipLaunchKernelGGL(small ? dequantize_minifloat_kernel<1> : dequantize_minifloat_kernel<kMiniItems>, dim3((unsigned)blocks),
+                       dim3(256), 0, (hipStream_t)stream, a, (int)__builtin_ctz((unsigned)f.block));
     MX_HIP_LAUNCH_CHECK();
     return MX_OK;
 }

@@ -5,7 +5,7 @@ import torch
 
 from oracle import mx_oracle as orc
 from paper_2307_15517_amd import mx
-from test_gpu_parity import check_product, gpu_operand, host, random_operand, run_attention
+from test_gpu_parity import check_product, gpu_operand, host, random_operand, run_attention, run_minifloat
 
 pytestmark = pytest.mark.gpu
 
@@ -268,3 +268,13 @@ def test_decode_rings_of_wide_records(M, wx, ww):
         y_ref, mag = orc.linear(x, wt, 64, wx, ww, want_mag=True)
         for k in (0, 1):
             check_product(host(y[k]), y_ref, mag, "M %d K %d widths %d %d" % (M, K, wx, ww))
+
+
+@pytest.mark.parametrize("rows,cols", [(512, 1024), (8193, 64), (1, 16)])
+def test_minifloat_dequantizer_forms(rows, cols):
+    """One item per thread up to 2^19 elements, four past that; the last workgroup full, ragged, and alone."""
+    rng = np.random.default_rng(rows)
+    x = (rng.standard_normal((rows, cols)) * np.exp2(rng.integers(-20, 20, size=(rows, 1)))).astype(np.float32)
+    x[rng.random(x.shape) < 0.05] = 0.0
+    for block, e, m in ((16, 4, 3), (8, 7, 0), (16, 1, 6)):
+        run_minifloat(x, block, e, m)
