@@ -85,10 +85,10 @@ __device__ __forceinline__ void pin(int v) { asm volatile("" ::"v"(v)); }
 
 constexpr int kAttnStages = 5;
 
-// KS: K steps of 32 along the head dimension (2 or 4); DT: tiles of 32 along the head dimension of V.  A wave owns one
-// tile of 32 queries; at most 256 registers and 80 KiB of LDS, so that two workgroups share a compute unit and their
-// waves fill each other's waits.
-template <int KS, int DT, int RND>
+// KS: K steps of 32 along the head dimension (2 or 4); DT: tiles of 32 along the head dimension of V; LAG: the second product
+// runs one key tile behind the scores (see pick_attention).  A wave owns one tile of 32 queries; at most 256 registers and
+// 80 KiB of LDS, so that two workgroups share a compute unit and their waves fill each other's waits.
+template <int KS, int DT, int RND, bool LAG>
 __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
     constexpr int S = kAttnStages;
     constexpr int NK = 2 * KS;                          // matrix instructions (16 elements) along the head dimension
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
     const int wm2 = g.wp - 2;
 
     // scores of two consecutive key tiles live in two register sets: while the arithmetic on one tile's
-    // scores runs on the vector units, the matrix cores take the next tile's.  The second product runs one tile
+    // scores runs on the vector units, the matrix cores take the next tile's.  With LAG the second product runs one tile
     // behind: P^ of a tile is multiplied with its V under the arithmetic on the tile after it.
     v16f s[2];
     v4i pf[2][2];                                       // P^ of the tile in set 0 / 1, two fragments of 16 keys
@@ -212,6 +212,10 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
             constexpr bool RAG = decltype(ragc)::value;
             const auto nset = std::integral_constant<int, set ^ 1>{};
             const int nxt = cur + 1 == S ? 0 : cur + 1, prv = cur == 0 ? S - 1 : cur - 1;
+            if constexpr (PV && !LAG) {
+#pragma unroll
+                for (int m = 0; m < 2 * DT; ++m) read_v(m, cur);
+            }
             // copies in flight, oldest first: tiles kt+1 .. kt+S-2.  Tile kt+1 has landed once only the newest
             // S-3 tiles' copies are outstanding; the barrier publishes it and tells that every wave has taken
             // what it needs of tile kt-1's stage, which the copy of tile kt+S-1 overwrites.
@@ -314,6 +318,21 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
                         pin(pf[set][b][d]);
                     }
                 };
+                if constexpr (!LAG) {
+                    unit(0);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int m = 0; m < NK; ++m) {
+                        score_mfma(m, nset);
+#pragma unroll
+                        for (int x = 1 + m * (NU - 1) / NK; x < 1 + (m + 1) * (NU - 1) / NK; ++x) unit(x);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                    for (int m = 0; m < 2 * DT; ++m) out_mfma(m, setc);
+                    __builtin_amdgcn_sched_barrier(0);
+                    return;
+                }
                 // matrix instructions in turn: the second product of the tile before (each followed by the read of this
                 // tile's V into the registers it has freed) and the next tile's scores; vector work under all of them
                 constexpr int NO = 2 * DT, NM = NO + NK;
@@ -335,7 +354,7 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
             }
         };
 
-        if constexpr (PV) {                               // no tile before the first one: adds zeros
+        if constexpr (PV && LAG) {                        // no tile before the first one: adds zeros
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 pf[1][b] = v4i{0, 0, 0, 0};
@@ -361,11 +380,11 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
         body(kt, cur, std::integral_constant<int, 0>{}, std::true_type{}); advance();
         if (kt < g.nt) {
             body(kt, cur, std::integral_constant<int, 1>{}, std::true_type{}); advance();
-            if constexpr (PV) {
+            if constexpr (PV && LAG) {
 #pragma unroll
                 for (int m = 0; m < 2 * DT; ++m) out_mfma(m, std::integral_constant<int, 1>{});
             }
-        } else if constexpr (PV) {
+        } else if constexpr (PV && LAG) {
 #pragma unroll
             for (int m = 0; m < 2 * DT; ++m) out_mfma(m, std::integral_constant<int, 0>{});
         }
@@ -624,12 +643,12 @@ mx_status launch_attention_split(AttnArgs& g, int64_t batch, int parts, int rnd,
     return MX_OK;
 }
 
-template <int KS, int DT>
+template <int KS, int DT, bool LAG>
 mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     constexpr int smem = kAttnStages * (KS + DT) * kBfUnitBytes;
     static_assert(smem * 2 <= 160 * 1024, "LDS budget of one compute unit");
-    auto k0 = attention_bf16_kernel<KS, DT, MX_RNE>;
-    auto k1 = attention_bf16_kernel<KS, DT, MX_RTZ>;
+    auto k0 = attention_bf16_kernel<KS, DT, MX_RNE, LAG>;
+    auto k1 = attention_bf16_kernel<KS, DT, MX_RTZ, LAG>;
     static std::atomic<uint64_t> done0{0}, done1{0};
     if (!allow_dynamic_lds((const void*)k0, smem, done0) || !allow_dynamic_lds((const void*)k1, smem, done1))
         return MX_ERR_DEVICE;
@@ -644,21 +663,27 @@ mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) 
 
 // The split kernel takes one round of workgroups in a time that hardly depends on the number of keys while they are few,
 // the 128-query workgroups one tile of keys at a time for as long whether there is one of them or 256: with one round
-// the split kernel is the faster one (8 heads x 512 queries x 2048 keys x 128: 70 us, 22 us split; 32 x 256 x 32 x 128:
-// 7.5 and 7.1 us), with two from ten key tiles on (16 x 1024 x 256 x 128: 15.0 and 16.3 us, 16 x 1024 x 320 x 96: 16.6
+// the split kernel is the faster one (8 heads x 512 queries x 2048 keys x 128: 70 us, 22 us split) from the second key tile
+// on (100 heads x 55 queries x 128, 32 keys: 6.5 and 7.2 us, 64 keys: 0.94 of the time and less), with two from ten key tiles on (16 x 1024 x 256 x 128: 15.0 and 16.3 us, 16 x 1024 x 320 x 96: 16.6
 // and 15.1 us, 32 x 512 x 2048 x 128: 74 and 45 us), with three from about forty (24 x 1024 x 960 x 128: 38.6 and 39.6 us,
 // 24 x 1024 x 2048 x 128: 75 and 64 us), beyond that no more (16 x 2040 x 2048 x 128: 71 and 81 us).
 // With room for it every 32 columns of the result get a workgroup of their own, which
 // repeats the scores and saves registers, V and the sum (32 heads, one query, 1936 keys: 16.8 against 20.0 us); with more
 // than one such workgroup per compute unit that costs more than it saves (32 x 100 x 2048 x 128: 35 against 22 us).
+// The second product of the 128-query form runs one key tile behind its scores (LAG), but not for one or two key tiles, where
+// the additional round of it costs more (54 heads x 1828 x 64 x 48: 13.1 and 14.7 us, 32 x 2000 x 64 x 128 2 percent), nor
+// for heads of 33 to 64 elements once a compute unit has more than four workgroups to take: the lag needs 148 registers for
+// 125, three workgroups at a time for four (106 x 3866 x 128 x 64: 52.3 and 57.5 us; median over 4096 query tiles and more
+// 5 to 10 percent up to eight key tiles, 2 at 24, even at 32).
 template <int KS, int DT>
 mx_status pick_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     const int64_t groups = g.q_tiles * batch;
     if (groups * DT <= 256) return launch_attention_split<KS, 1>(g, batch, DT, rnd, st);
     const int64_t rounds = ceil_div(groups, DT <= 2 ? 512 : 256);      // two workgroups of at most 128 registers share a compute unit
-    if (groups <= 768 && g.nt >= (rounds == 1 ? 1 : rounds == 2 ? 10 : 40))
+    if (groups <= 768 && g.nt >= (rounds == 1 ? 2 : rounds == 2 ? 10 : 40))
         return launch_attention_split<KS, DT>(g, batch, 1, rnd, st);
-    return launch_attention<KS, DT>(g, batch, rnd, st);
+    if (g.nt <= 2 || (KS == 2 && DT == 2 && groups > 4096 && g.nt <= 32)) return launch_attention<KS, DT, false>(g, batch, rnd, st);
+    return launch_attention<KS, DT, true>(g, batch, rnd, st);
 }
 
 }  // namespace

@@ -5,7 +5,7 @@ import torch
 
 from oracle import mx_oracle as orc
 from paper_2307_15517_amd import mx
-from test_gpu_parity import check_product, gpu_operand, host, random_operand, run_attention, run_minifloat
+from test_gpu_parity import attention_bound, check_product, gpu_operand, host, random_operand, run_attention, run_minifloat
 
 pytestmark = pytest.mark.gpu
 
@@ -278,3 +278,59 @@ def test_minifloat_dequantizer_forms(rows, cols):
     x[rng.random(x.shape) < 0.05] = 0.0
     for block, e, m in ((16, 4, 3), (8, 7, 0), (16, 1, 6)):
         run_minifloat(x, block, e, m)
+
+
+def long_attention_inputs(heads, Sq, Sk, dim):
+    rng = np.random.default_rng(heads * 1000 + Sk + dim)
+    Q = rng.standard_normal((heads, Sq, dim)).astype(np.float32)
+    K = rng.standard_normal((heads, Sk, dim)).astype(np.float32)
+    V = (rng.standard_normal((heads, Sk, dim)) * rng.choice([0.01, 1.0, 30.0], size=(heads, 1, dim))).astype(np.float32)
+    return Q, K, V
+
+
+@pytest.mark.parametrize("heads,Sq,Sk,dim", [
+    (100, 258, 352, 32), (100, 258, 368, 32),      # 900 tiles of 32 queries, eleven key tiles and twelve with a ragged one
+    (100, 258, 352, 64), (100, 258, 368, 64),
+    (100, 258, 352, 80), (100, 258, 368, 128),
+    (500, 258, 352, 64), (500, 258, 368, 48),      # 4500: heads of 33 to 64 without the lag of the second product
+    (500, 258, 1056, 64),                          # and with it from 33 key tiles on
+    (100, 258, 32, 64), (100, 258, 64, 128), (100, 258, 16, 96), (60, 100, 32, 128),    # one and two key tiles
+])
+def test_attention_of_128_queries_per_workgroup(heads, Sq, Sk, dim):
+    """The key loop past its prologue, with every stage of the ring reused, odd and even numbers of key tiles and a ragged
+    last one, a ragged last workgroup of queries; both rounding modes, two-row blocks, a narrow exponent of P and V."""
+    Q, K, V = long_attention_inputs(heads, Sq, Sk, dim)
+    some = dict(heads_checked=[0, heads // 2, heads - 1])
+    run_attention(Q, K, V, (8, 7, 6, 5), dim ** -0.5, rows=(Sq - 34, Sq), **some)
+    run_attention(Q, K, V, (7, 8, 5, 6), -0.7 * dim ** -0.5, rows=(0, 34), rounding=mx.MX_RTZ, block_rows=2, **some)
+    run_attention(Q, K, V, (8, 7, 8, 6), dim ** -0.5, rows=(Sq - 34, Sq), e_pv=4, **some)
+
+
+@pytest.mark.parametrize("heads,Sq,Sk,dim,R", [(100, 258, 352, 128, 1), (100, 258, 384, 64, 2), (100, 258, 352, 96, 2), (500, 258, 352, 64, 1),
+                                               (100, 258, 64, 32, 1)])
+def test_attention_of_128_queries_in_blocks_of_32(heads, Sq, Sk, dim, R):
+    """P in blocks of 32 keys, one whole key tile, with all tensors quantized in blocks of 32 (entered as blocks of 16)."""
+    Q, K, V = long_attention_inputs(heads, Sq, Sk, dim)
+    wq, wk, wp, wv = 8, 7, 6, 5
+
+    def operand(x, w, axis):
+        mant, exps = mx.quantize(torch.from_numpy(x).cuda(), mx.fmt(32, w, block_rows=R), axis)
+        rows, cols = (x.shape[1], x.shape[2]) if axis == 1 else (x.shape[2], x.shape[1])
+        if R == 2:
+            exps = exps.view(heads, rows // 2, cols // 32).repeat_interleave(2, dim=1).reshape(-1)
+        f = mx.fmt(16, w)
+        return mx.pack(mant, exps.repeat_interleave(2), heads, rows, cols, f, MAT), f
+    A, fq = operand(Q, wq, 1)
+    B, fk = operand(K, wk, 1)
+    Bv, fv = operand(V, wv, 0)
+    fp = mx.fmt(32, wp, block_rows=R)
+    O = torch.empty((heads, Sq, dim), device="cuda")
+    mx.mx_attention(heads, Sq, Sk, dim, A, fq, B, fk, Bv, fv, fp, dim ** -0.5, MAT, O, dim, Sq * dim)
+    torch.cuda.synchronize()
+    for hd in (0, heads // 2, heads - 1):
+        for rows in ((0, 34), (Sq - 34, Sq)):
+            o_ref, info = orc.attention(Q[hd], K[hd], V[hd], 32, wq, wk, wp, wv, dim ** -0.5, 8, mx.MX_RNE, rows, R)
+            bound, maybe = attention_bound(info, wp, wv, dim ** -0.5, mx.MX_RNE, 8, block=32)
+            assert maybe < 1e-2
+            r0, r1 = rows
+            assert (np.abs(host(O[hd, r0:r1]).astype(np.float64) - o_ref[r0:r1]) <= bound).all(), (hd, rows)
