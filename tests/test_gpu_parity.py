@@ -931,10 +931,11 @@ def test_check_finite_agrees_with_what_the_oracle_refuses():
 
 @pytest.mark.parametrize("wa,wb,block", [(8, 4, 32), (3, 4, 64), (8, 6, 32), (4, 8, 64)])
 def test_matrix_gemm_block_exponents_change_with_every_group_of_k_steps(wa, wb, block):
-    """Small products (one or two tiles: the form with copy waves and the deepest pipeline) repeated many times, the
-    magnitude of both operands moving by a few binades from one group of four K steps (256 elements) to the next, so
-    that scales read for the wrong group, or before their copy has landed, show in every element.  All four piece
-    combinations of the block-scaled kernel; whole output, every repetition."""
+    """A small product (the form whose waves split K and load operands and scales straight from global memory) repeated many
+    times, the magnitude of both operands moving by a few binades from one group of four K steps (256 elements) to the
+    next, so that scales of the wrong group show in every element.  All four piece combinations of the block-scaled kernel;
+    whole output, every repetition.  The forms that copy scales through LDS, where they could be read before they have
+    landed, are run the same way by test_matrix_product_on_long_k in test_gpu_tiles.py."""
     rng = np.random.default_rng(17 * wa + wb)
     M, N, K = 100, 300, 13 * 256
     grp = np.repeat(np.arange(K // 256), 256)

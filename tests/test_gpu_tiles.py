@@ -39,8 +39,8 @@ def test_fragment_product_tiles_and_waves(M, N, K, block, wa, wb):
 
 
 MAT = mx.MX_LAYOUT_MATRIX
-# (row tiles, column tiles) of 32: one size in the range of each form of the matrix-layout product, from the smallest
-# tile with K split over the waves to more than one round of the largest
+# (row tiles, column tiles) of 32: one size in the range of each form of the matrix-layout product but the last, from the
+# smallest tile with K split over the waves to a partial second round of the larger ones (K short: MATRIX_FORMS_LONG_K)
 MATRIX_FORMS = [(1, 2), (2, 200), (4, 200), (4, 400), (4, 900), (3, 1500), (4, 2400)]
 
 
@@ -70,8 +70,9 @@ def test_matrix_product_forms(rt, ct, block, wa, wb, K):
 @pytest.mark.parametrize("rt,ct", [(1, 3), (2, 200), (4, 200), (4, 400), (4, 900), (4, 2400)])
 @pytest.mark.parametrize("block,wx,wo", [(16, 8, 6), (32, 8, 8), (64, 6, 4), (32, 4, 8)])
 def test_matrix_product_forms_quantized_output(rt, ct, block, wx, wo):
-    """mx_gemm_q in each form, against mx_gemm of the same operands quantized afterwards: with exact sums (few
-    binades, 24 bits hold them) the packed bytes are the same, padding rows and columns included."""
+    """mx_gemm_q in the forms up to 64 x 256 and 128 x 128, without a bias and with a short K, against mx_gemm of the same
+    operands quantized afterwards: with exact sums (few binades, 24 bits hold them) the packed bytes are the same, padding
+    rows and columns included.  (All forms, with the rest of the ending: test_matrix_quantized_output_on_long_k.)"""
     M, N, K = rt * 32 - 13, ct * 32 - (block if block < 64 else 0), 2 * block
     N -= N % block
     rng = np.random.default_rng(M * 31 + N)
@@ -334,3 +335,83 @@ def test_attention_of_128_queries_in_blocks_of_32(heads, Sq, Sk, dim, R):
             assert maybe < 1e-2
             r0, r1 = rows
             assert (np.abs(host(O[hd, r0:r1]).astype(np.float64) - o_ref[r0:r1]) <= bound).all(), (hd, rows)
+
+
+# The forms of the matrix-layout product, (row tiles, column tiles) of 32 and what they select with blocks of 32 or 64 and a
+# two-piece left operand.  With a one-piece left operand 64 x 128 and 64 x 256 are 128 x 128, and so they are with blocks of
+# 16 from 64 x 256 on.  With a two-piece right operand, and with blocks of 16, no form has copy waves; with two pieces on
+# both sides everything from 64 x 256 on is 128 x 256.
+MATRIX_FORMS_LONG_K = [
+    (1, 100),      # 32 x 32, K split over the waves
+    (2, 200),      # 32 x 64, K split
+    (4, 240),      # 64 x 64, K split, with blocks of 16; 64 x 128 otherwise
+    (4, 400),      # 64 x 128
+    (4, 900),      # 64 x 256
+    (3, 1500),     # 128 x 256, one workgroup per compute unit with copy waves
+    (4, 2400),     # a second round of 128 x 256 less than three eighths full: 64 x 256 / 128 x 128, two per compute unit
+    (20, 830),     # 520 tiles of 128 x 256: two per compute unit
+]
+
+
+def exact_operands(g, batch, M, N, K):
+    """Small integers whose scale moves by binades from one group of 256 along K to the next, differently on the two sides:
+    every product and every sum is a whole number below 2^24, so any order of additions gives the same fp32 result, and a
+    scale byte, a stage or a fragment of another K step shows in it."""
+    grp = torch.arange(K, device="cuda") // 256
+    x = torch.randint(-3, 4, (batch, M, K), generator=g, device="cuda").float() * torch.exp2(((5 * grp) % 4).float())
+    w = torch.randint(-3, 4, (batch, N, K), generator=g, device="cuda").float() * torch.exp2(((3 * grp) % 3).float())
+    return x, w
+
+
+def long_k(block):
+    """Block 32/64: 22 steps of 64 (21 and a half with blocks of 32), six groups of four with padding, more than four turns
+    of five stages.  Block 16: 35 steps of 32, the last one half filled, more than five turns of six stages."""
+    return {16: 32 * 34 + 16, 32: 64 * 21 + 32, 64: 64 * 22}[block]
+
+
+@pytest.mark.parametrize("rt,ct", MATRIX_FORMS_LONG_K)
+@pytest.mark.parametrize("block,wa,wb", [(16, 8, 4), (32, 8, 4), (64, 6, 3), (32, 4, 3), (64, 3, 8), (32, 5, 6)])
+def test_matrix_product_on_long_k(rt, ct, block, wa, wb):
+    """Whole results of every form and every combination of mantissa pieces, ragged in rows and columns, ten
+    launches each."""
+    M, N, K = rt * 32 - 13, ct * 32 - 5, long_k(block)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rt * ct)
+    x, w = exact_operands(g, 1, M, N, K)
+    fa, fb = mx.fmt(block, wa), mx.fmt(block, wb)
+    A, B = mx.quantize_pack(x, fa, MAT), mx.quantize_pack(w, fb, MAT)
+    want = torch.mm(x[0].double(), w[0].t().double()).float()
+    assert want.abs().max() < 2.0 ** 24
+    for rep in range(10):
+        y = torch.full((M, N + 3), float("nan"), device="cuda")
+        mx.mx_gemm(1, M, N, K, A, fa, B, fb, MAT, y, N + 3, 0)
+        torch.cuda.synchronize()
+        assert torch.equal(y[:, :N], want), "launch %d" % rep
+        assert torch.isnan(y[:, N:]).all(), "columns past N written"
+
+
+@pytest.mark.parametrize("rt,ct", [(r, c // 2) for r, c in MATRIX_FORMS_LONG_K])
+@pytest.mark.parametrize("block,wa,wo,rows", [(16, 8, 8, 2), (16, 5, 4, 1), (32, 8, 8, 2), (64, 8, 6, 1), (32, 6, 4, 2), (64, 4, 8, 2),
+                                              (32, 3, 4, 1)])
+def test_matrix_quantized_output_on_long_k(rt, ct, block, wa, wo, rows):
+    """mx_gemm_q over a batch of two in every form, with an MXInt bias and one- and two-row blocks
+    of the result, one- and two-piece operands and results: byte for byte what mx_quantize_pack makes of product + bias,
+    padding rows and columns included, five launches each."""
+    batch, M, K = 2, rt * 32 - 14, long_k(block)
+    N = (ct * 32 - 8) // block * block
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rt * ct + wa)
+    x, w = exact_operands(g, batch, M, N, K)
+    bias = torch.randint(-3, 4, (1, N), generator=g, device="cuda").float() * 64.0
+    fa, fb, fo = mx.fmt(block, wa), mx.fmt(block, 4), mx.fmt(block, wo, block_rows=rows)
+    A, B = mx.quantize_pack(x, fa, MAT), mx.quantize_pack(w, fb, MAT)
+    y = torch.stack([torch.mm(x[b].double(), w[b].t().double()) for b in range(batch)]).float() + bias
+    assert y.abs().max() < 2.0 ** 24
+    want = torch.full((mx.mx_packed_bytes(batch, M, N, fo, MAT),), 255, dtype=torch.uint8, device="cuda")
+    mx.mx_quantize_pack(y, batch, M, N, N, M * N, fo, MAT, want)
+    mant, exps = mx.quantize(bias, fb)
+    for rep in range(5):
+        out = torch.full_like(want, 255)
+        mx.mx_gemm_q(batch, M, N, K, A, fa, B, fb, MAT, mant, exps, fb, fo, out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), "launch %d" % rep
