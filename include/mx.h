@@ -264,7 +264,10 @@ MX_API mx_status mx_unpack(const void* packed, int64_t batch, int64_t rows, int6
  * fa.block == fb.block and fa.exp_bits == fb.exp_bits are required.
  * Y: fp32, element (b, m, n) at Y[b*batch_stride_y + m*ldy + n]; ldy >= N.
  * With MX_LAYOUT_FRAGMENT, M <= 8 takes the bandwidth-bound decode path (one pass over the
- * right operand); MX_LAYOUT_MATRIX runs the tiled kernel whatever M is.
+ * right operand); otherwise, and with MX_LAYOUT_MATRIX whatever M is, the sizes choose among
+ * tiles and among splits of K, which add the same block sums in different orders.
+ * MX_ERR_UNSUPPORTED: batch > 65535; with MX_LAYOUT_FRAGMENT M > 8388480; with MX_LAYOUT_MATRIX
+ * and blocks of 32 or 64 K > 44739072.
  */
 MX_API mx_status mx_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, const void* A_packed, mx_format fa,
                   const void* B_packed, mx_format fb, int32_t layout, float* Y, int64_t ldy,

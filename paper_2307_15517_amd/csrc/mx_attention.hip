@@ -24,10 +24,11 @@
 // sweep 2 the V^T) units of one tile of 32 keys are copied global -> LDS with 16-byte direct-to-LDS loads, five
 // stages, one barrier per key tile.  Two query tiles per wave (363 registers, one workgroup) were slower, 128 us.
 //
-// Bound: vector issue (about 195 instructions, 33 of them exponentials, per tile and wave over both sweeps) at the clock
-// the matrix work leaves.  The second product of a key tile runs one tile behind its scores, so that no matrix
+// Bound: vector issue is the longest of the pipes' times (about 195 instructions, 33 of them exponentials, per tile and wave
+// over both sweeps; the vector ALU is active 63 % of the cycles, the matrix cores 44 %), not reached for the LDS reads and
+// the barrier of every key tile.  The second product of a key tile runs one tile behind its scores, so that no matrix
 // instruction is left without vector work under it: 16 heads x 2040 queries x 2048 keys x 128 76.7 -> 71 us, 32 x 2048 x
-// 2048 x 128 124.2 -> 122.5 us.
+// 2048 x 128 124.2 -> 122.5 us (where it does not pay: pick_attention).
 #include <type_traits>
 
 #include "mx_bf16.h"

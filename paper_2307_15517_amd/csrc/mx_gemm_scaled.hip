@@ -793,7 +793,8 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
 }
 
 // The smallest tile that needs no more than one workgroup per compute unit: small tiles put more compute units to work,
-// but load more bytes per product, and with a second round of workgroups the next larger tile was the faster one.  The
+// but load more bytes per product, and with a second round of workgroups the next larger tile was the faster one (not for
+// short K: 2048 x 3072 x 768 12.3 us, 10.4 with 64x128).  The
 // two smallest tiles split K over their waves, the others share their operands through LDS.  Measured with 8 by 4 bits,
 // block 32 (us; the form taken first): 128 x 4096 x 4096 32x64 9.3, 32x32 12.7, 64x128 13; 333 x 4096 x 4096 64x128 14.1,
 // 64x256 19.4, 128x256 28; 700 x 4096 x 4096 64x256 19.8, 64x128 20.9, 128x256 28; 1500 x 4096 x 4096 128x256 31, 64x256
