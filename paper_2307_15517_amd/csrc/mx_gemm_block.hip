@@ -485,7 +485,9 @@ __global__ __launch_bounds__(NW * 64) void gemv_stream_kernel(GemmArgs g) {
 // 26 and 40 us; 2048 x 4096 x 4096, 8 by 8 bits in blocks of 64, 194 and 261 us, but 6 by 5 bits in blocks of 32 218 and
 // 212 us, 8 by 4 bits in blocks of 16 or 32 366 and 274, 202 and 172 us.  The coefficients are least squares over 19159
 // shapes (M 9 to 32768, N 16 to 14000, K 16 to 12000, batch 1 to 32, all widths), both forms timed on each: the choice
-// costs 0.3 % against always taking the faster one, and more than 10 % at one shape in 120.
+// costs 0.3 % against always taking the faster one, and more than 10 % at one shape in 100.  Within 5 % of each other the
+// large tile is taken: its scaling is the same for any exponents, the small one's slower outside its narrow range (3363 x
+// 8704 x 10368, 8 by 8 bits in blocks of 64, exponents over 60 binades: 1537 us, 2060 with small tiles).
 struct FormCost { float base128, step128, chunk128, tile128, base32, step32, round_step32, round32, chunk32; };
 
 inline bool large_tiles_faster(int block, int64_t chunks, int64_t tiles32, int64_t tiles128, int nw) {
@@ -498,7 +500,7 @@ inline bool large_tiles_faster(int block, int64_t chunks, int64_t tiles32, int64
     const float t128 = k.base128 + k.step128 * c + share128 * (k.chunk128 * c + k.tile128);
     const float t32 = k.base32 + k.step32 * steps + rounds32 * (k.round_step32 * steps + k.round32) +
                       k.chunk32 * c * (float)tiles32 / 256.f;
-    return t128 < t32;
+    return t128 < 1.05f * t32;
 }
 
 // Chunks in flight per wave: five, and three or two where five do not fit the 128 registers of the 16-wave form (records of
