@@ -194,17 +194,22 @@ __device__ __forceinline__ void quantize_step(const ScaledArgs& g, uint8_t* obas
     }
 }
 
-// Zeros for the padding of a quantized result: `rows` row tiles from rt0 on, K steps from ks0 to the last (columns are
-// padded to 256), shared among the waves.  Written by the workgroups of the last columns (and rows); with tiles of their own
-// the padding took a whole product each, and five of eight XCDs nothing else: 736 x 64 x 10880, batch 32, 4 by 4 bits 86 us,
-// 50 us this way.
+// Zeros (codes and scale bytes) for the padding of a quantized result: `rows` row tiles from rt0 on, K steps ks0 to ks1 - 1,
+// shared among the waves.  Written by the workgroups of the last columns (padded to 256) and rows (to an even number of row
+// tiles); with tiles of their own the padding took a whole product each, and five of eight XCDs nothing else: 736 x 64 x
+// 10880, batch 32, 4 by 4 bits 86 us, 48 us this way.
 template <int QO>
-__device__ __forceinline__ void zero_padding(const ScaledArgs& g, uint8_t* obase, int64_t rt0, int rows, int64_t ks0, const float* lds,
+__device__ __forceinline__ void zero_padding(const ScaledArgs& g, uint8_t* obase, int64_t rt0, int rows, int64_t ks0, int64_t ks1,
                                              int wave, int waves, int lane) {
-    for (int64_t t = wave; t < rows * (g.go.ksteps - ks0); t += waves) {
-        const int64_t rt = rt0 + t % rows;
-        quantize_step<QO>(g, obase, rt, rt * 32 + (lane & 31), ks0 + t / rows, lds, lds, lane);
-    }
+    for (int64_t ks = ks0 + wave; ks < ks1; ks += waves)
+        for (int64_t rt = rt0; rt < rt0 + rows && rt < g.go.row_tiles; ++rt) {
+            uint8_t* unit = obase + mat_unit(g.go, QO == 2 ? rt : rt >> 1, ks);
+            for (int f = QO == 2 ? 0 : (int)(rt & 1); f < (QO == 2 ? 2 : (int)(rt & 1) + 1); ++f) {
+                *reinterpret_cast<uint4*>(unit + frag_lo(f, lane)) = make_uint4(0, 0, 0, 0);
+                *reinterpret_cast<uint2*>(unit + frag_hi(f, lane)) = make_uint2(0, 0);
+            }
+            obase[g.go.frag_bytes + ((rt * (g.go.ksteps / 4) + (ks >> 2)) * 64 + lane) * 4 + (ks & 3)] = 0;
+        }
 }
 
 // f(B), f(B + 1), ..., f(E - 1) with the number as a compile-time constant: what indexes register arrays below.
@@ -559,7 +564,7 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
             }
         }
         if (bn == g.tiles_n - 1)
-            zero_padding<QO>(g, obase, bm * 2 * TM, 2 * TM, (bn + 1) * TN, bias_lds, wave8, WS ? 8 : 4, lane);
+            zero_padding<QO>(g, obase, bm * 2 * TM, 2 * TM, (bn + 1) * TN, g.go.ksteps, wave8, WS ? 8 : 4, lane);
         return;
     }
     float* Y = g.Y + bz * g.batch_stride_y;
@@ -749,10 +754,9 @@ __global__ __launch_bounds__(kSplitWaves * 64) void gemm_scaled_split_kernel(Sca
         const bool last_n = bn == g.tiles_n - 1, last_m = bm == g.tiles_m - 1;
         const int64_t ks1 = (bn + 1) * (RB / 2);                      // the K step of the output behind this tile's
         const int64_t rt0 = bm * RA, rt1 = rt0 + RA;
-        const int more = last_m && rt1 < g.go.row_tiles ? (int)(g.go.row_tiles - rt1) : 0;    // row tiles are padded to an even number
-        if (last_n) zero_padding<QO>(g, obase, rt0, RA + more, ks1, bias_lds, wave, NW, lane);
-        for (int64_t t = wave; t < more * (RB / 2); t += NW)
-            quantize_step<QO>(g, obase, rt1 + t % more, (rt1 + t % more) * 32 + (lane & 31), ks1 - RB / 2 + t / more, bias_lds, bias_lds, lane);
+        if (last_n) zero_padding<QO>(g, obase, rt0, RA, ks1, g.go.ksteps, wave, NW, lane);
+        if (last_m && rt1 < g.go.row_tiles)
+            zero_padding<QO>(g, obase, rt1, (int)(g.go.row_tiles - rt1), ks1 - RB / 2, last_n ? g.go.ksteps : ks1, wave, NW, lane);
     }
 }
 
