@@ -415,6 +415,10 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
     // the bias of the workgroup's columns, decoded by the matrix waves while the first stage is on its way
     float* bias_lds = reinterpret_cast<float*>(smem + QoutLds<TN, WS>::bias_offset(kStages * STAGE + 2 * SCALES));
     if constexpr (QO != 0) {
+        if (!copier && bn == g.tiles_n - 1) {
+            zero_padding<QO>(g, g.out + bz * g.go.matrix, bm * 2 * TM, 2 * TM, (bn + 1) * TN, g.go.ksteps, wave, 4, lane);
+            wait_vmcnt<0>();                              // stores of its own would be counted among the copies awaited below
+        }
         if (!copier && g.bias_mant != nullptr)
             for (int c = threadIdx.x; c < 64 * TN; c += 256) bias_lds[c] = bias_value(g, bn * (64 * TN) + c);
     }
@@ -563,8 +567,6 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
                 __builtin_amdgcn_wave_barrier();
             }
         }
-        if (bn == g.tiles_n - 1)
-            zero_padding<QO>(g, obase, bm * 2 * TM, 2 * TM, (bn + 1) * TN, g.go.ksteps, wave8, WS ? 8 : 4, lane);
         return;
     }
     float* Y = g.Y + bz * g.batch_stride_y;
