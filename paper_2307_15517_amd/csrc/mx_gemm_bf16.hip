@@ -493,9 +493,11 @@ mx_status launch_bf16_split(BfArgs& g, int64_t batch, hipStream_t st) {
 // 19.6; 512 x 4096 x 4096 64x128 20.6, 64x64 32, 128x256 41; 700 x 4096 x 4096 128x128 26, 64x128 34, 128x256 41; 1500 x
 // 4096 x 4096 128x256 45, 128x128 53.  Tiles of 128 x 128 are taken again, two workgroups on a compute unit, where
 // 128 x 256 would need a second round that fills less than the chip (1024 x 11008 x 4096: 78 against 93 us): while that
-// round would be less than three eighths full, or K is short and the rounds' own cost counts.  Fuller and longer, the
-// larger tile's fewer operand bytes win (3687 x 3922 x 7152, 464 tiles: 176 us, 240 with 128x128; 424 random products with
-// such a round: 33 more than a tenth slower than with 128x256 where the round alone decided, 6 of them this way).  Nor where
+// round would be less than three eighths full (half, where the result is quantized), or K is at most 1024 (1280) and the
+// rounds' own cost counts, or the result has up to 128 columns, which 128x128 covers as often (8 x 7102 x 32 x 2336: 44 us, 62
+// with 128x256).  Fuller and longer, the larger tile's fewer operand bytes win (3687 x 3922 x 7152, 464 tiles: 176 us, 240
+// with 128x128; over 1078 random products past three eighths a median of 5 to 30 percent past a half; plain ones between the
+// two lie within a tenth either way).  Nor where
 // two columns of 128x128 would read a left operand past the last-level cache twice and one of 128x256 once (batch 32 of
 // 1221 x 140 x 9744: 244 us, 371 with 128x128).
 // With at least two tiles of 128 x 256 per compute unit two workgroups share one (three stages each), so that one
@@ -510,7 +512,8 @@ mx_status pick_bf16(BfArgs& g, int64_t batch, hipStream_t st) {
     if (groups(2, 2) <= kCus) return launch_bf16_split<2, 2, QOUT>(g, batch, st);
     if (groups(2, 4) <= kCus) return launch_bf16<1, 2, 6, 2, QOUT>(g, batch, st);
     const int64_t tiles = groups(4, 8);
-    const bool part_round = tiles > kCus && tiles < 2 * kCus && (tiles <= kCus * 11 / 8 || g.ksteps <= 48);
+    const bool part_round = tiles > kCus && tiles < 2 * kCus &&
+                            (cols <= 4 || tiles <= kCus * (QOUT ? 12 : 11) / 8 || g.ksteps <= (QOUT ? 40 : 32));
     const bool left_twice = cols > 4 && cols <= 8 && rows * g.ksteps * kBfUnitBytes * batch > (256LL << 20);
     if (!left_twice && (groups(4, 4) <= kCus || part_round)) return launch_bf16<2, 2, 5, 2, QOUT>(g, batch, st);
     if (tiles >= 2 * kCus) return launch_bf16<2, 4, 3, 2, QOUT>(g, batch, st);

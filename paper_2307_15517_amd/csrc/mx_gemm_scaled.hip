@@ -806,10 +806,11 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
 // 64x256 19.4, 128x256 28; 700 x 4096 x 4096 64x256 19.8, 64x128 20.9, 128x256 28; 1500 x 4096 x 4096 128x256 31, 64x256
 // 36.  Tiles of 64 x 256 are taken again, two workgroups on a compute unit, where 128 x 256 would need a second round
 // that fills less than the chip (700 x 11008 x 4096: 36 against 60 us, 1024 x 11008 x 4096: 52 against 61 us): while that
-// round would be less than three eighths full, or K is short and the rounds' own cost counts.  Fuller and longer, the
-// larger tile's fewer operand bytes win (3744 x 3456 x 8128, 420 tiles, 7 by 4 bits: 107 us, 124 with 64x256; batch 32 of
-// 1531 x 256 x 5632, 384 tiles, 4 by 4 bits: 71 us, 107 with 128x128), but for a two-piece right operand, whose large tile
-// has no copy waves.  A wave
+// round would be at most half full, or K is short and the rounds' own cost counts.  Fuller and longer, the larger tile's
+// fewer operand bytes win (3744 x 3456 x 8128, 420 tiles, 7 by 4 bits: 107 us, 124 with 64x256; over 1622 random products with a second round more than three eighths full: within a round up to
+// half full the smaller tile is 2 to 30 percent faster at any K, past it even at K = 3072 and up to 15 percent slower at
+// 10000; batches of 32 with twelve tiles each lie either way), but for a two-piece right operand, whose large tile has no
+// copy waves, and results of up to 128 columns, which 128 x 128 tiles cover as often as 128 x 256.  A wave
 // of a one-piece left operand takes whole units of 64 rows: it has 128 x 128 in the place of both 64-row forms (700 x
 // 4096 x 4096, 4 by 3 bits: 15 against 21.5 us for 128 x 256; 1024 x 11008 x 4096: 32 against 43 us).
 //
@@ -831,7 +832,7 @@ mx_status pick_tile(ScaledArgs& g, int64_t batch, hipStream_t st) {
     if (groups(1, 2) <= kCus) return launch_scaled_split<PA, PB, 1, 2, QO>(g, batch, st);
     const int64_t tiles = groups(4, 8);
     const bool part_round = tiles > kCus && tiles < MX_SCALED_TWO_PER_CU_TILES &&
-                            (PB == 2 || tiles <= kCus * 11 / 8 || g.ksteps <= 24);
+                            (PB == 2 || (PA == 1 && cols <= 4) || tiles <= kCus * 3 / 2 || g.ksteps <= 48);
     if constexpr (PA == 2) {
         if (groups(2, 4) <= kCus) return launch_scaled<PA, PB, 1, 2, 4, 2, QO>(g, batch, st);
         if constexpr (PB == 1) {
