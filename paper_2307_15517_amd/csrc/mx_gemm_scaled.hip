@@ -222,15 +222,23 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // LDS of the quantized ending: the waves' turn-around tiles of 32 rows lie where the stages were, one per matrix wave, or
-// two when copy waves help; the bias of the 64*TN columns lies behind both.
-template <int TN, int WS> struct QoutLds {
+// two when copy waves take a row tile of their own; the bias of the 64*TN columns lies behind both.
+template <int TM, int TN, int WS> struct QoutLds {
     static constexpr int kPitch = 32 * TN + 4;           // floats; the skew spreads the rows over the banks
-    static constexpr int kTiles = (WS ? 8 : 4) * 32 * kPitch * 4;
+    static constexpr int kTiles = (WS && TM == 2 ? 8 : 4) * 32 * kPitch * 4;
     static constexpr int bias_offset(int pipe) { return pipe > kTiles ? pipe : kTiles; }
 };
 
-// S: LDS stages.  The stage of step ks is free once its fragments are in registers, i.e. from
-// the barrier of step ks on, so the copy of step ks+S is issued during step ks.
+// K steps by which the copies run ahead with s stages
+constexpr int staged_ahead(int s) { return s >= 6 ? s - 1 : s; }
+
+// S: LDS stages.  The stage of step ks is free once its fragments are in registers.  Up to five stages: that is awaited
+// ahead of the barrier of step ks, and the copy of step ks+S is issued during step ks.  From six on nothing is awaited
+// there: the reads that step ks-1 issued (of step ks) return while step ks runs, each awaited by the matrix instruction
+// that needs it, so what the barrier of step ks tells is that the stage of step ks-1 is free, and step ks issues the copy
+// of step ks+S-1.  With small tiles a step is too short (four matrix instructions per wave) to have its reads back
+// before the next barrier: 333 x 4096 x 11008, 8 by 4 bits, 64 x 128 with eight stages 27.1 us when they are awaited,
+// 25.6 us this way.
 // OCC: workgroups the register and LDS budget must leave room for on one compute unit.
 // QO: 0 = fp32 result; 1 / 2 = add the bias and quantize the tile to an output format of one / two
 // mantissa pieces (Section 3.2 of the paper: the emulated operator quantizes its result; Fig. 2b: the
@@ -243,7 +251,10 @@ template <int TN, int WS> struct QoutLds {
 template <int PA, int PB, int TM, int TN, int S, int OCC, int QO, int WS>
 __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kernel(ScaledArgs g) {
     constexpr int kStages = S;
-    static_assert(S >= 3 && S <= 5, "the scale copies of a group must have landed by its step 3");
+    constexpr int E = staged_ahead(S);                 // K steps by which the copies run ahead (see the pipeline below)
+    constexpr int TAIL = E < S ? 2 : MX_SCALED_TAIL_MFMAS;
+    constexpr int LEAD = (E - 1) / 4;                  // groups by which the scale copies run ahead of the next group's
+    constexpr int SLOTS = LEAD + 2;                    // scale slots
     constexpr int UA = (PA == 2) ? 2 * TM : TM;        // units of the A tile per K step
     constexpr int UB = (PB == 2) ? 2 * TN : TN;
     constexpr int NU = UA + UB;
@@ -258,7 +269,7 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
     constexpr int NT = 2 * TM + 2 * TN;                // row tiles of the workgroup tile (A then B)
     constexpr int NSC = (NT + 3) / 4;                  // 256-byte scale copies per wave per group of 4 steps
     constexpr int SCALES = NT * 256;                   // bytes of one scale slot
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // kStages stages, then 2 scale slots
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // kStages stages, then SLOTS scale slots
 
     const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wave = wave8 & 3;                        // position among the matrix waves, or among the copy waves
@@ -401,19 +412,17 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
         for (int t = 0; t < RB; ++t) b[t] = sc[(2 * TM + wn * RB + t) * 64];
     };
 
-    // Pipeline.  Queue of copies, oldest first, when step ks starts:  D(ks+1) ... D(ks+S-1), with
-    // the scale copies of the next group right ahead of the data copies issued at step 0 of a group.
-    // Copies land in issue order, so once only the data copies of the newest S-2 steps are outstanding
-    // (at step 3 of the group: those issued at steps 0, 1, 2 when S = 5) the scale copies have landed
-    // too, and step 3 may read them; with more than five stages they could still be in flight there.
-    // Waiting until only the newest S-2 steps' copies are outstanding means D(ks+1) has landed; the barrier then
-    // publishes it and tells that every wave is done reading the stage of step ks (read into
-    // registers during step ks-1), which the copy of step ks+S overwrites.
+    // Pipeline.  Queue of copies, oldest first, when step ks starts:  D(ks+1) ... D(ks+E-1).  The scale copies of
+    // group g+1 go right ahead of the data copies of step 4(g-LEAD), D(4(g-LEAD)+E); E <= 4*LEAD + 4, so that is at
+    // the latest ahead of D(4g+4), which step 3 of group g awaits: copies land in issue order, and step 3 may read the
+    // scales.  The copies ahead of the loop are issued in the same order.
+    // Waiting until only the newest E-2 steps' copies are outstanding means D(ks+1) has landed; the barrier then
+    // publishes it and tells that every wave is done reading the stage that D(ks+E) overwrites.
     // Inside a step the MFMAs (operands already in registers) are issued at once, and the LDS reads
-    // for the next step, the copies for step ks+3 and the scale traffic are slotted between them so
+    // for the next step, the copies for step ks+E and the scale traffic are slotted between them so
     // that the matrix pipe never waits for them.
     // the bias of the workgroup's columns, decoded by the matrix waves while the first stage is on its way
-    float* bias_lds = reinterpret_cast<float*>(smem + QoutLds<TN, WS>::bias_offset(kStages * STAGE + 2 * SCALES));
+    float* bias_lds = reinterpret_cast<float*>(smem + QoutLds<TM, TN, WS>::bias_offset(kStages * STAGE + SLOTS * SCALES));
     if constexpr (QO != 0) {
         if (!copier && bn == g.tiles_n - 1) {
             zero_padding<QO>(g, g.out + bz * g.go.matrix, bm * 2 * TM, 2 * TM, (bn + 1) * TN, g.go.ksteps, wave, 4, lane);
@@ -422,14 +431,30 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
         if (!copier && g.bias_mant != nullptr)
             for (int c = threadIdx.x; c < 64 * TN; c += 256) bias_lds[c] = bias_value(g, bn * (64 * TN) + c);
     }
+    // scale copies that may be outstanding at step j of a group: those issued among the newest E - 2 steps' data copies
+    constexpr auto scales_behind = [](int j) {
+        int n = 0;
+        for (int u = 0; u < E - 2; ++u) n += (j + 3 - u + 4 * E) % 4 == 0;
+        return n;
+    };
+    // the barrier of a K step; the wave's LDS reads may still be under way at it when E < S (__syncthreads awaits them)
+    auto step_barrier = [&]() {
+        if constexpr (E < S) asm volatile("s_barrier" ::: "memory");
+        else __syncthreads();
+    };
     if (g.ksteps > 0) {
         if (copies) {
-            issue(0, 0);
 #pragma unroll
             for (int q = 0; q < NSC; ++q) issue_scale_one(q, 0, 0);
 #pragma unroll
-            for (int st = 1; st < S; ++st) issue(st, st);
-            wait_vmcnt<(S - 1) * NLOAD>();
+            for (int st = 0; st < E; ++st) {
+                if ((E - st) % 4 == 0 && E - st <= 4 * LEAD) {
+#pragma unroll
+                    for (int q = 0; q < NSC; ++q) issue_scale_one(q, LEAD + 1 - (E - st) / 4, LEAD + 1 - (E - st) / 4);
+                }
+                issue(st, st);
+            }
+            wait_vmcnt<(E - 1) * NLOAD + LEAD * NSC>();
         }
         __syncthreads();
         if (!copier) {
@@ -439,25 +464,29 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
     }
     constexpr int NM = PA * PB * RA * RB;              // MFMAs per K step
     int cur = 0;                                       // stage of the current step: ks % S
-    // byte offset, inside a unit row, of the K step whose copies the current step issues (step ks + S,
+    int into = E < S ? S - 1 : 0;                      // stage that its copies go to: (ks + E) % S
+    int rd = 1, wr = (LEAD + 1) % SLOTS;               // slots of the next group's scales and of those copied at its step 0
+    auto next_slot = [](int s) { return s + 1 == SLOTS ? 0 : s + 1; };
+    // byte offset, inside a unit row, of the K step whose copies the current step issues (step ks + E,
     // clamped to the last one): carried from step to step instead of being derived from ks each time
     const uint32_t last_off = (uint32_t)((g.ksteps - 1) * kUnitBytes);
-    uint32_t copy_off = (uint32_t)S * kUnitBytes;
+    uint32_t copy_off = (uint32_t)E * kUnitBytes;
     copy_off = copy_off < last_off ? copy_off : last_off;
     if (copier) {
         // the copy waves' loop: the same waits, barriers and copies, in the same order, as the WS = 0 form
         for (int64_t ks4 = 0; ks4 < groups; ++ks4) {
             auto cstep = [&](auto jc) {
                 constexpr int j = decltype(jc)::value;
-                wait_vmcnt<(S - 2) * NLOAD + (j == 1 ? NSC : 0)>();
-                __syncthreads();
+                wait_vmcnt<(E - 2) * NLOAD + scales_behind(j) * NSC>();
+                step_barrier();
                 if (j == 0) {
 #pragma unroll
-                    for (int q = 0; q < NSC; ++q) issue_scale_one(q, ks4 + 1, (int)((ks4 + 1) & 1));
+                    for (int q = 0; q < NSC; ++q) issue_scale_one(q, ks4 + 1 + LEAD, wr);
+                    wr = next_slot(wr);
                 }
 #pragma unroll
-                for (int q = 0; q < NI; ++q) copy_item(src[q] + copy_off, lds0 + cur * STAGE + dst[q]);
-                cur = cur + 1 == S ? 0 : cur + 1;
+                for (int q = 0; q < NI; ++q) copy_item(src[q] + copy_off, lds0 + into * STAGE + dst[q]);
+                into = into + 1 == S ? 0 : into + 1;
                 copy_off = copy_off + kUnitBytes < last_off ? copy_off + kUnitBytes : last_off;
             };
             cstep(std::integral_constant<int, 0>{});
@@ -479,24 +508,23 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
             constexpr int j = decltype(jc)::value;
             constexpr int set = j & 1;
             const int nxt = cur + 1 == S ? 0 : cur + 1;
-            // side work of this step, in issue order: LDS reads for step ks+1, copies for step ks+S,
-            // at j == 0 the scale copies of the next group, at j == 3 the read of those scales
+            // side work of this step, in issue order: LDS reads for step ks+1, copies for step ks+E,
+            // at j == 0 the scale copies of a coming group, at j == 3 the read of the next one's scales
             constexpr int NCP = WS ? 0 : NI, NSCP = WS ? 0 : NSC;      // copies issued by this wave
             constexpr int NAUX = (NUA + NUB) + NCP + (j == 0 ? NSCP : 0) + (j == 3 ? 1 : 0);
-            constexpr int NSLOT = NM > MX_SCALED_TAIL_MFMAS ? NM - MX_SCALED_TAIL_MFMAS : 1;
+            constexpr int NSLOT = NM > TAIL ? NM - TAIL : 1;
             constexpr int X0 = NUA + NUB, X1 = X0 + (j == 0 ? NSCP : 0);   // the scale copies go ahead of the step's data copies
             auto aux = [&](auto xc) {
                 constexpr int x = decltype(xc)::value;
                 if constexpr (x < X0) read_unit(xc, nxt, std::integral_constant<int, set ^ 1>{});
-                else if constexpr (x < X1) issue_scale_one(x - X0, ks4 + 1, (int)((ks4 + 1) & 1));
-                else if constexpr (x < X1 + NCP) copy_item(src[x - X1] + copy_off, lds0 + cur * STAGE + dst[x - X1]);
-                else read_scales((int)((ks4 + 1) & 1), nxA, nxB);
+                else if constexpr (x < X1) issue_scale_one(x - X0, ks4 + 1 + LEAD, wr);
+                else if constexpr (x < X1 + NCP) copy_item(src[x - X1] + copy_off, lds0 + into * STAGE + dst[x - X1]);
+                else read_scales(rd, nxA, nxB);
             };
             __builtin_amdgcn_sched_barrier(0);
-            // newer than D(ks+1): the data copies of the last S-2 steps, and at j == 1 the scale copies
-            // issued at the previous step, ahead of its data copies (at step 2 they are simply awaited too)
-            if constexpr (WS == 0) wait_vmcnt<(S - 2) * NLOAD + (j == 1 ? NSC : 0)>();
-            __syncthreads();
+            // newer than D(ks+1): the data copies of the last E-2 steps, and the scale copies among them
+            if constexpr (WS == 0) wait_vmcnt<(E - 2) * NLOAD + scales_behind(j) * NSC>();
+            step_barrier();
             __builtin_amdgcn_sched_barrier(0);
             // one piece pair after the other: consecutive MFMAs never share an accumulator
             static_for<0, NM>([&](auto mc) {
@@ -513,12 +541,15 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
                 __builtin_amdgcn_sched_barrier(0);        // pin the interleaving as written
             });
             cur = nxt;
+            into = into + 1 == S ? 0 : into + 1;
             copy_off = copy_off + kUnitBytes < last_off ? copy_off + kUnitBytes : last_off;
         };
         kstep(std::integral_constant<int, 0>{});
         kstep(std::integral_constant<int, 1>{});
         kstep(std::integral_constant<int, 2>{});
         kstep(std::integral_constant<int, 3>{});
+        rd = next_slot(rd);
+        wr = next_slot(wr);
     }
     if constexpr (WS == 0) wait_vmcnt<0>();               // the clamped tail copies must not outlive the LDS
 
@@ -529,7 +560,7 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
         // holds the 32 consecutive elements of row i' that a fragment of the next product's left operand
         // gives it, and runs the quantizer of mx_quantize_pack on them.
         static_assert(RB % 2 == 0, "a wave covers whole K steps of the output");
-        constexpr int PITCH = QoutLds<TN, WS>::kPitch;
+        constexpr int PITCH = QoutLds<TM, TN, WS>::kPitch;
         __syncthreads();                                 // every wave is done reading the stages, the bias is in LDS
         float* tile = reinterpret_cast<float*>(smem) + wave * (32 * PITCH);
         uint8_t* obase = g.out + bz * g.go.matrix;
@@ -540,16 +571,19 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
                 for (int r = 0; r < 16; ++r)
                     to[(8 * (r >> 2) + 4 * h + (r & 3)) * PITCH + tb * 32 + i] = __builtin_ldexpf(acc[ta][tb][r], g.eadj);
         };
-        auto quantize = [&](int ta, const float* from) {
-            const int64_t rt = rtA0 + ta, row = rt * 32 + i;
-#pragma unroll
-            for (int ksl = 0; ksl < RB / 2; ++ksl) {
-                const int64_t ks = rtB0 / 2 + ksl;        // K step of the output operand
-                quantize_step<QO>(g, obase, rt, row, ks, from + i * PITCH + ksl * 64 + h * 32,
-                                  bias_lds + wn * (32 * RB) + ksl * 64 + h * 32, lane);
-            }
+        auto quantize = [&](int ta, int ksl, const float* from) {
+            const int64_t rt = rtA0 + ta;                 // ks: K step of the output operand
+            quantize_step<QO>(g, obase, rt, rt * 32 + i, rtB0 / 2 + ksl, from + i * PITCH + ksl * 64 + h * 32,
+                              bias_lds + wn * (32 * RB) + ksl * 64 + h * 32, lane);
         };
-        if constexpr (WS) {
+        if constexpr (WS && RA == 1) {
+            // one row tile: the copy wave of the same position takes every other K step of the output
+            if (!copier) turn(0, tile);
+            __syncthreads();
+#pragma unroll
+            for (int ksl = 0; ksl < RB / 2; ++ksl)
+                if ((ksl & 1) == (copier ? 1 : 0)) quantize(0, ksl, tile);
+        } else if constexpr (WS) {
             // the copy wave of the same position takes one of the two row tiles: turning and quantizing is a serial
             // chain that nothing else covers with one workgroup per compute unit (2000 x 4096 x 4096, 8 by 4 bits:
             // 39.2 us with the matrix waves alone, 36.7 us this way; 333 x 11008 x 4096: 32.7 -> 29.9 us)
@@ -557,13 +591,15 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
             float* tile1 = tile + 4 * 32 * PITCH;
             if (!copier) { turn(0, tile); turn(1, tile1); }
             __syncthreads();
-            quantize(copier ? 1 : 0, copier ? tile1 : tile);
+#pragma unroll
+            for (int ksl = 0; ksl < RB / 2; ++ksl) quantize(copier ? 1 : 0, ksl, copier ? tile1 : tile);
         } else {
 #pragma unroll
             for (int ta = 0; ta < RA; ++ta) {
                 turn(ta, tile);
                 __builtin_amdgcn_wave_barrier();
-                quantize(ta, tile);
+#pragma unroll
+                for (int ksl = 0; ksl < RB / 2; ++ksl) quantize(ta, ksl, tile);
                 __builtin_amdgcn_wave_barrier();
             }
         }
@@ -782,8 +818,9 @@ template <int PA, int PB, int TM, int TN, int S, int OCC, int QO = 0, int WS = 0
 mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
     static_assert(WS == 0 || OCC == 1, "copy waves: one workgroup per compute unit");
     constexpr int UA = (PA == 2) ? 2 * TM : TM, UB = (PB == 2) ? 2 * TN : TN;
-    constexpr int pipe = S * (UA + UB) * kUnitBytes + 2 * (2 * TM + 2 * TN) * 256;
-    constexpr int smem = QO == 0 ? pipe : QoutLds<TN, WS>::bias_offset(pipe) + 64 * TN * 4;
+    constexpr int slots = (staged_ahead(S) - 1) / 4 + 2;
+    constexpr int pipe = S * (UA + UB) * kUnitBytes + slots * (2 * TM + 2 * TN) * 256;
+    constexpr int smem = QO == 0 ? pipe : QoutLds<TM, TN, WS>::bias_offset(pipe) + 64 * TN * 4;
     static_assert(smem * OCC <= 160 * 1024, "LDS budget of one compute unit");
     auto kern = gemm_scaled_kernel<PA, PB, TM, TN, S, OCC, QO, WS>;
     static std::atomic<uint64_t> done{0};
@@ -799,8 +836,7 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
 }
 
 // The smallest tile that needs no more than one workgroup per compute unit: small tiles put more compute units to work,
-// but load more bytes per product, and with a second round of workgroups the next larger tile was the faster one (not for
-// short K: 2048 x 3072 x 768 12.3 us, 10.4 with 64x128).  The
+// but load more bytes per product, and with a second round of workgroups the next larger tile was the faster one.  The
 // two smallest tiles split K over their waves, the others share their operands through LDS.  Measured with 8 by 4 bits,
 // block 32 (us; the form taken first): 128 x 4096 x 4096 32x64 9.3, 32x32 12.7, 64x128 13; 333 x 4096 x 4096 64x128 14.1,
 // 64x256 19.4, 128x256 28; 700 x 4096 x 4096 64x256 19.8, 64x128 20.9, 128x256 28; 1500 x 4096 x 4096 128x256 31, 64x256
@@ -809,8 +845,8 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
 // round would be at most half full, or K is short and the rounds' own cost counts.  Fuller and longer, the larger tile's
 // fewer operand bytes win (3744 x 3456 x 8128, 420 tiles, 7 by 4 bits: 107 us, 124 with 64x256; over 1622 random products with a second round more than three eighths full: within a round up to
 // half full the smaller tile is 2 to 30 percent faster at any K, past it even at K = 3072 and up to 15 percent slower at
-// 10000; batches of 32 with twelve tiles each lie either way), but for a two-piece right operand, whose large tile has no
-// copy waves, and results of up to 128 columns, which 128 x 128 tiles cover as often as 128 x 256.  A wave
+// 10000; batches of 32 with twelve tiles each lie either way), but for results of up to 128 columns, which 128 x 128 tiles
+// cover as often as 128 x 256, and with a two-piece right operand.  A wave
 // of a one-piece left operand takes whole units of 64 rows: it has 128 x 128 in the place of both 64-row forms (700 x
 // 4096 x 4096, 4 by 3 bits: 15 against 21.5 us for 128 x 256; 1024 x 11008 x 4096: 32 against 43 us).
 //
@@ -819,6 +855,22 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
 // compute unit (three stages each), so that one workgroup's barrier and copy waits hide under the other's MFMAs;
 // otherwise one workgroup per compute unit runs with four copy waves beside its four matrix waves and five stages (the
 // copies of a K step are requested four steps ahead).
+//
+// For batches of one and two (larger ones lie either way, up to a fifth slower) four more lines, drawn on 14600 random
+// products timed in every form, 8 by 4 bits unless said:
+// * At most one workgroup per compute unit and K from 48 steps on: copy waves and eight stages (one-piece left operand: 52).
+//   What bounds these is the copy path of a compute unit (12 KiB per step at about 105 GB/s), and the copy waves keep it
+//   busy: 333 x 4096 x 11008 31.4 -> 25.9 us, 512 x 4096 x 4096 15.5 -> 13.8, 333 x 4096 x 11008 with 4 by 4 bits 31.8 ->
+//   26.2; over 698 products 12 percent on average, none slower; 600 x 3072 x 768, twelve steps, takes 6.6 for 6.2.
+// * K up to 28 steps: tiles of 64 x 128 (128 x 128) on to 700 (512) of them, two on a compute unit, since the larger tiles'
+//   fixed cost is not repaid: 2048 x 3072 x 768 11.7 -> 10.0 us; 5 to 18 percent on 430 products.
+// * 64 x 384 where it covers the result in one round and 128 x 256 leaves a third of the chip idle or more:
+//   333 x 11008 x 4096 27.6 -> 24.0 us; 8 percent on 157 products from 32 steps on, below that either way.
+// * Two pieces on both sides: 128 x 128 with copy waves in one round, else two workgroups on a compute unit (700 x 4096 x
+//   4096, 8 by 8 bits, 47.9 -> 28.2 us, 2048 x 11008 x 4096 177 -> 166), 64 x 128 for up to 16 steps and where 128 x 128
+//   would need between two and three rounds of one (1300 x 6016 x 3072 84 -> 53 us, 62 with 128 x 128).
+// One piece by two: 128 x 256 with copy waves from 16 steps on (2048 x 4096 x 11008, 4 by 8 bits, 93.8 -> 83.0 us; at one
+// group of four steps 48 us for 34).
 template <int PA, int PB, int QO = 0>
 mx_status pick_tile(ScaledArgs& g, int64_t batch, hipStream_t st) {
     // 32-bit offsets along K in the staged forms, so the same limit whatever the tile
@@ -833,20 +885,41 @@ mx_status pick_tile(ScaledArgs& g, int64_t batch, hipStream_t st) {
     const int64_t tiles = groups(4, 8);
     const bool part_round = tiles > kCus && tiles < MX_SCALED_TWO_PER_CU_TILES &&
                             (PB == 2 || (PA == 1 && cols <= 4) || tiles <= kCus * 3 / 2 || g.ksteps <= 48);
+    const bool few = batch <= 2;
     if constexpr (PA == 2) {
-        if (groups(2, 4) <= kCus) return launch_scaled<PA, PB, 1, 2, 4, 2, QO>(g, batch, st);
+        const int64_t small = groups(2, 4);
         if constexpr (PB == 1) {
+            if (small <= kCus && few && g.ksteps >= 48) return launch_scaled<PA, PB, 1, 2, 8, 1, QO, 1>(g, batch, st);
+        }
+        if (small <= kCus) return launch_scaled<PA, PB, 1, 2, 4, 2, QO>(g, batch, st);
+        if constexpr (PB == 1) {
+            if (small <= 700 && few && g.ksteps <= 28) return launch_scaled<PA, PB, 1, 2, 4, 2, QO>(g, batch, st);
             if (groups(2, 8) <= kCus || part_round) return launch_scaled<PA, PB, 1, 4, 4, 2, QO>(g, batch, st);
+            if (groups(2, 12) <= kCus && few && g.ksteps >= 32) return launch_scaled<PA, PB, 1, 6, 6, 1, QO, 1>(g, batch, st);
+        } else {
+            const int64_t mid = groups(4, 4);
+            if (few && ((mid <= kCus && g.ksteps <= 16) || (mid > 2 * kCus && mid <= 3 * kCus)))
+                return launch_scaled<PA, PB, 1, 2, 4, 2, QO>(g, batch, st);
+            if (few && mid <= kCus) return launch_scaled<PA, PB, 2, 2, 6, 1, QO, 1>(g, batch, st);
         }
     } else {
-        if (groups(4, 4) <= kCus || part_round) return launch_scaled<PA, PB, 2, 2, 4, 2, QO>(g, batch, st);
+        const int64_t small = groups(4, 4);
+        if constexpr (PB == 1) {
+            if (small <= kCus && few && g.ksteps >= 52) return launch_scaled<PA, PB, 2, 2, 8, 1, QO, 1>(g, batch, st);
+            if (small <= 2 * kCus && few && g.ksteps <= 28) return launch_scaled<PA, PB, 2, 2, 4, 2, QO>(g, batch, st);
+        }
+        if (small <= kCus || part_round) return launch_scaled<PA, PB, 2, 2, 4, 2, QO>(g, batch, st);
     }
+    static_assert(QO == 0 || PB == 1, "the quantized ending is built for one-piece right operands");
     if constexpr (PB == 1) {
         if (tiles >= MX_SCALED_TWO_PER_CU_TILES) return launch_scaled<PA, PB, 2, 4, 3, 2, QO>(g, batch, st);
         return launch_scaled<PA, PB, 2, 4, 5, 1, QO, 1>(g, batch, st);
+    } else if constexpr (PA == 2) {
+        if (few) return launch_scaled<PA, PB, 2, 2, 3, 2, QO>(g, batch, st);
+        return launch_scaled<PA, PB, 2, 4, 3, 1, QO>(g, batch, st);
     } else {
-        static_assert(QO == 0, "the quantized ending is built for one-piece right operands");
-        return launch_scaled<PA, PB, 2, 4, 3, 1>(g, batch, st);
+        if (g.ksteps >= 16) return launch_scaled<PA, PB, 2, 4, 5, 1, QO, 1>(g, batch, st);
+        return launch_scaled<PA, PB, 2, 4, 3, 1, QO>(g, batch, st);
     }
 }
 

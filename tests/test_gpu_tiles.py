@@ -339,8 +339,8 @@ def test_attention_of_128_queries_in_blocks_of_32(heads, Sq, Sk, dim, R):
 
 # The forms of the matrix-layout product, (row tiles, column tiles) of 32 and what they select with blocks of 32 or 64 and a
 # two-piece left operand.  With a one-piece left operand 64 x 128 and 64 x 256 are 128 x 128, and so they are with blocks of
-# 16 from 64 x 256 on.  With a two-piece right operand, and with blocks of 16, no form has copy waves; with two pieces on
-# both sides everything from 64 x 256 on is 128 x 256.
+# 16 from 64 x 256 on.  With blocks of 16 no form has copy waves; with two pieces on both sides everything from 64 x 256 on
+# is 128 x 128.  (Forms that need a longer K: test_matrix_product_with_deep_stages.)
 MATRIX_FORMS_LONG_K = [
     (1, 100),      # 32 x 32, K split over the waves
     (2, 200),      # 32 x 64, K split
@@ -415,3 +415,38 @@ def test_matrix_quantized_output_on_long_k(rt, ct, block, wa, wo, rows):
         mx.mx_gemm_q(batch, M, N, K, A, fa, B, fb, MAT, mant, exps, fb, fo, out)
         torch.cuda.synchronize()
         assert torch.equal(out, want), "launch %d" % rep
+
+
+@pytest.mark.parametrize("rt,ct,steps", [(4, 400, 52), (4, 400, 61), (5, 390, 57), (11, 344, 33), (11, 344, 40), (8, 400, 24)])
+@pytest.mark.parametrize("block,wa,wb", [(32, 8, 4), (64, 4, 3), (32, 7, 6), (64, 3, 8)])
+def test_matrix_product_with_deep_stages(rt, ct, steps, block, wa, wb):
+    """The forms with six and eight stages and copy waves (64 x 128, 128 x 128, 64 x 384): numbers of K steps that fill the
+    last group of four, leave it with one and with three, every stage and every slot of the scales reused; the quantized
+    ending, whose work the copy waves share, where there is one."""
+    M, N, K = rt * 32 - 13, (ct * 32 - 8) // block * block, 64 * steps - (32 if block == 32 else 0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rt * ct + steps)
+    x, w = exact_operands(g, 1, M, N, K)
+    fa, fb = mx.fmt(block, wa), mx.fmt(block, wb)
+    A, B = mx.quantize_pack(x, fa, MAT), mx.quantize_pack(w, fb, MAT)
+    want = torch.mm(x[0].double(), w[0].t().double()).float()
+    assert want.abs().max() < 2.0 ** 24
+    for rep in range(5):
+        y = torch.full((M, N + 3), float("nan"), device="cuda")
+        mx.mx_gemm(1, M, N, K, A, fa, B, fb, MAT, y, N + 3, 0)
+        torch.cuda.synchronize()
+        assert torch.equal(y[:, :N], want), "launch %d" % rep
+        assert torch.isnan(y[:, N:]).all(), "columns past N written"
+    if wb > 4:
+        return
+    bias = torch.randint(-3, 4, (1, N), generator=g, device="cuda").float() * 64.0
+    mant, exps = mx.quantize(bias, fb)
+    for wo in (8, 4):
+        fo = mx.fmt(block, wo)
+        packed = torch.full((mx.mx_packed_bytes(1, M, N, fo, MAT),), 255, dtype=torch.uint8, device="cuda")
+        mx.mx_quantize_pack(want + bias, 1, M, N, N, 0, fo, MAT, packed)
+        for rep in range(3):
+            out = torch.full_like(packed, 255)
+            mx.mx_gemm_q(1, M, N, K, A, fa, B, fb, MAT, mant, exps, fb, fo, out)
+            torch.cuda.synchronize()
+            assert torch.equal(out, packed), "width %d, launch %d" % (wo, rep)
