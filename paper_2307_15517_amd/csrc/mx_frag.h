@@ -69,10 +69,9 @@ template <int W, int B> struct Unpack {
     }
 };
 
-// Exact int32 dot products of one block: D (32x32) = A half-blocks x B half-blocks.
+// Exact int32 dot products of one block, added to z: D (32x32) = A half-blocks x B half-blocks + z.
 template <int B>
-__device__ __forceinline__ v16i_t block_mfma(const uint32_t* a, const uint32_t* b) {
-    v16i_t z = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+__device__ __forceinline__ v16i_t block_mfma(const uint32_t* a, const uint32_t* b, v16i_t z) {
     if constexpr (B == 16) {
         const long la = (long)(((uint64_t)a[1] << 32) | a[0]);
         const long lb = (long)(((uint64_t)b[1] << 32) | b[0]);
@@ -86,6 +85,23 @@ __device__ __forceinline__ v16i_t block_mfma(const uint32_t* a, const uint32_t* 
         }
         return z;
     }
+}
+template <int B>
+__device__ __forceinline__ v16i_t block_mfma(const uint32_t* a, const uint32_t* b) {
+    return block_mfma<B>(a, b, v16i_t{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0});
+}
+
+// Block dots as fp32 without a conversion.  The integer accumulator starts at the bit pattern of 1.5 * 2^23, so the sum d
+// comes out as the bit pattern of the float 1.5 * 2^23 + d (|d| <= 2^20 < 2^22).  With s = 2^k, (1.5 * 2^23 + d) * s -
+// 1.5 * 2^23 * s is d * s in one fused multiply-add, exact since d * s fits the 24 bits of a float; both s and
+// -1.5 * 2^23 * s are bit patterns that integer adds build.
+constexpr uint32_t kDotBias = 0x4B400000u;
+constexpr uint32_t kDotBack = 0x80000000u + (23u << 23) + 0x00400000u;     // bits of -1.5 * 2^23 * s = bits of s + this
+__device__ __forceinline__ v16i_t dot_bias() {
+    v16i_t z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = (int)kDotBias;
+    return z;
 }
 
 }  // namespace mx

@@ -27,12 +27,15 @@ typedef v16i_t v16i;
 // round-robin and their partial tiles are added through LDS at the end.  Fragments come straight from global
 // memory in lane order, one chunk ahead of the arithmetic.
 //
-// Bound: vector instruction issue (at M = 128, N = K = 5120: 30.6 us, 234 us before; at 32 rows 12.5 us, 238 before;
-// 13824 -> 5120 at 32 rows 26 us, 631 before).  Every block of 32 x 32 outputs costs one MFMA (two for block 64) and 16 block
-// sums per lane, each of which is scaled and added: exponent sum, conversion, multiply-add (3 instructions) when all
-// block exponents of the chunk lie within [-31, 32], which makes 2^(Ea+Eb+c) a normal fp32 number that one integer
-// instruction builds; otherwise (also for zero blocks, whose byte is 0) with ldexp (4 instructions).  The row exponents
-// are turned through LDS, because a lane needs 16 rows' exponents and would otherwise extract each from its row's dword.
+// Bound: vector instruction issue (13824 -> 5120 at 32 rows, 8 by 4 bits, blocks of 16: 24.0 us on the 160 compute units that
+// have a tile).  Every block of 32 x 32 outputs costs one MFMA (two for block 64) and 16 block sums per lane, each of which
+// is scaled and added.  When all block exponents of the chunk lie within [-31, 32] that is two multiply-adds: the sums come
+// out of the matrix instruction as floats with a bias (dot_bias), the first takes the bias off and applies the row's
+// scale, exactly, the second applies the column's scale and adds.  With a conversion, an integer add for the scale and one
+// multiply-add it took 26.9 us (32 x 5120 x 5120 13.3 -> 12.4; 6 by 5 bits 35.6 -> 30.0), as it still does where the bias's
+// registers would cost a wave per SIMD (blocks of 64, of 32 with few bits, wide operands).  Otherwise (also for zero blocks,
+// whose byte is 0) it is done with ldexp, four instructions.  The row scales and what takes the bias off go through LDS,
+// because a lane needs those of 16 rows.
 // Waves split K rather than owning larger tiles because the products that arrive here are short in M (the batch of a
 // decode step, a short prompt): a 128 x 128 tile per workgroup left most of the chip idle, and the K loop of one wave
 // is a serial chain of loads, matrix instructions and scaling.
@@ -42,7 +45,9 @@ __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArg
     constexpr int kDwA = Piece<WA, B>::kDw, kDwB = Piece<WB, B>::kDw;
     constexpr int kHalfDw = B / 8;       // int8 dwords per lane per block
     constexpr int D = 2 * (kDwA + kDwB + 2) <= 64 ? 2 : 1;               // chunks in registers
-    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];       // xe[NW][4][32], red[NW/2][16][64]
+    // block sums with a bias (see above) where its sixteen registers leave the kernel its waves per SIMD
+    constexpr bool BIASED = B == 16 ? WA + WB <= (WB == 8 ? 13 : 14) : B == 32 && WA + WB >= 9 && WA + WB <= 14;
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];       // xe[NW][2][4][32], red[NW/2][16][64]
     const int nw = (int)blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = lane & 31, h = lane >> 5;
@@ -56,8 +61,8 @@ __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArg
     const uint8_t* Abase = g.A + bz * g.matrixA + ga * g.chunks * g.recordA;
     const uint8_t* Bbase = g.B + bz * g.matrixB + gb * g.chunks * g.recordB;
     const int eadj = g.eadj - Unpack<WA, B>::kScaleLog2 - Unpack<WB, B>::kScaleLog2;
-    uint32_t* xe = lds + wave * 128;
-    float* red = reinterpret_cast<float*>(lds + nw * 128);
+    uint32_t* xe = lds + wave * (BIASED ? 256 : 128);
+    float* red = reinterpret_cast<float*>(lds + nw * (BIASED ? 256 : 128));
 
     float acc[16];
 #pragma unroll
@@ -79,6 +84,10 @@ __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArg
     const uint32_t move = (uint32_t)(127 - g.bias + 32) * 0x01010101u, neutral = (uint32_t)g.bias * 0x01010101u;
     const bool arow = ga * 32 + i < g.M, brow = gb * 32 + i < g.N;       // padding rows take a neutral exponent
     const bool upper = ga * 32 + 16 < g.M;                               // rows 16..31 of the tile exist
+    // bits of the scales: 2^(Ea - bias) of a row, 2^(Eb - bias + all of eadj but the two biases) of a column
+    const uint32_t rowbits = (uint32_t)(127 - g.bias) << 23, colbits = (uint32_t)(127 + g.bias + eadj) << 23;
+    v16i bias = dot_bias();
+    if constexpr (BIASED) asm volatile("" : "+v"(bias));                 // sixteen registers, not a constant built per block
 
     const int64_t per_wave = (g.chunks - wave + nw - 1) / nw;           // may be negative: none
     if (per_wave > 0) {
@@ -90,38 +99,69 @@ __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArg
         for (int s = 0; s < D; ++s) {
             if (t0 + s < per_wave) {                                     // scalar condition: no load depends on it
                 const uint32_t ea = arow ? ea4[s] : neutral, eb = brow ? eb4[s] : neutral;
-                // row exponents -> LDS as integers [block][row]: each lane half writes two of its row's four blocks
-                const uint32_t e2 = h ? ea >> 16 : ea;
-                xe[(2 * h) * 32 + i] = e2 & 0xFFu;
-                xe[(2 * h + 1) * 32 + i] = (e2 >> 8) & 0xFFu;
+                const uint32_t e2 = h ? ea >> 16 : ea;                   // each lane half writes two of its row's four blocks
+                const uint32_t elo = e2 & 0xFFu, ehi = (e2 >> 8) & 0xFFu;
+                if constexpr (!BIASED) {
+                    xe[(2 * h) * 32 + i] = elo;                          // row exponents as integers -> LDS [block][row]
+                    xe[(2 * h + 1) * 32 + i] = ehi;
+                }
                 const uint32_t off = (((ea + move) ^ 0x80808080u) | ((eb + move) ^ 0x80808080u)) & 0xC0C0C0C0u;
                 const bool narrow = __builtin_amdgcn_ballot_w64(off != 0) == 0;
+                if constexpr (BIASED) {
+                    if (narrow) {                                        // row scales and what takes the bias off
+                        const uint32_t slo = (elo << 23) + rowbits, shi = (ehi << 23) + rowbits;
+                        xe[(2 * h) * 32 + i] = slo;
+                        xe[(2 * h + 1) * 32 + i] = shi;
+                        xe[128 + (2 * h) * 32 + i] = slo + kDotBack;
+                        xe[128 + (2 * h + 1) * 32 + i] = shi + kDotBack;
+                    } else {
+                        xe[(2 * h) * 32 + i] = elo;
+                        xe[(2 * h + 1) * 32 + i] = ehi;
+                    }
+                }
                 __builtin_amdgcn_wave_barrier();                         // the wave's own LDS writes come first
                 auto chunk = [&](auto narrowc, auto upperc) {
                     constexpr bool NARROW = decltype(narrowc)::value;
                     constexpr int NQ = decltype(upperc)::value ? 4 : 2;  // groups of eight rows
-                    auto term = [&](float& a, int d, int e, int ebj) {
-                        if constexpr (NARROW) a = __builtin_fmaf((float)d, __uint_as_float((uint32_t)(e + ebj) << 23), a);
-                        else a += __builtin_ldexpf((float)d, e + ebj - 127);
-                    };
                     // one block after the other, pinned: the other waves of the SIMD cover the matrix instruction's
                     // latency, two blocks' sums at a time would not fit the registers next to the prefetched chunk
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        int4 e[NQ];
-#pragma unroll
-                        for (int q = 0; q < NQ; ++q) e[q] = *reinterpret_cast<const int4*>(xe + j * 32 + 8 * q + 4 * h);
                         uint32_t fa[kHalfDw], fb[kHalfDw];
                         Unpack<WA, B>::run(pa[s], j, fa);
                         Unpack<WB, B>::run(pb[s], j, fb);
-                        const v16i d = block_mfma<B>(fa, fb);
-                        const int ebj = (int)((eb >> (8 * j)) & 0xFFu) + eadj + 127;
+                        const uint32_t* row = xe + j * 32 + 4 * h;
+                        if constexpr (NARROW && BIASED) {
+                            const v16i d = block_mfma<B>(fa, fb, bias);
+                            const float sb = __uint_as_float((((eb >> (8 * j)) & 0xFFu) << 23) + colbits);
+                            auto term = [&](int r, float sa, float back) {
+                                acc[r] = __builtin_fmaf(__builtin_fmaf(__uint_as_float((uint32_t)d[r]), sa, back), sb, acc[r]);
+                            };
 #pragma unroll
-                        for (int q = 0; q < NQ; ++q) {
-                            term(acc[4 * q], d[4 * q], e[q].x, ebj);
-                            term(acc[4 * q + 1], d[4 * q + 1], e[q].y, ebj);
-                            term(acc[4 * q + 2], d[4 * q + 2], e[q].z, ebj);
-                            term(acc[4 * q + 3], d[4 * q + 3], e[q].w, ebj);
+                            for (int q = 0; q < NQ; ++q) {
+                                const float4 sa = *reinterpret_cast<const float4*>(row + 8 * q);
+                                const float4 back = *reinterpret_cast<const float4*>(row + 128 + 8 * q);
+                                term(4 * q, sa.x, back.x);
+                                term(4 * q + 1, sa.y, back.y);
+                                term(4 * q + 2, sa.z, back.z);
+                                term(4 * q + 3, sa.w, back.w);
+                            }
+                        } else {
+                            const v16i d = block_mfma<B>(fa, fb);
+                            const int ebj = (int)((eb >> (8 * j)) & 0xFFu) + eadj + 127;
+                            auto term = [&](int r, int e) {
+                                if constexpr (NARROW)
+                                    acc[r] = __builtin_fmaf((float)d[r], __uint_as_float((uint32_t)(e + ebj) << 23), acc[r]);
+                                else acc[r] += __builtin_ldexpf((float)d[r], e + ebj - 127);
+                            };
+#pragma unroll
+                            for (int q = 0; q < NQ; ++q) {
+                                const int4 e = *reinterpret_cast<const int4*>(row + 8 * q);
+                                term(4 * q, e.x);
+                                term(4 * q + 1, e.y);
+                                term(4 * q + 2, e.z);
+                                term(4 * q + 3, e.w);
+                            }
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -476,27 +516,44 @@ __global__ __launch_bounds__(NW * 64) void gemv_stream_kernel(GemmArgs g) {
     }
 }
 
+// Waves of the 32 x 32 form that a compute unit holds: 16 of the kernel with blocks of 16, or of 32 with few bits, and 12
+// of the others (registers).
+constexpr int resident_waves(int block, int wa, int wb) { return block == 16 || (block == 32 && wa + wb <= 8) ? 16 : 12; }
+
+// Waves per tile of that form: as many as leave all tiles resident at once.  A workgroup spends most of a short K loop on
+// the way to its first records and in its sum over the waves, and only another workgroup's arithmetic covers that.  Two
+// workgroups of eight waves on a compute unit instead of one after the other with sixteen: 32 x 13824 x 5120, 8 by 4 bits,
+// blocks of 16, 22.9 -> 20.3 us; blocks of 32, four waves where it were eight: 32 x 13824 x 5120 19.0 -> 15.9 us, 40 x 11008
+// x 1024 12.7 -> 7.7 us.  Past three (blocks of 64: two) tiles per compute unit two waves win while K is short.  Drawn on
+// 14700 random products (M 9 to 4096, N 64 to 14000, K to 14000) timed with every number of waves; six never won.
+inline int waves_per_tile(int block, int resident, int64_t chunks, int64_t tiles) {
+    if (tiles <= 256) return block == 16 ? 16 : 8;
+    if (resident == 16) return tiles <= 512 || (tiles <= 768 && chunks > 40) ? 8 : 4;
+    if (tiles <= (block == 32 ? 768 : 512)) return 4;
+    return chunks <= (block == 32 || tiles <= 1024 ? 12 : 4) ? 2 : 4;
+}
+
 // Which of the two forms for M > 8 is the faster one: the sum that estimates its time (us) is the smaller.  The 128 x 128
 // form: every compute unit takes its share of the tiles, a cost per K chunk and one per tile (launch, store).  The 32 x 32
-// form: rounds of workgroups (8 waves of a compute unit are resident, 16 with blocks of 16), each with the chunks its
+// form: rounds of workgroups (resident_waves), each with the chunks its
 // slowest wave takes one after the other and a cost of its own (launch, sum over the waves, store), and the vector work of
 // all blocks.  So the split over the waves wins while K is long enough to divide or the tiles are too few to fill the chip,
 // and the large tile wins on short K: 32 x 2304 x 5504 x 32 (block 32) 357 us, 1601 us with small tiles; 2064 x 4992 x 160
 // 26 and 40 us; 2048 x 4096 x 4096, 8 by 8 bits in blocks of 64, 194 and 261 us, but 6 by 5 bits in blocks of 32 218 and
-// 212 us, 8 by 4 bits in blocks of 16 or 32 366 and 274, 202 and 172 us.  The coefficients are least squares over 19159
-// shapes (M 9 to 32768, N 16 to 14000, K 16 to 12000, batch 1 to 32, all widths), both forms timed on each: the choice
-// costs 0.3 % against always taking the faster one, and more than 10 % at one shape in 100.  Within 5 % of each other the
+// 212 us, 8 by 4 bits in blocks of 16 or 32 366 and 274, 202 and 172 us (before the small form's scaling took two instructions
+// for three).  The coefficients are least squares over shapes timed in both forms: the large one's over 19159 (M 9 to 32768,
+// N 16 to 14000, K 16 to 12000, batch 1 to 32, all widths), the small one's over 14700 (see waves_per_tile); there the choice
+// costs 0.1 to 0.3 % against always taking the faster one.  Within 5 % of each other the
 // large tile is taken: its scaling is the same for any exponents, the small one's slower outside its narrow range (3363 x
 // 8704 x 10368, 8 by 8 bits in blocks of 64, exponents over 60 binades: 1537 us, 2060 with small tiles).
 struct FormCost { float base128, step128, chunk128, tile128, base32, step32, round_step32, round32, chunk32; };
 
-inline bool large_tiles_faster(int block, int64_t chunks, int64_t tiles32, int64_t tiles128, int nw) {
-    const FormCost k = block == 16 ? FormCost{1.98f, 0.63f, 2.38f, 2.15f, 0.51f, 1.33f, 0.19f, 2.63f, 0.083f}
-                     : block == 32 ? FormCost{1.66f, 0.80f, 2.57f, 2.46f, 2.12f, 0.99f, 0.32f, 1.47f, 0.089f}
-                                   : FormCost{1.09f, 0.65f, 3.59f, 3.23f, 1.44f, 1.53f, 0.65f, 1.57f, 0.15f};
-    const int resident = (block == 16 ? 16 : 8) / nw;                // workgroups of the 32 x 32 form on a compute unit
+inline bool large_tiles_faster(int block, int resident, int64_t chunks, int64_t tiles32, int64_t tiles128, int nw) {
+    const FormCost k = block == 16 ? FormCost{1.98f, 0.63f, 2.38f, 2.15f, 1.74f, 0.80f, 0.40f, 2.70f, 0.054f}
+                     : block == 32 ? FormCost{1.66f, 0.80f, 2.57f, 2.46f, 1.43f, 0.69f, 0.18f, 3.53f, 0.094f}
+                                   : FormCost{1.09f, 0.65f, 3.59f, 3.23f, 0.37f, 1.59f, 0.12f, 3.99f, 0.20f};
     const float c = (float)chunks, steps = (float)ceil_div(chunks, nw);
-    const float share128 = (float)ceil_div(tiles128, 256), rounds32 = (float)ceil_div(tiles32, 256 * resident);
+    const float share128 = (float)ceil_div(tiles128, 256), rounds32 = (float)ceil_div(tiles32, 256 * (resident / nw));
     const float t128 = k.base128 + k.step128 * c + share128 * (k.chunk128 * c + k.tile128);
     const float t32 = k.base32 + k.step32 * steps + rounds32 * (k.round_step32 * steps + k.round32) +
                       k.chunk32 * c * (float)tiles32 / 256.f;
@@ -537,11 +594,10 @@ mx_status launch(const GemmArgs& g, int64_t batch, hipStream_t st) {
         dim3 grid((unsigned)g.groupsB, (unsigned)batch);
         hipLaunchKernelGGL((gemv_fragment_kernel<WA, WB, B, kGemvWaves>), grid, dim3(kGemvWaves * 64), 0, st, g);
     } else {
-        // waves per tile: as many as the tiles leave the chip room for (about 4096 waves fill it)
         const int64_t tiles = g.groupsA * g.groupsB * batch;
-        const int max_nw = B >= 32 ? 8 : 16;
-        const int nw = tiles >= 1024 ? 4 : tiles >= 512 ? 8 : max_nw;
-        const bool large = large_tiles_faster(B, g.chunks, tiles, ceil_div(g.groupsA, 4) * ceil_div(g.groupsB, 4) * batch, nw);
+        constexpr int kResident = resident_waves(B, WA, WB);
+        const int nw = waves_per_tile(B, kResident, g.chunks, tiles);
+        const bool large = large_tiles_faster(B, kResident, g.chunks, tiles, ceil_div(g.groupsA, 4) * ceil_div(g.groupsB, 4) * batch, nw);
         // a grid dimension holds fewer than 2^32 work items: from 2^24 tiles (a result of 64 GiB) on there are too many
         const bool past_grid = ceil_div(g.groupsA * g.groupsB, 8) * 8 * nw * 64 > 0xffffffffLL;
         if (large || past_grid) {
@@ -550,7 +606,7 @@ mx_status launch(const GemmArgs& g, int64_t batch, hipStream_t st) {
             MX_HIP_LAUNCH_CHECK();
             return MX_OK;
         }
-        const size_t smem = (size_t)nw * 512 + (size_t)(nw / 2) * 4096;
+        const size_t smem = (size_t)nw * 1024 + (size_t)(nw / 2) * 4096;
         dim3 grid((unsigned)(ceil_div(g.groupsA * g.groupsB, 8) * 8), (unsigned)batch);
         hipLaunchKernelGGL((gemm_tile_kernel<WA, WB, B>), grid, dim3(nw * 64), smem, st, g);
     }

@@ -38,6 +38,34 @@ def test_fragment_product_tiles_and_waves(M, N, K, block, wa, wb):
         check_product(host(y)[0], y_ref, mag, "%dx%dx%d bytes %d..%d" % (M, N, K, lo, hi - 1))
 
 
+@pytest.mark.parametrize("M,N,K,block,wa,wb", [
+    (40, 32 * 400, 3 * 128, 32, 8, 4),      # 800 tiles, two waves each, one with a second chunk
+    (33, 32 * 150, 5 * 128 + 32, 32, 5, 6), # 300 tiles, four waves each
+    (50, 32 * 270, 3 * 256, 64, 6, 5),      # 540 tiles, two waves each
+    (40, 32 * 200, 41 * 64, 16, 8, 6),      # 400 tiles, eight waves each
+    (20, 96, 20 * 64, 16, 6, 8), (20, 96, 20 * 128, 32, 4, 3), (20, 96, 20 * 128, 32, 7, 8),   # sums without the bias
+])
+def test_fragment_product_block_sums_with_a_bias(M, N, K, block, wa, wb):
+    """The largest block sums there are, of either sign, and sums of zero, with the exponents of both operands at the ends of
+    the range in which the scales are built by integer adds, and just past them."""
+    rng = np.random.default_rng(M + N + K + wa)
+    qa, _ = random_operand(rng, M, K, block, wa, 100, 101)
+    qb, _ = random_operand(rng, N, K, block, wb, 100, 101)
+    ma, mb = (1 << (wa - 1)) - 1, (1 << (wb - 1)) - 1
+    qa[::3], qb[::3] = ma, mb                    # every product the largest
+    qa[1::3, ::2], qa[1::3, 1::2] = ma, -ma      # block sums of zero against constant rows
+    qb[2::3] = -mb
+    for (alo, ahi), (blo, bhi) in (((96, 98), (96, 98)), ((158, 160), (158, 160)), ((96, 98), (158, 160)), ((159, 161), (95, 97))):
+        ea = rng.integers(alo, ahi, size=(M, K // block)).astype(np.uint8)
+        eb = rng.integers(blo, bhi, size=(N, K // block)).astype(np.uint8)
+        A, fa = gpu_operand(qa, ea, block, wa)
+        B, fb = gpu_operand(qb, eb, block, wb)
+        y = mx.gemm(A, fa, B, fb, M, N, K)
+        torch.cuda.synchronize()
+        y_ref, mag = orc.gemm(qa, ea, wa, qb, eb, wb, block, want_mag=True)
+        check_product(host(y)[0], y_ref, mag, "%dx%dx%d bytes %d %d" % (M, N, K, alo, blo))
+
+
 MAT = mx.MX_LAYOUT_MATRIX
 # (row tiles, column tiles) of 32: one size in the range of each form of the matrix-layout product but the last, from the
 # smallest tile with K split over the waves to a partial second round of the larger ones (K short: MATRIX_FORMS_LONG_K)
