@@ -12,8 +12,8 @@ constexpr int64_t kDecodeMaxSplit = 64;
 
 struct DecodePlan {
     bool ok;                 // the one-launch kernel takes the shape
-    int32_t ksplit, slice;   // K slices, records (chunks of four blocks) per slice
-    int64_t partial_floats;  // fp32 partial sums kept in the workspace (0 with one slice)
+    int32_t ksplit;          // K slices at most
+    int64_t partial_floats;  // fp32 partial sums that the workspace holds (0 with one slice)
 };
 DecodePlan decode_plan(int64_t M, int64_t K, int64_t N, int block, int wb);
 

@@ -8,32 +8,29 @@
 // to eight rows; one and two rows go to the dot-product kernel of mx_gemv_dot.hip, which needs no exchange
 // between workgroups.
 //
-// Work split: the path is bound by one pass over the packed weights, so every compute unit has to stream.
-// The grid is (column groups of 32) x (K slices); a workgroup quantizes only its own slice of the
-// activations (no workgroup repeats the whole row), keeps a ring of weight records in flight per wave and
-// ends with 32 partial sums per row.  With more than one slice the partial sums go to the caller's workspace
-// and the workgroup that arrives last at the column group's counter adds them in slice order, so the result
-// does not depend on the order of arrival.
+// Work split: the path is bound by one pass over the packed weights, so every compute unit has to stream.  A workgroup
+// owns a few neighbouring column groups of 32 (NW) and a K slice, which KS waves per column group divide among them; it
+// quantizes its own slice of the activations into LDS, every wave keeps a ring of weight records in flight, and the KS
+// partial tiles are added through LDS in wave order.  With more than one K slice the partial sums go to the caller's
+// workspace and the workgroup that arrives last at the columns' counter adds them in slice order, so the result does
+// not depend on the order of arrival.
+//
+// What a call takes beyond the pass over the weights: quantizing (repeated by every workgroup of a slice, so wide
+// workgroups), the exchange between slices (three dependent trips to memory, so few slices) and workgroups enough for
+// 256 compute units; choose_split weighs them.  Eight elements per quantizer item, waves that divide the slice inside
+// the workgroup, 16 x 16 results of which all elements are used: 8 rows, 8 by 4 bits, blocks of 16, 5120 -> 5120 12.0 ->
+// 9.4 us, 5120 -> 13824 17.0 -> 14.9, 13824 -> 5120 17.4 -> 15.0; 5 rows, 6 by 5 bits, blocks of 32, 11008 -> 4096 17.2 ->
+// 13.3; 3 rows 768 -> 3072 6.8 -> 4.4.  A bare read of 39.9 MB of weights (5120 -> 13824) takes 8.4 us.
 #include <type_traits>
 
 #include "mx_decode.h"
 #include "mx_frag.h"
 
-#ifndef MX_DECODE_TARGET_WAVES
-#define MX_DECODE_TARGET_WAVES 2560    // (column group, K slice) pairs aimed at: ten waves per compute unit
-#endif
-#ifndef MX_DECODE_WAVES
-#define MX_DECODE_WAVES 4              // waves, i.e. column groups, per workgroup
-#endif
-#ifndef MX_DECODE_DEPTH
-#define MX_DECODE_DEPTH 5              // weight records in flight per wave (narrow records)
-#endif
-#ifndef MX_DECODE_MIN_SLICE
-#define MX_DECODE_MIN_SLICE 4          // records per wave at least
-#endif
-
 namespace mx {
 namespace {
+
+constexpr int64_t kTargetPairs = 2560;     // (column group, K slice) pairs that the workspace is sized for
+constexpr int64_t kMinSlice = 4;           // and records per such slice at least
 
 struct DecodeArgs {
     const float* x;
@@ -44,84 +41,111 @@ struct DecodeArgs {
     uint32_t* counters;      // one per workgroup column: zero on entry, zero again on exit
     float* partial;          // [ksplit][M][32*groups]
     int32_t M, N, K;
-    int32_t groups, quads, quads8, chunks, slice, ksplit;
+    int32_t groups, columns, chunks, ksplit;       // columns of workgroups, K slices
+    int32_t slice, part;     // records per slice and per wave
     int32_t recordB;
     int32_t wa, bias, emax, rounding;
-    int32_t eadj;            // -2*bias - (wa-2) - (wb-2)
+    int32_t eadj;            // -bias - (wa-2) - (wb-2)
 };
 
-// Grid: (workgroup columns) x (K slices); a workgroup of NW waves owns NW neighbouring column groups of 32
-// and one K slice: its waves share the quantized activations of the slice (LDS), wave w streams the records of
-// column group NW*column + w.
-// Up to eight rows: one int8 MFMA per block with the activations as the 32-row operand (rows 8..31 of it are
-// never looked at, so the lanes that would hold them may hold anything).
-// D: weight records a wave keeps in flight.  It is sized so that a wave requests most of its slice before the
-// activations are quantized: the weights stream while the workgroup prepares the other operand.
-template <int WB, int B, int NW, int D>
-__global__ __launch_bounds__(NW * 64, (D * (Piece<WB, B>::kDw + 1) + (B == 16 ? 92 : 112) <= 128 ? 4 : (D * (Piece<WB, B>::kDw + 1) + (B == 16 ? 92 : 112) <= 168 ? 3 : 2)))
+// Weight records a wave keeps in flight: it requests most of its part before the activations are quantized, so the weights
+// stream while the workgroup prepares the other operand.  They live in registers, which are what bounds the waves of a
+// compute unit: 16 with blocks of 16 and of 32, but for the widest records.
+constexpr int ring_depth(int wb, int block) {
+    const int dw = block * wb / 16 + 1, most = block <= 32 ? 40 / dw : 96 / dw, least = block <= 32 ? 3 : 2;
+    return most >= 5 ? 5 : most < least ? least : most;
+}
+constexpr int waves_per_simd(int wb, int block) {
+    const int regs = ring_depth(wb, block) * (block * wb / 16 + 1) + (block == 16 ? 65 : block == 32 ? 78 : 110);
+    return regs <= 128 ? 4 : regs <= 168 ? 3 : 2;
+}
+
+// Grid: (columns of workgroups) x (K slices).  Wave kw * NW + g of a workgroup streams the records of column group
+// NW * column + g that belong to part kw of the slice; all share the quantized activations of the slice (LDS).
+// Up to eight rows: one int8 MFMA per block (two for block 64), 32 columns at a time (block_mfma16).
+template <int B> constexpr int kZeroDw = ((48 + 1) * (B / 8) + 3) & ~3;     // what a lane without codes reads for a record
+template <int WB, int B, int NW, int KS>
+__global__ __launch_bounds__(NW * KS * 64, waves_per_simd(WB, B))
 void linear_splitk_kernel(DecodeArgs a) {
-    constexpr int kDwB = Piece<WB, B>::kDw;
+    constexpr int kDwB = Piece<WB, B>::kDw, D = ring_depth(WB, B);
     constexpr int kHalfDw = B / 8;                       // int8 dwords of a half block
     constexpr int MP = 8;                                 // rows with a slot in LDS
-    constexpr int MR = 4;                                 // accumulators per lane: rows 4h .. 4h+3
-    constexpr int T = NW * 64;
+    constexpr int MR = 4;                                 // accumulators per lane: rows row0 .. row0 + 3
+    constexpr int T = NW * KS * 64;
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ int is_last;
+    __shared__ uint32_t wide_any[NW * KS];
 
-    const int gq = (int)(blockIdx.x % (unsigned)a.quads8), ks = (int)(blockIdx.x / (unsigned)a.quads8);
-    if (gq >= a.quads) return;                            // whole workgroup, before any barrier
+    const int gq = (int)(blockIdx.x % (unsigned)a.columns), ks = (int)(blockIdx.x / (unsigned)a.columns);
     const int c0 = ks * a.slice;
     const int nc = (a.chunks - c0 < a.slice) ? a.chunks - c0 : a.slice;     // records of this slice, >= 1
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int i = lane & 31, h = lane >> 5;
-    const int gb = gq * NW + wave;                        // this wave's column group
+    const int h = lane >> 5, row = lane & 7;
+    const int col = 16 * h + (lane & 15);                 // this lane's column of the results, inside the group
+    const int row0 = 4 * ((lane >> 4) & 1);               // and the first of its four rows
+    const bool arow = ((lane >> 3) & 1) == ((lane >> 4) & 1);     // the left operand's lane carries codes
+    const int kw = wave / NW;                             // this wave's part of the slice
+    const int gb = gq * NW + wave - kw * NW;              // this wave's column group
     const bool wave_live = gb < a.groups;                 // wave-uniform
 
-    // LDS: x8[nc*4 blocks][2 halves][8 rows][kHalfDw], xe[nc*4 blocks][8 rows] (Ea + eadj as int)
+    // LDS: x8[slice*4 blocks][2 halves][8 rows][kHalfDw], xe[slice*4 blocks][8 rows] (bits of 2^Ea), zeros for the other
+    // lanes of the left operand
     uint32_t* x8 = lds;
     uint32_t* xe = x8 + MP * a.slice * 4 * 2 * kHalfDw;
+    uint32_t* none = xe + MP * a.slice * 4;
+    for (int d = (int)threadIdx.x; d < kZeroDw<B>; d += T) none[d] = 0;
+
+    const int w0 = kw * a.part;                           // first record of the wave inside the slice
+    const int nw = nc - w0 < 0 ? 0 : nc - w0 < a.part ? nc - w0 : a.part;   // its records, none in the parts past a short slice
 
     // ring of D records of this wave's column group; a record past the slice reads zeros without touching
     // memory, so no load sits under a condition and the waits stay exact
-    const uint8_t* Bbase = a.B + ((int64_t)(wave_live ? gb : 0) * a.chunks + c0) * a.recordB;
-    const BufRsrc rB = make_rsrc(Bbase, wave_live ? (uint32_t)(nc * a.recordB) : 0u);
+    const uint8_t* Bbase = a.B + ((int64_t)(wave_live ? gb : 0) * a.chunks + c0 + (nw > 0 ? w0 : 0)) * a.recordB;
+    const BufRsrc rB = make_rsrc(Bbase, wave_live ? (uint32_t)(nw * a.recordB) : 0u);
     uint32_t pb[D][kDwB], eb[D];
     auto fetch = [&](int slot, int t) {
         const uint32_t off = (uint32_t)t * (uint32_t)a.recordB;
         buf_load_dwords<kDwB>(rB, off + lane * (kDwB * 4), pb[slot]);
-        buf_load_dwords<1>(rB, off + 64 * (kDwB * 4) + i * 4, &eb[slot]);
+        buf_load_dwords<1>(rB, off + 64 * (kDwB * 4) + col * 4, &eb[slot]);
     };
 
+    bool wide = false;                                    // an exponent of the activations outside [-63, 64]
+
     // ---- activations of this slice: fp32 -> MXInt (the arithmetic of mx_quantize) -> int8 in LDS.
-    // One item is four consecutive elements of a row; consecutive lanes take consecutive items, so a block is
-    // B/4 neighbouring lanes and its maximum takes log2(B/4) DPP steps.  Loads return in the order of issue:
-    // the first items are requested before the ring of weights.
+    // One item is eight consecutive elements of a row, a half block or a part of one; consecutive lanes take consecutive
+    // items, so a block is B/8 neighbouring lanes and its maximum takes log2(B/8) DPP steps.  Loads return in the order of
+    // issue: the first items are requested before the ring of weights.
     {
-        const int ipr = nc * B;                            // items per row (slice elements / 4)
-        const int n_it = a.M * ipr;
+        const int per_row = nc * 4 * B;                    // elements of a row in this slice
         const float qmax = (float)((1 << (a.wa - 1)) - 1);
         const int64_t k0 = (int64_t)c0 * 4 * B;
-        constexpr int XU = 8;                              // items per thread requested before the weights
+        constexpr int XU = 4, XR = 2;                      // items per thread requested before the weights, and at a time after that
         constexpr float kMagic = 12582912.0f;              // 1.5 * 2^23: adding it rounds to an integer, ties to even
         // item -> (row, first element inside the slice), advanced without divisions
-        int m_it = 0, e_it = 4 * (int)threadIdx.x;
-        auto settle = [&]() {
-            while (e_it >= 4 * ipr && m_it < a.M) { e_it -= 4 * ipr; ++m_it; }
+        const int step_m = (8 * T) / per_row, step_e = 8 * T - step_m * per_row;
+        int m_it = (int)(8 * threadIdx.x) / per_row, e_it = (int)(8 * threadIdx.x) - m_it * per_row;
+        auto advance = [&]() {
+            m_it += step_m; e_it += step_e;
+            if (e_it >= per_row) { e_it -= per_row; ++m_it; }
         };
-        settle();
-        auto item_load = [&](int m, int e) -> float4 {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (m < a.M && k0 + e < a.K) v = *reinterpret_cast<const float4*>(a.x + (int64_t)m * a.x_stride + k0 + e);   // K % 4 == 0
-            return v;
+        auto item_load = [&](int m, int e, float4 (&v)[2]) {
+            v[0] = v[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (m < a.M && k0 + e < a.K) {                  // K is a multiple of the block
+                const float4* src = reinterpret_cast<const float4*>(a.x + (int64_t)m * a.x_stride + k0 + e);
+                v[0] = src[0]; v[1] = src[1];
+            }
         };
-        auto item_store = [&](int m, int e, const float4& v) {
-            float am = __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v.x), __builtin_fabsf(v.y)),
-                                       __builtin_fmaxf(__builtin_fabsf(v.z), __builtin_fabsf(v.w)));
-            uint32_t ab = __float_as_uint(am), o;
+        auto item_store = [&](auto rndc, int m, int e, const float4 (&v)[2]) {
+            const float x[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
+            auto max4 = [](const float4& f) {
+                return __float_as_uint(__builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(f.x), __builtin_fabsf(f.y)),
+                                                       __builtin_fmaxf(__builtin_fabsf(f.z), __builtin_fabsf(f.w))));
+            };
+            uint32_t ab = max4(v[0]), o = max4(v[1]);
+            ab = o > ab ? o : ab;
             o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0xB1, 0xF, 0xF, true);  ab = o > ab ? o : ab;   // lane ^ 1
-            o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x4E, 0xF, 0xF, true);  ab = o > ab ? o : ab;   // lane ^ 2
-            if (B >= 32) { o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x141, 0xF, 0xF, true); ab = o > ab ? o : ab; }   // 7 - lane within 8
-            if (B >= 64) { o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x140, 0xF, 0xF, true); ab = o > ab ? o : ab; }   // 15 - lane within 16
+            if (B >= 32) { o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x4E, 0xF, 0xF, true); ab = o > ab ? o : ab; }    // lane ^ 2
+            if (B >= 64) { o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x141, 0xF, 0xF, true); ab = o > ab ? o : ab; }   // 7 - lane within 8
             if (m >= a.M) return;                          // after the cross-lane steps: every lane of a block takes part in them
             const int ef = (int)(ab >> 23);
             int E = ef == 0 ? -127 : ef - 127;
@@ -130,94 +154,141 @@ void linear_splitk_kernel(DecodeArgs a) {
             const int shift = (a.wa - 2) - E;
             // round(x * 2^shift), clamped: the sum with kMagic holds the integer in its low mantissa bits (a
             // value beyond the clamp, however large, ends at the clamp as well), its low byte is the int8 code
-            auto code = [&](float xx) -> uint32_t {
-                float sc = __builtin_ldexpf(xx, shift);
-                if (a.rounding != MX_RNE) sc = __builtin_truncf(sc);
-                const float z = __builtin_fminf(__builtin_fmaxf(sc + kMagic, kMagic - qmax), kMagic + qmax);
-                return __float_as_uint(z);
-            };
-            const uint32_t lo = __builtin_amdgcn_perm(code(v.y), code(v.x), 0x0C0C0400u);
-            const uint32_t hi = __builtin_amdgcn_perm(code(v.w), code(v.z), 0x04000C0Cu);
-            const uint32_t word = lo | hi;
+            uint32_t z[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                float sc = __builtin_ldexpf(x[k], shift);
+                if (decltype(rndc)::value != MX_RNE) sc = __builtin_truncf(sc);
+                z[k] = __float_as_uint(__builtin_fminf(__builtin_fmaxf(sc + kMagic, kMagic - qmax), kMagic + qmax));
+            }
+            uint32_t word[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                word[k] = __builtin_amdgcn_perm(z[4 * k + 1], z[4 * k], 0x0C0C0400u) | __builtin_amdgcn_perm(z[4 * k + 3], z[4 * k + 2], 0x04000C0Cu);
             const int blk = e / B, p = e - blk * B;         // block of the slice, position inside it (B is a power of two)
             const int hh = p / (B / 2), d = (p - hh * (B / 2)) >> 2;
-            const int ebyte = (k0 + e < a.K) ? E + a.bias : 0;
-            x8[((blk * 2 + hh) * 8 + m) * kHalfDw + d] = word;
-            if (p == 0) xe[blk * 8 + m] = (uint32_t)(ebyte + a.eadj - Unpack<WB, B>::kScaleLog2);
+            // 2^Ea; a block of zeros takes 1, its sums are zero whatever the scale
+            const int ebits = ab == 0 ? 127 : E + 127;
+            wide |= (uint32_t)(ebits - (127 - 63)) > 127u;
+            *reinterpret_cast<uint2*>(x8 + ((blk * 2 + hh) * 8 + m) * kHalfDw + d) = make_uint2(word[0], word[1]);
+            if (p == 0) xe[blk * 8 + m] = (uint32_t)ebits << 23;
         };
         // every thread runs the same number of rounds (the DPP steps need whole blocks of lanes)
-        const int rounds = (n_it + T - 1) / T;
-        float4 xv[XU];
+        const int rounds = (a.M * per_row + 8 * T - 1) / (8 * T);
+        auto load_items = [&](auto& xv, auto& mm, auto& ee) {
+            for (auto& v : xv) {
+                const int u = (int)(&v - &xv[0]);
+                mm[u] = m_it; ee[u] = e_it;
+                item_load(m_it, e_it, v);
+                advance();
+            }
+        };
+        float4 xv[XU][2];
         int mm[XU], ee[XU];
-#pragma unroll
-        for (int u = 0; u < XU; ++u) {
-            mm[u] = m_it; ee[u] = e_it;
-            xv[u] = item_load(m_it, e_it);
-            e_it += 4 * T; settle();
-        }
+        load_items(xv, mm, ee);
 #pragma unroll
         for (int u = 0; u < D; ++u) fetch(u, u);
+        auto quantize = [&](auto rndc) {
 #pragma unroll
-        for (int u = 0; u < XU; ++u)
-            if (u < rounds) item_store(mm[u], ee[u], xv[u]);
-        for (int r = XU; r < rounds; ++r) {
-            const float4 v = item_load(m_it, e_it);
-            item_store(m_it, e_it, v);
-            e_it += 4 * T; settle();
-        }
+            for (int u = 0; u < XU; ++u)
+                if (u < rounds) item_store(rndc, mm[u], ee[u], xv[u]);
+#pragma unroll 1
+            for (int r = XU; r < rounds; r += XR) {
+                float4 yv[XR][2];
+                int ym[XR], ye[XR];
+                load_items(yv, ym, ye);
+#pragma unroll
+                for (int u = 0; u < XR; ++u)
+                    if (r + u < rounds) item_store(rndc, ym[u], ye[u], yv[u]);
+            }
+        };
+        if (a.rounding == MX_RNE) quantize(std::integral_constant<int, MX_RNE>{});
+        else quantize(std::integral_constant<int, MX_RTZ>{});
     }
+    const bool wide_wave = __builtin_amdgcn_ballot_w64(wide) != 0;
+    if (lane == 0) wide_any[wave] = wide_wave;
     __syncthreads();
+    uint32_t rows_wide = 0;
+#pragma unroll
+    for (int w = 0; w < NW * KS; ++w) rows_wide |= wide_any[w];
 
     float acc[MR];
 #pragma unroll
     for (int r = 0; r < MR; ++r) acc[r] = 0.f;
-    const int per_wave = wave_live ? nc : 0;
+    const int per_wave = wave_live ? nw : 0;
+    const bool rows_narrow = __builtin_amdgcn_readfirstlane(rows_wide) == 0;
+    const bool bcol = (int64_t)gb * 32 + col < a.N;           // columns past N take a neutral exponent
+    const uint32_t neutral = (uint32_t)a.bias * 0x01010101u, move = (uint32_t)(127 - a.bias + 32) * 0x01010101u;
+    const int eadj = a.eadj - Unpack<WB, B>::kScaleLog2;      // of an exponent byte of the weights
+    const uint32_t colbits = (uint32_t)(127 + eadj) << 23;
+    v4i_t bias = {(int)kDotBias, (int)kDotBias, (int)kDotBias, (int)kDotBias};
+    asm volatile("" : "+v"(bias));                            // four registers, not a constant built per block
+    const uint32_t* xa = arow ? x8 + w0 * (64 * kHalfDw) + (h * 8 + row) * kHalfDw : none;
+    const int xstep = arow ? 64 * kHalfDw : 0;
+    const uint32_t* xs = xe + w0 * 32 + row0;
     for (int t0 = 0; t0 < per_wave; t0 += D) {
 #pragma unroll
         for (int u = 0; u < D; ++u) {
-            const int c = t0 + u;                             // record inside the slice
+            const int c = t0 + u;                             // record inside the wave's part
             const bool live = c < per_wave;                   // scalar condition: no load depends on it
             uint32_t fb[4][kHalfDw];
             uint32_t ebv = 0;
             if (live) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) Unpack<WB, B>::run(pb[u], j, fb[j]);
-                ebv = eb[u];
+                ebv = bcol ? eb[u] : neutral;
             }
             fetch(u, c + D);                                  // the slot is free: refill it
             if (!live) continue;
-            // the four blocks of the record: operands from LDS first, then the matrix instructions issued ahead
-            // of the scaling of the block before, so that their latency is covered by vector work
             uint32_t fa[4][kHalfDw];
-            int4 ea[4];
+            uint4 ea[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int blk = c * 4 + j;
-                const uint32_t* xa = x8 + ((blk * 2 + h) * 8 + (i & 7)) * kHalfDw;
 #pragma unroll
-                for (int q = 0; q < kHalfDw; ++q) fa[j][q] = xa[q];
-                ea[j] = *reinterpret_cast<const int4*>(xe + blk * 8 + 4 * h);
+                for (int q = 0; q < kHalfDw; ++q) fa[j][q] = xa[j * 16 * kHalfDw + q];
+                ea[j] = *reinterpret_cast<const uint4*>(xs + j * 8);
             }
-            auto scale = [&](const v16i_t& d, int j) {
-                const int ebj = (int)((ebv >> (8 * j)) & 0xFFu);
-                acc[0] += __builtin_ldexpf((float)d[0], ea[j].x + ebj);
-                acc[1] += __builtin_ldexpf((float)d[1], ea[j].y + ebj);
-                acc[2] += __builtin_ldexpf((float)d[2], ea[j].z + ebj);
-                acc[3] += __builtin_ldexpf((float)d[3], ea[j].w + ebj);
-            };
-            const v16i_t d0 = block_mfma<B>(fa[0], fb[0]);
-            const v16i_t d1 = block_mfma<B>(fa[1], fb[1]);
-            __builtin_amdgcn_sched_barrier(0);
-            scale(d0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            const v16i_t d2 = block_mfma<B>(fa[2], fb[2]);
-            __builtin_amdgcn_sched_barrier(0);
-            scale(d1, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            const v16i_t d3 = block_mfma<B>(fa[3], fb[3]);
-            __builtin_amdgcn_sched_barrier(0);
-            scale(d2, 2);
-            scale(d3, 3);
+            xa += xstep;
+            xs += 32;
+            v4i_t d[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = block_mfma16<B>(fa[j], fb[j], bias);
+            const bool narrow = rows_narrow && __builtin_amdgcn_ballot_w64((((ebv + move) ^ 0x80808080u) & 0xC0C0C0C0u) != 0) == 0;
+            if (narrow) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float sb = __uint_as_float((((ebv >> (8 * j)) & 0xFFu) << 23) + colbits);
+                    auto term = [&](int r, uint32_t sa) {
+                        const float t = __builtin_fmaf(__uint_as_float((uint32_t)d[j][r]), __uint_as_float(sa), __uint_as_float(sa + kDotBack));
+                        acc[r] = __builtin_fmaf(t, sb, acc[r]);
+                    };
+                    term(0, ea[j].x); term(1, ea[j].y); term(2, ea[j].z); term(3, ea[j].w);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int ebj = (int)((ebv >> (8 * j)) & 0xFFu) + eadj - 127;
+                    auto term = [&](int r, uint32_t sa) {
+                        acc[r] += __builtin_ldexpf((float)(d[j][r] - (int)kDotBias), (int)(sa >> 23) + ebj);
+                    };
+                    term(0, ea[j].x); term(1, ea[j].y); term(2, ea[j].z); term(3, ea[j].w);
+                }
+            }
+        }
+    }
+
+    if constexpr (KS > 1) {                                   // the parts of the slice, in their order
+        float* part = reinterpret_cast<float*>(none + kZeroDw<B>);
+        if (kw > 0) {
+#pragma unroll
+            for (int r = 0; r < MR; ++r) part[((wave - NW) * MR + r) * 64 + lane] = acc[r];
+        }
+        __syncthreads();
+        if (kw == 0) {
+#pragma unroll
+            for (int k = 0; k < KS - 1; ++k)
+#pragma unroll
+                for (int r = 0; r < MR; ++r) acc[r] += part[((k * NW + wave) * MR + r) * 64 + lane];
         }
     }
 
@@ -225,17 +296,17 @@ void linear_splitk_kernel(DecodeArgs a) {
     // partial sums are written and read with device-coherent accesses (they pass between workgroups that may
     // sit behind different L2 caches), so no cache has to be written back or invalidated as a whole.
     const int64_t np = (int64_t)a.groups * 32;
-    const int64_t n = (int64_t)gb * 32 + i;
+    const int64_t n = (int64_t)gb * 32 + col;
     // buffer accesses with the device-scope bit: written through / read at the level every compute unit shares
     constexpr int kDeviceScope = 0x10;
     const BufRsrc rP = make_rsrc(a.partial, (uint32_t)((int64_t)a.ksplit * a.M * np * 4));
     auto put = [&](int m, float s) {
-        if (m >= a.M || !wave_live) return;
+        if (m >= a.M || !wave_live || kw > 0) return;
         if (a.ksplit == 1) { if (n < a.N) a.Y[(int64_t)m * a.ldy + n] = s; }
         else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s), rP, (uint32_t)((((int64_t)ks * a.M + m) * np + n) * 4), 0, kDeviceScope);
     };
 #pragma unroll
-    for (int r = 0; r < 4; ++r) put(4 * h + r, acc[r]);
+    for (int r = 0; r < 4; ++r) put(row0 + r, acc[r]);
     if (a.ksplit == 1) return;
 
     // ---- the K slices of this workgroup column: whoever arrives last adds the partial sums in slice order.
@@ -298,33 +369,84 @@ void linear_splitk_kernel(DecodeArgs a) {
     if (threadIdx.x == 0) __hip_atomic_store(a.counters + gq, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int B> constexpr int lds_per_chunk() { return (4 * 2 * 8 * (B / 8) + 4 * 8) * 4; }
+// LDS of a workgroup: per record of the slice the codes and scales of eight rows, the zeros, the partial tiles.
+constexpr int64_t record_lds(int block) { return (4 * 2 * 8 * (block / 8) + 4 * 8) * 4; }
+constexpr int64_t slice_lds(int block, int64_t slice, int groups, int parts) {
+    return slice * record_lds(block) + (((48 + 1) * (block / 8) + 3) & ~3) * 4 + (int64_t)(parts - 1) * groups * 4 * 64 * 4;
+}
+constexpr int kMaxLds = 72 * 1024;
 
-template <int WB, int B>
-mx_status launch_decode(const DecodeArgs& a, hipStream_t st) {
-    // records in flight per wave: up to a whole slice, fewer when a record's lane piece is wide (the ring
-    // lives in registers)
-    constexpr int NW = MX_DECODE_WAVES;
-    constexpr int kRegs = Piece<WB, B>::kDw + 1;
-    constexpr int D = MX_DECODE_DEPTH * kRegs <= 96 ? MX_DECODE_DEPTH : (96 / kRegs < 2 ? 2 : 96 / kRegs);
-    const size_t smem = (size_t)a.slice * lds_per_chunk<B>();
-    auto kern = linear_splitk_kernel<WB, B, NW, D>;
-    if (smem > 64 * 1024) return MX_ERR_UNSUPPORTED;          // the default limit of dynamic LDS; decode_plan stays below it
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.quads8 * a.ksplit)), dim3(NW * 64), smem, st, a);
+// Column groups of a workgroup, parts of its slice, K slices and the records per part.
+struct DecodeSplit { int groups, parts, slices, part; };
+
+// The split that takes the least of: the items a thread quantizes and the records a wave streams, per round of resident
+// workgroups; the waves of the fullest compute unit with the bytes they stream; the exchange between slices and the
+// partial sums a thread adds there.  (4, 2), (2, 4), (1, 8) and (1, 4) are the best of nine forms over 3300 random shapes
+// (3 to 8 rows, K and N 256 to 14000, all blocks), 0.6 % above always the best of the nine.  The coefficients (us) are
+// least squares over 2800 shapes, every number of slices timed in each form: the choice costs 2.1 % against the best of
+// them, and takes 0.82 of what four column groups with one wave each and about 2560 (column group, slice) pairs take.
+// No more than `most` slices: the workspace holds the partial sums of that many.
+DecodeSplit choose_split(int M, int chunks, int groups, int block, int wb, int record, int most) {
+    static constexpr int forms[4][2] = {{4, 2}, {2, 4}, {1, 8}, {1, 4}};
+    static constexpr int counts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64};
+    DecodeSplit best = {0, 0, 0, 0};
+    float least = 0.f;
+    const int resident_waves = 4 * waves_per_simd(wb, block);
+    for (const auto& form : forms) {
+        const int nw = form[0], ks = form[1], waves = nw * ks, columns = (groups + nw - 1) / nw;
+        int before = 0;
+        for (int count : counts) {
+            const int n = count < most ? count : most;
+            const int part = (chunks + n * ks - 1) / (n * ks);
+            const int slice = part * ks < chunks ? part * ks : chunks, slices = (chunks + slice - 1) / slice;
+            if (slices == before || slices > most) continue;
+            before = slices;
+            const int64_t lds = slice_lds(block, slice, nw, ks);
+            if (lds > kMaxLds) continue;
+            const int by_lds = (int)(160 * 1024 / (lds + 1024)), by_regs = resident_waves / waves;
+            const int resident = 256 * (by_lds < by_regs ? by_lds : by_regs);
+            const int64_t wgs = (int64_t)columns * slices;
+            const float per_cu = (float)((wgs + 255) / 256) * (float)waves * 0.25f, rounds = (float)((wgs + resident - 1) / resident);
+            const int items = (M * slice * block / 2 + waves * 64 - 1) / (waves * 64);
+            const float t = rounds * (0.45f * (float)items + 0.07f * (float)part) +
+                            per_cu * (0.315f + 4e-5f * (float)part * (float)record) +
+                            (slices > 1 ? 1.55f + 0.088f * (float)(slices * M) / (float)(2 * ks) : 0.f);
+            if (best.parts == 0 || t < least) { least = t; best = {nw, ks, slices, part}; }
+        }
+    }
+    return best;
+}
+
+template <int WB, int B, int NW, int KS>
+mx_status launch_form(const DecodeArgs& a, hipStream_t st) {
+    const size_t smem = (size_t)slice_lds(B, a.slice, NW, KS);
+    auto kern = linear_splitk_kernel<WB, B, NW, KS>;
+    static std::atomic<uint64_t> done{0};
+    if (smem > kMaxLds) return MX_ERR_UNSUPPORTED;            // choose_split stays below it
+    if (smem > 64 * 1024 && !allow_dynamic_lds(reinterpret_cast<const void*>(kern), kMaxLds, done)) return MX_ERR_DEVICE;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)a.columns * a.ksplit)), dim3(NW * KS * 64), smem, st, a);
     MX_HIP_LAUNCH_CHECK();
     return MX_OK;
 }
 
+template <int WB, int B>
+mx_status launch_decode(const DecodeArgs& a, const DecodeSplit& s, hipStream_t st) {
+    if (s.groups == 4) return launch_form<WB, B, 4, 2>(a, st);
+    if (s.groups == 2) return launch_form<WB, B, 2, 4>(a, st);
+    if (s.parts == 4) return launch_form<WB, B, 1, 4>(a, st);
+    return launch_form<WB, B, 1, 8>(a, st);
+}
+
 template <int B>
-mx_status dispatch_wb(const DecodeArgs& a, int wb, hipStream_t st) {
+mx_status dispatch_wb(const DecodeArgs& a, int wb, const DecodeSplit& s, hipStream_t st) {
     switch (wb) {
-        case 2: return launch_decode<2, B>(a, st);
-        case 3: return launch_decode<3, B>(a, st);
-        case 4: return launch_decode<4, B>(a, st);
-        case 5: return launch_decode<5, B>(a, st);
-        case 6: return launch_decode<6, B>(a, st);
-        case 7: return launch_decode<7, B>(a, st);
-        case 8: return launch_decode<8, B>(a, st);
+        case 2: return launch_decode<2, B>(a, s, st);
+        case 3: return launch_decode<3, B>(a, s, st);
+        case 4: return launch_decode<4, B>(a, s, st);
+        case 5: return launch_decode<5, B>(a, s, st);
+        case 6: return launch_decode<6, B>(a, s, st);
+        case 7: return launch_decode<7, B>(a, s, st);
+        case 8: return launch_decode<8, B>(a, s, st);
     }
     return MX_ERR_BAD_ARG;
 }
@@ -335,21 +457,20 @@ mx_status dispatch_wb(const DecodeArgs& a, int wb, hipStream_t st) {
 // one-launch kernel does not take the shape (the caller then quantizes and multiplies in two launches).
 DecodePlan decode_plan(int64_t M, int64_t K, int64_t N, int block, int wb) {
     DecodePlan p;
-    p.ok = false; p.ksplit = 1; p.slice = 0; p.partial_floats = 0;
+    p.ok = false; p.ksplit = 1; p.partial_floats = 0;
     const FragGeom gb = frag_geom(N, K, block, wb);
     if (M < 1 || M > 8 || K <= 0 || gb.groups > kDecodeMaxGroups || gb.chunks > (1 << 20)) return p;
     if ((gb.chunks + 1024) * (int64_t)gb.record >= (1LL << 31)) return p;       // 32-bit ring offsets
-    const int64_t per_chunk = (int64_t)(4 * 2 * 8 * (block / 8) + 32) * 4;          // LDS bytes per record of a slice
-    const int64_t lds_cap = (56 * 1024) / per_chunk;
-    int64_t ksplit = (MX_DECODE_TARGET_WAVES + gb.groups / 2) / gb.groups;
+    // the most K slices a call uses, which its workspace is sized for
+    int64_t ksplit = (kTargetPairs + gb.groups / 2) / gb.groups;
     ksplit = ksplit < 1 ? 1 : ksplit;
     int64_t slice = ceil_div(gb.chunks, ksplit);
-    slice = slice < MX_DECODE_MIN_SLICE ? MX_DECODE_MIN_SLICE : slice;
-    slice = slice > lds_cap ? lds_cap : slice;
+    slice = slice < kMinSlice ? kMinSlice : slice;
+    slice = slice > (56 * 1024) / record_lds(block) ? (56 * 1024) / record_lds(block) : slice;
     slice = slice > gb.chunks ? gb.chunks : slice;
     ksplit = ceil_div(gb.chunks, slice);                                         // every slice holds a record
     if (ksplit > kDecodeMaxSplit) return p;
-    p.ok = true; p.ksplit = (int32_t)ksplit; p.slice = (int32_t)slice;
+    p.ok = true; p.ksplit = (int32_t)ksplit;
     p.partial_floats = ksplit > 1 ? ksplit * M * gb.groups * 32 : 0;
     return p;
 }
@@ -365,19 +486,21 @@ mx_status linear_decode(const float* x, int64_t M, int64_t K, int64_t row_stride
     a.partial = reinterpret_cast<float*>((uint8_t*)workspace + kDecodeCounterBytes);
     a.M = (int32_t)M; a.N = (int32_t)N; a.K = (int32_t)K;
     a.groups = (int32_t)gb.groups;
-    a.quads = (int32_t)ceil_div(gb.groups, MX_DECODE_WAVES); a.quads8 = (a.quads + 7) / 8 * 8;
-    a.chunks = (int32_t)gb.chunks; a.slice = p.slice; a.ksplit = p.ksplit;
+    const DecodeSplit s = choose_split(a.M, (int)gb.chunks, a.groups, fb.block, fb.mant_bits, gb.record, p.ksplit);
+    if (s.parts == 0) return MX_ERR_UNSUPPORTED;              // not reached: `most` slices of the smallest form fit the LDS
+    a.columns = (a.groups + s.groups - 1) / s.groups;
+    a.chunks = (int32_t)gb.chunks; a.part = s.part; a.ksplit = s.slices;
+    a.slice = s.part * s.parts < a.chunks ? s.part * s.parts : a.chunks;
     a.recordB = gb.record;
     a.wa = fx.mant_bits;
     a.bias = (1 << (fx.exp_bits - 1)) - 1;
     a.emax = ((1 << fx.exp_bits) - 1) - a.bias;
     a.rounding = fx.rounding;
-    a.eadj = -2 * a.bias - (fx.mant_bits - 2) - (fb.mant_bits - 2);
-    if ((int64_t)a.quads8 * a.ksplit > 0x7fffffffLL) return MX_ERR_UNSUPPORTED;
+    a.eadj = -a.bias - (fx.mant_bits - 2) - (fb.mant_bits - 2);
     switch (fb.block) {
-        case 16: return dispatch_wb<16>(a, fb.mant_bits, st);
-        case 32: return dispatch_wb<32>(a, fb.mant_bits, st);
-        case 64: return dispatch_wb<64>(a, fb.mant_bits, st);
+        case 16: return dispatch_wb<16>(a, fb.mant_bits, s, st);
+        case 32: return dispatch_wb<32>(a, fb.mant_bits, s, st);
+        case 64: return dispatch_wb<64>(a, fb.mant_bits, s, st);
     }
     return MX_ERR_UNSUPPORTED;
 }

@@ -91,6 +91,27 @@ __device__ __forceinline__ v16i_t block_mfma(const uint32_t* a, const uint32_t* 
     return block_mfma<B>(a, b, v16i_t{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0});
 }
 
+// The same for up to eight rows in a 16 x 16 result of which every element is used: half the matrix cycles and a quarter
+// of the result registers of the 32 x 32 form.  Lane 32h + 16c + i of a record carries half h of column 16c + i; the
+// instruction takes it as K range 2h + c of its column i.  Its rows 0..7 are the activations in the lanes with c = 0 and
+// zeros in the others, rows 8..15 the reverse, so element (8c + r, i) is row r against column 16c + i.
+template <int B>
+__device__ __forceinline__ v4i_t block_mfma16(const uint32_t* a, const uint32_t* b, v4i_t z) {
+    if constexpr (B == 16) {
+        const long la = (long)(((uint64_t)a[1] << 32) | a[0]);
+        const long lb = (long)(((uint64_t)b[1] << 32) | b[0]);
+        return __builtin_amdgcn_mfma_i32_16x16x32_i8(la, lb, z, 0, 0, 0);
+    } else {
+#pragma unroll
+        for (int s = 0; s < B / 32; ++s) {
+            v4i_t va = {(int)a[4 * s], (int)a[4 * s + 1], (int)a[4 * s + 2], (int)a[4 * s + 3]};
+            v4i_t vb = {(int)b[4 * s], (int)b[4 * s + 1], (int)b[4 * s + 2], (int)b[4 * s + 3]};
+            z = __builtin_amdgcn_mfma_i32_16x16x64_i8(va, vb, z, 0, 0, 0);
+        }
+        return z;
+    }
+}
+
 // Block dots as fp32 without a conversion.  The integer accumulator starts at the bit pattern of 1.5 * 2^23, so the sum d
 // comes out as the bit pattern of the float 1.5 * 2^23 + d (|d| <= 2^20 < 2^22).  With s = 2^k, (1.5 * 2^23 + d) * s -
 // 1.5 * 2^23 * s is d * s in one fused multiply-add, exact since d * s fits the 24 bits of a float; both s and

@@ -299,6 +299,46 @@ def test_decode_rings_of_wide_records(M, wx, ww):
             check_product(host(y[k]), y_ref, mag, "M %d K %d widths %d %d" % (M, K, wx, ww))
 
 
+@pytest.mark.parametrize("M,K,N,block,wx,ww,rounding", [
+    (3, 48, 33, 16, 8, 8, mx.MX_RNE),          # one partial chunk: three of four waves have no record; two column groups
+    (5, 37 * 16, 100, 16, 2, 4, mx.MX_RTZ),    # eight parts of two chunks, the last ones short, a partial chunk
+    (6, 70 * 64, 41 * 32 + 5, 16, 8, 4, mx.MX_RNE),   # two column groups, four parts, nine slices, half a column of workgroups
+    (8, 13 * 32, 13007, 32, 8, 2, mx.MX_RNE),  # four column groups, two parts, one slice
+    (8, 80 * 64, 432 * 32, 16, 8, 4, mx.MX_RNE),      # four column groups, two parts, four slices
+    (4, 45 * 32, 2000, 32, 6, 8, mx.MX_RNE),
+    (7, 17 * 64, 321, 64, 8, 7, mx.MX_RNE),
+])
+def test_decode_splits_and_scales(M, K, N, block, wx, ww, rounding):
+    """Three to eight rows in every form of the split.  Block exponents at the ends of the range in which the block sums take
+    two multiply-adds (activations -63 to 64, weights -31 to 32), one past them, and blocks of zeros on both sides."""
+    rng = np.random.default_rng(M * K + N)
+    x0 = rng.standard_normal((M, K)).astype(np.float32)
+    w0 = rng.standard_normal((N, K)).astype(np.float32)
+    x0.reshape(M, -1, block)[rng.random((M, K // block)) < 0.1] = 0.0
+    w0.reshape(N, -1, block)[rng.random((N, K // block)) < 0.02] = 0.0
+    fx, fw = mx.fmt(block, wx, 8, rounding), mx.fmt(block, ww, 8, rounding)
+
+    def blocks_at(a, exponents):                 # every block's largest value gets one of these exponents
+        v = a.reshape(a.shape[0], -1, block)
+        e = np.frexp(np.abs(v).max(axis=2, keepdims=True))[1] - 1
+        return np.ldexp(v, rng.choice(exponents, size=e.shape) - e).reshape(a.shape).astype(np.float32)
+
+    for xe, we in (([-2, 3], [-6, -5]), ([-63, -62], [-31, -30]), ([63, 64], [31, 32]), ([-64, -63], [-31, -30]), ([64, 65], [0, 1]),
+                   ([0, 1], [-32, 33])):
+        x, wt = blocks_at(x0, xe), blocks_at(w0, we)
+        xd = torch.from_numpy(x).cuda()
+        B = mx.quantize_pack(torch.from_numpy(wt).cuda(), fw)
+        y = torch.full((2, M, N), 3.0, device="cuda")
+        ws = mx.linear_workspace(M, K, N, fx, fw, "cuda")
+        for k in (0, 1):                         # the counters are left at zero, the order of arrival does not matter
+            mx.mx_linear(xd, M, K, K, fx, ws, B, N, fw, mx.MX_LAYOUT_FRAGMENT, y[k], N)
+        torch.cuda.synchronize()
+        assert torch.equal(y[0], y[1]) and int(ws[:16384].max()) == 0
+        cols = np.unique(np.r_[0, N - 1, rng.integers(0, N, size=200)])
+        y_ref, mag = orc.linear(x, wt[cols], block, wx, ww, rounding=rounding, want_mag=True)
+        check_product(host(y[0])[:, cols], y_ref, mag, "M %d exponents %s %s" % (M, xe, we))
+
+
 @pytest.mark.parametrize("rows,cols", [(512, 1024), (8193, 64), (1, 16)])
 def test_minifloat_dequantizer_forms(rows, cols):
     """One item per thread up to 2^19 elements, four past that; the last workgroup full, ragged, and alone."""
