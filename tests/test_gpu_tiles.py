@@ -307,9 +307,10 @@ def test_decode_rings_of_wide_records(M, wx, ww):
     (8, 80 * 64, 432 * 32, 16, 8, 4, mx.MX_RNE),      # four column groups, two parts, four slices
     (4, 45 * 32, 2000, 32, 6, 8, mx.MX_RNE),
     (7, 17 * 64, 321, 64, 8, 7, mx.MX_RNE),
+    (1, 45 * 32, 2000, 32, 8, 5, mx.MX_RNE), (1, 64, 31, 64, 4, 8, mx.MX_RTZ), (2, 81 * 64, 5120, 16, 8, 4, mx.MX_RNE),
 ])
 def test_decode_splits_and_scales(M, K, N, block, wx, ww, rounding):
-    """Three to eight rows in every form of the split.  Block exponents at the ends of the range in which the block sums take
+    """One to eight rows in every form of the split.  Block exponents at the ends of the range in which the block sums take
     two multiply-adds (activations -63 to 64, weights -31 to 32), one past them, and blocks of zeros on both sides."""
     rng = np.random.default_rng(M * K + N)
     x0 = rng.standard_normal((M, K)).astype(np.float32)
