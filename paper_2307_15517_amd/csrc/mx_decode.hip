@@ -4,8 +4,9 @@
 // integer block dots, the two shared exponents applied once per block; format of Section 4.1): the fp32
 // activations are quantized with the arithmetic of mx_quantize on their way into on-chip memory, the block
 // dots are taken with one int8 MFMA per block, each block's integer is scaled by
-// 2^(Ea + Eb - (wa-2) - (wb-2)) and added into an fp32 accumulator.  mx_linear uses this kernel for two to
-// eight rows, and for one row where it is faster than the dot-product kernel of mx_gemv_dot.hip.
+// 2^(Ea + Eb - (wa-2) - (wb-2)) and added into an fp32 accumulator.  mx_linear uses this kernel for three
+// to eight rows; one and two rows go to the dot-product kernel of mx_gemv_dot.hip, which needs no exchange
+// between workgroups.
 //
 // Work split: the path is bound by one pass over the packed weights, so every compute unit has to stream.  A workgroup
 // owns a few neighbouring column groups of 32 (NW) and a K slice, which KS waves per column group divide among them; it

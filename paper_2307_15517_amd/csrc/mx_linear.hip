@@ -239,21 +239,18 @@ mx_status linear_run(const float* x, int64_t M, int64_t K, int64_t row_stride, m
     hipStream_t st = (hipStream_t)stream;
     const DecodePlan p = decode_plan(M, K, N, fb.block, fb.mant_bits);
     const bool fused_ok = K > 0 && fx.block_rows == 1 && ((uintptr_t)x & 15) == 0 && (row_stride & 3) == 0;
-    // One row stays with the dot-product kernel where that is the faster one.  Time of the other over its time, random shapes:
-    // blocks of 16 1.14 (4 bits) to 0.97 (8), of 32 1.00 and 0.98 (3, 4 bits), 0.88, 0.89 and 0.63 (5, 6, 8), of 64 0.97,
-    // 0.68, 0.96, 1.03, 0.81 (3, 4, 5, 6, 8 bits), where a third of the shapes with 3 and 5 bits are slower.  Two rows: 0.91,
-    // 0.80 and 0.75.
-    const bool split = M > 1 || (fb.block == 32 && fb.mant_bits >= 5) || (fb.block == 64 && (fb.mant_bits == 4 || fb.mant_bits == 8));
-    if (fused_ok && p.ok && split) {
-        // one launch: column groups x K slices, the activations of a slice quantized inside the kernel
-        const mx_status s = linear_decode(x, M, K, row_stride, fx, workspace, B_packed, N, fb, Y, ldy, st);
-        if (s != MX_ERR_UNSUPPORTED) return s;
-    }
     if (fused_ok && M <= 2) {
         // one launch, one workgroup per column group: the dot-product decode kernel quantizes the activations on
-        // its way into LDS; nothing passes between workgroups, the workspace is not touched
+        // its way into LDS; nothing passes between workgroups, the workspace is not touched, and a row has the bits
+        // that mx_gemm gives it.  For these the splitting kernel is not taken where it is the faster one (2 x 13824 x
+        // 5120, 8 by 4 bits, blocks of 16, 13.5 us for 16.6; one row with blocks of 32 from 5 bits 0.6 to 0.9 of the time).
         const GemmArgs g = fragment_args(M, N, K, nullptr, fx, B_packed, fb, Y, ldy, M * ldy);
         const mx_status s = gemv_dot(g, fx.mant_bits, fb.mant_bits, fx.block, 1, st, x, row_stride, &fx);
+        if (s != MX_ERR_UNSUPPORTED) return s;
+    }
+    if (fused_ok && M > 2 && p.ok) {
+        // one launch: column groups x K slices, the activations of a slice quantized inside the kernel
+        const mx_status s = linear_decode(x, M, K, row_stride, fx, workspace, B_packed, N, fb, Y, ldy, st);
         if (s != MX_ERR_UNSUPPORTED) return s;
     }
     // two launches: quantize into the fragment layout, then the decode product of mx_gemm

@@ -340,6 +340,44 @@ def test_decode_splits_and_scales(M, K, N, block, wx, ww, rounding):
         check_product(host(y[0])[:, cols], y_ref, mag, "M %d exponents %s %s" % (M, xe, we))
 
 
+def spread(g, rows, K, block):
+    """Blocks whose exponents lie far enough apart that a sum over them is rounded: another order shows in its bits."""
+    x = torch.randn((rows, K // block, block), generator=g, device="cuda")
+    return (x * torch.exp2(torch.randint(-8, 9, (rows, K // block, 1), generator=g, device="cuda").float())).reshape(rows, K)
+
+
+@pytest.mark.parametrize("K,N,block,wx,ww", [
+    (81 * 64, 5120, 16, 8, 4),
+    (33 * 128, 2000, 32, 8, 8),
+    (9 * 256, 1100, 64, 6, 4),
+    (5 * 256 + 64, 70, 64, 4, 8),
+])
+def test_decode_of_one_and_two_rows_keeps_nothing_between_workgroups(K, N, block, wx, ww):
+    """At one and two rows no workgroup waits for another's sums: the bits of a row are those of the product of packed
+    operands, with one row or two, aligned or not, and a workspace that other calls are using is neither read nor written."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + N)
+    fx, fw = mx.fmt(block, wx), mx.fmt(block, ww)
+    rows, w = spread(g, 2, K, block), spread(g, N, K, block)
+    shifted = torch.zeros((2, K + 4), device="cuda")
+    shifted[:, 1:K + 1] = rows
+    B = mx.quantize_pack(w, fw)
+    want = mx.gemm(mx.quantize_pack(rows, fx), fx, B, fw, 2, N, K)[0]
+    ws = mx.linear_workspace(2, K, N, fx, fw, "cuda")
+
+    def linear(M, x, stride):
+        y = torch.full((M, N), 3.0, device="cuda")
+        mx.mx_linear(x, M, K, stride, fx, ws, B, N, fw, mx.MX_LAYOUT_FRAGMENT, y, N)
+        return y
+    for M in (1, 2):
+        assert torch.equal(linear(M, rows, K), want[:M]), "%d rows" % M
+        assert torch.equal(linear(M, shifted[:, 1:], K + 4), want[:M]), "%d rows, not aligned" % M
+    ws.fill_(0xAB)
+    for M in (1, 2):
+        assert torch.equal(linear(M, rows, K), want[:M]), "%d rows, workspace in use" % M
+    assert int(ws.min()) == int(ws.max()) == 0xAB
+
+
 @pytest.mark.parametrize("rows,cols", [(512, 1024), (8193, 64), (1, 16)])
 def test_minifloat_dequantizer_forms(rows, cols):
     """One item per thread up to 2^19 elements, four past that; the last workgroup full, ragged, and alone."""
