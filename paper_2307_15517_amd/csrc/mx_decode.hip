@@ -381,12 +381,15 @@ struct DecodeSplit { int groups, parts, slices, part; };
 
 // The split that takes the least of: the items a thread quantizes and the records a wave streams, per round of resident
 // workgroups; the waves of the fullest compute unit with the bytes they stream; the exchange between slices and the
-// partial sums a thread adds there.  (4, 2), (2, 4), (1, 8) and (1, 4) are the best of nine forms over 3300 random shapes
-// (3 to 8 rows, K and N 256 to 14000, all blocks), 0.6 % above always the best of the nine.  The coefficients (us) are
-// least squares over 2800 shapes, every number of slices timed in each form: the choice costs 2.1 % against the best of
-// them, and takes 0.82 of what four column groups with one wave each and about 2560 (column group, slice) pairs take.
+// partial sums a thread adds there; all of it on average over three to eight rows.  It does not look at the number of rows
+// of the call: the split says in what order a row's sums are added, so a sequence gets the same bits in a batch of three as
+// in one of eight.  That costs nothing (130 random shapes of 3 to 8 rows: 0.998 of the time with the split that the rule
+// takes for each number alone; 5 rows 5120 -> 5120 9.8 us for 9.45, 8 rows 11008 -> 4096 13.8 either way).
+// (4, 2), (2, 4), (1, 8) and (1, 4) are the best of nine forms over 3300 random shapes (3 to 8 rows, K and N 256 to 14000,
+// all blocks), 0.6 % above always the best of the nine.  The coefficients (us) are least squares over 2800 shapes, every
+// number of slices timed in each form.
 // No more than `most` slices: the workspace holds the partial sums of that many.
-DecodeSplit choose_split(int M, int chunks, int groups, int block, int wb, int record, int most) {
+DecodeSplit choose_split(int chunks, int groups, int block, int wb, int record, int most) {
     static constexpr int forms[4][2] = {{4, 2}, {2, 4}, {1, 8}, {1, 4}};
     static constexpr int counts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64};
     DecodeSplit best = {0, 0, 0, 0};
@@ -407,10 +410,11 @@ DecodeSplit choose_split(int M, int chunks, int groups, int block, int wb, int r
             const int resident = 256 * (by_lds < by_regs ? by_lds : by_regs);
             const int64_t wgs = (int64_t)columns * slices;
             const float per_cu = (float)((wgs + 255) / 256) * (float)waves * 0.25f, rounds = (float)((wgs + resident - 1) / resident);
-            const int items = (M * slice * block / 2 + waves * 64 - 1) / (waves * 64);
-            const float t = rounds * (0.45f * (float)items + 0.07f * (float)part) +
+            int items = 0;
+            for (int rows = 3; rows <= 8; ++rows) items += (rows * slice * block / 2 + waves * 64 - 1) / (waves * 64);
+            const float t = rounds * (0.45f * (float)items / 6.f + 0.07f * (float)part) +
                             per_cu * (0.315f + 4e-5f * (float)part * (float)record) +
-                            (slices > 1 ? 1.55f + 0.088f * (float)(slices * M) / (float)(2 * ks) : 0.f);
+                            (slices > 1 ? 1.55f + 0.088f * (float)slices * 5.5f / (float)(2 * ks) : 0.f);
             if (best.parts == 0 || t < least) { least = t; best = {nw, ks, slices, part}; }
         }
     }
@@ -486,7 +490,7 @@ mx_status linear_decode(const float* x, int64_t M, int64_t K, int64_t row_stride
     a.partial = reinterpret_cast<float*>((uint8_t*)workspace + kDecodeCounterBytes);
     a.M = (int32_t)M; a.N = (int32_t)N; a.K = (int32_t)K;
     a.groups = (int32_t)gb.groups;
-    const DecodeSplit s = choose_split(a.M, (int)gb.chunks, a.groups, fb.block, fb.mant_bits, gb.record, p.ksplit);
+    const DecodeSplit s = choose_split((int)gb.chunks, a.groups, fb.block, fb.mant_bits, gb.record, p.ksplit);
     if (s.parts == 0) return MX_ERR_UNSUPPORTED;              // not reached: `most` slices of the smallest form fit the LDS
     a.columns = (a.groups + s.groups - 1) / s.groups;
     a.chunks = (int32_t)gb.chunks; a.part = s.part; a.ksplit = s.slices;

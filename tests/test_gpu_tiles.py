@@ -378,6 +378,28 @@ def test_decode_of_one_and_two_rows_keeps_nothing_between_workgroups(K, N, block
     assert int(ws.min()) == int(ws.max()) == 0xAB
 
 
+@pytest.mark.parametrize("K,N,block,wx,ww", [
+    (80 * 64, 5120, 16, 8, 4), (80 * 64, 13824, 16, 8, 4), (86 * 128, 4096, 32, 6, 5), (32 * 128, 11008, 32, 6, 5),
+    (12 * 256, 1100, 64, 6, 4), (30 * 128, 3000, 32, 8, 8),
+])
+def test_decode_rows_have_the_same_bits_with_three_to_eight_of_them(K, N, block, wx, ww):
+    """The split of K follows from the weights alone: a sequence gets the same sums, added in the same order, in a batch of
+    three as in one of eight, wherever its row lies."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + N)
+    fx, fw = mx.fmt(block, wx), mx.fmt(block, ww)
+    x = spread(g, 8, K, block)
+    B = mx.quantize_pack(spread(g, N, K, block), fw)
+    ws = mx.linear_workspace(8, K, N, fx, fw, "cuda")
+    y8 = torch.full((8, N), 3.0, device="cuda")
+    mx.mx_linear(x, 8, K, K, fx, ws, B, N, fw, mx.MX_LAYOUT_FRAGMENT, y8, N)
+    for M in (3, 4, 5, 6, 7):
+        for first in (0, 8 - M):
+            y = torch.full((M, N), 3.0, device="cuda")
+            mx.mx_linear(x[first:], M, K, K, fx, ws, B, N, fw, mx.MX_LAYOUT_FRAGMENT, y, N)
+            assert torch.equal(y, y8[first:first + M]), "%d rows from row %d" % (M, first)
+
+
 @pytest.mark.parametrize("rows,cols", [(512, 1024), (8193, 64), (1, 16)])
 def test_minifloat_dequantizer_forms(rows, cols):
     """One item per thread up to 2^19 elements, four past that; the last workgroup full, ragged, and alone."""
