@@ -40,14 +40,22 @@ typedef v16i_t v16i;
 // decode step, a short prompt): a 128 x 128 tile per workgroup left most of the chip idle, and the K loop of one wave
 // is a serial chain of loads, matrix instructions and scaling.
 // ------------------------------------------------------------------------------------------------
+// Block sums with a bias where its sixteen registers leave the kernel its waves per SIMD: four with blocks of 16, three with
+// blocks of 32, and four without it where both operands are narrow (tests/test_kernel_resources.py holds the built kernels to
+// this).
+constexpr bool biased_sums(int wa, int wb, int block) {
+    return block == 16 ? wa + wb <= (wb == 8 ? 13 : 14) : block == 32 && wa + wb >= 9 && wa + wb <= 14;
+}
+// LDS of a wave for the rows' exponents, or with the bias for their scales and what takes it off.
+constexpr size_t scale_lds(bool biased) { return biased ? 1024 : 512; }
+
 template <int WA, int WB, int B>
 __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArgs g) {
     constexpr int kDwA = Piece<WA, B>::kDw, kDwB = Piece<WB, B>::kDw;
     constexpr int kHalfDw = B / 8;       // int8 dwords per lane per block
     constexpr int D = 2 * (kDwA + kDwB + 2) <= 64 ? 2 : 1;               // chunks in registers
-    // block sums with a bias (see above) where its sixteen registers leave the kernel its waves per SIMD
-    constexpr bool BIASED = B == 16 ? WA + WB <= (WB == 8 ? 13 : 14) : B == 32 && WA + WB >= 9 && WA + WB <= 14;
-    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];       // xe[NW][2][4][32], red[NW/2][16][64]
+    constexpr bool BIASED = biased_sums(WA, WB, B);
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];       // xe[NW][1 or 2][4][32], red[NW/2][16][64]
     const int nw = (int)blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = lane & 31, h = lane >> 5;
@@ -61,8 +69,8 @@ __global__ __launch_bounds__(B >= 32 ? 512 : 1024) void gemm_tile_kernel(GemmArg
     const uint8_t* Abase = g.A + bz * g.matrixA + ga * g.chunks * g.recordA;
     const uint8_t* Bbase = g.B + bz * g.matrixB + gb * g.chunks * g.recordB;
     const int eadj = g.eadj - Unpack<WA, B>::kScaleLog2 - Unpack<WB, B>::kScaleLog2;
-    uint32_t* xe = lds + wave * (BIASED ? 256 : 128);
-    float* red = reinterpret_cast<float*>(lds + nw * (BIASED ? 256 : 128));
+    uint32_t* xe = lds + wave * (int)(scale_lds(BIASED) / 4);
+    float* red = reinterpret_cast<float*>(lds + nw * (int)(scale_lds(BIASED) / 4));
 
     float acc[16];
 #pragma unroll
@@ -516,8 +524,9 @@ __global__ __launch_bounds__(NW * 64) void gemv_stream_kernel(GemmArgs g) {
     }
 }
 
-// Waves of the 32 x 32 form that a compute unit holds: 16 of the kernel with blocks of 16, or of 32 with few bits, and 12
-// of the others (registers).
+// Waves of the 32 x 32 form that a compute unit holds (registers): 16 of the kernel with blocks of 16, or of 32 with few bits,
+// and 12 of the others.  Not told apart: 8 with blocks of 64 and 7 or 8 bits on both sides, 16 with 8 by 8 bits in blocks of
+// 32 and 2 by 2 in blocks of 64.
 constexpr int resident_waves(int block, int wa, int wb) { return block == 16 || (block == 32 && wa + wb <= 8) ? 16 : 12; }
 
 // Waves per tile of that form: as many as leave all tiles resident at once.  A workgroup spends most of a short K loop on
@@ -606,7 +615,7 @@ mx_status launch(const GemmArgs& g, int64_t batch, hipStream_t st) {
             MX_HIP_LAUNCH_CHECK();
             return MX_OK;
         }
-        const size_t smem = (size_t)nw * 1024 + (size_t)(nw / 2) * 4096;
+        const size_t smem = (size_t)nw * scale_lds(biased_sums(WA, WB, B)) + (size_t)(nw / 2) * 4096;
         dim3 grid((unsigned)(ceil_div(g.groupsA * g.groupsB, 8) * 8), (unsigned)batch);
         hipLaunchKernelGGL((gemm_tile_kernel<WA, WB, B>), grid, dim3(nw * 64), smem, st, g);
     }

@@ -251,6 +251,7 @@ constexpr int staged_ahead(int s) { return s >= 6 ? s - 1 : s; }
 template <int PA, int PB, int TM, int TN, int S, int OCC, int QO, int WS>
 __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kernel(ScaledArgs g) {
     constexpr int kStages = S;
+    static_assert(S >= 3, "with fewer every copy is awaited at the step after its issue");
     constexpr int E = staged_ahead(S);                 // K steps by which the copies run ahead (see the pipeline below)
     constexpr int TAIL = E < S ? 2 : MX_SCALED_TAIL_MFMAS;
     constexpr int LEAD = (E - 1) / 4;                  // groups by which the scale copies run ahead of the next group's

@@ -14,8 +14,8 @@ READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 
 
 @pytest.fixture(scope="module")
-def scratch_bytes(tmp_path_factory):
-    """Demangled kernel name -> bytes of scratch memory per work item."""
+def kernel_notes(tmp_path_factory):
+    """Demangled kernel name -> (bytes of scratch memory, vector registers) per work item."""
     if not os.path.exists(READELF) or shutil.which("c++filt") is None:
         pytest.skip("no llvm-readelf")
     if not os.path.exists(mx.LIB_PATH):
@@ -37,10 +37,21 @@ def scratch_bytes(tmp_path_factory):
                 notes = subprocess.run([READELF, "--notes", path], stdout=subprocess.PIPE, text=True, check=True).stdout
                 for kernel in notes.split(".agpr_count:")[1:]:
                     found[re.search(r"\.name:\s+(\S+)", kernel).group(1)] = \
-                        int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", kernel).group(1))
+                        tuple(int(re.search(r"\.%s:\s+(\d+)" % key, kernel).group(1))
+                              for key in ("private_segment_fixed_size", "vgpr_count"))
         at = data.find(b"__CLANG_OFFLOAD_BUNDLE__", at + 24)
     names = subprocess.run(["c++filt"], input="\n".join(found), stdout=subprocess.PIPE, text=True, check=True).stdout.split("\n")
     return dict(zip((n.replace("mx::(anonymous namespace)::", "") for n in names), found.values()))
+
+
+@pytest.fixture(scope="module")
+def scratch_bytes(kernel_notes):
+    return {name: scratch for name, (scratch, _) in kernel_notes.items()}
+
+
+def waves_per_simd(vgprs):
+    """512 registers per lane of a SIMD, handed out eight at a time, to no more than eight waves."""
+    return min(8, 512 // ((vgprs + 7) // 8 * 8))
 
 
 @pytest.mark.parametrize("width", [5, 6, 7, 8])
@@ -56,3 +67,34 @@ def test_product_and_attention_kernels_stay_in_registers(scratch_bytes):
                             r"attention_bf16|attention_split|linear_splitk)_kernel<", n)]
     assert len(kernels) > 300
     assert not [(n, scratch_bytes[n]) for n in kernels if scratch_bytes[n]]
+
+
+def test_waves_of_the_fragment_product_are_those_its_forms_are_chosen_by(kernel_notes):
+    """The rules for the 32 x 32 form count on 16 waves per compute unit with blocks of 16, or of 32 with few bits, and on 12 of
+    the others (8 with blocks of 64 and 7 or 8 bits on both sides); the sums with a bias keep to them."""
+    seen = 0
+    for name, (_, vgprs) in kernel_notes.items():
+        m = re.search(r"\bgemm_tile_kernel<(\d), (\d), (\d+)>", name)
+        if not m:
+            continue
+        wa, wb, block = (int(v) for v in m.groups())
+        least = 4 if block == 16 or (block == 32 and wa + wb <= 8) else 2 if block == 64 and min(wa, wb) >= 7 else 3
+        assert waves_per_simd(vgprs) >= least, (name, vgprs)
+        seen += 1
+    assert seen == 3 * 7 * 7
+
+
+def test_waves_of_the_decode_kernel_are_those_its_split_is_chosen_by(kernel_notes):
+    """Up to 16 waves per compute unit with blocks of 16 and 32, fewer where the ring of weight records is wide."""
+    seen = 0
+    for name, (_, vgprs) in kernel_notes.items():
+        m = re.search(r"\blinear_splitk_kernel<(\d), (\d+), \d, \d>", name)
+        if not m:
+            continue
+        width, block = (int(v) for v in m.groups())
+        record = block * width // 16 + 1                               # registers of one record and its exponents
+        depth = min(5, max(40 // record, 3) if block <= 32 else max(96 // record, 2))
+        registers = depth * record + {16: 65, 32: 78, 64: 110}[block]
+        assert waves_per_simd(vgprs) >= (4 if registers <= 128 else 3 if registers <= 168 else 2), (name, vgprs)
+        seen += 1
+    assert seen == 3 * 7 * 4
