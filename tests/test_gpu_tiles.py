@@ -67,8 +67,8 @@ def test_fragment_product_block_sums_with_a_bias(M, N, K, block, wa, wb):
 
 
 MAT = mx.MX_LAYOUT_MATRIX
-# (row tiles, column tiles) of 32: one size in the range of each form of the matrix-layout product but the last, from the
-# smallest tile with K split over the waves to a partial second round of the larger ones (K short: MATRIX_FORMS_LONG_K)
+# (row tiles, column tiles) of 32, from the smallest tile with K split over the waves to a partial second round of the larger
+# ones.  K is short in the tests that take these, which moves some to smaller tiles: MATRIX_FORMS_LONG_K has every form.
 MATRIX_FORMS = [(1, 2), (2, 200), (4, 200), (4, 400), (4, 900), (3, 1500), (4, 2400)]
 
 
@@ -300,13 +300,18 @@ def test_decode_rings_of_wide_records(M, wx, ww):
 
 
 @pytest.mark.parametrize("M,K,N,block,wx,ww,rounding", [
-    (3, 48, 33, 16, 8, 8, mx.MX_RNE),          # one partial chunk: three of four waves have no record; two column groups
-    (5, 37 * 16, 100, 16, 2, 4, mx.MX_RTZ),    # eight parts of two chunks, the last ones short, a partial chunk
-    (6, 70 * 64, 41 * 32 + 5, 16, 8, 4, mx.MX_RNE),   # two column groups, four parts, nine slices, half a column of workgroups
-    (8, 13 * 32, 13007, 32, 8, 2, mx.MX_RNE),  # four column groups, two parts, one slice
-    (8, 80 * 64, 432 * 32, 16, 8, 4, mx.MX_RNE),      # four column groups, two parts, four slices
-    (4, 45 * 32, 2000, 32, 6, 8, mx.MX_RNE),
+    (3, 48, 33, 16, 8, 8, mx.MX_RNE),          # one column group, four parts: one partial chunk, three of the waves have none
+    (5, 37 * 16, 100, 16, 2, 4, mx.MX_RTZ),    # one group, eight parts of two chunks, the last ones short, a partial chunk
+    (6, 70 * 64, 41 * 32 + 5, 16, 8, 4, mx.MX_RNE),   # one group, eight parts, five slices, the last one short
+    (5, 24 * 128, 669, 32, 6, 5, mx.MX_RTZ),   # one group, four parts, six slices
+    (6, 179 * 32, 2075, 32, 6, 5, mx.MX_RNE),  # two groups, four parts, six slices, half a column of workgroups, a partial chunk
+    (8, 13 * 32, 13007, 32, 8, 2, mx.MX_RNE),  # two groups, four parts, one slice, half a column
+    (8, 8 * 128, 20000, 32, 8, 2, mx.MX_RNE),  # four groups, two parts, one slice, a column with one group of the four
+    (8, 80 * 64, 432 * 32, 16, 8, 4, mx.MX_RNE),      # four groups, two parts, four slices
+    (8, 80 * 64, 13889, 16, 8, 4, mx.MX_RNE),  # the same with three of the four groups in the last column
+    (4, 45 * 32, 2000, 32, 6, 8, mx.MX_RNE),   # one group, eight parts, one slice
     (7, 17 * 64, 321, 64, 8, 7, mx.MX_RNE),
+    # one and two rows: the dot-product kernel
     (1, 45 * 32, 2000, 32, 8, 5, mx.MX_RNE), (1, 64, 31, 64, 4, 8, mx.MX_RTZ), (2, 81 * 64, 5120, 16, 8, 4, mx.MX_RNE),
 ])
 def test_decode_splits_and_scales(M, K, N, block, wx, ww, rounding):
@@ -466,19 +471,19 @@ def test_attention_of_128_queries_in_blocks_of_32(heads, Sq, Sk, dim, R):
             assert (np.abs(host(O[hd, r0:r1]).astype(np.float64) - o_ref[r0:r1]) <= bound).all(), (hd, rows)
 
 
-# The forms of the matrix-layout product, (row tiles, column tiles) of 32 and what they select with blocks of 32 or 64 and a
-# two-piece left operand.  With a one-piece left operand 64 x 128 and 64 x 256 are 128 x 128, and so they are with blocks of
-# 16 from 64 x 256 on.  With blocks of 16 no form has copy waves; with two pieces on both sides everything from 64 x 256 on
-# is 128 x 128.  (Forms that need a longer K: test_matrix_product_with_deep_stages.)
+# The forms of the matrix-layout product, (row tiles, column tiles) of 32 and what they select, with K of long_k.  Blocks of 32
+# and 64 with pieces of the left by pieces of the right operand; a quantized result takes what 2 x 1 and 1 x 1 take.  "copy":
+# with copy waves, "x 2": two workgroups per compute unit.  (Forms that need another K: test_matrix_product_with_deep_stages.)
+#                2 x 1             1 x 1             1 x 2             2 x 2             blocks of 16
 MATRIX_FORMS_LONG_K = [
-    (1, 100),      # 32 x 32, K split over the waves
-    (2, 200),      # 32 x 64, K split
-    (4, 240),      # 64 x 64, K split, with blocks of 16; 64 x 128 otherwise
-    (4, 400),      # 64 x 128
-    (4, 900),      # 64 x 256
-    (3, 1500),     # 128 x 256, one workgroup per compute unit with copy waves
-    (4, 2400),     # a second round of 128 x 256 less than three eighths full: 64 x 256 / 128 x 128, two per compute unit
-    (20, 830),     # 520 tiles of 128 x 256: two per compute unit
+    (1, 100),  # 32 x 32, K split over the waves, in all of them
+    (2, 200),  # 32 x 64, K split
+    (4, 240),  # 64 x 128         128 x 128         128 x 128         64 x 128          64 x 64, K split
+    (4, 400),  # the same                                                               64 x 128
+    (4, 900),  # 64 x 256         128 x 128         128 x 128         128 x 128 copy    128 x 128
+    (4, 1600), # 128 x 256 copy   128 x 256 copy    128 x 256 copy    128 x 128 x 2     128 x 256
+    (4, 2400), # 64 x 256         128 x 128         128 x 128         64 x 128          128 x 128: a second round little filled
+    (20, 830), # 128 x 256 x 2    128 x 256 x 2     128 x 256 copy    128 x 128 x 2     128 x 256 x 2
 ]
 
 
@@ -493,9 +498,9 @@ def exact_operands(g, batch, M, N, K):
 
 
 def long_k(block):
-    """Block 32/64: 22 steps of 64 (21 and a half with blocks of 32), six groups of four with padding, more than four turns
-    of five stages.  Block 16: 35 steps of 32, the last one half filled, more than five turns of six stages."""
-    return {16: 32 * 34 + 16, 32: 64 * 21 + 32, 64: 64 * 22}[block]
+    """Block 32/64: 30 steps of 64 (29 and a half with blocks of 32), eight groups of four with padding, six turns of five
+    stages.  Block 16: 35 steps of 32, the last one half filled, more than five turns of six stages."""
+    return {16: 32 * 34 + 16, 32: 64 * 29 + 32, 64: 64 * 30}[block]
 
 
 @pytest.mark.parametrize("rt,ct", MATRIX_FORMS_LONG_K)
@@ -546,36 +551,42 @@ def test_matrix_quantized_output_on_long_k(rt, ct, block, wa, wo, rows):
         assert torch.equal(out, want), "launch %d" % rep
 
 
-@pytest.mark.parametrize("rt,ct,steps", [(4, 400, 52), (4, 400, 61), (5, 390, 57), (11, 344, 33), (11, 344, 40), (8, 400, 24)])
+@pytest.mark.parametrize("rt,ct,steps,batch", [
+    (4, 400, 52, 1), (4, 400, 61, 1), (4, 400, 55, 1), (4, 200, 55, 2),         # eight stages: 64 x 128 and 128 x 128 with one piece
+    (5, 390, 57, 1), (5, 195, 57, 2),                       # the same, 64 x 256 beside it, six stages with two pieces on both sides
+    (11, 344, 33, 1), (11, 344, 35, 1), (11, 344, 40, 1), (11, 172, 35, 2),     # 64 x 384 with six stages
+    (8, 400, 24, 1),                                        # short K: 64 x 128 and 128 x 128
+    (4, 400, 20, 3),                                        # past a batch of two: two pieces on both sides take 128 x 256
+])
 @pytest.mark.parametrize("block,wa,wb", [(32, 8, 4), (64, 4, 3), (32, 7, 6), (64, 3, 8)])
-def test_matrix_product_with_deep_stages(rt, ct, steps, block, wa, wb):
-    """The forms with six and eight stages and copy waves (64 x 128, 128 x 128, 64 x 384): numbers of K steps that fill the
-    last group of four, leave it with one and with three, every stage and every slot of the scales reused; the quantized
-    ending, whose work the copy waves share, where there is one."""
+def test_matrix_product_with_deep_stages(rt, ct, steps, batch, block, wa, wb):
+    """The forms with six and eight stages and copy waves (64 x 128, 128 x 128, 64 x 384) and others that this K selects:
+    numbers of K steps that fill the last group of four, leave it with one and with three, every stage and every slot of the
+    scales reused, alone and over a batch; the quantized ending, whose work the copy waves share, where there is one."""
     M, N, K = rt * 32 - 13, (ct * 32 - 8) // block * block, 64 * steps - (32 if block == 32 else 0)
     g = torch.Generator(device="cuda")
     g.manual_seed(rt * ct + steps)
-    x, w = exact_operands(g, 1, M, N, K)
+    x, w = exact_operands(g, batch, M, N, K)
     fa, fb = mx.fmt(block, wa), mx.fmt(block, wb)
     A, B = mx.quantize_pack(x, fa, MAT), mx.quantize_pack(w, fb, MAT)
-    want = torch.mm(x[0].double(), w[0].t().double()).float()
+    want = torch.stack([torch.mm(x[b].double(), w[b].t().double()) for b in range(batch)]).float()
     assert want.abs().max() < 2.0 ** 24
     for rep in range(5):
-        y = torch.full((M, N + 3), float("nan"), device="cuda")
-        mx.mx_gemm(1, M, N, K, A, fa, B, fb, MAT, y, N + 3, 0)
+        y = torch.full((batch, M, N + 3), float("nan"), device="cuda")
+        mx.mx_gemm(batch, M, N, K, A, fa, B, fb, MAT, y, N + 3, M * (N + 3))
         torch.cuda.synchronize()
-        assert torch.equal(y[:, :N], want), "launch %d" % rep
-        assert torch.isnan(y[:, N:]).all(), "columns past N written"
+        assert torch.equal(y[:, :, :N], want), "launch %d" % rep
+        assert torch.isnan(y[:, :, N:]).all(), "columns past N written"
     if wb > 4:
         return
     bias = torch.randint(-3, 4, (1, N), generator=g, device="cuda").float() * 64.0
     mant, exps = mx.quantize(bias, fb)
     for wo in (8, 4):
         fo = mx.fmt(block, wo)
-        packed = torch.full((mx.mx_packed_bytes(1, M, N, fo, MAT),), 255, dtype=torch.uint8, device="cuda")
-        mx.mx_quantize_pack(want + bias, 1, M, N, N, 0, fo, MAT, packed)
+        packed = torch.full((mx.mx_packed_bytes(batch, M, N, fo, MAT),), 255, dtype=torch.uint8, device="cuda")
+        mx.mx_quantize_pack(want + bias, batch, M, N, N, M * N, fo, MAT, packed)
         for rep in range(3):
             out = torch.full_like(packed, 255)
-            mx.mx_gemm_q(1, M, N, K, A, fa, B, fb, MAT, mant, exps, fb, fo, out)
+            mx.mx_gemm_q(batch, M, N, K, A, fa, B, fb, MAT, mant, exps, fb, fo, out)
             torch.cuda.synchronize()
             assert torch.equal(out, packed), "width %d, launch %d" % (wo, rep)
