@@ -329,10 +329,13 @@ MX_API mx_status mx_attention(int64_t batch, int64_t Sq, int64_t Sk, int64_t D, 
  * Linear layer on fp32 activations for decode (M <= 8): quantizes x [M x K] with fx
  * on the fly (same arithmetic as mx_quantize, axis 1), then the product above
  * against B_packed [N x K] (Section 3.2: quantize the input, then the operator).  The result
- * equals mx_quantize + mx_pack + mx_gemm.  One launch when x is 16-byte aligned, row_stride a
- * multiple of 4 and fx.block_rows = 1: the weights are split over column groups and K slices so that
- * every compute unit streams its share once, each workgroup quantizes only its slice of x, and the
- * slices' partial sums are added in slice order by the last workgroup to finish (the result does not
+ * is that of mx_quantize + mx_pack + mx_gemm up to the order in which the block terms are added in fp32
+ * (within the bound stated there; the same bits at one and two rows).  That order follows from K, N and the
+ * formats and from whether M is 1, 2 or more, not from M otherwise: of aligned rows, a row has the same bits
+ * in a call of three as in one of eight.  One launch when x is 16-byte aligned, row_stride a
+ * multiple of 4 and fx.block_rows = 1: with three rows and more the weights are split over column groups and
+ * K slices so that every compute unit streams its share once, each workgroup quantizes only its slice of x,
+ * and the slices' partial sums are added in slice order by the last workgroup to finish (the result does not
  * depend on the order of arrival).  Otherwise two launches (quantize, then the decode product).
  * workspace: device buffer of mx_linear_workspace_bytes(M, K, N, fx, fb, layout) bytes, 256-byte
  *   aligned, caller-owned.  Its first 16384 bytes are arrival counters: they must be zero when the call

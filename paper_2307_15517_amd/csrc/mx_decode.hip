@@ -15,12 +15,15 @@
 // workspace and the workgroup that arrives last at the columns' counter adds them in slice order, so the result does
 // not depend on the order of arrival.
 //
-// What a call takes beyond the pass over the weights: quantizing (repeated by every workgroup of a slice, so wide
-// workgroups), the exchange between slices (three dependent trips to memory, so few slices) and workgroups enough for
-// 256 compute units; choose_split weighs them.  Eight elements per quantizer item, waves that divide the slice inside
-// the workgroup, 16 x 16 results of which all elements are used: 8 rows, 8 by 4 bits, blocks of 16, 5120 -> 5120 12.0 ->
-// 9.4 us, 5120 -> 13824 17.0 -> 14.9, 13824 -> 5120 17.4 -> 15.0; 5 rows, 6 by 5 bits, blocks of 32, 11008 -> 4096 17.2 ->
-// 13.3; 3 rows 768 -> 3072 6.8 -> 4.4.  A bare read of 39.9 MB of weights (5120 -> 13824) takes 8.4 us.
+// What a call takes beyond the pass over the weights (8 rows, 8 by 4 bits, blocks of 16, 5120 -> 5120, 5120 -> 13824 and
+// 13824 -> 5120: 10.3, 14.7 and 15.3 us; timed on copies of this kernel with the part left out): the exchange between slices,
+// three dependent trips to memory, 2.4, 1.9 and 1.6 us (so few slices); quantizing, which every workgroup of a slice repeats,
+// 1.5, 1.5 and 3.2 (so wide workgroups); scaling the block sums 1.5, 2.6 and 2.8.  Without all three it takes 5.0, 8.5 and
+// 8.3 us, the time of a bare read of the same bytes.  choose_split weighs the first two with the number of workgroups.
+// Eight elements per quantizer item (four, and a row found in a loop, before) and waves that divide the slice inside the
+// workgroup (slices that meet through memory, before): 12.0 -> 9.5 us, 17.0 -> 14.9 and 17.4 -> 15.0; 5 rows, 6 by 5 bits,
+// blocks of 32, 11008 -> 4096 17.2 -> 13.3; 3 rows 768 -> 3072 6.8 -> 4.4.  The 16 x 16 results, of which all elements are used,
+// are 0.4 us of 17 of that with blocks of 16 and nothing with blocks of 32.
 #include <type_traits>
 
 #include "mx_decode.h"

@@ -860,8 +860,8 @@ mx_status launch_scaled(ScaledArgs& g, int64_t batch, hipStream_t st) {
 // For batches of one and two (larger ones lie either way, up to a fifth slower) four more lines, drawn on 14600 random
 // products timed in every form, 8 by 4 bits unless said:
 // * At most one workgroup per compute unit and K from 48 steps on: copy waves and eight stages (one-piece left operand: 52).
-//   What bounds these is the copy path of a compute unit (12 KiB per step at about 105 GB/s), and the copy waves keep it
-//   busy: 333 x 4096 x 11008 31.4 -> 25.9 us, 512 x 4096 x 4096 15.5 -> 13.8, 333 x 4096 x 11008 with 4 by 4 bits 31.8 ->
+//   What bounds these is the copy path of a compute unit (a step copies 12 KiB and takes 0.11 us, from the times of 333 x 4096
+//   and 333 x 3072 at K = 4096 and 8192: 110 GB/s, with the matrix cores busy 41 %), and the copy waves keep it busy: 333 x 4096 x 11008 31.4 -> 25.9 us, 512 x 4096 x 4096 15.5 -> 13.8, 333 x 4096 x 11008 with 4 by 4 bits 31.8 ->
 //   26.2; over 698 products 12 percent on average, none slower; 600 x 3072 x 768, twelve steps, takes 6.6 for 6.2.
 // * K up to 28 steps: tiles of 64 x 128 (128 x 128) on to 700 (512) of them, two on a compute unit, since the larger tiles'
 //   fixed cost is not repaid: 2048 x 3072 x 768 11.7 -> 10.0 us; 5 to 18 percent on 430 products.
