@@ -24,11 +24,16 @@
 // sweep 2 the V^T) units of one tile of 32 keys are copied global -> LDS with 16-byte direct-to-LDS loads, five
 // stages, one barrier per key tile.  Two query tiles per wave (363 registers, one workgroup) were slower, 128 us.
 //
-// Bound: vector issue is the longest of the pipes' times (about 195 instructions, 33 of them exponentials, per tile and wave
-// over both sweeps; the vector ALU is active 63 % of the cycles, the matrix cores 44 %), not reached for the LDS reads and
-// the barrier of every key tile.  The second product of a key tile runs one tile behind its scores, so that no matrix
-// instruction is left without vector work under it: 16 heads x 2040 queries x 2048 keys x 128 76.7 -> 71 us, 32 x 2048 x
-// 2048 x 128 124.2 -> 122.5 us (where it does not pay: pick_attention).
+// Bound: on real operands the power that they draw.  32 heads x 2048 x 2048 x 128 takes 102 us, 88 us on operands that are
+// all zero (the same instructions at the full clock); the three products alone are 85 us at the rate that a large bfloat16
+// product reaches.  At the full clock it is vector issue: a matrix instruction takes 8 of its 32 cycles from the vector
+// ALU, an exponential 8, any other vector instruction 4, an LDS read about 5.  Hence few vector instructions: no search for the
+// maximum in most tiles of sweep 1, the exponents of both blocks of a tile computed at once (block_scales): 108 -> 102 us,
+// on zero operands 94 -> 88; 24 heads x 2040 x 2048 x 80 91 -> 85, 32 x 1500 x 1536 x 64 59 -> 54.5.  The LDS reads of a
+// tile's K run a tile ahead, each into the registers that a matrix instruction has just freed, so that no
+// instruction waits for them; V^T straight from global memory instead of through LDS: 111 for 108 us.  The second product of a
+// key tile runs one tile behind its scores, so that no matrix instruction is left without vector work under it: 16 heads x
+// 2040 queries x 2048 keys x 128 76.7 -> 71 us (where it does not pay: pick_attention).
 #include <type_traits>
 
 #include "mx_bf16.h"
@@ -58,6 +63,7 @@ struct AttnArgs {
     int32_t vec;                   // O rows may be stored as float4
     float pair;                    // 0 when two neighbouring queries share the exponents of P, else -inf
     float wide;                    // 0 when P is quantized in blocks of 32 keys (a whole key tile), else -inf
+    int32_t join;                  // one of the two
 };
 
 // 16 bytes per lane from global memory straight into LDS: lane L's bytes land at lds_addr + 16*L.
@@ -79,10 +85,65 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// s_waitcnt lgkmcnt(n), every other counter left alone (bits 11:8)
+template <int N>
+__device__ __forceinline__ void wait_lgkmcnt() {
+    static_assert(N >= 0 && N < 16, "lgkmcnt is a 4-bit counter");
+    __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
+}
+
+// A workgroup barrier at which up to N of the wave's newest LDS reads may be under way
+template <int N>
+__device__ __forceinline__ void step_barrier() {
+    wait_lgkmcnt<N>();
+    asm volatile("s_barrier" ::: "memory");
+}
+
 // The value is computed before this point of the program: an empty volatile statement is ordered with the
 // scheduling fences, and so, through it, is the (otherwise freely movable) arithmetic that produces v.
 __device__ __forceinline__ void pin(float v) { asm volatile("" ::"v"(v)); }
 __device__ __forceinline__ void pin(int v) { asm volatile("" ::"v"(v)); }
+
+// The larger one; __builtin_fmaxf spends an instruction on either operand whose origin the compiler cannot see
+__device__ __forceinline__ float max_of(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// The exponents of the two blocks of 16 keys of a key tile, from the scores s0 and s1 that are the largest of this lane's
+// half of either: the quantizer's floor(log2 max) with a = log2 of a probability in place of the probability (exp2 grows with
+// the score, so the maximum is taken over the scores).  Out: t[b], a mantissa q of block b stands for q * 2^t[b], and off[b],
+// so that 2^(c * score + off[b]) is the probability in units of that.  One exchange between the lane halves turns two
+// half maxima into one whole one per lane (lower half: block 0, upper half: block 1), so that what follows is done
+// once for both; with an exchange per block and everything done twice it took 19 instructions more.
+__device__ __forceinline__ void block_scales(const AttnArgs& g, float s0, float s1, float c, float mrow, int wm2, float (&off)[2],
+                                             int (&t)[2]) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(s0), __float_as_uint(s1), false, false);
+    float m = __builtin_fmaf(max_of(__uint_as_float(sw[0]), __uint_as_float(sw[1])), c, -mrow);
+    int join = g.join;
+    asm("" : "+s"(join));                                 // a scalar branch
+    if (join) {
+        // two-row blocks: queries 2t and 2t+1 (neighbouring lanes) share the exponent, the larger of the two
+        // log-probabilities; one-row blocks add -inf to the neighbour's and keep their own
+        m = __builtin_fmaxf(m, g.pair + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                            0, __builtin_bit_cast(int, m), 0xB1, 0xF, 0xF, true)));
+        // blocks of 32: the tile's two runs of 16 keys are one block (the same trick: + 0 or + -inf)
+        const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+        m = __builtin_fmaxf(m, g.wide + __builtin_fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1])));
+    }
+    // the integer part, between the bounds of the exponent; -200 also for all keys masked, or c = 0 with them
+    int E;
+    asm("v_max_f32 %0, 0xc3480000, %1\n\tv_cvt_flr_i32_f32 %0, %0\n\tv_med3_i32 %0, %0, %2, %3"
+        : "=&v"(E) : "v"(m), "v"(-g.bias_p), "s"(g.emax_p));
+    const int tm = E - wm2;
+    const auto tb = __builtin_amdgcn_permlane32_swap(tm, tm, false, false);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        t[b] = (int)tb[b];
+        off[b] = -(float)t[b] - mrow;
+    }
+}
 
 constexpr int kAttnStages = 5;
 
@@ -151,40 +212,42 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
 
     auto sweep = [&](auto pvc) {
         constexpr bool PV = decltype(pvc)::value;
-        constexpr int NP = 2 * (PV ? KS + DT : KS);     // 1 KiB pieces per key tile
-        constexpr int NL = (NP + 3) / 4;                // per wave
-        const uint8_t* src[NL];
-        int64_t adv[NL];
-        int dst[NL];
+        // 1 KiB pieces of a key tile that this wave copies: of K, and of V^T (the last one twice rather than a branch)
+        constexpr int KP = KS / 2, VP = PV ? (2 * DT + 3) / 4 : 0;
+        static_assert(KS % 2 == 0, "the four waves share the pieces of K evenly");
+        constexpr int NL = KP + VP;                     // copies in flight per tile step
+        constexpr int NREAD = NK + (PV && LAG ? 2 * DT : 0);   // LDS reads of a step that the next step's work needs
+        const uint8_t* ksrc = Kbase + wave * 1024;
+        const uint8_t* vsrc[VP + 1];
+        int vdst[VP + 1];
 #pragma unroll
-        for (int q = 0; q < NL; ++q) {
-            int t = q * 4 + wave;
-            if (t >= NP) t = NP - 1;                    // duplicate the last copy instead of branching
-            const int n = t >> 1, part = t & 1;
-            if (n < KS) {
-                src[q] = Kbase + n * kBfUnitBytes + part * 1024;
-                adv[q] = KS * kBfUnitBytes;
-            } else {
-                src[q] = Vbase + (n - KS) * g.v_ksteps * kBfUnitBytes + part * 1024;
-                adv[q] = kBfUnitBytes;
-            }
-            dst[q] = n * kBfUnitBytes + part * 1024;
+        for (int q = 0; q < VP; ++q) {
+            const int t = q * 4 + wave < 2 * DT ? q * 4 + wave : 2 * DT - 1;
+            vsrc[q] = Vbase + (t >> 1) * g.v_ksteps * kBfUnitBytes + (t & 1) * 1024;
+            vdst[q] = KS * kBfUnitBytes + t * 1024;
         }
-        // Copies are always issued in full, with the key tile clamped to the last one, so that the
+        // Copies are always issued in full, past the last key tile that tile again, so that the
         // number of copies in flight is the same at every step and the vmcnt waits stay exact.
-        auto issue = [&](int64_t kt, int stage) {
-            kt = kt < g.nt ? kt : g.nt - 1;
+        const int nt = (int)g.nt;
+        int k_next = 0, v_next = 0;
+        auto issue_k = [&](uint32_t slot) {
 #pragma unroll
-            for (int q = 0; q < NL; ++q) copy16_to_lds(src[q] + kt * adv[q], lane16, lds0 + stage * STAGE + dst[q]);
+            for (int q = 0; q < KP; ++q) copy16_to_lds(ksrc + q * 4096, lane16, lds0 + slot + wave * 1024 + q * 4096);
+            ksrc += ++k_next < nt ? KS * kBfUnitBytes : 0;
         };
-        // S^T of the key tile in `stage` into register set `set`: fragments first, then matrix instruction
-        // kk = 0 .. NK-1 one at a time (the caller slots vector work between them)
-        v4i kf[NK];
-        auto read_k = [&](int stage) {
-            const uint8_t* st = smem + stage * STAGE;
+        auto issue_v = [&](uint32_t slot) {
+            ++v_next;
 #pragma unroll
-            for (int kk = 0; kk < NK; ++kk)
-                kf[kk] = *reinterpret_cast<const v4i*>(st + (kk >> 1) * kBfUnitBytes + (kk & 1) * 1024 + koff);
+            for (int q = 0; q < VP; ++q) {
+                copy16_to_lds(vsrc[q], lane16, lds0 + slot + vdst[q]);
+                vsrc[q] += v_next < nt ? kBfUnitBytes : 0;
+            }
+        };
+        // S^T of a key tile into register set `set`: matrix instruction kk = 0 .. NK-1 one at a time (the caller slots
+        // vector work between them), each followed by the read of the tile after it into the registers it has freed
+        v4i kf[NK];
+        auto read_k = [&](int kk, uint32_t slot) {
+            kf[kk] = *reinterpret_cast<const v4i*>(smem + slot + (kk >> 1) * kBfUnitBytes + (kk & 1) * 1024 + koff);
         };
         auto score_mfma = [&](int kk, auto setc) {
             constexpr int set = decltype(setc)::value;
@@ -200,107 +263,102 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
             o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, vf[dt][b]),
                                                             __builtin_bit_cast(v8bf, pf[set][b]), o[dt], 0, 0, 0);
         };
-        auto read_v = [&](int m, int stage) {
+        auto read_v = [&](int m, uint32_t slot) {
             const int b = m / DT, dt = m % DT;
-            vf[dt][b] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + (KS + dt) * kBfUnitBytes + b * 1024 + lane16);
+            vf[dt][b] = *reinterpret_cast<const v4i*>(smem + slot + (KS + dt) * kBfUnitBytes + b * 1024 + lane16);
         };
         // One key tile: tile kt's scores are in set kt % 2, tile kt+1's are started into the other set, and (sweep 2)
         // tile kt-1's P^ V is added.  RAG: keys past Sk are masked (only the last tile can have them).
         // The instruction order is written out and pinned: one matrix instruction, then its share of the
         // vector work (given as numbered units), so that both pipes stay busy.
-        auto body = [&](int64_t kt, int cur, auto setc, auto ragc) {
+        auto body = [&](int kt, uint32_t s0, uint32_t s2, uint32_t s3, auto setc, auto ragc) {
             constexpr int set = decltype(setc)::value;
             constexpr bool RAG = decltype(ragc)::value;
             const auto nset = std::integral_constant<int, set ^ 1>{};
-            const int nxt = cur + 1 == S ? 0 : cur + 1, prv = cur == 0 ? S - 1 : cur - 1;
+            // What is awaited is K of tile kt+2 and V of tile kt; in flight stay the copies of the two newest steps.  The
+            // barrier publishes them.  LDS reads of tile kt-1's step may be under way at it, none from before (reads return in
+            // order), so K's slot of tile kt and V's of tile kt-2 are free for the copies of this step.
+            wait_vmcnt<2 * NL>();
+            step_barrier<(NREAD < 15 ? NREAD : 15)>();
             if constexpr (PV && !LAG) {
 #pragma unroll
-                for (int m = 0; m < 2 * DT; ++m) read_v(m, cur);
+                for (int m = 0; m < 2 * DT; ++m) read_v(m, s0);
             }
-            // copies in flight, oldest first: tiles kt+1 .. kt+S-2.  Tile kt+1 has landed once only the newest
-            // S-3 tiles' copies are outstanding; the barrier publishes it and tells that every wave has taken
-            // what it needs of tile kt-1's stage, which the copy of tile kt+S-1 overwrites.
-            wait_vmcnt<(S - 3) * NL>();
-            __syncthreads();
-            issue(kt + S - 1, prv);
-            read_k(nxt);
-            const int valid = (int)(g.Sk - kt * 32) - 8 * h;   // this lane's key 16*b + e is real iff 16*b + e < valid
+            __builtin_amdgcn_sched_barrier(0);
+            auto next_score = [&](int kk) {
+                score_mfma(kk, nset);
+                __builtin_amdgcn_sched_barrier(0);        // the read takes the registers that the instruction has freed
+                read_k(kk, s2);
+                if (kk == 0) {
+                    issue_k(s0);
+                    if constexpr (PV) issue_v(s3);
+                }
+            };
+            const int valid = (int)(g.Sk - (int64_t)kt * 32) - 8 * h;   // this lane's key 16*b + e is real iff 16*b + e < valid
             auto masked = [&](int r) { return RAG && 16 * (r >> 3) + (r & 7) >= valid; };
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!PV) {
-                // units: 0 = tile maximum and the new running maximum, 1..4 = four exponentials each, 5 = the running sum
-                constexpr int NU = 6;
-                float m_old, m_use, sum;
+                // m_run is what the exponentials are taken against: a maximum, but not always the newest.  A tile whose sum
+                // against it stays below 2^20 in every lane is added as it is (l_run stays below 2^20 times the number of
+                // tiles, and is 1 or more from m_run's own term); only another one, the first among them, looks for its maximum, which
+                // takes m_run's place.  That saves the search in nearly every tile: 15 of 84 vector issue slots.
+                // Units: 0..7 = two exponentials each, 8 = the running sum.
+                constexpr int NU = 9;
+                float sum = 0.f;
                 auto unit = [&](int u) {
-                    if (u == 0) {
+                    if (u < NU - 1) {
+#pragma unroll
+                        for (int r = 2 * u; r < 2 * u + 2; ++r) {
+                            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[set][r], c, -m_run));
+                            sum = r == 0 ? p : sum + p;
+                        }
+                        pin(sum);
+                    } else if (!RAG && __builtin_amdgcn_ballot_w64(!(sum < 0x1p20f)) == 0) {
+                        l_run += sum;
+                    } else {
                         float sm = -__builtin_inff();
 #pragma unroll
                         for (int r = 0; r < 16; ++r) sm = __builtin_fmaxf(sm, masked(r) ? -__builtin_inff() : s[set][r]);
-                        m_old = m_run;
+                        const float m_old = m_run;
                         m_run = __builtin_fmaxf(m_run, sm * c);
-                        m_use = m_run == -__builtin_inff() ? 0.f : m_run;
+                        const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;
                         sum = 0.f;
-                        pin(m_use);
-                    } else if (u < 5) {
 #pragma unroll
-                        for (int r = 4 * (u - 1); r < 4 * u; ++r) {
+                        for (int r = 0; r < 16; ++r) {
                             float arg = __builtin_fmaf(s[set][r], c, -m_use);
                             if (masked(r)) arg = -__builtin_inff();   // also when c is 0
                             sum += __builtin_amdgcn_exp2f(arg);
                         }
-                        pin(sum);
-                    } else {
                         l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
-                        pin(l_run);
                     }
                 };
 #pragma unroll
                 for (int m = 0; m < NK; ++m) {
-                    score_mfma(m, nset);
+                    next_score(m);
 #pragma unroll
-                    for (int x = m * NU / NK; x < (m + 1) * NU / NK; ++x) unit(x);
+                    for (int x = m * NU / NK; x < (m + 1) * NU / NK; ++x)
+                        if (!RAG || x == NU - 1) unit(x);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
-                // The tile is two blocks of 16 keys, this lane's half of each.  With a = log2 of the
-                // probability, the block exponent is the integer part of the largest a (the quantizer's
-                // floor(log2 max)) and the mantissas are round(2^(a - E + w - 2)): the arithmetic of mx_quantize
-                // on P.  exp2 grows with the score, so the maximum is taken over the scores themselves.
-                // Units: 0 = half-block maxima, their exchange with the other lane half, the exponents;
-                // 1..8 = two elements each, packed into their operand register.
+                // The tile is two blocks of 16 keys, this lane's half of each: the arithmetic of mx_quantize on P, the
+                // mantissas being round(2^(a - E + w - 2)).  Units: 0 = half-block maxima, the exponents; 1..8 = two elements
+                // each, packed into their operand register.
                 constexpr int NU = 9;
                 float off[2];
-                int sh[2];
+                int t[2];
                 auto unit = [&](int u) {
                     if (u == 0) {
-                        float mb[2];
+                        float sm[2];
 #pragma unroll
                         for (int b = 0; b < 2; ++b) {
-                            float sm = -__builtin_inff();
+                            sm[b] = -__builtin_inff();
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) sm = __builtin_fmaxf(sm, masked(8 * b + e) ? -__builtin_inff() : s[set][8 * b + e]);
-                            // both lane halves get the larger of the two halves' values
-                            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sm), __float_as_uint(sm), false, false);
-                            sm = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-                            float m = __builtin_fmaf(sm, c, -mrow);
-                            // two-row blocks: queries 2t and 2t+1 (neighbouring lanes) share the exponent, the larger
-                            // of the two log-probabilities; one-row blocks add -inf to the neighbour's and keep their own
-                            m = __builtin_fmaxf(m, g.pair + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-                                                                0, __builtin_bit_cast(int, m), 0xB1, 0xF, 0xF, true)));
-                            mb[b] = m;
+                            for (int e = 0; e < 8; ++e) sm[b] = __builtin_fmaxf(sm[b], masked(8 * b + e) ? -__builtin_inff() : s[set][8 * b + e]);
                         }
-#pragma unroll
-                        for (int b = 0; b < 2; ++b) {
-                            // blocks of 32: the tile's two runs of 16 keys are one block (the same trick: + 0 or + -inf)
-                            float m = __builtin_fmaxf(mb[b], g.wide + mb[b ^ 1]);
-                            m = __builtin_fmaxf(m, -200.f);                   // also for all keys masked, or c = 0 with them
-                            int E = (int)__builtin_floorf(m);
-                            E = E < -g.bias_p ? -g.bias_p : E;
-                            E = E > g.emax_p ? g.emax_p : E;
-                            sh[b] = wm2 - E;
-                            off[b] = (float)sh[b] - mrow;
-                            pin(off[b]);
-                        }
+                        block_scales(g, sm[0], sm[1], c, mrow, wm2, off, t);
+                        pin(off[0]);
+                        pin(off[1]);
                     } else {
                         const int b = (u - 1) >> 2, d = (u - 1) & 3;
                         float el[2];
@@ -312,7 +370,7 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
                             const float sc = __builtin_amdgcn_exp2f(arg);
                             float v = RND == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
                             v = __builtin_fminf(v, qmax);                     // probabilities are not negative
-                            el[x] = __builtin_ldexpf(v, -sh[b]);              // an exact bfloat16 number
+                            el[x] = __builtin_ldexpf(v, t[b]);                // an exact bfloat16 number
                         }
                         // the upper halves of two fp32 values
                         pf[set][b][d] = (int)__builtin_amdgcn_perm(__float_as_uint(el[1]), __float_as_uint(el[0]), 0x07060302u);
@@ -324,7 +382,7 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int m = 0; m < NK; ++m) {
-                        score_mfma(m, nset);
+                        next_score(m);
 #pragma unroll
                         for (int x = 1 + m * (NU - 1) / NK; x < 1 + (m + 1) * (NU - 1) / NK; ++x) unit(x);
                         __builtin_amdgcn_sched_barrier(0);
@@ -342,10 +400,11 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
                 for (int m = 0; m < NM; ++m) {
                     if ((m + 1) * NO / NM > mo) {
                         out_mfma(mo, nset);
-                        read_v(mo, cur);
+                        __builtin_amdgcn_sched_barrier(0);
+                        read_v(mo, s0);
                         ++mo;
                     } else {
-                        score_mfma(mk, nset);
+                        next_score(mk);
                         ++mk;
                     }
 #pragma unroll
@@ -363,24 +422,39 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
                 for (int dt = 0; dt < DT; ++dt) vf[dt][b] = v4i{0, 0, 0, 0};
             }
         }
+        // tile step j copies K of tile j+5 and V of tile j+3; the steps before the first one, and K of two tiles ahead of them
+        issue_k(0);
+        issue_k(STAGE);
 #pragma unroll
-        for (int st = 0; st < S - 1; ++st) issue(st, st);
-        wait_vmcnt<(S - 2) * NL>();
-        __syncthreads();
-        read_k(0);
-#pragma unroll
-        for (int m = 0; m < NK; ++m) score_mfma(m, std::integral_constant<int, 0>{});
-        // tiles in pairs (the register sets alternate); the last one or two tiles take the masking form
-        int64_t kt = 0;
-        int cur = 0;
-        auto advance = [&]() { cur = cur + 1 == S ? 0 : cur + 1; ++kt; };
-        while (kt + 2 < g.nt) {
-            body(kt, cur, std::integral_constant<int, 0>{}, std::false_type{}); advance();
-            body(kt, cur, std::integral_constant<int, 1>{}, std::false_type{}); advance();
+        for (int st = 0; st < 3; ++st) {
+            issue_k((st + 2) * STAGE);
+            if constexpr (PV) issue_v(st * STAGE);
         }
-        body(kt, cur, std::integral_constant<int, 0>{}, std::true_type{}); advance();
-        if (kt < g.nt) {
-            body(kt, cur, std::integral_constant<int, 1>{}, std::true_type{}); advance();
+        wait_vmcnt<3 * NL>();
+        step_barrier<0>();
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) read_k(kk, 0);
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) {
+            score_mfma(kk, std::integral_constant<int, 0>{});
+            read_k(kk, STAGE);
+        }
+        wait_lgkmcnt<NK>();                               // tile 0 has been read
+        __builtin_amdgcn_sched_barrier(0);
+        // tiles in pairs (the register sets alternate); the last one or two tiles take the masking form.  slot[x]: where tile
+        // kt+x lies
+        int kt = 0;
+        uint32_t slot[S] = {0, STAGE, 2 * STAGE, 3 * STAGE, 4 * STAGE};
+        while (kt + 2 < nt) {
+            body(kt, slot[0], slot[2], slot[3], std::integral_constant<int, 0>{}, std::false_type{});
+            body(kt + 1, slot[1], slot[3], slot[4], std::integral_constant<int, 1>{}, std::false_type{});
+            kt += 2;
+            const uint32_t t0 = slot[0], t1 = slot[1];
+            slot[0] = slot[2]; slot[1] = slot[3]; slot[2] = slot[4]; slot[3] = t0; slot[4] = t1;
+        }
+        body(kt, slot[0], slot[2], slot[3], std::integral_constant<int, 0>{}, std::true_type{});
+        if (kt + 1 < nt) {
+            body(kt + 1, slot[1], slot[3], slot[4], std::integral_constant<int, 1>{}, std::true_type{});
             if constexpr (PV && LAG) {
 #pragma unroll
                 for (int m = 0; m < 2 * DT; ++m) out_mfma(m, std::integral_constant<int, 1>{});
@@ -559,36 +633,26 @@ __global__ __launch_bounds__(kSplitWaves * 64) void attention_split_kernel(AttnA
         auto tile = [&](auto ragc) {
             constexpr bool RAG = decltype(ragc)::value;
             auto masked = [&](int r) { return RAG && 16 * (r >> 3) + (r & 7) >= valid; };
-            float mb[2];
+            float sm[2], off[2];
+            int t[2];
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                float sm = -__builtin_inff();
+                sm[b] = -__builtin_inff();
 #pragma unroll
-                for (int e = 0; e < 8; ++e) sm = __builtin_fmaxf(sm, masked(8 * b + e) ? -__builtin_inff() : s[8 * b + e]);
-                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sm), __float_as_uint(sm), false, false);
-                sm = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-                const float m = __builtin_fmaf(sm, c, -mrow);
-                mb[b] = __builtin_fmaxf(m, g.pair + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-                                               0, __builtin_bit_cast(int, m), 0xB1, 0xF, 0xF, true)));
+                for (int e = 0; e < 8; ++e) sm[b] = __builtin_fmaxf(sm[b], masked(8 * b + e) ? -__builtin_inff() : s[8 * b + e]);
             }
+            block_scales(g, sm[0], sm[1], c, mrow, wm2, off, t);
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                float m = __builtin_fmaxf(mb[b], g.wide + mb[b ^ 1]);
-                m = __builtin_fmaxf(m, -200.f);                       // also for all keys masked, or c = 0 with them
-                int E = (int)__builtin_floorf(m);
-                E = E < -g.bias_p ? -g.bias_p : E;
-                E = E > g.emax_p ? g.emax_p : E;
-                const int sh = wm2 - E;
-                const float off = (float)sh - mrow;
                 float el[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    float arg = __builtin_fmaf(s[8 * b + e], c, off);
+                    float arg = __builtin_fmaf(s[8 * b + e], c, off[b]);
                     if (masked(8 * b + e)) arg = -__builtin_inff();
                     const float sc = __builtin_amdgcn_exp2f(arg);
                     float v = RND == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
                     v = __builtin_fminf(v, qmax);                     // probabilities are not negative
-                    el[e] = __builtin_ldexpf(v, -sh);                 // an exact bfloat16 number
+                    el[e] = __builtin_ldexpf(v, t[b]);                // an exact bfloat16 number
                 }
 #pragma unroll
                 for (int d = 0; d < 4; ++d)                           // the upper halves of two fp32 values
@@ -735,6 +799,7 @@ extern "C" mx_status mx_attention(int64_t batch, int64_t Sq, int64_t Sk, int64_t
     g.vec = (((uintptr_t)O & 15) == 0 && ldo % 4 == 0 && o_batch_stride % 4 == 0) ? 1 : 0;
     g.pair = fp.block_rows == 2 ? 0.f : -__builtin_inff();
     g.wide = fp.block == 32 ? 0.f : -__builtin_inff();
+    g.join = fp.block_rows == 2 || fp.block == 32;
     const int dt = (int)ceil_div(D, 32);
     hipStream_t st = (hipStream_t)stream;
     if (gq.ksteps == 2)

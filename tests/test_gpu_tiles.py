@@ -441,6 +441,27 @@ def test_attention_of_128_queries_per_workgroup(heads, Sq, Sk, dim):
     run_attention(Q, K, V, (8, 7, 8, 6), dim ** -0.5, rows=(Sq - 34, Sq), e_pv=4, **some)
 
 
+@pytest.mark.parametrize("dim", [32, 64, 128])
+@pytest.mark.parametrize("tops", [
+    (0, 5, 40, 42, 61, 62, 100, 60, 130, 110, 0),      # rises below and past 20 binades, in odd and even tiles, then falls
+    (130, 0, 0, 0, 120, 0, 0, 100, 0, 0, 149),         # a first tile above all until the last, masked, one
+    (-90, -110, -71, -100, -69, -50, -49, -48, -29, -28, -27),
+])
+def test_attention_row_maximum_that_moves(tops, dim):
+    """128 queries per workgroup: sums against an older maximum while a tile stays within 2^20 of it, against its own
+    otherwise.  tops: the largest score of each key tile in binades, the two signs of the scale."""
+    heads, Sq, Sk = 100, 258, 336
+    rng = np.random.default_rng(dim + abs(tops[1]))
+    u = np.full(dim, dim ** -0.5, np.float32)
+    Q = (u + 0.02 * rng.standard_normal((heads, Sq, dim))).astype(np.float32)
+    top = np.repeat(np.array(tops, np.float32), 32)[:Sk] - 8 * rng.random((heads, Sk)).astype(np.float32)
+    K = (np.log(2) / 0.25 * top[:, :, None] * u + 0.1 * rng.standard_normal((heads, Sk, dim))).astype(np.float32)
+    V = rng.standard_normal((heads, Sk, dim)).astype(np.float32)
+    some = dict(heads_checked=[0, heads - 1], max_maybe=5e-2)
+    run_attention(Q, K, V, (8, 8, 6, 5), 0.25, rows=(Sq - 34, Sq), **some)
+    run_attention(Q, -K, V, (8, 8, 8, 5), -0.25, rows=(0, 34), block_rows=2, **some)
+
+
 @pytest.mark.parametrize("heads,Sq,Sk,dim,R", [(100, 258, 352, 128, 1), (100, 258, 384, 64, 2), (100, 258, 352, 96, 2), (500, 258, 352, 64, 1),
                                                (100, 258, 64, 32, 1)])
 def test_attention_of_128_queries_in_blocks_of_32(heads, Sq, Sk, dim, R):
