@@ -513,13 +513,39 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
 // above.
 // ------------------------------------------------------------------------------------------------
 constexpr int kSplitWaves = 8;
+constexpr int kSplitPitch = 65;                         // floats per result register of 64 lanes, skewed over the banks
+
+// The waves' partial results, one tile of 32 columns after the other: every output is one thread's sum over the waves.  Two
+// buffers: the next tile is written while slower threads still read this one.
+template <int DTW>
+__device__ __forceinline__ void add_waves(const AttnArgs& g, const v16f (&o)[DTW], float* red, int wave, int lane, int64_t bz, int64_t qt,
+                                          int part) {
+    constexpr int NW = kSplitWaves, PITCH = kSplitPitch;
+    float* O = g.O + bz * g.o_batch_stride;
+#pragma unroll
+    for (int dt = 0; dt < DTW; ++dt) {
+        float* buf = red + (dt & 1) * NW * 16 * PITCH;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) buf[(wave * 16 + r) * PITCH + lane] = o[dt][r];
+        __syncthreads();
+        for (int t = threadIdx.x; t < 1024; t += NW * 64) {
+            // register r of lane 32h + i is element 8*(r/4) + 4h + r%4 of the tile's 32, query i
+            const int q = t >> 5, e = t & 31, r = 4 * (e >> 3) + (e & 3), l = 8 * (e & 4) + q;
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sum += buf[(w * 16 + r) * PITCH + l];
+            const int64_t row = qt * 32 + q;
+            const int d = (part * DTW + dt) * 32 + e;
+            if (row < g.Sq && d < (int)g.D) O[row * g.ldo + d] = sum;
+        }
+    }
+}
 
 template <int KS, int DTW, int RND>
 __global__ __launch_bounds__(kSplitWaves * 64) void attention_split_kernel(AttnArgs g) {
     constexpr int NW = kSplitWaves, NK = 2 * KS;
-    constexpr int PITCH = 65;                           // floats per result register of 64 lanes, skewed over the banks
     __shared__ float stat[2][NW][64];
-    extern __shared__ __attribute__((aligned(16))) float red[];       // [2][NW][16][PITCH]
+    extern __shared__ __attribute__((aligned(16))) float red[];       // [1 or 2][NW][16][kSplitPitch]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = lane & 31, h = lane >> 5;
     // an XCD gets one contiguous range of (head, query tile, column part): those of a head share its K and V in the L2
@@ -668,44 +694,204 @@ __global__ __launch_bounds__(kSplitWaves * 64) void attention_split_kernel(AttnA
         fetch_v(kt + NW);
     }
 
-    // the waves' partial results, one tile of 32 columns after the other: every output is one thread's sum over the
-    // waves.  Two buffers: the next tile is written while slower threads still read this one.
-    float* O = g.O + bz * g.o_batch_stride;
-#pragma unroll
-    for (int dt = 0; dt < DTW; ++dt) {
-        float* buf = red + (dt & 1) * NW * 16 * PITCH;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) buf[(wave * 16 + r) * PITCH + lane] = o[dt][r];
-        __syncthreads();
-        for (int t = threadIdx.x; t < 1024; t += NW * 64) {
-            // register r of lane 32h + i is element 8*(r/4) + 4h + r%4 of the tile's 32, query i
-            const int q = t >> 5, e = t & 31, r = 4 * (e >> 3) + (e & 3), l = 8 * (e & 4) + q;
-            float sum = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) sum += buf[(w * 16 + r) * PITCH + l];
-            const int64_t row = qt * 32 + q;
-            const int d = (part * DTW + dt) * 32 + e;
-            if (row < g.Sq && d < (int)g.D) O[row * g.ldo + d] = sum;
-        }
-    }
+    add_waves<DTW>(g, o, red, wave, lane, bz, qt, part);
 }
 
-template <int KS, int DTW>
-mx_status launch_attention_split(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
-    constexpr int smem = (DTW == 1 ? 1 : 2) * kSplitWaves * 16 * 65 * 4;
-    auto k0 = attention_split_kernel<KS, DTW, MX_RNE>;
-    auto k1 = attention_split_kernel<KS, DTW, MX_RTZ>;
-    static std::atomic<uint64_t> done0{0}, done1{0};
-    if (!allow_dynamic_lds((const void*)k0, smem, done0) || !allow_dynamic_lds((const void*)k1, smem, done1))
-        return MX_ERR_DEVICE;
+// ------------------------------------------------------------------------------------------------
+// Few queries and 17 to 64 key tiles: the split kernel with the scores kept.  A workgroup of eight waves owns 32 queries of one
+// head and 32*DTW columns of the result, its waves take the key tiles round-robin, at most T each, and hold the scores of
+// all of them in registers between the row statistics and the second product: K is read and multiplied once.
+//
+// Bound: vector issue, about 900 cycles per key tile of which an exponential is 8, and the K and V^T of a head that one
+// compute unit loads.  With the scores taken again in a second sweep 32 heads x 1 query x 1936 keys x 128 took 16.2 us,
+// 13.3 this way, 32 x 100 x 2048 x 128 21.7 and 17.2, 32 x 512 x 2048 x 128 45.9 and 32.4.
+// K comes through a ring of two tiles per wave, V^T through one of RV tiles whose first loads go out under the exchange of
+// the row statistics.  Loads past the last key tile are out of the buffer's range: they read zeros and touch no memory, so none
+// sits under a condition.
+// ------------------------------------------------------------------------------------------------
+template <int KS, int DTW, int T, int RND>
+__global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(AttnArgs g) {
+    constexpr int NW = kSplitWaves, NK = 2 * KS, RV = DTW == 1 ? 4 : T < 8 ? 2 : 1, RK = 2;
+    __shared__ float stat[2][NW][64];
+    extern __shared__ __attribute__((aligned(16))) float red[];       // [1 or 2][NW][16][kSplitPitch]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = lane & 31, h = lane >> 5;
+    // an XCD gets one contiguous range of (head, query tile, column part): those of a head share its K and V in the L2
+    const int64_t per_xcd = (g.total + 7) / 8;
+    const int64_t lin = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per_xcd || lin >= g.total) return;          // whole workgroup, before any barrier
+    const int part = (int)(lin % g.parts);
+    const int64_t tq = lin / g.parts, bz = tq / g.tiles_q, qt = tq - bz * g.tiles_q;
+    const int nt = (int)g.nt, v_row = (int)g.v_ksteps * kBfUnitBytes;
+    const BufRsrc rK = make_rsrc(g.K + bz * g.matrixK, (uint32_t)(nt * KS * kBfUnitBytes));
+    const BufRsrc rV = make_rsrc(g.V + bz * g.matrixV + (int64_t)part * DTW * v_row, (uint32_t)(DTW * v_row));
+    constexpr uint32_t kNowhere = 0x40000000u;          // past the end of either buffer
+    const uint32_t lane16 = lane * 16;
+
+    // The wave's Q fragments and the permuted K rows: as in attention_bf16_kernel.  A scale of zero is a Q of zeros, so that a
+    // masked score of -inf stays one.
+    const int flip = g.c < 0.f ? (int)0x80008000u : 0, keep = g.c == 0.f ? 0 : -1;
+    const float c = g.c == 0.f ? 1.f : __builtin_fabsf(g.c);
+    v4i qf[NK];
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+        qf[kk] = *reinterpret_cast<const v4i*>(g.Q + bz * g.matrixQ + (qt * KS + (kk >> 1)) * kBfUnitBytes + (kk & 1) * 1024 + lane16);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) qf[kk][d] = (qf[kk][d] ^ flip) & keep;
+    }
+    const int sig = (i & 0x13) | ((i & 4) << 1) | ((i & 8) >> 1);
+    const uint32_t koff = (32 * h + sig) * 16;
+
+    v4i kf[RK][NK];
+    auto fetch_k = [&](int slot, int t) {
+        const int kt = wave + t * NW;
+        const uint32_t at = koff + (kt < nt ? (uint32_t)(kt * KS * kBfUnitBytes) : kNowhere);
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk)
+            kf[slot][kk] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rK, at + kk * 1024, 0, 0));
+    };
+    v4i vf[RV][DTW][2];
+    auto fetch_v = [&](int slot, int t) {
+        const int kt = wave + t * NW;
+        const uint32_t at = lane16 + (kt < nt ? (uint32_t)(kt * kBfUnitBytes) : kNowhere);
+#pragma unroll
+        for (int dt = 0; dt < DTW; ++dt)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                vf[slot][dt][b] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rV, at + (uint32_t)(dt * v_row) + b * 1024, 0, 0));
+    };
+    // only the last key tile can hold keys past Sk; this lane's key 16*b + e is real iff 16*b + e < valid
+    const bool ragged = (g.Sk & 31) != 0;
+    const int valid = (int)(g.Sk - (g.nt - 1) * 32) - 8 * h;
+
+    v16f s[T];
+    float m_run = -__builtin_inff(), l_run = 0.f;
+#pragma unroll
+    for (int t = 0; t < RK; ++t) fetch_k(t, t);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int kt = wave + t * NW;
+        if (kt >= nt) break;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk)
+            s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, kf[t % RK][kk]), __builtin_bit_cast(v8bf, qf[kk]), s[t], 0, 0, 0);
+        if (t + RK < T) fetch_k(t % RK, t + RK);
+        if (ragged && kt == nt - 1) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[t][r] = 16 * (r >> 3) + (r & 7) >= valid ? -__builtin_inff() : s[t][r];
+        }
+        // the sum against an older maximum while it stays below 2^20 in every lane, as in attention_bf16_kernel
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], c, -m_run));
+        if (t > 0 && __builtin_amdgcn_ballot_w64(!(sum < 0x1p20f)) == 0) {
+            l_run += sum;
+        } else {
+            float sm = s[t][0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) sm = __builtin_fmaxf(sm, s[t][r]);
+            const float m_old = m_run;
+            m_run = __builtin_fmaxf(m_run, sm * c);
+            const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;      // no key in this lane's tiles so far
+            sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], c, -m_use));
+            l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
+        }
+    }
+
+    // row statistics: the waves, and the two lane halves of each, hold disjoint keys of the same query
+#pragma unroll
+    for (int t = 0; t < RV; ++t) fetch_v(t, t);
+    stat[0][wave][lane] = m_run;
+    stat[1][wave][lane] = l_run;
+    __syncthreads();
+    float mrow;
+    {
+        float mf = -__builtin_inff();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mf = __builtin_fmaxf(mf, __builtin_fmaxf(stat[0][w][i], stat[0][w][32 + i]));
+        float l = 0.f;                                  // mf is finite: there is at least one key
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            l += stat[1][w][i] * __builtin_amdgcn_exp2f(stat[0][w][i] - mf);
+            l += stat[1][w][32 + i] * __builtin_amdgcn_exp2f(stat[0][w][32 + i] - mf);
+        }
+        mrow = mf + __builtin_amdgcn_logf(l);           // the same value in both halves and in every wave
+    }
+
+    v16f o[DTW];
+#pragma unroll
+    for (int dt = 0; dt < DTW; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+    const float qmax = (float)((1 << (g.wp - 1)) - 1);
+    const int wm2 = g.wp - 2;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        if (wave + t * NW >= nt) break;
+        float sm[2], off[2];
+        int te[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            sm[b] = s[t][8 * b];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) sm[b] = __builtin_fmaxf(sm[b], s[t][8 * b + e]);
+        }
+        block_scales(g, sm[0], sm[1], c, mrow, wm2, off, te);
+        v4i pf[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            float el[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float sc = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][8 * b + e], c, off[b]));
+                float v = RND == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
+                v = __builtin_fminf(v, qmax);                     // probabilities are not negative
+                el[e] = __builtin_ldexpf(v, te[b]);               // an exact bfloat16 number
+            }
+#pragma unroll
+            for (int d = 0; d < 4; ++d)                           // the upper halves of two fp32 values
+                pf[b][d] = (int)__builtin_amdgcn_perm(__float_as_uint(el[2 * d + 1]), __float_as_uint(el[2 * d]), 0x07060302u);
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int dt = 0; dt < DTW; ++dt)
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, vf[t % RV][dt][b]), __builtin_bit_cast(v8bf, pf[b]), o[dt], 0, 0, 0);
+        if (t + RV < T) fetch_v(t % RV, t + RV);
+    }
+    add_waves<DTW>(g, o, red, wave, lane, bz, qt, part);
+}
+
+// One of the kernels for few queries: a workgroup per 32 queries and column part.
+mx_status launch_few(AttnArgs& g, void (*kern)(AttnArgs), std::atomic<uint64_t>& done, int buffers, int64_t batch, int parts, hipStream_t st) {
+    const int smem = buffers * kSplitWaves * 16 * kSplitPitch * 4;
+    if (!allow_dynamic_lds((const void*)kern, smem, done)) return MX_ERR_DEVICE;
     g.tiles_q = g.q_tiles;
     g.parts = parts;
     g.total = g.tiles_q * batch * parts;
     if (g.total > 0x7fffff00LL) return MX_ERR_UNSUPPORTED;
     dim3 grid((unsigned)(ceil_div(g.total, 8) * 8));
-    hipLaunchKernelGGL(rnd == MX_RNE ? k0 : k1, grid, dim3(kSplitWaves * 64), smem, st, g);
+    hipLaunchKernelGGL(kern, grid, dim3(kSplitWaves * 64), smem, st, g);
     MX_HIP_LAUNCH_CHECK();
     return MX_OK;
+}
+
+template <int KS, int DTW>
+mx_status launch_attention_split(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
+    static std::atomic<uint64_t> done[2];
+    auto kern = rnd == MX_RNE ? attention_split_kernel<KS, DTW, MX_RNE> : attention_split_kernel<KS, DTW, MX_RTZ>;
+    return launch_few(g, kern, done[rnd == MX_RNE], DTW == 1 ? 1 : 2, batch, parts, st);
+}
+
+template <int KS, int DTW, int T>
+mx_status launch_attention_kept(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
+    static std::atomic<uint64_t> done[2];
+    auto kern = rnd == MX_RNE ? attention_kept_kernel<KS, DTW, T, MX_RNE> : attention_kept_kernel<KS, DTW, T, MX_RTZ>;
+    return launch_few(g, kern, done[rnd == MX_RNE], DTW == 1 ? 1 : 2, batch, parts, st);
 }
 
 template <int KS, int DT, bool LAG>
@@ -726,6 +912,21 @@ mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) 
     return MX_OK;
 }
 
+template <int KS, int DTW>
+mx_status pick_kept(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
+    if constexpr (KS == 4)
+        if (g.nt <= 4 * kSplitWaves) return launch_attention_kept<KS, DTW, 4>(g, batch, parts, rnd, st);
+    return launch_attention_kept<KS, DTW, 8>(g, batch, parts, rnd, st);
+}
+
+// Heads of more than 64 elements, see pick_attention.
+bool keeps_scores(const AttnArgs& g, int64_t groups, int64_t batch) {
+    const int64_t rounds = ceil_div(groups, 256);
+    if (g.nt <= 16 || g.nt > 64) return false;
+    if (rounds <= 3) return rounds <= 2 || g.nt >= 24;
+    return rounds <= 5 && g.nt >= 40 && ceil_div(g.Sq, 128) * batch > 256;
+}
+
 // The split kernel takes one round of workgroups in a time that hardly depends on the number of keys while they are few,
 // the 128-query workgroups one tile of keys at a time for as long whether there is one of them or 256: with one round
 // the split kernel is the faster one (8 heads x 512 queries x 2048 keys x 128: 70 us, 22 us split) from the second key tile
@@ -735,6 +936,13 @@ mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) 
 // With room for it every 32 columns of the result get a workgroup of their own, which
 // repeats the scores and saves registers, V and the sum (32 heads, one query, 1936 keys: 16.8 against 20.0 us); with more
 // than one such workgroup per compute unit that costs more than it saves (32 x 100 x 2048 x 128: 35 against 22 us).
+// The scores are kept (attention_kept_kernel) from 17 key tiles on where heads have more than 64 elements: in one round of
+// workgroups always (us, scores taken twice and kept: 17 tiles 10.8 and 10.0, 32 tiles 14.9 and 12.5, 54 tiles 18.8 and 15.6), in two as
+// well (297 workgroups x 17 tiles 19.8 and 17.9, 360 x 62 40.3 and 31.6; up to 16 tiles, 405 x 12, 16.7 and 17.3), in three from
+// 24 tiles on against the 128-query workgroups (744 x 41 43.1 and 34.3, 540 x 30 33.9 and 30.5, 713 x 21 27.6 and 27.9), in four and five
+// from 40 on if there are more than 256 of those (988 x 42 61.5 and 44.3, 1088 x 47 67.4 and 61.2; 961 x 30 34.9 and 36.7, six
+// rounds 1335 x 47 69.3 and 72.4).  Heads of up to 64 elements in one round from 33 tiles on (209 x 46 12.2 and 11.3; 232 x 17
+// 7.1 and 7.9): with fewer, two workgroups of the other form share a compute unit.
 // The second product of the 128-query form runs one key tile behind its scores (LAG), but not for one or two key tiles, where
 // the additional round of it costs more (54 heads x 1828 x 64 x 48: 13.1 and 14.7 us, 32 x 2000 x 64 x 128 2 percent), nor
 // for heads of 33 to 64 elements once a compute unit has more than four workgroups to take: the lag needs 148 registers for
@@ -743,6 +951,10 @@ mx_status launch_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) 
 template <int KS, int DT>
 mx_status pick_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     const int64_t groups = g.q_tiles * batch;
+    if (KS == 2 ? groups <= 256 && g.nt > 32 && g.nt <= 64 : keeps_scores(g, groups, batch)) {
+        if (groups * DT <= 256) return pick_kept<KS, 1>(g, batch, DT, rnd, st);
+        return pick_kept<KS, DT>(g, batch, 1, rnd, st);
+    }
     if (groups * DT <= 256) return launch_attention_split<KS, 1>(g, batch, DT, rnd, st);
     const int64_t rounds = ceil_div(groups, DT <= 2 ? 512 : 256);      // two workgroups of at most 128 registers share a compute unit
     if (groups <= 768 && g.nt >= (rounds == 1 ? 2 : rounds == 2 ? 10 : 40))

@@ -131,6 +131,19 @@ def test_attention_forms(heads, Sq, Sk, dim):
         run_attention(Q, K, V, (8, 7, 6, 5), scale, heads_checked=[0, heads - 1], rounding=rounding, block_rows=rows)
 
 
+@pytest.mark.parametrize("dim", [32, 64, 80, 128])
+@pytest.mark.parametrize("heads,Sq,Sk", [(3, 7, 528), (3, 33, 1024), (2, 40, 1040), (2, 1, 2048), (2, 5, 2064), (12, 702, 784),
+                                         (12, 702, 1200), (24, 702, 768), (40, 800, 1296)])
+def test_attention_with_kept_scores(heads, Sq, Sk, dim):
+    """17 to 64 key tiles and one more, waves with all their tiles, with fewer and with none, a ragged last one; a workgroup per
+    32 columns and per 32 queries, one to four rounds of them; both rounding modes, two-row blocks, a scale below and of zero."""
+    Q, K, V = long_attention_inputs(heads, Sq, Sk, dim)
+    some = dict(heads_checked=[0, heads - 1], rows=(max(0, Sq - 34), Sq))
+    run_attention(Q, K, V, (8, 7, 6, 5), dim ** -0.5, **some)
+    run_attention(Q, K, V, (7, 8, 5, 6), -0.7 * dim ** -0.5, rounding=mx.MX_RTZ, block_rows=2 if Sq % 2 == 0 else 1, **some)
+    run_attention(Q, K, V, (8, 7, 8, 6), 0.0, max_maybe=3.0, **some)     # 1 / Sk may be a power of two
+
+
 def test_fragment_product_past_one_grid_dimension():
     """131072 x 131072 results, 64 GiB: 2^24 tiles of 32 x 32, more than the work items of one grid dimension hold as
     workgroups of 256.  Every element is written, sampled rows and columns (first and last among them) are right."""

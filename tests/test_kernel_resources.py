@@ -98,3 +98,9 @@ def test_waves_of_the_decode_kernel_are_those_its_split_is_chosen_by(kernel_note
         assert waves_per_simd(vgprs) >= (4 if registers <= 128 else 3 if registers <= 168 else 2), (name, vgprs)
         seen += 1
     assert seen == 3 * 7 * 4
+
+
+def test_attention_with_kept_scores_stays_in_registers(scratch_bytes):
+    """Up to eight tiles of scores per wave, 128 registers of the 256."""
+    kernels = [n for n in scratch_bytes if re.search(r"\battention_kept_kernel<", n)]
+    assert len(kernels) == 16 and not [n for n in kernels if scratch_bytes[n]]
