@@ -10,7 +10,7 @@
 //
 // Work split: the path is bound by one pass over the packed weights, so every compute unit has to stream.  A workgroup
 // owns a few neighbouring column groups of 32 (NW) and a K slice, which KS waves per column group divide among them; it
-// quantizes its own slice of the activations into LDS, every wave keeps a ring of weight records in flight, and the KS
+// quantizes its own slice of the activations into LDS, every wave keeps one to four weight records in flight, and the KS
 // partial tiles are added through LDS in wave order.  With more than one K slice the partial sums go to the caller's
 // workspace and the workgroup that arrives last at the columns' counter adds them in slice order, so the result does
 // not depend on the order of arrival.
@@ -51,12 +51,15 @@ struct DecodeArgs {
     int32_t eadj;            // -bias - (wa-2) - (wb-2)
 };
 
-// Weight records a wave keeps in flight: it requests most of its part before the activations are quantized, so the weights
-// stream while the workgroup prepares the other operand.  They live in registers, which are what bounds the waves of a
-// compute unit: 16 with blocks of 16 and of 32, but for the widest records.
+// Weight records a wave keeps in flight: about eight dwords a lane, requested once its activations are quantized.  More of
+// them, or earlier ones, only stand in the way of the activations, which every workgroup waits for first: with five records
+// requested ahead of the quantizer 8 rows by 8 and 4 bits, blocks of 16, 5120 -> 5120, 5120 -> 13824 and 13824 -> 5120 took
+// 9.9, 14.9 and 15.8 us, with two ahead of it 9.0, 13.9 and 14.9, with two after it 8.9, 13.5 and 14.5 (three 9.1, 14.1, 14.3,
+// one 8.9, 14.7, 15.4); 5 rows by 6 and 5 bits, blocks of 32, 4096 -> 4096, 4096 -> 11008 and 11008 -> 4096 five 8.6, 13.0 and 13.1, two
+// 7.9, 12.5 and 11.7, one 7.4, 12.4 and 11.0.
 constexpr int ring_depth(int wb, int block) {
-    const int dw = block * wb / 16 + 1, most = block <= 32 ? 40 / dw : 96 / dw, least = block <= 32 ? 3 : 2;
-    return most >= 5 ? 5 : most < least ? least : most;
+    const int dw = block * wb / 16;
+    return dw <= 2 ? 4 : dw <= 4 ? 2 : 1;
 }
 constexpr int waves_per_simd(int wb, int block) {
     const int regs = ring_depth(wb, block) * (block * wb / 16 + 1) + (block == 16 ? 65 : block == 32 ? 78 : 110);
@@ -117,12 +120,12 @@ void linear_splitk_kernel(DecodeArgs a) {
     // ---- activations of this slice: fp32 -> MXInt (the arithmetic of mx_quantize) -> int8 in LDS.
     // One item is eight consecutive elements of a row, a half block or a part of one; consecutive lanes take consecutive
     // items, so a block is B/8 neighbouring lanes and its maximum takes log2(B/8) DPP steps.  Loads return in the order of
-    // issue: the first items are requested before the ring of weights.
+    // issue: the weights are requested after them.
     {
         const int per_row = nc * 4 * B;                    // elements of a row in this slice
         const float qmax = (float)((1 << (a.wa - 1)) - 1);
         const int64_t k0 = (int64_t)c0 * 4 * B;
-        constexpr int XU = 4, XR = 2;                      // items per thread requested before the weights, and at a time after that
+        constexpr int XU = 4, XR = 2;                      // items per thread requested at first, and at a time after that
         constexpr float kMagic = 12582912.0f;              // 1.5 * 2^23: adding it rounds to an integer, ties to even
         // item -> (row, first element inside the slice), advanced without divisions
         const int step_m = (8 * T) / per_row, step_e = 8 * T - step_m * per_row;
@@ -189,8 +192,6 @@ void linear_splitk_kernel(DecodeArgs a) {
         float4 xv[XU][2];
         int mm[XU], ee[XU];
         load_items(xv, mm, ee);
-#pragma unroll
-        for (int u = 0; u < D; ++u) fetch(u, u);
         auto quantize = [&](auto rndc) {
 #pragma unroll
             for (int u = 0; u < XU; ++u)
@@ -208,6 +209,8 @@ void linear_splitk_kernel(DecodeArgs a) {
         if (a.rounding == MX_RNE) quantize(std::integral_constant<int, MX_RNE>{});
         else quantize(std::integral_constant<int, MX_RTZ>{});
     }
+#pragma unroll
+    for (int u = 0; u < D; ++u) fetch(u, u);
     const bool wide_wave = __builtin_amdgcn_ballot_w64(wide) != 0;
     if (lane == 0) wide_any[wave] = wide_wave;
     __syncthreads();

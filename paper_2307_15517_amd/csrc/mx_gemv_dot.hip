@@ -70,9 +70,7 @@ __global__ __launch_bounds__(NW * 64) void gemv_dot_kernel(DotArgs a) {
         buf_load_dwords<kDwB>(rB, off + lane * (kDwB * 4), pb[slot]);
         buf_load_dwords<1>(rB, off + 64 * (kDwB * 4) + i * 4, &eb[slot]);
     };
-    // Loads return in the order of issue, so whatever the workgroup needs first is requested first:
-    // the activations, then the ring of weights; the arithmetic on the activations then runs while
-    // the weights are in flight.
+    // The activations first, the weights once they are quantized (see kDotDepth).
     if (a.x != nullptr) {
         // fp32 activations -> MXInt (the arithmetic of mx_quantize) -> int8 in LDS.  One item is four
         // consecutive elements of a row, items of consecutive lanes are consecutive (a wave reads 1 KB
@@ -80,7 +78,7 @@ __global__ __launch_bounds__(NW * 64) void gemv_dot_kernel(DotArgs a) {
         // steps.  Every workgroup reads the same activations; each starts at a different sweep so that
         // they do not all ask the same cache channel at the same time.
         constexpr int T = NW * 64;
-        constexpr int XU = 8;                                   // items per thread requested before the weights
+        constexpr int XU = 8;                                   // items per thread requested at first
         const int kpad = chunks * 4 * B;                        // row length in LDS (slots past K hold zeros)
         const int sweeps = (kpad / 4 + T - 1) / T;
         const int n_it = MP * sweeps;
@@ -136,8 +134,6 @@ __global__ __launch_bounds__(NW * 64) void gemv_dot_kernel(DotArgs a) {
         for (int it = 0; it < XU; ++it)
             if (it < n_it) xv[it] = item_load(it);
 #pragma unroll
-        for (int u = 0; u < D; ++u) fetch(u, u);
-#pragma unroll
         for (int it = 0; it < XU; ++it)
             if (it < n_it) item_store(it, xv[it]);
         for (int it = XU; it < n_it; ++it) item_store(it, item_load(it));
@@ -171,9 +167,9 @@ __global__ __launch_bounds__(NW * 64) void gemv_dot_kernel(DotArgs a) {
             if (hh == 0) xe[m * chunks + c] = 0;
         }
     }
+    }
 #pragma unroll
     for (int u = 0; u < D; ++u) fetch(u, u);
-    }
     __syncthreads();
 
     float acc[MP];
@@ -247,9 +243,12 @@ __global__ __launch_bounds__(NW * 64) void gemv_dot_kernel(DotArgs a) {
     }
 }
 
-// Chunks of weights in flight per wave: five, and three or two where five do not fit the 128 registers of the 16-wave form
-// (records of 20 and more dwords per lane) and would be spilled to memory and read back for every chunk.
-template <int WB, int B, int NW> constexpr int kDotDepth = NW < 16 || Piece<WB, B>::kDw < 20 ? 5 : Piece<WB, B>::kDw < 24 ? 3 : 2;
+// Chunks of weights in flight per wave: about eight dwords a lane.  More of them, or ahead of the activations, keep the
+// workgroup from the activations it waits for first.  One row, 8 by 4 bits, blocks of 16, 5120 -> 5120, 5120 -> 13824 and 13824 ->
+// 5120: five ahead of the quantizer 6.7, 10.3 and 11.7 us, two ahead 5.6, 9.6 and 11.1, two after it 5.5, 9.9 and 10.6, one
+// 5.5, 10.6 and 12.8; blocks of 32, 4096 -> 11008 by 4 bits and 11008 -> 4096 by 5 bits: five 8.9 and 14.7, two 7.6 and 11.3, one 7.2
+// and 10.9; two rows, 4096 -> 4096 by 8 bits 12.4, 7.3 and 6.6.
+template <int WB, int B> constexpr int kDotDepth = Piece<WB, B>::kDw <= 2 ? 4 : Piece<WB, B>::kDw <= 4 ? 2 : 1;
 
 // NW: 8 waves per workgroup when there are enough column groups to fill the chip, 16 when there are
 // few (each workgroup then has to keep twice as many bytes in flight).
@@ -258,7 +257,7 @@ mx_status launch_dot_nw(const DotArgs& a, int64_t batch, hipStream_t st) {
     const size_t smem = ((size_t)MP * a.g.chunks * 4 * 2 * (B / 8) + (size_t)MP * a.g.chunks) * 4 +
                         (size_t)NW * MP * 32 * 4;
     if (smem > 160 * 1024) return MX_ERR_UNSUPPORTED;
-    auto kern = gemv_dot_kernel<WB, B, MP, NW, kDotDepth<WB, B, NW>>;
+    auto kern = gemv_dot_kernel<WB, B, MP, NW, kDotDepth<WB, B>>;
     static std::atomic<uint64_t> done{0};
     if (!allow_dynamic_lds((const void*)kern, 160 * 1024, done)) return MX_ERR_DEVICE;
     dim3 grid((unsigned)a.g.groupsB, (unsigned)batch);
