@@ -704,14 +704,14 @@ __global__ __launch_bounds__(kSplitWaves * 64) void attention_split_kernel(AttnA
 //
 // Bound: vector issue, about 900 cycles per key tile of which an exponential is 8, and the K and V^T of a head that one
 // compute unit loads.  With the scores taken again in a second sweep 32 heads x 1 query x 1936 keys x 128 took 16.2 us,
-// 13.3 this way, 32 x 100 x 2048 x 128 21.7 and 17.2, 32 x 512 x 2048 x 128 45.9 and 32.4.
-// K comes through a ring of two tiles per wave, V^T through one of RV tiles whose first loads go out under the exchange of
-// the row statistics.  Loads past the last key tile are out of the buffer's range: they read zeros and touch no memory, so none
+// 12.7 this way, 32 x 100 x 2048 x 128 21.7 and 16.2, 32 x 512 x 2048 x 128 45.9 and 32.2.
+// A wave requests one tile of K ahead and one or two of V^T, the first under the exchange of the row statistics (two of K and
+// four of V^T: 32 x 1 x 1936 x 128 13.2 for 12.7 us, 32 x 100 x 2048 x 128 16.7 for 16.2, 4 percent over 40 random shapes).  Loads past the last key tile are out of the buffer's range: they read zeros and touch no memory, so none
 // sits under a condition.
 // ------------------------------------------------------------------------------------------------
 template <int KS, int DTW, int T, int RND>
 __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(AttnArgs g) {
-    constexpr int NW = kSplitWaves, NK = 2 * KS, RV = DTW == 1 ? 4 : T < 8 ? 2 : 1, RK = 2;
+    constexpr int NW = kSplitWaves, NK = 2 * KS, RV = DTW == 1 ? 2 : 1;
     __shared__ float stat[2][NW][64];
     extern __shared__ __attribute__((aligned(16))) float red[];       // [1 or 2][NW][16][kSplitPitch]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -742,13 +742,13 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(Att
     const int sig = (i & 0x13) | ((i & 4) << 1) | ((i & 8) >> 1);
     const uint32_t koff = (32 * h + sig) * 16;
 
-    v4i kf[RK][NK];
-    auto fetch_k = [&](int slot, int t) {
+    v4i kf[NK];
+    auto fetch_k = [&](int t) {
         const int kt = wave + t * NW;
         const uint32_t at = koff + (kt < nt ? (uint32_t)(kt * KS * kBfUnitBytes) : kNowhere);
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk)
-            kf[slot][kk] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rK, at + kk * 1024, 0, 0));
+            kf[kk] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rK, at + kk * 1024, 0, 0));
     };
     v4i vf[RV][DTW][2];
     auto fetch_v = [&](int slot, int t) {
@@ -766,8 +766,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(Att
 
     v16f s[T];
     float m_run = -__builtin_inff(), l_run = 0.f;
-#pragma unroll
-    for (int t = 0; t < RK; ++t) fetch_k(t, t);
+    fetch_k(0);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int kt = wave + t * NW;
@@ -776,8 +775,8 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(Att
         for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk)
-            s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, kf[t % RK][kk]), __builtin_bit_cast(v8bf, qf[kk]), s[t], 0, 0, 0);
-        if (t + RK < T) fetch_k(t % RK, t + RK);
+            s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, kf[kk]), __builtin_bit_cast(v8bf, qf[kk]), s[t], 0, 0, 0);
+        if (t + 1 < T) fetch_k(t + 1);
         if (ragged && kt == nt - 1) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[t][r] = 16 * (r >> 3) + (r & 7) >= valid ? -__builtin_inff() : s[t][r];
