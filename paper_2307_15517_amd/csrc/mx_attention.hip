@@ -44,6 +44,7 @@ namespace {
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 struct AttnArgs {
     const uint8_t* Q;
@@ -111,6 +112,15 @@ __device__ __forceinline__ float max_of(float a, float b) {
     return r;
 }
 
+// The integer part of a block's largest log2, between the bounds of the exponent; -200 also for all keys masked, or c = 0 with
+// them
+__device__ __forceinline__ int block_exponent(const AttnArgs& g, float m) {
+    int E;
+    asm("v_max_f32 %0, 0xc3480000, %1\n\tv_cvt_flr_i32_f32 %0, %0\n\tv_med3_i32 %0, %0, %2, %3"
+        : "=&v"(E) : "v"(m), "v"(-g.bias_p), "s"(g.emax_p));
+    return E;
+}
+
 // The exponents of the two blocks of 16 keys of a key tile, from the scores s0 and s1 that are the largest of this lane's
 // half of either: the quantizer's floor(log2 max) with a = log2 of a probability in place of the probability (exp2 grows with
 // the score, so the maximum is taken over the scores).  Out: t[b], a mantissa q of block b stands for q * 2^t[b], and off[b],
@@ -132,10 +142,7 @@ __device__ __forceinline__ void block_scales(const AttnArgs& g, float s0, float 
         const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
         m = __builtin_fmaxf(m, g.wide + __builtin_fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1])));
     }
-    // the integer part, between the bounds of the exponent; -200 also for all keys masked, or c = 0 with them
-    int E;
-    asm("v_max_f32 %0, 0xc3480000, %1\n\tv_cvt_flr_i32_f32 %0, %0\n\tv_med3_i32 %0, %0, %2, %3"
-        : "=&v"(E) : "v"(m), "v"(-g.bias_p), "s"(g.emax_p));
+    const int E = block_exponent(g, m);
     const int tm = E - wm2;
     const auto tb = __builtin_amdgcn_permlane32_swap(tm, tm, false, false);
 #pragma unroll
@@ -143,6 +150,20 @@ __device__ __forceinline__ void block_scales(const AttnArgs& g, float s0, float 
         t[b] = (int)tb[b];
         off[b] = -(float)t[b] - mrow;
     }
+}
+
+// The same where a lane holds half of one block, its other half 16 lanes away (attention_short_kernel).
+__device__ __forceinline__ void block_scale(const AttnArgs& g, float s, float c, float mrow, int wm2, float& off, int& t) {
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    float m = __builtin_fmaf(max_of(__uint_as_float(sw[0]), __uint_as_float(sw[1])), c, -mrow);
+    if (g.join) {
+        m = __builtin_fmaxf(m, g.pair + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                            0, __builtin_bit_cast(int, m), 0xB1, 0xF, 0xF, true)));
+        const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+        m = __builtin_fmaxf(m, g.wide + __builtin_fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1])));
+    }
+    t = block_exponent(g, m) - wm2;
+    off = -(float)t - mrow;
 }
 
 constexpr int kAttnStages = 5;
@@ -706,8 +727,9 @@ __global__ __launch_bounds__(kSplitWaves * 64) void attention_split_kernel(AttnA
 // compute unit loads.  With the scores taken again in a second sweep 32 heads x 1 query x 1936 keys x 128 took 16.2 us,
 // 12.7 this way, 32 x 100 x 2048 x 128 21.7 and 16.2, 32 x 512 x 2048 x 128 45.9 and 32.2.
 // A wave requests one tile of K ahead and one or two of V^T, the first under the exchange of the row statistics (two of K and
-// four of V^T: 32 x 1 x 1936 x 128 13.2 for 12.7 us, 32 x 100 x 2048 x 128 16.7 for 16.2, 4 percent over 40 random shapes).  Loads past the last key tile are out of the buffer's range: they read zeros and touch no memory, so none
-// sits under a condition.
+// four of V^T: 32 x 1 x 1936 x 128 13.2 for 12.7 us, 32 x 100 x 2048 x 128 16.7 for 16.2, 4 percent over 40 random shapes).
+// Loads past the last key tile are out of the buffer's range: they read zeros and touch no memory, so none sits under a
+// condition.
 // ------------------------------------------------------------------------------------------------
 template <int KS, int DTW, int T, int RND>
 __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(AttnArgs g) {
@@ -865,9 +887,192 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(Att
     add_waves<DTW>(g, o, red, wave, lane, bz, qt, part);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Decoding, one to sixteen queries and up to 64 key tiles: attention_kept_kernel on 16 x 16 results, so that the vector work on a
+// key tile is half of what 32 queries take.  A workgroup of eight waves owns all queries of one head and 32*DTW columns of the
+// result.
+//
+// S^T of a tile of 32 keys is two results of 16 keys x 16 queries, the K rows of which are read so that lane 16g + j holds keys
+// 8g .. 8g+7 of query j: the operand of O^T = V^T P^T, and one half of one block of 16 keys, so that a lane has one exponent.
+//
+// Bound: as there, vector issue and what one compute unit loads.  32 heads x 1 query x 1936 keys x 128 13.0 us with 32 queries, 11.0
+// this way, 8 x 1 x 2048 x 64 10.1 and 7.2, 32 x 8 x 1024 x 128 8.5 and 7.3, 32 x 3 x 512 x 128 (against the split kernel) 6.7 and
+// 4.7, 1000 x 1 x 512 x 128 72.5 and 45.1.  Sixteen waves: 11.5, 7.8, 8.0, 5.6 us.
+// ------------------------------------------------------------------------------------------------
+template <int KS, int DTW, int T, int RND>
+__global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_short_kernel(AttnArgs g) {
+    constexpr int NW = kSplitWaves;
+    __shared__ float stat[2][NW][16];
+    extern __shared__ __attribute__((aligned(16))) float red[];       // [1 or 2][NW][8][kSplitPitch]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int j = lane & 15, o8 = lane >> 4;
+    // an XCD gets one contiguous range of (head, column part): those of a head share its K and V in the L2
+    const int64_t per_xcd = (g.total + 7) / 8;
+    const int64_t lin = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per_xcd || lin >= g.total) return;          // whole workgroup, before any barrier
+    const int part = (int)(lin % g.parts);
+    const int64_t bz = lin / g.parts;
+    const int nt = (int)g.nt, v_row = (int)g.v_ksteps * kBfUnitBytes;
+    const BufRsrc rK = make_rsrc(g.K + bz * g.matrixK, (uint32_t)(nt * KS * kBfUnitBytes));
+    const BufRsrc rV = make_rsrc(g.V + bz * g.matrixV + (int64_t)part * DTW * v_row, (uint32_t)(DTW * v_row));
+    constexpr uint32_t kNowhere = 0x40000000u;          // past the end of either buffer
+    // 16 bytes of row r, elements 8*o8 .. 8*o8+7 of a unit's 32
+    const uint32_t oct = (o8 >> 1) * 1024 + (o8 & 1) * 512;
+
+    // a scale below zero or of zero: as in attention_kept_kernel
+    const int flip = g.c < 0.f ? (int)0x80008000u : 0, keep = g.c == 0.f ? 0 : -1;
+    const float c = g.c == 0.f ? 1.f : __builtin_fabsf(g.c);
+    v4i qf[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+        qf[kk] = *reinterpret_cast<const v4i*>(g.Q + bz * g.matrixQ + kk * kBfUnitBytes + oct + j * 16);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) qf[kk][d] = (qf[kk][d] ^ flip) & keep;
+    }
+    const uint32_t koff = oct + (8 * (j >> 2) + (j & 3)) * 16;
+
+    v4i kf[2 * KS];                                     // the first and the second four keys of every eight
+    auto fetch_k = [&](int t) {
+        const int kt = wave + t * NW;
+        const uint32_t at = koff + (kt < nt ? (uint32_t)(kt * KS * kBfUnitBytes) : kNowhere);
+#pragma unroll
+        for (int kk = 0; kk < 2 * KS; ++kk)
+            kf[kk] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rK, at + (kk >> 1) * kBfUnitBytes + (kk & 1) * 64, 0, 0));
+    };
+    v4i vf[2 * DTW];
+    auto fetch_v = [&](int t) {
+        const int kt = wave + t * NW;
+        const uint32_t at = oct + j * 16 + (kt < nt ? (uint32_t)(kt * kBfUnitBytes) : kNowhere);
+#pragma unroll
+        for (int x = 0; x < 2 * DTW; ++x)
+            vf[x] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rV, at + (uint32_t)((x >> 1) * v_row) + (x & 1) * 256, 0, 0));
+    };
+    // only the last key tile can hold keys past Sk; this lane's key e is real iff e < valid
+    const bool ragged = (g.Sk & 31) != 0;
+    const int valid = (int)(g.Sk - (g.nt - 1) * 32) - 8 * o8;
+
+    float s[T][8];
+    float m_run = -__builtin_inff(), l_run = 0.f;
+    fetch_k(0);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int kt = wave + t * NW;
+        if (kt >= nt) break;
+        v4f d[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            d[x] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk)
+                d[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, kf[2 * kk + x]), __builtin_bit_cast(v8bf, qf[kk]), d[x], 0, 0, 0);
+        }
+        if (t + 1 < T) fetch_k(t + 1);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[t][e] = d[e >> 2][e & 3];
+        if (ragged && kt == nt - 1) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[t][e] = e >= valid ? -__builtin_inff() : s[t][e];
+        }
+        // the sum against an older maximum while it stays below 2^20 in every lane, as in attention_bf16_kernel
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e], c, -m_run));
+        if (t > 0 && __builtin_amdgcn_ballot_w64(!(sum < 0x1p20f)) == 0) {
+            l_run += sum;
+        } else {
+            float sm = s[t][0];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) sm = __builtin_fmaxf(sm, s[t][e]);
+            const float m_old = m_run;
+            m_run = __builtin_fmaxf(m_run, sm * c);
+            const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;      // no key in this lane's tiles so far
+            sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e], c, -m_use));
+            l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
+        }
+    }
+
+    // row statistics: the four lane groups of a wave, then the waves, hold disjoint keys of the same query
+    fetch_v(0);
+#pragma unroll
+    for (int step = 16; step <= 32; step *= 2) {
+        const float mo = __shfl_xor(m_run, step, 64), lo = __shfl_xor(l_run, step, 64);
+        const float mf = __builtin_fmaxf(m_run, mo), m_use = mf == -__builtin_inff() ? 0.f : mf;
+        l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_use) + lo * __builtin_amdgcn_exp2f(mo - m_use);
+        m_run = mf;
+    }
+    if (lane < 16) {
+        stat[0][wave][j] = m_run;
+        stat[1][wave][j] = l_run;
+    }
+    __syncthreads();
+    float mrow;
+    {
+        float mf = -__builtin_inff();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mf = __builtin_fmaxf(mf, stat[0][w][j]);
+        float l = 0.f;                                  // mf is finite: there is at least one key
+#pragma unroll
+        for (int w = 0; w < NW; ++w) l += stat[1][w][j] * __builtin_amdgcn_exp2f(stat[0][w][j] - mf);
+        mrow = mf + __builtin_amdgcn_logf(l);           // the same value in every lane group and wave
+    }
+
+    v4f o[2 * DTW];
+#pragma unroll
+    for (int x = 0; x < 2 * DTW; ++x) o[x] = v4f{0.f, 0.f, 0.f, 0.f};
+    const float qmax = (float)((1 << (g.wp - 1)) - 1);
+    const int wm2 = g.wp - 2;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        if (wave + t * NW >= nt) break;
+        float sm = s[t][0], off;
+#pragma unroll
+        for (int e = 1; e < 8; ++e) sm = __builtin_fmaxf(sm, s[t][e]);
+        int te;
+        block_scale(g, sm, c, mrow, wm2, off, te);
+        float el[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float sc = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e], c, off));
+            float v = RND == MX_RNE ? __builtin_rintf(sc) : __builtin_truncf(sc);
+            v = __builtin_fminf(v, qmax);                         // probabilities are not negative
+            el[e] = __builtin_ldexpf(v, te);                      // an exact bfloat16 number
+        }
+        v4i pf;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)                               // the upper halves of two fp32 values
+            pf[d] = (int)__builtin_amdgcn_perm(__float_as_uint(el[2 * d + 1]), __float_as_uint(el[2 * d]), 0x07060302u);
+#pragma unroll
+        for (int x = 0; x < 2 * DTW; ++x)
+            o[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, vf[x]), __builtin_bit_cast(v8bf, pf), o[x], 0, 0, 0);
+        if (t + 1 < T) fetch_v(t + 1);
+    }
+
+    // the waves' partial results as in add_waves: 32 columns are two results of 16 columns x 16 queries, of which register r of
+    // lane 16g + j is column 4g + r of query j
+    float* O = g.O + bz * g.o_batch_stride;
+#pragma unroll
+    for (int dt = 0; dt < DTW; ++dt) {
+        float* buf = red + (dt & 1) * NW * 8 * kSplitPitch;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) buf[(wave * 8 + r) * kSplitPitch + lane] = o[2 * dt + (r >> 2)][r & 3];
+        __syncthreads();
+        for (int t = threadIdx.x; t < 512; t += NW * 64) {
+            const int q = t >> 5, e = t & 31, r = 4 * (e >> 4) + (e & 3), l = 16 * ((e >> 2) & 3) + q;
+            const int d = (part * DTW + dt) * 32 + e;
+            if (q < g.Sq && d < (int)g.D) {
+                float sum = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) sum += buf[(w * 8 + r) * kSplitPitch + l];
+                O[q * g.ldo + d] = sum;
+            }
+        }
+    }
+}
+
 // One of the kernels for few queries: a workgroup per 32 queries and column part.
-mx_status launch_few(AttnArgs& g, void (*kern)(AttnArgs), std::atomic<uint64_t>& done, int buffers, int64_t batch, int parts, hipStream_t st) {
-    const int smem = buffers * kSplitWaves * 16 * kSplitPitch * 4;
+mx_status launch_few(AttnArgs& g, void (*kern)(AttnArgs), std::atomic<uint64_t>& done, int smem, int64_t batch, int parts, hipStream_t st) {
     if (!allow_dynamic_lds((const void*)kern, smem, done)) return MX_ERR_DEVICE;
     g.tiles_q = g.q_tiles;
     g.parts = parts;
@@ -878,19 +1083,34 @@ mx_status launch_few(AttnArgs& g, void (*kern)(AttnArgs), std::atomic<uint64_t>&
     MX_HIP_LAUNCH_CHECK();
     return MX_OK;
 }
+constexpr int few_lds(int dtw, int regs) { return (dtw == 1 ? 1 : 2) * kSplitWaves * regs * kSplitPitch * 4; }
 
 template <int KS, int DTW>
 mx_status launch_attention_split(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
     static std::atomic<uint64_t> done[2];
     auto kern = rnd == MX_RNE ? attention_split_kernel<KS, DTW, MX_RNE> : attention_split_kernel<KS, DTW, MX_RTZ>;
-    return launch_few(g, kern, done[rnd == MX_RNE], DTW == 1 ? 1 : 2, batch, parts, st);
+    return launch_few(g, kern, done[rnd == MX_RNE], few_lds(DTW, 16), batch, parts, st);
 }
 
 template <int KS, int DTW, int T>
 mx_status launch_attention_kept(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
     static std::atomic<uint64_t> done[2];
     auto kern = rnd == MX_RNE ? attention_kept_kernel<KS, DTW, T, MX_RNE> : attention_kept_kernel<KS, DTW, T, MX_RTZ>;
-    return launch_few(g, kern, done[rnd == MX_RNE], DTW == 1 ? 1 : 2, batch, parts, st);
+    return launch_few(g, kern, done[rnd == MX_RNE], few_lds(DTW, 16), batch, parts, st);
+}
+
+template <int KS, int DTW, int T>
+mx_status launch_attention_short(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
+    static std::atomic<uint64_t> done[2];
+    auto kern = rnd == MX_RNE ? attention_short_kernel<KS, DTW, T, MX_RNE> : attention_short_kernel<KS, DTW, T, MX_RTZ>;
+    return launch_few(g, kern, done[rnd == MX_RNE], few_lds(DTW, 8), batch, parts, st);
+}
+
+template <int KS, int DTW>
+mx_status pick_short(AttnArgs& g, int64_t batch, int parts, int rnd, hipStream_t st) {
+    if (g.nt <= 2 * kSplitWaves) return launch_attention_short<KS, DTW, 2>(g, batch, parts, rnd, st);
+    if (g.nt <= 4 * kSplitWaves) return launch_attention_short<KS, DTW, 4>(g, batch, parts, rnd, st);
+    return launch_attention_short<KS, DTW, 8>(g, batch, parts, rnd, st);
 }
 
 template <int KS, int DT, bool LAG>
@@ -935,6 +1155,8 @@ bool keeps_scores(const AttnArgs& g, int64_t groups, int64_t batch) {
 // With room for it every 32 columns of the result get a workgroup of their own, which
 // repeats the scores and saves registers, V and the sum (32 heads, one query, 1936 keys: 16.8 against 20.0 us); with more
 // than one such workgroup per compute unit that costs more than it saves (32 x 100 x 2048 x 128: 35 against 22 us).
+// Up to sixteen queries take attention_short_kernel whenever their scores fit its registers (52 random shapes of 8 to 2000 heads, 2 to
+// 64 key tiles: 0.55 to 1.02 of the time of what the rules below pick).
 // The scores are kept (attention_kept_kernel) from 17 key tiles on where heads have more than 64 elements: in one round of
 // workgroups always (us, scores taken twice and kept: 17 tiles 10.8 and 10.0, 32 tiles 14.9 and 12.5, 54 tiles 18.8 and 15.6), in two as
 // well (297 workgroups x 17 tiles 19.8 and 17.9, 360 x 62 40.3 and 31.6; up to 16 tiles, 405 x 12, 16.7 and 17.3), in three from
@@ -950,6 +1172,8 @@ bool keeps_scores(const AttnArgs& g, int64_t groups, int64_t batch) {
 template <int KS, int DT>
 mx_status pick_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     const int64_t groups = g.q_tiles * batch;
+    if (g.Sq <= 16 && g.nt <= 8 * kSplitWaves)
+        return groups * DT <= 256 ? pick_short<KS, 1>(g, batch, DT, rnd, st) : pick_short<KS, DT>(g, batch, 1, rnd, st);
     if (KS == 2 ? groups <= 256 && g.nt > 32 && g.nt <= 64 : keeps_scores(g, groups, batch)) {
         if (groups * DT <= 256) return pick_kept<KS, 1>(g, batch, DT, rnd, st);
         return pick_kept<KS, DT>(g, batch, 1, rnd, st);

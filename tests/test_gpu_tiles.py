@@ -144,6 +144,20 @@ def test_attention_with_kept_scores(heads, Sq, Sk, dim):
     run_attention(Q, K, V, (8, 7, 8, 6), 0.0, max_maybe=3.0, **some)     # 1 / Sk may be a power of two
 
 
+@pytest.mark.parametrize("dim", [16, 48, 80, 128])
+@pytest.mark.parametrize("heads,Sq,Sk", [(3, 1, 16), (3, 16, 256), (2, 5, 272), (5, 3, 512), (2, 13, 784), (2, 16, 2032), (2, 2, 2048),
+                                         (130, 2, 304), (300, 1, 48)])
+def test_attention_of_up_to_sixteen_queries(heads, Sq, Sk, dim):
+    """One to 64 key tiles, waves with all their tiles, with fewer and with none, a ragged last one; a workgroup per 32 columns and
+    per head; both rounding modes, two-row blocks, a narrow exponent of P and V, a scale below and of zero."""
+    Q, K, V = long_attention_inputs(heads, Sq, Sk, dim)
+    some = dict(heads_checked=[0, heads - 1])
+    run_attention(Q, K, V, (8, 7, 6, 5), dim ** -0.5, **some)
+    run_attention(Q, K, V, (7, 8, 5, 6), -0.7 * dim ** -0.5, rounding=mx.MX_RTZ, block_rows=2 if Sq % 2 == 0 else 1, **some)
+    run_attention(Q, K, V, (8, 7, 8, 6), dim ** -0.5, e_pv=4, **some)
+    run_attention(Q, K, V, (8, 7, 8, 6), 0.0, max_maybe=3.0, **some)     # 1 / Sk may be a power of two
+
+
 def test_fragment_product_past_one_grid_dimension():
     """131072 x 131072 results, 64 GiB: 2^24 tiles of 32 x 32, more than the work items of one grid dimension hold as
     workgroups of 256.  Every element is written, sampled rows and columns (first and last among them) are right."""
@@ -503,6 +517,41 @@ def test_attention_of_128_queries_in_blocks_of_32(heads, Sq, Sk, dim, R):
             assert maybe < 1e-2
             r0, r1 = rows
             assert (np.abs(host(O[hd, r0:r1]).astype(np.float64) - o_ref[r0:r1]) <= bound).all(), (hd, rows)
+
+
+@pytest.mark.parametrize("heads,Sq,Sk,dim,R", [(3, 6, 352, 128, 1), (3, 12, 1024, 64, 2), (2, 34, 1024, 128, 2), (2, 33, 1056, 64, 1)])
+def test_attention_of_few_queries_in_blocks_of_32(heads, Sq, Sk, dim, R):
+    """The same with one to sixteen queries and with kept scores."""
+    Q, K, V = long_attention_inputs(heads, Sq, Sk, dim)
+    A, B = mx.quantize_pack(torch.from_numpy(Q).cuda(), mx.fmt(16, 8), MAT), mx.quantize_pack(torch.from_numpy(K).cuda(), mx.fmt(16, 7), MAT)
+    mant, exps = mx.quantize(torch.from_numpy(V).cuda(), mx.fmt(32, 5), 0)
+    Bv = mx.pack(mant, exps.repeat_interleave(2), heads, dim, Sk, mx.fmt(16, 5), MAT)
+    O = torch.empty((heads, Sq, dim), device="cuda")
+    mx.mx_attention(heads, Sq, Sk, dim, A, mx.fmt(16, 8), B, mx.fmt(16, 7), Bv, mx.fmt(16, 5), mx.fmt(32, 6, block_rows=R), dim ** -0.5, MAT,
+                    O, dim, Sq * dim)
+    torch.cuda.synchronize()
+    for hd in (0, heads - 1):
+        # Q and K enter the oracle as what blocks of 16 made of them, at a width that holds every one of these values
+        q, k = (orc.dequantize(*orc.quantize(x[hd], 16, w), 16, w).astype(np.float32) for x, w in ((Q, 8), (K, 7)))
+        s64 = q.astype(np.float64) @ k.astype(np.float64).T * dim ** -0.5
+        P = np.exp(s64 - s64.max(axis=1, keepdims=True))
+        P = (P / P.sum(axis=1, keepdims=True)).astype(np.float32)
+        rows = np.arange(Sq) if R == 1 else np.arange(Sq) ^ 1
+        amax = np.maximum(P, P[rows]).reshape(Sq, -1, 32).max(axis=2)
+        E = np.floor(np.log2(amax.astype(np.float64)))
+        step = np.repeat(np.ldexp(1.0, (E - 4).astype(int)), 32, axis=1)
+        x = P / step
+        pq = np.minimum(np.round(x), 31) * step
+        vabs = np.abs(orc.dequantize(*orc.quantize(V[hd].T.copy(), 32, 5), 32, 5))
+        v = orc.dequantize(*orc.quantize(V[hd].T.copy(), 32, 5), 32, 5)
+        # eps: 1e-5 of the fp32 softmax and 1e-6 of the terms of a score (below 9 in sum).  A probability that close to a tie may
+        # take the neighbouring mantissa, a block maximum that close to a power of two the neighbouring exponent (two steps)
+        eps = 2e-5
+        frac = np.repeat(amax / np.ldexp(1.0, E.astype(int)), 32, axis=1)
+        may = (np.abs(x - np.floor(x) - 0.5) <= eps * np.maximum(x, 1)) + 2.0 * ((frac < 1 + eps) | (frac > 2 - 2 * eps))
+        assert may.mean() < 1e-2
+        bound = 1e-5 * pq @ vabs.T + (may * step) @ vabs.T + 1e-12
+        assert (np.abs(O[hd].cpu().numpy().astype(np.float64) - pq @ v.T) <= bound).all(), hd
 
 
 # The forms of the matrix-layout product, (row tiles, column tiles) of 32 and what they select, with K of long_k.  Blocks of 32

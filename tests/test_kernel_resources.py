@@ -102,5 +102,5 @@ def test_waves_of_the_decode_kernel_are_those_its_split_is_chosen_by(kernel_note
 
 def test_attention_with_kept_scores_stays_in_registers(scratch_bytes):
     """Up to eight tiles of scores per wave, 128 registers of the 256."""
-    kernels = [n for n in scratch_bytes if re.search(r"\battention_kept_kernel<", n)]
-    assert len(kernels) == 16 and not [n for n in kernels if scratch_bytes[n]]
+    kernels = [n for n in scratch_bytes if re.search(r"\battention_(kept|short)_kernel<", n)]
+    assert len(kernels) == 16 + 30 and not [n for n in kernels if scratch_bytes[n]]
