@@ -325,7 +325,9 @@ __global__ __launch_bounds__(256, OCC) void gemm_bf16_kernel(BfArgs g) {
 // the eight partial tiles are added through LDS in wave order at the end.  No barrier and no LDS traffic in the K loop.
 //
 // Bound: the latency of the operand loads (a step comes from the last-level cache or HBM), so what counts is how many
-// compute units work and how many bytes each has in flight: eight waves hold up to 24 KiB each.  The 128 x 256 tile
+// compute units work and how many bytes each has in flight.  Two steps: a third took 1.03 of the time over 30 random
+// products (412 x 1984 x 1984 10.2 us for 9.3, 231 x 2720 x 2720 11.9 for 11.3, 229 x 912 x 912 4.15 for 3.8), but not with the
+// 32 x 64 tile (128 x 768 x 3072 4.9 for 5.1), which keeps it; one step, 360 x 9360 x 2608 46.6 for 39.4.  The 128 x 256 tile
 // of the kernel above leaves most of the chip idle at these sizes and walks K in one serial chain of barriers.
 // Measured, widths 6 and 4: 128 x 768 x 768 13.2 -> 4.7 us, 128 x 768 x 3072 31.2 -> 6.4 us, 128 x 4096 x 4096
 // 39.7 -> 13.4 us, 256 x 4096 x 4096 40 -> 17.6 us.
@@ -336,7 +338,7 @@ constexpr int kSplitPitch = 36;                                       // floats 
 template <int RA, int RB, bool QOUT>
 __global__ __launch_bounds__(kSplitWaves * 64) void gemm_bf16_split_kernel(BfArgs g) {
     constexpr int NW = kSplitWaves;
-    constexpr int D = 3;                                             // K steps in registers
+    constexpr int D = RA * RB == 2 ? 3 : 2;                          // K steps in registers
     constexpr int BUFS = RA * RB == 1 ? 1 : 2;
     extern __shared__ __attribute__((aligned(16))) float red[];      // [buffers][NW][16][64], then QOUT: tile, bias
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;

@@ -632,7 +632,9 @@ __global__ __launch_bounds__(WS ? 512 : 256, WS ? 2 : OCC) void gemm_scaled_kern
 // compute units work and how many bytes each has in flight.  The 128 x 256 tile of the kernel above leaves most of the
 // chip idle at these sizes and walks K in one serial chain of barriers.  Measured, 8 by 4 bits, block 32: 128 x 768 x
 // 768 11.3 -> 4.9 us, 128 x 768 x 3072 20.9 -> 6.2 us, 128 x 4096 x 4096 25.4 -> 9.3 us.
-// D: one step more was slower at both tiles (5.6 and 9.9 us at the first and the last of these sizes).
+// D: one.  Three with the 32 x 32 tile and two with the larger one took 1.04 of the time over 30 random products (82 x 1856 x 1856 5.6 us
+// for 4.7, 67 x 1024 x 2624 4.3 for 3.8; 28 x 4448 x 4448 7.05 for 7.15), two with the 32 x 32 tile as long on average but for some
+// much longer (79 x 1184 x 2400 4.3 for 3.9).
 // ------------------------------------------------------------------------------------------------
 constexpr int kSplitWaves = 8;
 constexpr int kSplitPitch = 68;                                       // floats per row of a summed 32 x 64 tile
@@ -640,7 +642,7 @@ constexpr int kSplitPitch = 68;                                       // floats 
 template <int PA, int PB, int RA, int RB, int QO>
 __global__ __launch_bounds__(kSplitWaves * 64) void gemm_scaled_split_kernel(ScaledArgs g) {
     constexpr int NW = kSplitWaves;
-    constexpr int D = RA * RB == 1 ? 3 : 2;                          // K steps in registers
+    constexpr int D = 1;                                             // K steps in registers
     constexpr int BUFS = RA * RB == 1 ? 1 : 2;
     static_assert(QO == 0 || RB % 2 == 0, "the quantized ending takes whole K steps of the output");
     extern __shared__ __attribute__((aligned(16))) float red[];      // [buffers][NW][16][64], then QO: tile, bias
