@@ -31,6 +31,52 @@ typedef short s2v __attribute__((ext_vector_type(2)));
 typedef unsigned short u2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ s2v splat(int v) { s2v r; r.x = (short)v; r.y = (short)v; return r; }
 
+// To nearest, the arithmetic runs on half-precision numbers, two per register: every mantissa is one (|q| <= 128), and adding
+// 1536 + 2^(wd-1) to q * 2^sh in one fused multiply-add rounds it to an integer, ties to even (the sum's last place is 1, the
+// number added is even), whose low bits are the destination's code with its sign bit inverted.
+//
+// Bound: bytes and vector instructions about alike.  With packed 16-bit integers, as toward zero still, 2048 x 11008 in blocks
+// of 32 took 11.2 us for 8 -> 5 bits and 10.0 for 8 -> 4, 8.9 for either this way (315 vector instructions per 32 elements before,
+// 263 now).
+typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ h2v as_half(uint32_t v) { return __builtin_bit_cast(h2v, v); }
+__device__ __forceinline__ uint32_t half_bits(h2v v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ h2v half_splat(float v) { return h2v{(_Float16)v, (_Float16)v}; }
+
+// Elements 4g .. 4g+3 of a stream of W-bit codes as numbers: (4g, 4g+2) and (4g+1, 4g+3).  A code with its sign bit inverted is
+// the offset of the mantissa from -2^(W-1), and with 0x6400 above it the number 1024 + that.
+template <int W>
+__device__ __forceinline__ void four_numbers(const uint32_t* in, int g, h2v (&out)[2]) {
+    constexpr uint32_t kSign = 1u << (W - 1);
+    uint32_t p0, p1;
+    if constexpr (W == 8) {
+        const uint32_t x = in[g] ^ 0x80808080u;
+        p0 = __builtin_amdgcn_perm(0x64646464u, x, 0x04020400u);
+        p1 = __builtin_amdgcn_perm(0x64646464u, x, 0x04030401u);
+    } else {
+        constexpr uint32_t kMask = ((1u << W) - 1u) * 0x00010001u, kFlip = (0x6400u | kSign) * 0x00010001u;
+        const int bit = 4 * g * W, sh = bit & 31;
+        uint32_t x = in[bit >> 5] >> sh;
+        if (sh + 4 * W > 32) x = __builtin_amdgcn_alignbit(in[(bit >> 5) + 1], in[bit >> 5], sh);
+        const uint32_t y = (x & 0xFFFFu & ((1u << (2 * W)) - 1u)) | ((x << (16 - 2 * W)) & 0xFFFF0000u);   // 0, 1 and 2, 3
+        p0 = (y & kMask) ^ kFlip;
+        p1 = ((y >> W) & kMask) ^ kFlip;
+    }
+    out[0] = as_half(p0) - half_splat(1024.f + (float)kSign);
+    out[1] = as_half(p1) - half_splat(1024.f + (float)kSign);
+}
+
+// Four codes with inverted sign bits, above whatever an addend of 0x6600 left, as 4W consecutive bits with their signs back
+template <int W>
+__device__ __forceinline__ uint32_t four_codes(uint32_t p0, uint32_t p1) {
+    constexpr uint16_t kOver = (uint16_t)(0x6600u * ((1u << W) + 1u));
+    constexpr uint32_t kSigns = (1u << (W - 1)) * ((1u << W) + 1u) * 0x00010001u;
+    const u2v two = __builtin_bit_cast(u2v, p1) * (u2v)(unsigned short)(1u << W) + __builtin_bit_cast(u2v, p0) - (u2v)kOver;
+    const uint32_t t = __builtin_bit_cast(uint32_t, two) ^ kSigns;       // codes 0, 1 in the lower half and 2, 3 in the upper
+    constexpr uint32_t kLow = (uint32_t)((1ull << (2 * W)) - 1u);
+    return W == 8 ? t : (t & kLow) | ((t >> (16 - 2 * W)) & ~kLow);
+}
+
 template <int WS, int WD, int B, int RND>
 __global__ __launch_bounds__(256) void cast_kernel(CastArgs a) {
     constexpr int NB = B >= 32 ? 1 : 32 / B;          // blocks (or the half block) of a thread
@@ -60,108 +106,154 @@ __global__ __launch_bounds__(256) void cast_kernel(CastArgs a) {
     } else {
         for (int byte = 0; byte < n * WS / 8; ++byte) in[byte >> 2] |= (uint32_t)src[byte] << (8 * (byte & 3));
     }
-    // Two elements per register as 16-bit halves (|q| <= 128, and every intermediate of the shift below fits
-    // 16 bits), so the arithmetic runs as packed 16-bit instructions: of the four elements 4g..4g+3, pair
-    // 2g holds (4g, 4g+2) and pair 2g+1 holds (4g+1, 4g+3) -- for 8-bit sources these are the even and the
-    // odd bytes of one dword, sign-extended in place.
-    s2v pr[16];
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-        if (WS == 8) {
-            const s2v x = __builtin_bit_cast(s2v, in[g]);
-            pr[2 * g] = __builtin_bit_cast(s2v, __builtin_bit_cast(u2v, in[g]) << (unsigned short)8) >> splat(8);
-            pr[2 * g + 1] = x >> splat(8);
-        } else {
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                s2v v;
-                v.x = (short)stream_get<WS>(in, (4 * g + p) * WS);
-                v.y = (short)stream_get<WS>(in, (4 * g + p + 2) * WS);
-                pr[2 * g + p] = v;
-            }
-        }
-    }
-
     uint32_t out[WD];
 #pragma unroll
     for (int d = 0; d < WD; ++d) out[d] = 0;
     const int64_t blk0 = e0 / B;
+    if constexpr (RND == MX_RNE) {
+        h2v v[8][2];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        constexpr int NP = BE / 2;                    // pairs of the block
-        s2v hi = pr[j * NP], lo = pr[j * NP];
+        for (int g = 0; g < 8; ++g) four_numbers<WS>(in, g, v[g]);
 #pragma unroll
-        for (int t = 1; t < NP; ++t) {
-            hi = __builtin_elementwise_max(hi, pr[j * NP + t]);
-            lo = __builtin_elementwise_min(lo, pr[j * NP + t]);
-        }
-        int mx = max(max((int)hi.x, (int)hi.y), max(-(int)lo.x, -(int)lo.y));
-        if (B == 64) {                                // lanes 2t, 2t+1 hold the halves of one block
-            const int o = __builtin_amdgcn_update_dpp(0, mx, 0xB1, 0xF, 0xF, true);
-            mx = o > mx ? o : mx;
-        }
-        const bool have = j * BE < n;
-        int ebyte = 0;
-        if (have && mx != 0) {
-            const int E = (int)a.exps[blk0 + j] - a.bias_s;
-            int E2 = E - (WS - 2) + (31 - __builtin_clz((unsigned)mx));
+        for (int j = 0; j < NB; ++j) {
+            constexpr int NG = BE / 4;                // fours of the block
+            h2v hi = v[j * NG][0], lo = v[j * NG][0];
+#pragma unroll
+            for (int t = 1; t < 2 * NG; ++t) {
+                hi = __builtin_elementwise_max(hi, v[j * NG + t / 2][t & 1]);
+                lo = __builtin_elementwise_min(lo, v[j * NG + t / 2][t & 1]);
+            }
+            // without the sign that a zero may have, what is not negative is ordered like its bits
+            const uint32_t m2 = half_bits(__builtin_elementwise_max(hi, -lo)) & 0x7FFF7FFFu;
+            uint32_t mx = max(m2 & 0xFFFFu, m2 >> 16);
+            if (B == 64) {                            // lanes 2t, 2t+1 hold the halves of one block
+                const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mx, 0xB1, 0xF, 0xF, true);
+                mx = o > mx ? o : mx;
+            }
+            const bool have = j * BE < n;
+            const bool zero = mx == 0;
+            const int E = have ? (int)a.exps[blk0 + j] - a.bias_s : 0;
+            int E2 = E - (WS - 2) + (int)(mx >> 10) - 15;
             E2 = E2 < a.emin_d ? a.emin_d : E2;
             E2 = E2 > a.emax_d ? a.emax_d : E2;
-            const int sh = (E - (WS - 2)) - (E2 - (WD - 2));
-            ebyte = E2 + a.bias_d;
-            // |q| <= 128 and qmax <= 127: a left shift beyond 7 saturates every nonzero element like 7 does, a
-            // right shift beyond 9 gives zero like 9 does, and within these limits nothing leaves 16 bits
-            const int up = sh > 0 ? (sh > 7 ? 7 : sh) : 0;
-            const int k = sh < 0 ? (sh < -9 ? 9 : -sh) : 0;
-            // arithmetic right shift = floor; to nearest with ties to even: add half - 1 + (the bit that becomes
-            // the last one), then floor; toward zero: add 2^k - 1 to negatives, then floor.  k = 0 adds nothing.
-            const s2v ups = splat(up), ks = splat(k);
-            const s2v add = splat(RND == MX_RNE ? (k > 0 ? (1 << (k - 1)) - 1 : 0) : (1 << k) - 1);
-            const s2v one = splat(k > 0 ? 1 : 0);
+            // |q| <= 128: a left shift beyond 7 saturates every nonzero element like 7 does, a right shift beyond 9 gives zero
+            // like 9 does
+            int sh = (E - (WS - 2)) - (E2 - (WD - 2));
+            sh = sh > 7 ? 7 : sh < -9 ? -9 : sh;
+            const h2v scale = as_half((uint32_t)(sh + 15) * 0x04000400u);
+            constexpr float kMagic = 1536.f + (float)(1 << (WD - 1));
 #pragma unroll
-            for (int t = 0; t < NP; ++t) {
-                const s2v v = pr[j * NP + t] << ups;
-                s2v r;
-                if (RND == MX_RNE) r = (v + add + ((v >> ks) & one)) >> ks;
-                else r = (v + ((v >> splat(15)) & add)) >> ks;
-                r = __builtin_elementwise_min(__builtin_elementwise_max(r, splat(-qmax)), splat(qmax));
-                pr[j * NP + t] = r;
+            for (int t = 0; t < 2 * NG; ++t) {
+                h2v r = __builtin_elementwise_fma(v[j * NG + t / 2][t & 1], scale, half_splat(kMagic));
+                r = __builtin_elementwise_min(__builtin_elementwise_max(r, half_splat(kMagic - qmax)), half_splat(kMagic + qmax));
+                v[j * NG + t / 2][t & 1] = r;
+            }
+            // one exponent byte per block: every block of the thread, or the even lane for a block of 64
+            if (have && (B < 64 || (e0 & 63) == 0)) a.exps_out[blk0 + j] = zero ? (uint8_t)0 : (uint8_t)(E2 + a.bias_d);
+        }
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {                 // back into the bit stream
+            const uint32_t c = four_codes<WD>(half_bits(v[g][0]), half_bits(v[g][1]));
+            const int bit = 4 * g * WD;
+            out[bit >> 5] |= c << (bit & 31);
+            if ((bit & 31) + 4 * WD > 32) out[(bit >> 5) + 1] |= c >> (32 - (bit & 31));
+        }
+    } else {
+        // Two elements per register as 16-bit halves (|q| <= 128, and every intermediate of the shift below fits
+        // 16 bits), so the arithmetic runs as packed 16-bit instructions: of the four elements 4g..4g+3, pair
+        // 2g holds (4g, 4g+2) and pair 2g+1 holds (4g+1, 4g+3) -- for 8-bit sources these are the even and the
+        // odd bytes of one dword, sign-extended in place.
+        s2v pr[16];
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            if (WS == 8) {
+                const s2v x = __builtin_bit_cast(s2v, in[g]);
+                pr[2 * g] = __builtin_bit_cast(s2v, __builtin_bit_cast(u2v, in[g]) << (unsigned short)8) >> splat(8);
+                pr[2 * g + 1] = x >> splat(8);
+            } else {
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    s2v v;
+                    v.x = (short)stream_get<WS>(in, (4 * g + p) * WS);
+                    v.y = (short)stream_get<WS>(in, (4 * g + p + 2) * WS);
+                    pr[2 * g + p] = v;
+                }
+            }
+        }
+
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            constexpr int NP = BE / 2;                    // pairs of the block
+            s2v hi = pr[j * NP], lo = pr[j * NP];
+#pragma unroll
+            for (int t = 1; t < NP; ++t) {
+                hi = __builtin_elementwise_max(hi, pr[j * NP + t]);
+                lo = __builtin_elementwise_min(lo, pr[j * NP + t]);
+            }
+            int mx = max(max((int)hi.x, (int)hi.y), max(-(int)lo.x, -(int)lo.y));
+            if (B == 64) {                                // lanes 2t, 2t+1 hold the halves of one block
+                const int o = __builtin_amdgcn_update_dpp(0, mx, 0xB1, 0xF, 0xF, true);
+                mx = o > mx ? o : mx;
+            }
+            const bool have = j * BE < n;
+            int ebyte = 0;
+            if (have && mx != 0) {
+                const int E = (int)a.exps[blk0 + j] - a.bias_s;
+                int E2 = E - (WS - 2) + (31 - __builtin_clz((unsigned)mx));
+                E2 = E2 < a.emin_d ? a.emin_d : E2;
+                E2 = E2 > a.emax_d ? a.emax_d : E2;
+                const int sh = (E - (WS - 2)) - (E2 - (WD - 2));
+                ebyte = E2 + a.bias_d;
+                // |q| <= 128 and qmax <= 127: a left shift beyond 7 saturates every nonzero element like 7 does, a
+                // right shift beyond 9 gives zero like 9 does, and within these limits nothing leaves 16 bits
+                const int up = sh > 0 ? (sh > 7 ? 7 : sh) : 0;
+                const int k = sh < 0 ? (sh < -9 ? 9 : -sh) : 0;
+                // arithmetic right shift = floor; toward zero: add 2^k - 1 to negatives, then floor.  k = 0 adds nothing.
+                const s2v ups = splat(up), ks = splat(k);
+                const s2v add = splat((1 << k) - 1);
+#pragma unroll
+                for (int t = 0; t < NP; ++t) {
+                    const s2v v = pr[j * NP + t] << ups;
+                    s2v r = (v + ((v >> splat(15)) & add)) >> ks;
+                    r = __builtin_elementwise_min(__builtin_elementwise_max(r, splat(-qmax)), splat(qmax));
+                    pr[j * NP + t] = r;
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < NP; ++t) pr[j * NP + t] = splat(0);
+            }
+            // one exponent byte per block: every block of the thread, or the even lane for a block of 64
+            if (have && (B < 64 || (e0 & 63) == 0)) a.exps_out[blk0 + j] = (uint8_t)ebyte;
+        }
+        // back into the bit stream
+        if (WD == 8) {
+#pragma unroll
+            for (int g = 0; g < 8; ++g)                   // bytes: pair 2g gives 0 and 2, pair 2g+1 gives 1 and 3
+                out[g] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, pr[2 * g + 1]),
+                                               __builtin_bit_cast(uint32_t, pr[2 * g]), 0x06020400u);
+        } else if (WD == 4) {
+#pragma unroll
+            for (int G = 0; G < 4; ++G) {                 // eight elements per dword
+                uint32_t x[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t ev = __builtin_bit_cast(uint32_t, pr[4 * G + 2 * h]) & 0x000F000Fu;
+                    const uint32_t od = __builtin_bit_cast(uint32_t, pr[4 * G + 2 * h + 1]) & 0x000F000Fu;
+                    x[h] = (od << 4) | ev;                // byte 0: elements 0, 1; byte 2: elements 2, 3 of the group
+                }
+                out[G] = __builtin_amdgcn_perm(x[1], x[0], 0x06040200u);
             }
         } else {
 #pragma unroll
-            for (int t = 0; t < NP; ++t) pr[j * NP + t] = splat(0);
-        }
-        // one exponent byte per block: every block of the thread, or the even lane for a block of 64
-        if (have && (B < 64 || (e0 & 63) == 0)) a.exps_out[blk0 + j] = (uint8_t)ebyte;
-    }
-    // back into the bit stream
-    if (WD == 8) {
+            for (int t = 0; t < 16; ++t) {
+                const uint32_t c = __builtin_bit_cast(uint32_t, pr[t]) & (((1u << WD) - 1u) * 0x00010001u);
 #pragma unroll
-        for (int g = 0; g < 8; ++g)                   // bytes: pair 2g gives 0 and 2, pair 2g+1 gives 1 and 3
-            out[g] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, pr[2 * g + 1]),
-                                           __builtin_bit_cast(uint32_t, pr[2 * g]), 0x06020400u);
-    } else if (WD == 4) {
-#pragma unroll
-        for (int G = 0; G < 4; ++G) {                 // eight elements per dword
-            uint32_t x[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint32_t ev = __builtin_bit_cast(uint32_t, pr[4 * G + 2 * h]) & 0x000F000Fu;
-                const uint32_t od = __builtin_bit_cast(uint32_t, pr[4 * G + 2 * h + 1]) & 0x000F000Fu;
-                x[h] = (od << 4) | ev;                // byte 0: elements 0, 1; byte 2: elements 2, 3 of the group
-            }
-            out[G] = __builtin_amdgcn_perm(x[1], x[0], 0x06040200u);
-        }
-    } else {
-#pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            const uint32_t c = __builtin_bit_cast(uint32_t, pr[t]) & (((1u << WD) - 1u) * 0x00010001u);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int bit = (4 * (t >> 1) + (t & 1) + 2 * h) * WD;   // compile time after unrolling
-                const uint32_t code = h == 0 ? (c & 0xFFFFu) : (c >> 16);
-                out[bit >> 5] |= code << (bit & 31);
-                if ((bit & 31) + WD > 32) out[(bit >> 5) + 1] |= code >> (32 - (bit & 31));
+                for (int h = 0; h < 2; ++h) {
+                    const int bit = (4 * (t >> 1) + (t & 1) + 2 * h) * WD;   // compile time after unrolling
+                    const uint32_t code = h == 0 ? (c & 0xFFFFu) : (c >> 16);
+                    out[bit >> 5] |= code << (bit & 31);
+                    if ((bit & 31) + WD > 32) out[(bit >> 5) + 1] |= code >> (32 - (bit & 31));
+                }
             }
         }
     }

@@ -5,7 +5,7 @@ import torch
 
 from oracle import mx_oracle as orc
 from paper_2307_15517_amd import mx
-from test_gpu_parity import attention_bound, check_product, gpu_operand, host, random_operand, run_attention, run_minifloat
+from test_gpu_parity import attention_bound, check_cast, check_product, gpu_operand, host, random_operand, run_attention, run_minifloat
 
 pytestmark = pytest.mark.gpu
 
@@ -552,6 +552,23 @@ def test_attention_of_few_queries_in_blocks_of_32(heads, Sq, Sk, dim, R):
         assert may.mean() < 1e-2
         bound = 1e-5 * pq @ vabs.T + (may * step) @ vabs.T + 1e-12
         assert (np.abs(O[hd].cpu().numpy().astype(np.float64) - pq @ v.T) <= bound).all(), hd
+
+
+@pytest.mark.parametrize("block", [8, 16, 32, 64])
+def test_cast_to_nearest_by_any_shift(block):
+    """Every width pair, code and tie; blocks of zeros and of one sign; a narrow destination exponent makes the shift anything from
+    the widest left one to the widest right one; the tensor ends inside a run of 32 elements for small blocks."""
+    rng = np.random.default_rng(970 + block)
+    rows, cols = 33, 5 * 64 + (block if block < 32 else 0)
+    for ws in range(2, 9):
+        for wd in range(2, 9):
+            q = rng.integers(-(2 ** (ws - 1)), 2 ** (ws - 1), size=(rows, cols)).astype(np.int8)
+            q[::4] //= 2 ** (ws // 2)
+            q[3] = 0
+            q[5], q[6] = np.maximum(q[5], 0), -(2 ** (ws - 1))
+            check_cast(q, rng.integers(0, 256, size=(rows, cols // block)).astype(np.uint8), block, ws, wd)
+            ex = rng.integers(112, 144, size=(rows, cols // block)).astype(np.uint8)
+            check_cast(q, ex, block, ws, wd, ed=3)
 
 
 # The forms of the matrix-layout product, (row tiles, column tiles) of 32 and what they select, with K of long_k.  Blocks of 32
