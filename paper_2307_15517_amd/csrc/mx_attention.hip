@@ -895,9 +895,10 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(Att
 // S^T of a tile of 32 keys is two results of 16 keys x 16 queries, the K rows of which are read so that lane 16g + j holds keys
 // 8g .. 8g+7 of query j: the operand of O^T = V^T P^T, and one half of one block of 16 keys, so that a lane has one exponent.
 //
-// Bound: as there, vector issue and what one compute unit loads.  32 heads x 1 query x 1936 keys x 128 13.0 us with 32 queries, 11.0
-// this way, 8 x 1 x 2048 x 64 10.1 and 7.2, 32 x 8 x 1024 x 128 8.5 and 7.3, 32 x 3 x 512 x 128 (against the split kernel) 6.7 and
-// 4.7, 1000 x 1 x 512 x 128 72.5 and 45.1.  Sixteen waves: 11.5, 7.8, 8.0, 5.6 us.
+// Bound: what one compute unit loads, K of a head and 32 columns of V^T in each of the workgroups that share a head (0.6 MB at 64
+// bytes per cycle for 1936 keys x 128; vector ALUs active 36 percent, matrix cores 10).  32 heads x 1 query x 1936 keys x 128
+// 12.7 us with 32 queries, 11.0 this way, 8 x 1 x 2048 x 64 10.1 and 7.2, 32 x 8 x 1024 x 128 8.5 and 7.3, 32 x 3 x 512 x 128
+// (against the split kernel) 6.7 and 4.7, 1000 x 1 x 512 x 128 72.5 and 45.1.  Sixteen waves: 11.5, 7.8, 8.0, 5.6 us.
 // ------------------------------------------------------------------------------------------------
 template <int KS, int DTW, int T, int RND>
 __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_short_kernel(AttnArgs g) {
