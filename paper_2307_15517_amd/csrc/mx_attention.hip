@@ -24,16 +24,16 @@
 // sweep 2 the V^T) units of one tile of 32 keys are copied global -> LDS with 16-byte direct-to-LDS loads, five
 // stages, one barrier per key tile.  Two query tiles per wave (363 registers, one workgroup) were slower, 128 us.
 //
-// Bound: on real operands the power that they draw.  32 heads x 2048 x 2048 x 128 takes 102 us, 88 us on operands that are
-// all zero (the same instructions at the full clock); the three products alone are 85 us at the rate that a large bfloat16
-// product reaches.  At the full clock it is vector issue: a matrix instruction takes 8 of its 32 cycles from the vector
-// ALU, an exponential 8, any other vector instruction 4, an LDS read about 5.  Hence few vector instructions: no search for the
-// maximum in most tiles of sweep 1, the exponents of both blocks of a tile computed at once (block_scales): 108 -> 102 us,
-// on zero operands 94 -> 88; 24 heads x 2040 x 2048 x 80 91 -> 85, 32 x 1500 x 1536 x 64 59 -> 54.5.  The LDS reads of a
-// tile's K run a tile ahead, each into the registers that a matrix instruction has just freed, so that no
-// instruction waits for them; V^T straight from global memory instead of through LDS: 111 for 108 us.  The second product of a
-// key tile runs one tile behind its scores, so that no matrix instruction is left without vector work under it: 16 heads x
-// 2040 queries x 2048 keys x 128 76.7 -> 71 us (where it does not pay: pick_attention).
+// Bound: on real operands the power that they draw, at the full clock vector issue: a matrix instruction takes 8 of its 32
+// cycles from the vector ALU, an exponential 8, any other vector instruction 4, an LDS read about 5.  32 heads x 2048 x 2048 x
+// 128 takes 125 us, 100 us on operands that are all zero (the same instructions; medians of launches back to back under the
+// kernel trace, as all times of this paragraph).  Hence few vector instructions: the exponents of both blocks of a tile are
+// computed at once (block_scales).  The LDS reads of a tile's K run a tile ahead, each into the registers that a matrix
+// instruction has just freed, so that no instruction waits for them.  Together 131 -> 125 us, on zeros 108 -> 100; 30 heads x 1999
+// x 2016 x 96 108 -> 98, 24 x 2040 x 2048 x 80 99 -> 92, 32 x 1500 x 1536 x 64 61.7 -> 55.6, 32 x 900 x 1024 x 128 39.3 -> 37.5.
+// V^T straight from global memory instead of through LDS was 3 percent slower.  The second product of a key tile runs one tile
+// behind its scores, so that no matrix instruction is left without vector work under it: 16 heads x 2040 queries x 2048 keys x
+// 128 7 percent less (where it does not pay: pick_attention).
 #include <type_traits>
 
 #include "mx_bf16.h"
@@ -319,46 +319,42 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
             auto masked = [&](int r) { return RAG && 16 * (r >> 3) + (r & 7) >= valid; };
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!PV) {
-                // m_run is what the exponentials are taken against: a maximum, but not always the newest.  A tile whose sum
-                // against it stays below 2^20 in every lane is added as it is (l_run stays below 2^20 times the number of
-                // tiles, and is 1 or more from m_run's own term); only another one, the first among them, looks for its maximum, which
-                // takes m_run's place.  That saves the search in nearly every tile: 15 of 84 vector issue slots.
-                // Units: 0..7 = two exponentials each, 8 = the running sum.
-                constexpr int NU = 9;
-                float sum = 0.f;
+                // The exponentials are taken against the running maximum, tile by tile: the terms that dominate the sum then have
+                // arguments near 0, which are not rounded, and a lane's sum depends on its own query alone.  Against an older
+                // maximum while a tile stays within 2^20 of it the search is saved in most tiles (0 to 3 percent: 32 x 2048 x 2048 x
+                // 128 124 us for 125, on zeros 97 for 100), but those arguments have rounding errors of up to 2^-20, log2 of the
+                // sum as much again.
+                // Units: 0 = tile maximum and the new running maximum, 1..4 = four exponentials each, 5 = the running sum.
+                constexpr int NU = 6;
+                float m_old, m_use, sum;
                 auto unit = [&](int u) {
-                    if (u < NU - 1) {
-#pragma unroll
-                        for (int r = 2 * u; r < 2 * u + 2; ++r) {
-                            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[set][r], c, -m_run));
-                            sum = r == 0 ? p : sum + p;
-                        }
-                        pin(sum);
-                    } else if (!RAG && __builtin_amdgcn_ballot_w64(!(sum < 0x1p20f)) == 0) {
-                        l_run += sum;
-                    } else {
+                    if (u == 0) {
                         float sm = -__builtin_inff();
 #pragma unroll
                         for (int r = 0; r < 16; ++r) sm = __builtin_fmaxf(sm, masked(r) ? -__builtin_inff() : s[set][r]);
-                        const float m_old = m_run;
+                        m_old = m_run;
                         m_run = __builtin_fmaxf(m_run, sm * c);
-                        const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;
+                        m_use = m_run == -__builtin_inff() ? 0.f : m_run;
                         sum = 0.f;
+                        pin(m_use);
+                    } else if (u < 5) {
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) {
+                        for (int r = 4 * (u - 1); r < 4 * u; ++r) {
                             float arg = __builtin_fmaf(s[set][r], c, -m_use);
                             if (masked(r)) arg = -__builtin_inff();   // also when c is 0
                             sum += __builtin_amdgcn_exp2f(arg);
                         }
+                        pin(sum);
+                    } else {
                         l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
+                        pin(l_run);
                     }
                 };
 #pragma unroll
                 for (int m = 0; m < NK; ++m) {
                     next_score(m);
 #pragma unroll
-                    for (int x = m * NU / NK; x < (m + 1) * NU / NK; ++x)
-                        if (!RAG || x == NU - 1) unit(x);
+                    for (int x = m * NU / NK; x < (m + 1) * NU / NK; ++x) unit(x);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
@@ -493,9 +489,10 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(AttnArgs g) {
     {
         const float mo = __shfl_xor(m_run, 32, 64), lo = __shfl_xor(l_run, 32, 64);
         const float mf = __builtin_fmaxf(m_run, mo);     // finite: there is at least one key
-        const float a = __fmul_rn(l_run, __builtin_amdgcn_exp2f(m_run - mf));
-        const float b = __fmul_rn(lo, __builtin_amdgcn_exp2f(mo - mf));
-        mrow = mf + __builtin_amdgcn_logf(__fadd_rn(a, b));                   // the same value in both halves
+        // The halves may differ in the last place of the sum, in which either half's own product is not rounded.  (What has to
+        // be one value for a block, its exponent, comes from one half: block_scales.)
+        const float other = lo * __builtin_amdgcn_exp2f(mo - mf);
+        mrow = mf + __builtin_amdgcn_logf(__builtin_fmaf(l_run, __builtin_amdgcn_exp2f(m_run - mf), other));
     }
     sweep(std::true_type{});
 
@@ -803,24 +800,16 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(Att
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[t][r] = 16 * (r >> 3) + (r & 7) >= valid ? -__builtin_inff() : s[t][r];
         }
-        // the sum against an older maximum while it stays below 2^20 in every lane, as in attention_bf16_kernel
+        float sm = s[t][0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) sm = __builtin_fmaxf(sm, s[t][r]);
+        const float m_old = m_run;
+        m_run = __builtin_fmaxf(m_run, sm * c);
+        const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;          // no key in this lane's tiles so far
         float sum = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], c, -m_run));
-        if (t > 0 && __builtin_amdgcn_ballot_w64(!(sum < 0x1p20f)) == 0) {
-            l_run += sum;
-        } else {
-            float sm = s[t][0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) sm = __builtin_fmaxf(sm, s[t][r]);
-            const float m_old = m_run;
-            m_run = __builtin_fmaxf(m_run, sm * c);
-            const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;      // no key in this lane's tiles so far
-            sum = 0.f;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], c, -m_use));
-            l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
-        }
+        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], c, -m_use));
+        l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
     }
 
     // row statistics: the waves, and the two lane halves of each, hold disjoint keys of the same query
@@ -974,24 +963,16 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_short_kernel(At
 #pragma unroll
             for (int e = 0; e < 8; ++e) s[t][e] = e >= valid ? -__builtin_inff() : s[t][e];
         }
-        // the sum against an older maximum while it stays below 2^20 in every lane, as in attention_bf16_kernel
+        float sm = s[t][0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) sm = __builtin_fmaxf(sm, s[t][e]);
+        const float m_old = m_run;
+        m_run = __builtin_fmaxf(m_run, sm * c);
+        const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;          // no key in this lane's tiles so far
         float sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e], c, -m_run));
-        if (t > 0 && __builtin_amdgcn_ballot_w64(!(sum < 0x1p20f)) == 0) {
-            l_run += sum;
-        } else {
-            float sm = s[t][0];
-#pragma unroll
-            for (int e = 1; e < 8; ++e) sm = __builtin_fmaxf(sm, s[t][e]);
-            const float m_old = m_run;
-            m_run = __builtin_fmaxf(m_run, sm * c);
-            const float m_use = m_run == -__builtin_inff() ? 0.f : m_run;      // no key in this lane's tiles so far
-            sum = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e], c, -m_use));
-            l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
-        }
+        for (int e = 0; e < 8; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e], c, -m_use));
+        l_run = l_run * __builtin_amdgcn_exp2f(m_old - m_use) + sum;
     }
 
     // row statistics: the four lane groups of a wave, then the waves, hold disjoint keys of the same query

@@ -475,8 +475,8 @@ def test_attention_of_128_queries_per_workgroup(heads, Sq, Sk, dim):
     (-90, -110, -71, -100, -69, -50, -49, -48, -29, -28, -27),
 ])
 def test_attention_row_maximum_that_moves(tops, dim):
-    """128 queries per workgroup: sums against an older maximum while a tile stays within 2^20 of it, against its own
-    otherwise.  tops: the largest score of each key tile in binades, the two signs of the scale."""
+    """128 queries per workgroup: the sum so far is rescaled whenever a key tile raises the maximum.  tops: the largest score of
+    each key tile in binades, the two signs of the scale."""
     heads, Sq, Sk = 100, 258, 336
     rng = np.random.default_rng(dim + abs(tops[1]))
     u = np.full(dim, dim ** -0.5, np.float32)
@@ -487,6 +487,74 @@ def test_attention_row_maximum_that_moves(tops, dim):
     some = dict(heads_checked=[0, heads - 1], max_maybe=5e-2)
     run_attention(Q, K, V, (8, 8, 6, 5), 0.25, rows=(Sq - 34, Sq), **some)
     run_attention(Q, -K, V, (8, 8, 8, 5), -0.25, rows=(0, 34), block_rows=2, **some)
+
+
+@pytest.mark.parametrize("heads,Sq,Sk,dim", [(2, 33, 1040, 128), (2, 40, 2032, 64), (3, 5, 1040, 128), (2, 16, 528, 64)])
+@pytest.mark.parametrize("tops", [(0, 5, 40, 42, 61, 62, 100, 60), (130, 0, 0, 120, 0, 100, 0, 149), (-90, -110, -71, -69, -50, -48, -29, -27)])
+def test_attention_row_maximum_that_moves_with_few_queries(heads, Sq, Sk, dim, tops):
+    """The same where eight waves take the key tiles in turn and keep the scores, 33 queries and more and up to sixteen: the tiles
+    of a wave rise or fall by tops, one step ahead from wave to wave, the last one is ragged."""
+    rng = np.random.default_rng(dim + Sk + abs(tops[1]))
+    tile = np.arange(Sk) // 32
+    u = np.full(dim, dim ** -0.5, np.float32)
+    Q = (u + 0.02 * rng.standard_normal((heads, Sq, dim))).astype(np.float32)
+    top = np.array(tops, np.float32)[(tile // 8 + tile) % 8] - 8 * rng.random((heads, Sk)).astype(np.float32)
+    K = (np.log(2) / 0.25 * top[:, :, None] * u + 0.1 * rng.standard_normal((heads, Sk, dim))).astype(np.float32)
+    V = rng.standard_normal((heads, Sk, dim)).astype(np.float32)
+    run_attention(Q, K, V, (8, 8, 6, 5), 0.25, max_maybe=5e-2)
+    run_attention(Q, -K, V, (8, 8, 8, 5), -0.25, block_rows=2 if Sq % 2 == 0 else 1, max_maybe=5e-2)
+
+
+# One shape of every form of the attention kernels: 128 queries per workgroup, split, kept scores and up to sixteen queries, with
+# all columns of the result and with 32 of them per workgroup
+ATTENTION_KERNELS = [(100, 258, 352, 128), (100, 258, 352, 64), (100, 32, 544, 64), (100, 32, 512, 128), (100, 32, 1024, 128),
+                     (60, 32, 2048, 128), (200, 32, 1200, 64), (200, 16, 1024, 128), (100, 16, 608, 64), (40, 13, 2048, 128)]
+
+
+def attention_output(Q, K, V, widths, scale):
+    heads, Sq, dim = Q.shape
+    Sk = K.shape[1]
+    fq, fk, fp, fv = (mx.fmt(16, w) for w in widths)
+    Bv = torch.empty((mx.mx_packed_bytes(heads, dim, Sk, fv, MAT),), dtype=torch.uint8, device="cuda")
+    mx.mx_quantize_pack_axis0(torch.from_numpy(V).cuda(), heads, Sk, dim, dim, Sk * dim, fv, MAT, Bv)
+    O = torch.empty((heads, Sq, dim), device="cuda")
+    mx.mx_attention(heads, Sq, Sk, dim, mx.quantize_pack(torch.from_numpy(Q).cuda(), fq, MAT), fq,
+                    mx.quantize_pack(torch.from_numpy(K).cuda(), fk, MAT), fk, Bv, fv, fp, scale, MAT, O, dim, Sq * dim)
+    torch.cuda.synchronize()
+    return host(O)
+
+
+@pytest.mark.parametrize("heads,Sq,Sk,dim", ATTENTION_KERNELS)
+def test_attention_of_a_query_does_not_depend_on_the_others(heads, Sq, Sk, dim):
+    """The same bits whether the queries beside it are ordinary ones or have a maximum that rises by 25 binades from key tile to
+    key tile (element 0, which is zero in the others)."""
+    Q, K, V = long_attention_inputs(heads, Sq, Sk, dim)
+    Q[:, :, 0] = 0.0
+    K[:, :, 0] = np.arange(Sk) // 32
+    others = np.arange(Sq) % 3 == 1
+    jump = Q.copy()
+    jump[:, others, 0] = 25 * np.log(2) * dim ** 0.5
+    alone, beside = (attention_output(q, K, V, (8, 7, 8, 6), dim ** -0.5)[:, ~others] for q in (Q, jump))
+    assert np.array_equal(alone.view(np.uint32), beside.view(np.uint32))
+
+
+@pytest.mark.parametrize("heads,Sq,Sk,dim", ATTENTION_KERNELS)
+def test_attention_probability_just_below_a_power_of_two(heads, Sq, Sk, dim):
+    """Two keys of score 0 and one, in an earlier tile, d = 19.6 to 19.97 binades below: the row sum is 2 + 2^-d, the two
+    probabilities 1/2 less a relative 2^-(d+1), which 8 bits hold as 127/256.  In fp32 the logarithm of that sum is 1 + 7e-7 or
+    more, at least five of its last places above 1, as long as the exponentials are taken against the row maximum; against the
+    earlier key it is rounded near d + 1, where 7e-7 is less than half a last place, and 128/256 comes out."""
+    c = 19.97 / 127                                      # of the exponent in binades
+    far, near = -4.0 * 127, np.array([-125.0, -126.0, -127.0], np.float32)
+    tops = (8 * 32 + 1, (16 if Sk > 16 * 32 else 9) * 32 + 2)    # with eight waves on the key tiles: those of the first one's wave
+    Q, K, V = (np.zeros((heads, n, dim), np.float32) for n in (Sq, Sk, Sk))
+    Q[:, :, 0] = 1.0
+    K[:, :, 0] = far
+    K[:, 0, 0] = near[np.arange(heads) % 3]
+    K[:, tops, 0] = 0.0
+    V[:, tops] = 1.0
+    O = attention_output(Q, K, V, (8, 8, 8, 8), c * np.log(2))
+    assert (O == 2 * 127 / 256).all(), (O != 2 * 127 / 256).mean()
 
 
 @pytest.mark.parametrize("heads,Sq,Sk,dim,R", [(100, 258, 352, 128, 1), (100, 258, 384, 64, 2), (100, 258, 352, 96, 2), (500, 258, 352, 64, 1),
