@@ -385,6 +385,17 @@ constexpr int kMaxLds = 72 * 1024;
 // Column groups of a workgroup, parts of its slice, K slices and the records per part.
 struct DecodeSplit { int groups, parts, slices, part; };
 
+// The waves per SIMD that choose_split counts on.  Its coefficients were fitted with them, on kernels whose rings of weight
+// records took 25 to 165 registers.  The kernels have room for as many or more, but the split says in what order a row's sums are
+// added, so it does not follow the ring.  With waves_per_simd in their place 18 percent of the sizes of 512 to 13824 with
+// blocks of 32 and 8 bits, or of 64, are split otherwise, to no one side's gain (3 and 8 rows, that way and this: 8 bits, blocks of 32,
+// 11008 -> 4096 11.5 and 12.2 us, 12.0 and 12.5, 5504 -> 2860 8.9 and 9.2, 7.5 and 8.3; 2 bits, blocks of 64, 5120 -> 12643 11.2 and 11.9,
+// 11.2 and 14.3).
+constexpr int split_waves(int wb, int block) {
+    if (block == 64) return wb == 2 ? 3 : 2;
+    return block == 32 && wb == 8 ? 3 : 4;
+}
+
 // The split that takes the least of: the items a thread quantizes and the records a wave streams, per round of resident
 // workgroups; the waves of the fullest compute unit with the bytes they stream; the exchange between slices and the
 // partial sums a thread adds there; all of it on average over three to eight rows.  It does not look at the number of rows
@@ -399,7 +410,7 @@ DecodeSplit choose_split(int chunks, int groups, int block, int wb, int record, 
     static constexpr int counts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64};
     DecodeSplit best = {0, 0, 0, 0};
     float least = 0.f;
-    const int resident_waves = 4 * waves_per_simd(wb, block), record_bytes = (int)record_lds(block);
+    const int resident_waves = 4 * split_waves(wb, block), record_bytes = (int)record_lds(block);
     // Every call comes through here: two divisions per split and the rest in shifts and multiplications, 0.27 to 0.43 us of host
     // time at 80 to 216 chunks by 128 to 432 groups; 0.7 to 1.0 us with a division for each quotient.
     static constexpr unsigned inverse[5] = {0, 65536, 32768, 21846, 16384};      // of 1 to 4, in 2^-16, rounded up

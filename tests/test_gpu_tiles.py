@@ -432,6 +432,40 @@ def test_decode_rows_have_the_same_bits_with_three_to_eight_of_them(K, N, block,
             assert torch.equal(y, y8[first:first + M]), "%d rows from row %d" % (M, first)
 
 
+@pytest.mark.parametrize("K,N,block,ww,parts,slices,part", [
+    (11008, 4096, 32, 8, 2, 8, 6), (5504, 2860, 32, 8, 4, 4, 3), (4096, 4096, 32, 5, 4, 4, 2),
+    (5120, 12643, 64, 2, 4, 1, 5), (4736, 12316, 64, 3, 4, 1, 5), (4672, 11773, 64, 4, 4, 1, 5), (3072, 768, 64, 8, 4, 3, 1),
+])
+def test_decode_sums_are_added_in_the_order_of_the_split(K, N, block, ww, parts, slices, part):
+    """The bits of a result are those of the split of K that the rule has for these weights: runs of `part` records of four
+    blocks added one after the other, `parts` runs to a slice, the slices in their order.  How many records a wave keeps
+    in flight is none of it."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + N)
+    fx, fw = mx.fmt(block, 8), mx.fmt(block, ww)
+    x, w = spread(g, 3, K, block), spread(g, N, K, block)
+    y = torch.full((3, N), 3.0, device="cuda")
+    mx.mx_linear(x, 3, K, K, fx, mx.linear_workspace(3, K, N, fx, fw, "cuda"), mx.quantize_pack(w, fw), N, fw, mx.MX_LAYOUT_FRAGMENT, y, N)
+    cols = np.r_[0:48, N - 48:N]
+    (qa, ea), (qb, eb) = orc.quantize(host(x), block, 8), orc.quantize(host(w[torch.from_numpy(cols).cuda()]), block, ww)
+    dots = np.einsum("mkb,nkb->kmn", *(q.reshape(len(q), -1, block).astype(np.int64) for q in (qa, qb)))
+    scale = ea.T[:, :, None].astype(int) + eb.T[:, None, :].astype(int) - 2 * 127 - (8 - 2) - (ww - 2)
+    terms = np.ldexp(dots.astype(np.float32), scale)                         # exact
+    chunks = -(-K // (4 * block))
+    total = np.zeros((3, len(cols)), np.float32)
+    for sl in range(slices):
+        first, last = sl * part * parts, min(chunks, (sl + 1) * part * parts)
+        in_slice = None
+        for p in range(parts):
+            acc = np.zeros_like(total)
+            for t in terms[4 * min(last, first + p * part):4 * min(last, first + (p + 1) * part)]:
+                acc = acc + t
+            in_slice = acc if p == 0 else in_slice + acc
+        total = total + in_slice
+    assert last == chunks
+    assert np.array_equal(host(y)[:, cols], total)
+
+
 @pytest.mark.parametrize("rows,cols", [(512, 1024), (8193, 64), (1, 16)])
 def test_minifloat_dequantizer_forms(rows, cols):
     """One item per thread up to 2^19 elements, four past that; the last workgroup full, ragged, and alone."""
