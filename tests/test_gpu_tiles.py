@@ -131,6 +131,35 @@ def test_attention_forms(heads, Sq, Sk, dim):
         run_attention(Q, K, V, (8, 7, 6, 5), scale, heads_checked=[0, heads - 1], rounding=rounding, block_rows=rows)
 
 
+def attention_output(Q, K, V, widths, scale):
+    heads, Sq, dim = Q.shape
+    Sk = K.shape[1]
+    fq, fk, fp, fv = (mx.fmt(16, w) for w in widths)
+    Bv = torch.empty((mx.mx_packed_bytes(heads, dim, Sk, fv, MAT),), dtype=torch.uint8, device="cuda")
+    mx.mx_quantize_pack_axis0(torch.from_numpy(V).cuda(), heads, Sk, dim, dim, Sk * dim, fv, MAT, Bv)
+    O = torch.empty((heads, Sq, dim), device="cuda")
+    mx.mx_attention(heads, Sq, Sk, dim, mx.quantize_pack(torch.from_numpy(Q).cuda(), fq, MAT), fq,
+                    mx.quantize_pack(torch.from_numpy(K).cuda(), fk, MAT), fk, Bv, fv, fp, scale, MAT, O, dim, Sq * dim)
+    torch.cuda.synchronize()
+    return host(O)
+
+
+def run_attention_of_scale_zero(Q, K, V, widths, heads_checked, rows=None):
+    """Every probability is 1 / Sk.  Where that is a power of two the row statistic, exact or a last place above it, decides
+    between it and the largest mantissa one exponent below, for a whole row: all of a row has to be one of the two."""
+    Sk, (wp, wv) = K.shape[1], widths[2:]
+    if Sk & (Sk - 1):
+        run_attention(Q, K, V, widths, 0.0, heads_checked=heads_checked, rows=rows)
+        return
+    O = attention_output(Q, K, V, widths, 0.0)[:, slice(*rows) if rows else slice(None)]
+    below = (2 ** (wp - 1) - 1) / 2 ** (wp - 1) / Sk
+    for hd in heads_checked:
+        v = orc.dequantize(*orc.quantize(V[hd].T.copy(), 16, wv), 16, wv).astype(np.float64)
+        bound = 1e-5 * np.abs(v).sum(axis=1) / Sk                           # fp32 sums, as every product's
+        exact, less = (np.abs(O[hd] - p * v.sum(axis=1)) <= bound for p in (1 / Sk, below))
+        assert (exact.all(axis=1) | less.all(axis=1)).all(), hd
+
+
 @pytest.mark.parametrize("dim", [32, 64, 80, 128])
 @pytest.mark.parametrize("heads,Sq,Sk", [(3, 7, 528), (3, 33, 1024), (2, 40, 1040), (2, 1, 2048), (2, 5, 2064), (12, 702, 784),
                                          (12, 702, 1200), (24, 702, 768), (40, 800, 1296)])
@@ -141,7 +170,7 @@ def test_attention_with_kept_scores(heads, Sq, Sk, dim):
     some = dict(heads_checked=[0, heads - 1], rows=(max(0, Sq - 34), Sq))
     run_attention(Q, K, V, (8, 7, 6, 5), dim ** -0.5, **some)
     run_attention(Q, K, V, (7, 8, 5, 6), -0.7 * dim ** -0.5, rounding=mx.MX_RTZ, block_rows=2 if Sq % 2 == 0 else 1, **some)
-    run_attention(Q, K, V, (8, 7, 8, 6), 0.0, max_maybe=3.0, **some)     # 1 / Sk may be a power of two
+    run_attention_of_scale_zero(Q, K, V, (8, 7, 8, 6), **some)
 
 
 @pytest.mark.parametrize("dim", [16, 48, 80, 128])
@@ -155,7 +184,7 @@ def test_attention_of_up_to_sixteen_queries(heads, Sq, Sk, dim):
     run_attention(Q, K, V, (8, 7, 6, 5), dim ** -0.5, **some)
     run_attention(Q, K, V, (7, 8, 5, 6), -0.7 * dim ** -0.5, rounding=mx.MX_RTZ, block_rows=2 if Sq % 2 == 0 else 1, **some)
     run_attention(Q, K, V, (8, 7, 8, 6), dim ** -0.5, e_pv=4, **some)
-    run_attention(Q, K, V, (8, 7, 8, 6), 0.0, max_maybe=3.0, **some)     # 1 / Sk may be a power of two
+    run_attention_of_scale_zero(Q, K, V, (8, 7, 8, 6), **some)
 
 
 def test_fragment_product_past_one_grid_dimension():
@@ -543,19 +572,6 @@ def test_attention_row_maximum_that_moves_with_few_queries(heads, Sq, Sk, dim, t
 # all columns of the result and with 32 of them per workgroup
 ATTENTION_KERNELS = [(100, 258, 352, 128), (100, 258, 352, 64), (100, 32, 544, 64), (100, 32, 512, 128), (100, 32, 1024, 128),
                      (60, 32, 2048, 128), (200, 32, 1200, 64), (200, 16, 1024, 128), (100, 16, 608, 64), (40, 13, 2048, 128)]
-
-
-def attention_output(Q, K, V, widths, scale):
-    heads, Sq, dim = Q.shape
-    Sk = K.shape[1]
-    fq, fk, fp, fv = (mx.fmt(16, w) for w in widths)
-    Bv = torch.empty((mx.mx_packed_bytes(heads, dim, Sk, fv, MAT),), dtype=torch.uint8, device="cuda")
-    mx.mx_quantize_pack_axis0(torch.from_numpy(V).cuda(), heads, Sk, dim, dim, Sk * dim, fv, MAT, Bv)
-    O = torch.empty((heads, Sq, dim), device="cuda")
-    mx.mx_attention(heads, Sq, Sk, dim, mx.quantize_pack(torch.from_numpy(Q).cuda(), fq, MAT), fq,
-                    mx.quantize_pack(torch.from_numpy(K).cuda(), fk, MAT), fk, Bv, fv, fp, scale, MAT, O, dim, Sq * dim)
-    torch.cuda.synchronize()
-    return host(O)
 
 
 @pytest.mark.parametrize("heads,Sq,Sk,dim", ATTENTION_KERNELS)
