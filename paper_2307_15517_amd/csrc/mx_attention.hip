@@ -721,8 +721,8 @@ __global__ __launch_bounds__(kSplitWaves * 64) void attention_split_kernel(AttnA
 // all of them in registers between the row statistics and the second product: K is read and multiplied once.
 //
 // Bound: vector issue, about 900 cycles per key tile of which an exponential is 8, and the K and V^T of a head that one
-// compute unit loads.  With the scores taken again in a second sweep 32 heads x 1 query x 1936 keys x 128 took 16.2 us,
-// 12.7 this way, 32 x 100 x 2048 x 128 21.7 and 16.2, 32 x 512 x 2048 x 128 45.9 and 32.2.
+// compute unit loads.  With the scores taken again in a second sweep 32 heads x 100 queries x 2048 keys x 128 took 21.4 us, 16.5 this
+// way, 32 x 512 x 2048 x 128 43.3 and 33.1, 24 x 700 x 2048 x 128 58.8 and 44.5.
 // A wave requests one tile of K ahead and one or two of V^T, the first under the exchange of the row statistics (two of K and
 // four of V^T: 32 x 1 x 1936 x 128 13.2 for 12.7 us, 32 x 100 x 2048 x 128 16.7 for 16.2, 4 percent over 40 random shapes).
 // Loads past the last key tile are out of the buffer's range: they read zeros and touch no memory, so none sits under a
@@ -884,10 +884,12 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(Att
 // S^T of a tile of 32 keys is two results of 16 keys x 16 queries, the K rows of which are read so that lane 16g + j holds keys
 // 8g .. 8g+7 of query j: the operand of O^T = V^T P^T, and one half of one block of 16 keys, so that a lane has one exponent.
 //
-// Bound: what one compute unit loads, K of a head and 32 columns of V^T in each of the workgroups that share a head (0.6 MB at 64
-// bytes per cycle for 1936 keys x 128; vector ALUs active 36 percent, matrix cores 10).  32 heads x 1 query x 1936 keys x 128
-// 12.7 us with 32 queries, 11.0 this way, 8 x 1 x 2048 x 64 10.1 and 7.2, 32 x 8 x 1024 x 128 8.5 and 7.3, 32 x 3 x 512 x 128
-// (against the split kernel) 6.7 and 4.7, 1000 x 1 x 512 x 128 72.5 and 45.1.  Sixteen waves: 11.5, 7.8, 8.0, 5.6 us.
+// Bound: the serial chain of one workgroup.  Of 11.2 us for 32 heads x 1 query x 1936 keys x 128 a launch that does next to nothing
+// takes 3.6; the loads of a compute unit, K of a head and 32 columns of V^T in each of the four workgroups that share it, take
+// 4.4 (0.6 MB at 64 bytes per cycle); what is left is the waits between the tiles of a wave and its two meetings with the
+// others, which nothing tells apart (vector ALUs of the busy units active 36 percent, matrix cores 10).  Against the kernels that
+// it took the place of (scores taken twice, for 1000 heads 128 queries per workgroup): 15.7 -> 11.2 us, 8 x 1 x 2048 x 64 12.2 -> 7.3,
+// 32 x 8 x 1024 x 128 10.4 -> 7.4, 32 x 3 x 512 x 128 7.3 -> 5.4, 1000 x 1 x 512 x 128 72 -> 45.  Sixteen waves: 4 to 10 percent more.
 // ------------------------------------------------------------------------------------------------
 template <int KS, int DTW, int T, int RND>
 __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_short_kernel(AttnArgs g) {
@@ -1137,8 +1139,9 @@ bool keeps_scores(const AttnArgs& g, int64_t groups, int64_t batch) {
 // With room for it every 32 columns of the result get a workgroup of their own, which
 // repeats the scores and saves registers, V and the sum (32 heads, one query, 1936 keys: 16.8 against 20.0 us); with more
 // than one such workgroup per compute unit that costs more than it saves (32 x 100 x 2048 x 128: 35 against 22 us).
-// Up to sixteen queries take attention_short_kernel whenever their scores fit its registers (52 random shapes of 8 to 2000 heads, 2 to
-// 64 key tiles: 0.55 to 1.02 of the time of what the rules below pick).
+// Up to sixteen queries take attention_short_kernel up to 64 key tiles (52 random shapes of 8 to 2000 heads, 2 to 64 key tiles: 0.55
+// to 1.02 of the time of what the rules below pick).  64 is where its forms end, eight tiles per wave in 98 to 136 registers; one
+// for more keys would fit the registers but has not been built, so they take the scores twice.
 // The scores are kept (attention_kept_kernel) from 17 key tiles on where heads have more than 64 elements: in one round of
 // workgroups always (us, scores taken twice and kept: 17 tiles 10.8 and 10.0, 32 tiles 14.9 and 12.5, 54 tiles 18.8 and 15.6), in two as
 // well (297 workgroups x 17 tiles 19.8 and 17.9, 360 x 62 40.3 and 31.6; up to 16 tiles, 405 x 12, 16.7 and 17.3), in three from
@@ -1147,10 +1150,11 @@ bool keeps_scores(const AttnArgs& g, int64_t groups, int64_t batch) {
 // rounds 1335 x 47 69.3 and 72.4).  Heads of up to 64 elements in one round from 33 tiles on (209 x 46 12.2 and 11.3; 232 x 17
 // 7.1 and 7.9): with fewer, two workgroups of the other form share a compute unit.
 // The second product of the 128-query form runs one key tile behind its scores (LAG), but not for one or two key tiles, where
-// the additional round of it costs more (54 heads x 1828 x 64 x 48: 13.1 and 14.7 us, 32 x 2000 x 64 x 128 2 percent), nor
-// for heads of 33 to 64 elements once a compute unit has more than four workgroups to take: the lag needs 148 registers for
-// 125, three workgroups at a time for four (106 x 3866 x 128 x 64: 52.3 and 57.5 us; median over 4096 query tiles and more
-// 5 to 10 percent up to eight key tiles, 2 at 24, even at 32).
+// the additional round of it costs more or as much (54 heads x 1828 x 64 x 48: 12.5 and 13.4 us, 32 x 2000 x 64 x 128 15.4
+// either way), nor for heads of 33 to 64 elements once a compute unit has more than four workgroups to take: the lag needs 139
+// registers for 126, three workgroups at a time for four (106 x 3866 x 128 x 64: 61 and 65 us, 500 x 258 x 352 x 64 43.1 and 44.0, 106 x
+// 3866 x 512 x 64 127 and 129; even from 24 to 32 key tiles: 106 x 3866 x 768 x 64 171 and 171, 300 x 512 x 800 x 48 68.3 and 67.2).
+// With fewer workgroups the lag pays: 64 x 1024 x 512 x 64 26.1 and 25.0.
 template <int KS, int DT>
 mx_status pick_attention(AttnArgs& g, int64_t batch, int rnd, hipStream_t st) {
     const int64_t groups = g.q_tiles * batch;

@@ -1,5 +1,6 @@
 // mx_cast: MXInt (block, es, ws) -> MXInt (block, ed, wd) on the canonical form, in integer
-// arithmetic, without going through floating point (Section 4 of the paper, the paragraph on
+// arithmetic (one-row blocks to nearest: in half-precision numbers that are these integers), without
+// going through the values' fp32 (Section 4 of the paper, the paragraph on
 // mixed-precision quantization: casting mantissas is bit extension or truncation, the exponent
 // takes a shift).  The result is what quantizing the block's exact values to the destination
 // format gives: with mx = max |q_i| and p = floor(log2 mx) the new shared exponent is
@@ -36,8 +37,8 @@ __device__ __forceinline__ s2v splat(int v) { s2v r; r.x = (short)v; r.y = (shor
 // number added is even), whose low bits are the destination's code with its sign bit inverted.
 //
 // Bound: bytes and vector instructions about alike.  With packed 16-bit integers, as toward zero still, 2048 x 11008 in blocks
-// of 32 took 11.2 us for 8 -> 5 bits and 10.0 for 8 -> 4, 8.9 for either this way (315 vector instructions per 32 elements before,
-// 263 now).
+// of 32 took 11.2 us for 8 -> 5 bits and 10.0 for 8 -> 4, 8.9 for either this way (231 vector instructions per wave of 64 x 32
+// elements; the vector ALUs of a busy compute unit are active 71 percent of its cycles).
 typedef _Float16 h2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ h2v as_half(uint32_t v) { return __builtin_bit_cast(h2v, v); }
 __device__ __forceinline__ uint32_t half_bits(h2v v) { return __builtin_bit_cast(uint32_t, v); }

@@ -51,8 +51,8 @@ struct DecodeArgs {
     int32_t eadj;            // -bias - (wa-2) - (wb-2)
 };
 
-// Weight records a wave keeps in flight: about eight dwords a lane, requested once its activations are quantized.  More of
-// them, or earlier ones, only stand in the way of the activations, which every workgroup waits for first: with five records
+// Weight records a wave keeps in flight: about eight dwords a lane, or one record where it has more (up to 32), requested
+// once its activations are quantized.  More of them, or earlier ones, only stand in the way of the activations, which every workgroup waits for first: with five records
 // requested ahead of the quantizer 8 rows by 8 and 4 bits, blocks of 16, 5120 -> 5120, 5120 -> 13824 and 13824 -> 5120 took
 // 9.9, 14.9 and 15.8 us, with two ahead of it 9.0, 13.9 and 14.9, with two after it 8.9, 13.5 and 14.5 (three 9.1, 14.1, 14.3,
 // one 8.9, 14.7, 15.4); 5 rows by 6 and 5 bits, blocks of 32, 4096 -> 4096, 4096 -> 11008 and 11008 -> 4096 five 8.6, 13.0 and 13.1, two

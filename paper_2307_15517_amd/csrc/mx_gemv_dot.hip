@@ -243,7 +243,7 @@ __global__ __launch_bounds__(NW * 64) void gemv_dot_kernel(DotArgs a) {
     }
 }
 
-// Chunks of weights in flight per wave: about eight dwords a lane.  More of them, or ahead of the activations, keep the
+// Chunks of weights in flight per wave: about eight dwords a lane, or one chunk where it has more (up to 32).  More of them, or ahead of the activations, keep the
 // workgroup from the activations it waits for first.  One row, 8 by 4 bits, blocks of 16, 5120 -> 5120, 5120 -> 13824 and 13824 ->
 // 5120: five ahead of the quantizer 6.7, 10.3 and 11.7 us, two ahead 5.6, 9.6 and 11.1, two after it 5.5, 9.9 and 10.6, one
 // 5.5, 10.6 and 12.8; blocks of 32, 4096 -> 11008 by 4 bits and 11008 -> 4096 by 5 bits: five 8.9 and 14.7, two 7.6 and 11.3, one 7.2
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(NW * 64) void gemv_dot_kernel(DotArgs a) {
 template <int WB, int B> constexpr int kDotDepth = Piece<WB, B>::kDw <= 2 ? 4 : Piece<WB, B>::kDw <= 4 ? 2 : 1;
 
 // NW: 8 waves per workgroup when there are enough column groups to fill the chip, 16 when there are
-// few (each workgroup then has to keep twice as many bytes in flight).
+// few: a workgroup that has a compute unit to itself then has twice as many requests under way.
 template <int WB, int B, int MP, int NW>
 mx_status launch_dot_nw(const DotArgs& a, int64_t batch, hipStream_t st) {
     const size_t smem = ((size_t)MP * a.g.chunks * 4 * 2 * (B / 8) + (size_t)MP * a.g.chunks) * 4 +

@@ -334,7 +334,7 @@ def dequantize(mant: torch.Tensor, exps: torch.Tensor, batch: int, rows: int, co
 
 def cast(mant: torch.Tensor, exps: torch.Tensor, batch: int, rows: int, cols: int, fs: mx_format,
          fd: mx_format) -> Tuple[torch.Tensor, torch.Tensor]:
-    """Canonical form in fs -> canonical form in fd (same block size), in integer arithmetic."""
+    """Canonical form in fs -> canonical form in fd (same block size), on the integers of the format."""
     mant_out = torch.empty(mx_mant_bytes(batch, rows, cols, fd), dtype=torch.uint8, device=mant.device)
     exps_out = torch.empty(mx_exps_bytes(batch, rows, cols, fd), dtype=torch.uint8, device=mant.device)
     mx_cast(mant, exps, batch, rows, cols, fs, fd, mant_out, exps_out)
