@@ -887,7 +887,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void attention_kept_kernel(Att
 // Bound: the serial chain of one workgroup.  Of 11.2 us for 32 heads x 1 query x 1936 keys x 128 a launch that does next to nothing
 // takes 3.6; the loads of a compute unit, K of a head and 32 columns of V^T in each of the four workgroups that share it, take
 // 4.4 (0.6 MB at 64 bytes per cycle); what is left is the waits between the tiles of a wave and its two meetings with the
-// others, which nothing tells apart (vector ALUs of the busy units active 36 percent, matrix cores 10).  Against the kernels that
+// others, which nothing tells apart (vector ALUs of the busy units active 38 percent, matrix cores 10).  Against the kernels that
 // it took the place of (scores taken twice, for 1000 heads 128 queries per workgroup): 15.7 -> 11.2 us, 8 x 1 x 2048 x 64 12.2 -> 7.3,
 // 32 x 8 x 1024 x 128 10.4 -> 7.4, 32 x 3 x 512 x 128 7.3 -> 5.4, 1000 x 1 x 512 x 128 72 -> 45.  Sixteen waves: 4 to 10 percent more.
 // ------------------------------------------------------------------------------------------------
