@@ -571,6 +571,7 @@ inline bool large_tiles_faster(int block, int resident, int64_t chunks, int64_t 
 
 // Chunks in flight per wave: five, and three or two where five do not fit the 128 registers of the 16-wave form (records of
 // 20 and more dwords per lane) and would be spilled to memory and read back for every chunk.
+// Fewer, which pay in the kernels that quantize their activations (kDotDepth, ring_depth), have not been timed here.
 template <int WB, int B, int NW> constexpr int kStreamDepth = NW < 16 || Piece<WB, B>::kDw < 20 ? 5 : Piece<WB, B>::kDw < 24 ? 3 : 2;
 
 template <int WA, int WB, int B, int MR, int NW>
